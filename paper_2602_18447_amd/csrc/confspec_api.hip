@@ -365,7 +365,9 @@ int run_gemm(confspec_ctx *ctx, const void *A, const void *W, void *out, int M, 
              const cs::PrefetchArgs *pf = nullptr, const cs::NormAfter *norm = nullptr, bool *norm_done = nullptr) {
     if (norm_done) *norm_done = false;
     if (ctx->cfg.dtype == CONFSPEC_DTYPE_FP32) {
-        HIP_TRY(cs::launch_gemm_f32((const float *)A, (const float *)W, out, M, N, K, epi, s));
+        cs::GemmF32 g = {};
+        g.A = (const float *)A; g.W = (const float *)W; g.out = (float *)out; g.M = M; g.N = N; g.K = K;
+        HIP_TRY(cs::launch_gemm_f32(g, epi, s));
     } else {
         HIP_TRY(cs::launch_gemm_bf16(ctx->set.gemm, (const cs::bf16 *)A, (const cs::bf16 *)W, out, M, N, K, epi, a_terms, out_terms,
                                      splitk_ws, splitk_bytes, s, pf, norm, norm_done));
@@ -395,11 +397,31 @@ cs::AttnArgs make_attn_args(const confspec_model_cfg &c, const confspec_kv *kv, 
     return a;
 }
 
+int longest_suffix(const confspec_batch *b) {
+    int m = 1;
+    for (int i = 0; i < b->B; ++i) m = std::max(m, b->h_cu_suffix[i + 1] - b->h_cu_suffix[i]);
+    return m;
+}
+
+// The token maps of a batch, with the rotary tables (rope) and the embedding rows (w not null).
+int run_front(confspec_ctx *ctx, const confspec_batch *b, int max_L, char *ws, const WsLayout &L, bool rope,
+              const confspec_weights *w, hipStream_t s) {
+    const confspec_model_cfg &c = ctx->cfg;
+    cs::FrontArgs f = {};
+    f.cu = b->cu_suffix; f.plens = b->prefix_lens; f.B = b->B; f.T = b->T; f.max_L = max_L;
+    f.tok_trace = (int32_t *)(ws + L.tok_trace); f.tok_pos = (int32_t *)(ws + L.tok_pos); f.last_row = (int32_t *)(ws + L.last_row);
+    f.theta = c.rope_theta;
+    if (rope) { f.cos_t = (float *)(ws + L.rope_cos); f.sin_t = (float *)(ws + L.rope_sin); f.half_hd = c.head_dim / 2; }
+    if (w) { f.ids = b->suffix_ids; f.E = w->embed; f.x = (float *)(ws + L.x); f.d = c.d_model; f.vocab = c.vocab; }
+    HIP_TRY(cs::launch_front(c.dtype, f, s));
+    return CONFSPEC_OK;
+}
+
 // Attention of one layer on an already planned batch; last_only selects the plan of the last positions.
 int run_attention(confspec_ctx *ctx, const cs::AttnArgs &a, char *ws, const WsLayout &L,
-                  const cs::AttnPlanCounts &pc, bool last_only, hipStream_t s) {
+                  const cs::AttnPlanCounts &pc, bool last_only, int max_S, hipStream_t s) {
     if (ctx->cfg.dtype == CONFSPEC_DTYPE_FP32) {
-        HIP_TRY(cs::launch_attn_f32(a, (const int32_t *)(ws + L.tok_trace), (const int32_t *)(ws + L.tok_pos), s));
+        HIP_TRY(cs::launch_attn_f32(a, max_S, s));
     } else {
         size_t items = last_only ? L.plan2_items : L.plan_items, tiles = last_only ? L.plan2_tiles : L.plan_tiles;
         size_t counts = last_only ? L.plan2_counts : L.plan_counts;
@@ -436,17 +458,6 @@ int run_attn_plan(confspec_ctx *ctx, const confspec_batch *b, const Groups &gr, 
                                  (cs::AttnTile *)(ws + (last_only ? L.plan2_tiles : L.plan_tiles)),
                                  (cs::AttnItem *)(ws + (last_only ? L.plan2_items : L.plan_items)),
                                  (int32_t *)(ws + (last_only ? L.plan2_counts : L.plan_counts)), s));
-    return CONFSPEC_OK;
-}
-
-// prep + (bf16) attention plan of all rows; fills pc.
-int run_plan(confspec_ctx *ctx, const confspec_batch *b, const Groups &gr, int max_L, char *ws, const WsLayout &L,
-             cs::AttnPlanCounts *pc, hipStream_t s) {
-    const confspec_model_cfg &c = ctx->cfg;
-    HIP_TRY(cs::launch_prep(b->cu_suffix, b->prefix_lens, b->B, b->T, max_L, (int32_t *)(ws + L.tok_trace),
-                            (int32_t *)(ws + L.tok_pos), (int32_t *)(ws + L.last_row), s));
-    *pc = cs::AttnPlanCounts{};
-    if (c.dtype == CONFSPEC_DTYPE_BF16) return run_attn_plan(ctx, b, gr, max_L, ws, L, false, pc, s);
     return CONFSPEC_OK;
 }
 
@@ -711,16 +722,11 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
     // Only the last position of each trace feeds the verdict head, so everything of the last layer that
     // comes after its keys and values - attention rows, output projection, MLP - runs on those B rows.
     const bool prune = c.dtype == CONFSPEC_DTYPE_BF16 && set.prune_last_layer && c.n_layers > 0;
-    if (use_dec) {   // the generation-step attention has its own, fixed cut into pieces: no plan
-        HIP_TRY(cs::launch_prep(batch->cu_suffix, batch->prefix_lens, B, T, max_L, (int32_t *)(ws + L.tok_trace),
-                                (int32_t *)(ws + L.tok_pos), (int32_t *)(ws + L.last_row), s));
-    } else {
-        if ((rc = run_plan(ctx, batch, gr, max_L, ws, L, &pc, s)) != CONFSPEC_OK) return rc;
+    if ((rc = run_front(ctx, batch, max_L, ws, L, true, w, s)) != CONFSPEC_OK) return rc;
+    if (c.dtype == CONFSPEC_DTYPE_BF16 && !use_dec) {   // (the generation-step attention has its own, fixed cut into pieces)
+        if ((rc = run_attn_plan(ctx, batch, gr, max_L, ws, L, false, &pc, s)) != CONFSPEC_OK) return rc;
         if (prune && (rc = run_attn_plan(ctx, batch, gr, max_L, ws, L, true, &pc_last, s)) != CONFSPEC_OK) return rc;
     }
-    HIP_TRY(cs::launch_rope_table((const int32_t *)(ws + L.tok_pos), T, c.head_dim, c.rope_theta,
-                                  (float *)(ws + L.rope_cos), (float *)(ws + L.rope_sin), s));
-    HIP_TRY(cs::launch_embed(c.dtype, batch->suffix_ids, w->embed, x, T, d, c.vocab, s));
     const int32_t *last_row = (const int32_t *)(ws + L.last_row);
     if (use_dec) {
         int32_t *ctl = (int32_t *)(ws + L.dec_ctl);
@@ -794,8 +800,40 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
             HIP_TRY(cs::launch_dec_gemm(gd, cs::DEC_EPI_RESID, f16, s));
         }
     }
+    const bool f32 = c.dtype == CONFSPEC_DTYPE_FP32;
+    const int max_S = f32 ? longest_suffix(batch) : 0;
+    for (int l = 0; l < c.n_layers && f32; ++l) {
+        // RMSNorm, rotation and SwiGLU are part of the projections (path_f32.hip)
+        cs::GemmF32 g = {};
+        g.A = x; g.W = (const float *)w->wqkv[l]; g.M = T; g.N = qw + 2 * kw; g.K = d; g.g = (const float *)w->attn_norm[l]; g.eps = c.rms_eps;
+        g.rope = cs::RopeArgs{(const float *)(ws + L.rope_cos), (const float *)(ws + L.rope_sin), ws + L.q, ws + L.ksuf, ws + L.vsuf,
+                              nullptr, nullptr, nullptr, c.n_q_heads, c.n_kv_heads};
+        g.hd = c.head_dim;
+        HIP_TRY(mark(CONFSPEC_PHASE_QKV));
+        HIP_TRY(cs::launch_gemm_f32(g, cs::EPI_ROPE, s));
+        cs::AttnArgs a = make_attn_args(c, kv, batch, (const int32_t *)(ws + L.tok_trace), l, ws + L.q, ws + L.ksuf, ws + L.vsuf,
+                                        nullptr, nullptr, nullptr, ws + L.attn, 1);
+        HIP_TRY(mark(CONFSPEC_PHASE_ATTN));
+        if ((rc = run_attention(ctx, a, ws, L, pc, false, max_S, s))) return rc;
+        if (dev_n_append) {
+            HIP_TRY(mark(CONFSPEC_PHASE_OTHER));
+            size_t layer_bytes = (size_t)kv->n_blocks * c.n_kv_heads * kv->block_size * c.head_dim * eb;
+            HIP_TRY(cs::launch_kv_append(ws + L.ksuf, ws + L.vsuf, (char *)const_cast<void *>(kv->k_pages) + layer_bytes * l,
+                                         (char *)const_cast<void *>(kv->v_pages) + layer_bytes * l, kv->block_table,
+                                         batch->cu_suffix, batch->prefix_lens, dev_n_append,
+                                         (const int32_t *)(ws + L.tok_trace), B, T, c.n_kv_heads, (size_t)c.head_dim * eb,
+                                         kv->block_size, kv->max_blocks_per_seq, kv->n_blocks, s));
+        }
+        HIP_TRY(mark(CONFSPEC_PHASE_O_PROJ));
+        if ((rc = run_gemm(ctx, ws + L.attn, w->wo[l], x, T, d, qw, cs::EPI_RESID_F32, 1, 1, s))) return rc;
+        g.W = (const float *)w->w_gate_up[l]; g.out = (float *)(ws + L.act); g.N = 2 * c.d_ffn; g.g = (const float *)w->mlp_norm[l];
+        HIP_TRY(mark(CONFSPEC_PHASE_GATE_UP));
+        HIP_TRY(cs::launch_gemm_f32(g, cs::EPI_SWIGLU, s));
+        HIP_TRY(mark(CONFSPEC_PHASE_DOWN));
+        if ((rc = run_gemm(ctx, ws + L.act, w->w_down[l], x, T, d, c.d_ffn, cs::EPI_RESID_F32, 1, 1, s))) return rc;
+    }
     bool attn_norm_done = false;   // the previous layer's down projection already wrote this layer's normalised input
-    for (int l = 0; l < c.n_layers && !use_dec; ++l) {
+    for (int l = 0; l < c.n_layers && !use_dec && !f32; ++l) {
         const int tm = format_of(l);
         const void *wqkv = w->wqkv[l], *wo = w->wo[l], *wgu = w->w_gate_up[l], *wdn = w->w_down[l];
         const bool rope_fused = rope_fused_in(l);
@@ -827,7 +865,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         cs::AttnArgs a = make_attn_args(c, kv, batch, (const int32_t *)(ws + L.tok_trace), l, ws + L.q, ws + L.ksuf, ws + L.vsuf, prec ? ws + L.q_lo : nullptr,
                                         prec ? ws + L.ksuf_lo : nullptr, prec ? ws + L.vsuf_lo : nullptr, ws + L.attn, tm);
         HIP_TRY(mark(prec ? CONFSPEC_PHASE_ATTN_PRECISE : CONFSPEC_PHASE_ATTN));
-        if ((rc = run_attention(ctx, a, ws, L, last ? pc_last : pc, last, s))) return rc;
+        if ((rc = run_attention(ctx, a, ws, L, last ? pc_last : pc, last, 0, s))) return rc;
         HIP_TRY(mark(CONFSPEC_PHASE_OTHER));
         if (dev_n_append) {
             // after this layer's attention has read the pages (it never reads rows at or past L_b anyway)
@@ -1123,10 +1161,7 @@ int confspec_op_rope_split(confspec_ctx *ctx, const confspec_batch *batch, int32
     char *ws = (char *)dev_workspace;
     if (int rd = check_device(ctx)) return rd;
     hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(cs::launch_prep(batch->cu_suffix, batch->prefix_lens, batch->B, batch->T, max_L, (int32_t *)(ws + L.tok_trace),
-                            (int32_t *)(ws + L.tok_pos), (int32_t *)(ws + L.last_row), s));
-    HIP_TRY(cs::launch_rope_table((const int32_t *)(ws + L.tok_pos), batch->T, c.head_dim, c.rope_theta,
-                                  (float *)(ws + L.rope_cos), (float *)(ws + L.rope_sin), s));
+    if ((rc = run_front(ctx, batch, max_L, ws, L, true, nullptr, s)) != CONFSPEC_OK) return rc;
     HIP_TRY(cs::launch_rope_split(c.dtype, dev_qkv, (const float *)(ws + L.rope_cos), (const float *)(ws + L.rope_sin),
                                   dev_q, dev_k, dev_v, dev_q_lo, dev_k_lo, dev_v_lo, batch->T, c.n_q_heads, c.n_kv_heads,
                                   c.head_dim, s));
@@ -1151,10 +1186,7 @@ int confspec_op_qkv_rope(confspec_ctx *ctx, const confspec_batch *batch, int32_t
     char *ws = (char *)dev_workspace;
     if (int rd = check_device(ctx)) return rd;
     hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(cs::launch_prep(batch->cu_suffix, batch->prefix_lens, batch->B, batch->T, max_L, (int32_t *)(ws + L.tok_trace),
-                            (int32_t *)(ws + L.tok_pos), (int32_t *)(ws + L.last_row), s));
-    HIP_TRY(cs::launch_rope_table((const int32_t *)(ws + L.tok_pos), batch->T, c.head_dim, c.rope_theta,
-                                  (float *)(ws + L.rope_cos), (float *)(ws + L.rope_sin), s));
+    if ((rc = run_front(ctx, batch, max_L, ws, L, true, nullptr, s)) != CONFSPEC_OK) return rc;
     cs::RopeArgs ra = {(const float *)(ws + L.rope_cos), (const float *)(ws + L.rope_sin), dev_q, dev_k, dev_v,
                        dev_q_lo, dev_k_lo, dev_v_lo, c.n_q_heads, c.n_kv_heads};
     HIP_TRY(cs::launch_gemm_bf16_rope(ctx->set.gemm, (const cs::bf16 *)dev_h, (const cs::bf16 *)dev_wqkv_perm, batch->T,
@@ -1182,11 +1214,13 @@ int confspec_op_attention(confspec_ctx *ctx, const confspec_kv *kv, const confsp
     char *ws = (char *)dev_workspace;
     if (int rd = check_device(ctx)) return rd;
     hipStream_t s = (hipStream_t)stream;
-    cs::AttnPlanCounts pc;
-    if ((rc = run_plan(ctx, batch, Groups{}, max_L, ws, L, &pc, s)) != CONFSPEC_OK) return rc;
+    cs::AttnPlanCounts pc = {};
+    if ((rc = run_front(ctx, batch, max_L, ws, L, false, nullptr, s)) != CONFSPEC_OK) return rc;
+    if (ctx->cfg.dtype == CONFSPEC_DTYPE_BF16 && (rc = run_attn_plan(ctx, batch, Groups{}, max_L, ws, L, false, &pc, s)) != CONFSPEC_OK)
+        return rc;
     cs::AttnArgs a = make_attn_args(ctx->cfg, kv, batch, (const int32_t *)(ws + L.tok_trace), layer, dev_q, dev_k_suffix, dev_v_suffix, dev_q_lo, dev_k_lo,
                                     dev_v_lo, dev_out, out_terms);
-    return run_attention(ctx, a, ws, L, pc, false, s);
+    return run_attention(ctx, a, ws, L, pc, false, longest_suffix(batch), s);
 }
 
 int confspec_op_verdict_gate(confspec_ctx *ctx, const confspec_batch *batch, const float *dev_x,
@@ -1207,8 +1241,7 @@ int confspec_op_verdict_gate(confspec_ctx *ctx, const confspec_batch *batch, con
     char *ws = (char *)dev_workspace;
     if (int rd = check_device(ctx)) return rd;
     hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(cs::launch_prep(batch->cu_suffix, batch->prefix_lens, batch->B, batch->T, max_L, (int32_t *)(ws + L.tok_trace),
-                            (int32_t *)(ws + L.tok_pos), (int32_t *)(ws + L.last_row), s));
+    if ((rc = run_front(ctx, batch, max_L, ws, L, false, nullptr, s)) != CONFSPEC_OK) return rc;
     HIP_TRY(cs::launch_verdict(c.dtype, dev_x, (const int32_t *)(ws + L.last_row), dev_final_norm, dev_lm_head, va,
                                batch->B, batch->T, c.d_model, c.rms_eps, dev_verdict_logits, dev_conf, dev_verdict,
                                dev_accept, s));

@@ -56,12 +56,21 @@ struct RopeArgs {
 };
 
 // ---- small kernels (templated on storage type: float or bf16) ----
-hipError_t launch_prep(const int32_t *cu, const int32_t *plens, int B, int T, int max_L,
-                       int32_t *tok_trace, int32_t *tok_pos, int32_t *last_row, hipStream_t s);
-hipError_t launch_rope_table(const int32_t *tok_pos, int T, int hd, float theta, float *cos_t, float *sin_t,
-                             hipStream_t s);
-hipError_t launch_embed(int dtype, const int32_t *ids, const void *E, float *x, int T, int d, int vocab,
-                        hipStream_t s);
+// What a pass needs to know about its tokens, in one launch: trace and position of every token, the last row of every
+// trace, and where asked for (pointers not null) the rotary tables [T, hd / 2] and the fp32 embedding rows x [T, d].
+struct FrontArgs {
+    const int32_t *cu, *plens;
+    int32_t B, T, max_L;
+    int32_t *tok_trace, *tok_pos, *last_row;
+    float *cos_t, *sin_t;
+    int32_t half_hd;
+    float theta;
+    const int32_t *ids;
+    const void *E;
+    float *x;
+    int32_t d, vocab;
+};
+hipError_t launch_front(int dtype, const FrontArgs &a, hipStream_t s);
 // x fp32 [T,d] -> out (storage dtype) [T, d]; terms == 2 (bf16 only): [T, 2d] hi | lo two-term form;
 // terms == 3 (bf16 only): IEEE half values
 hipError_t launch_rmsnorm(int dtype, const float *x, const void *g, void *out, int T, int d, float eps,
@@ -97,8 +106,18 @@ hipError_t launch_head_reduce(const float *logits, int B, int V, const float *ve
 //  EPI_STORE_F32: out fp32 [M,N]
 //  EPI_RESID_F32: out fp32 [M,N] += result (in place)
 //  EPI_SWIGLU   : W rows are gate/up interleaved in groups of 32; out (storage dtype) [M, N/2]
-hipError_t launch_gemm_f32(const float *A, const float *W, void *out, int M, int N, int K, int epi,
-                           hipStream_t s);
+// fp32 storage.  g (not null: store, SwiGLU, rotating epilogue): A holds rows x of the residual stream and the operand is
+// RMSNorm(x) * g.  EPI_ROPE: rope (float pointers, no second terms) and hd, W rows in their natural order.
+struct GemmF32 {
+    const float *A, *W;
+    float *out;
+    int32_t M, N, K;
+    const float *g;
+    float eps;
+    RopeArgs rope;
+    int32_t hd;
+};
+hipError_t launch_gemm_f32(const GemmF32 &p, int epi, hipStream_t s);
 // Activation formats (a_terms / out_terms): 1 = bf16; 2 = two bf16 terms, A is [M, 2K] = hi | lo and a
 // SwiGLU result is written as [M, 2 * N/2] = hi | lo; 3 = fp16 (A and W hold IEEE half values, a SwiGLU
 // result is written as fp16).
@@ -149,7 +168,7 @@ struct AttnArgs {
     float scale;            // 1/sqrt(hd)
     int32_t out_terms;
 };
-hipError_t launch_attn_f32(const AttnArgs &a, const int32_t *tok_trace, const int32_t *tok_pos, hipStream_t s);
+hipError_t launch_attn_f32(const AttnArgs &a, int max_S, hipStream_t s);   // max_S: longest suffix of the batch
 
 // group_start: null (every trace is its own context unit) or n_units + 1 trace indices, dev (attn_plan.h)
 hipError_t launch_attn_plan(const int32_t *cu, const int32_t *plens, const int32_t *group_start, int n_units, int B,

@@ -21,72 +21,56 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// token -> (trace, absolute position); last suffix row of each trace.  All indices are clamped to
-// the host-validated bounds so that inconsistent device arrays cannot cause out-of-range accesses.
-__global__ void prep_kernel(const int32_t *__restrict__ cu, const int32_t *__restrict__ plens, int B, int T,
-                            int max_L, int32_t *__restrict__ tok_trace, int32_t *__restrict__ tok_pos,
-                            int32_t *__restrict__ last_row) {
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < T) {
-        int lo = 0, hi = B - 1;  // largest b with cu[b] <= t
-        while (lo < hi) {
-            int mid = (lo + hi + 1) >> 1;
-            if (cu[mid] <= t) lo = mid; else hi = mid - 1;
-        }
-        int L = min(max(plens[lo], 0), max_L);
-        int off = min(max(t - cu[lo], 0), T - 1);
-        tok_trace[t] = lo;
-        tok_pos[t] = L + off;
+// Front of a pass, one workgroup per token: token -> (trace, absolute position); last suffix row of each trace; the
+// token's rotary table row, cos / sin of pos * theta^(-2i/hd), evaluated in double so that positions in the tens of
+// thousands keep full fp32 accuracy after the final rounding; its embedding row widened to fp32.  All indices are
+// clamped to the host-validated bounds so that inconsistent device arrays cannot cause out-of-range accesses.
+// Bound by the embedding rows written (114 MB at 18606 tokens of width 1536); as three launches with 2-byte loads
+// this was 52 + 8 + 4 us there and 9 us where a pass has few tokens.
+template <typename E>
+__global__ __launch_bounds__(128) void front_kernel(FrontArgs a, double log_theta) {
+    const int t = blockIdx.x;
+    if (threadIdx.x == 0 && t < a.B) a.last_row[t] = min(max(a.cu[t + 1] - 1, 0), a.T - 1);
+    if (t >= a.T) return;
+    int lo = 0, hi = a.B - 1;  // largest b with cu[b] <= t
+    while (lo < hi) {
+        int mid = (lo + hi + 1) >> 1;
+        if (a.cu[mid] <= t) lo = mid; else hi = mid - 1;
     }
-    if (t < B) last_row[t] = min(max(cu[t + 1] - 1, 0), T - 1);
+    const int L = min(max(a.plens[lo], 0), a.max_L);
+    const int pos = L + min(max(t - a.cu[lo], 0), a.T - 1);
+    if (threadIdx.x == 0) {
+        a.tok_trace[t] = lo;
+        a.tok_pos[t] = pos;
+    }
+    if (a.x) {
+        const int id = min(max(a.ids[t], 0), a.vocab - 1);
+        const E *row = reinterpret_cast<const E *>(a.E) + (size_t)id * a.d;
+        float4 *dst = reinterpret_cast<float4 *>(a.x + (size_t)t * a.d);
+        for (int j = threadIdx.x; j < a.d >> 2; j += blockDim.x) {
+            if constexpr (sizeof(E) == 4) {
+                dst[j] = reinterpret_cast<const float4 *>(row)[j];
+            } else {
+                const uint2 v = reinterpret_cast<const uint2 *>(row)[j];
+                dst[j] = make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
+                                     __uint_as_float(v.y & 0xffff0000u));
+            }
+        }
+    }
+    if (a.cos_t)
+        for (int i = threadIdx.x; i < a.half_hd; i += blockDim.x) {
+            double inv_freq = exp(-log_theta * (double)i / (double)a.half_hd);  // theta^(-2i/hd)
+            double sv, cv;
+            sincos((double)pos * inv_freq, &sv, &cv);
+            a.cos_t[(size_t)t * a.half_hd + i] = (float)cv;
+            a.sin_t[(size_t)t * a.half_hd + i] = (float)sv;
+        }
 }
 
-hipError_t launch_prep(const int32_t *cu, const int32_t *plens, int B, int T, int max_L, int32_t *tok_trace,
-                       int32_t *tok_pos, int32_t *last_row, hipStream_t s) {
-    int n = T > B ? T : B;
-    prep_kernel<<<(n + 255) / 256, 256, 0, s>>>(cu, plens, B, T, max_L, tok_trace, tok_pos, last_row);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------------------
-// cos/sin of pos * theta^(-2i/hd), evaluated in double so that positions in the tens of thousands
-// keep full fp32 accuracy after the final rounding.
-__global__ void rope_table_kernel(const int32_t *__restrict__ tok_pos, int T, int half, double log_theta,
-                                  float *__restrict__ cos_t, float *__restrict__ sin_t) {
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= T * half) return;
-    int t = idx / half, i = idx - t * half;
-    double inv_freq = exp(-log_theta * (double)i / (double)half);  // theta^(-2i/hd), hd = 2*half
-    double phi = (double)tok_pos[t] * inv_freq;
-    double sv, cv;
-    sincos(phi, &sv, &cv);
-    cos_t[idx] = (float)cv;
-    sin_t[idx] = (float)sv;
-}
-
-hipError_t launch_rope_table(const int32_t *tok_pos, int T, int hd, float theta, float *cos_t, float *sin_t,
-                             hipStream_t s) {
-    int half = hd / 2;
-    int n = T * half;
-    rope_table_kernel<<<(n + 255) / 256, 256, 0, s>>>(tok_pos, T, half, log((double)theta), cos_t, sin_t);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------------------
-template <typename T>
-__global__ void embed_kernel(const int32_t *__restrict__ ids, const T *__restrict__ E, float *__restrict__ x,
-                             int n_tok, int d, int vocab) {
-    int t = blockIdx.x;
-    int id = min(max(ids[t], 0), vocab - 1);
-    const T *row = E + (size_t)id * d;
-    float *dst = x + (size_t)t * d;
-    for (int j = threadIdx.x; j < d; j += blockDim.x) dst[j] = to_f32<T>(row[j]);
-}
-
-hipError_t launch_embed(int dtype, const int32_t *ids, const void *E, float *x, int T, int d, int vocab,
-                        hipStream_t s) {
-    if (dtype == 0) embed_kernel<float><<<T, 256, 0, s>>>(ids, (const float *)E, x, T, d, vocab);
-    else embed_kernel<bf16><<<T, 256, 0, s>>>(ids, (const bf16 *)E, x, T, d, vocab);
+hipError_t launch_front(int dtype, const FrontArgs &a, hipStream_t s) {
+    const int n = a.T > a.B ? a.T : a.B;
+    if (dtype == 0) front_kernel<float><<<n, 128, 0, s>>>(a, log((double)a.theta));
+    else front_kernel<bf16><<<n, 128, 0, s>>>(a, log((double)a.theta));
     return hipGetLastError();
 }
 
