@@ -106,7 +106,7 @@ struct WsLayout {
     size_t plan_counts, plan_tiles, plan_items, part_o, part_ml;
     size_t x_last, h_last, attn_last, act_last, plan2_counts, plan2_tiles, plan2_items;   // last layer, last rows only
     size_t splitk, splitk_bytes;                                                        // split-K partial products
-    size_t dec_ctl, dec_ssq;                            // generation-step kernels: control block, partial sums of squares
+    size_t dec_ctl, sk_ssq, sk_sc, kv_row;              // passes over few rows: arrival counters, row statistics; write-back rows
     size_t part_o_bytes, part_ml_bytes;
     size_t total;
     int64_t max_tiles, max_items, max_tiles2, max_items2;
@@ -114,22 +114,24 @@ struct WsLayout {
     int n_slices;
 };
 
-// A pass that the generation-step kernels can take, as far as the model and the batch shape decide it: a bf16 model
-// with 128-wide heads, one new token in each of at most 32 traces.
-bool dec_shape_ok(const confspec_model_cfg &c, int64_t T, int64_t B) {
-    if (c.dtype != CONFSPEC_DTYPE_BF16 || T != B || B < 1 || B > cs::DEC_MAX_ROWS) return false;
-    if (c.head_dim != 128 || c.n_kv_heads < 1 || c.n_q_heads % c.n_kv_heads != 0) return false;
-    const int G = c.n_q_heads / c.n_kv_heads;
-    if (G > cs::DEC_MAX_G || B * c.n_kv_heads > cs::DEC_CTL_TILE - cs::DEC_CTL_ATTN) return false;
-    return c.d_model % 64 == 0 && c.d_ffn % 64 == 0 && c.n_layers > 0;
+// A pass over few rows, as far as the model and the batch shape decide it: its projections are those of skinny_bf16.hip.
+bool skinny_shape_ok(const confspec_model_cfg &c, int64_t T) {
+    return c.dtype == CONFSPEC_DTYPE_BF16 && T >= 1 && T <= cs::SK_MAX_ROWS && c.n_layers > 0 && c.head_dim == 128;
 }
-// Partial planes of the step's four projections (the largest one).
-size_t dec_plane_bytes(const confspec_model_cfg &c) {
+// A pass that the generation-step attention can take, as far as the model and the batch shape decide it: one new token
+// in every trace.
+bool dec_shape_ok(const confspec_model_cfg &c, int64_t T, int64_t B) {
+    if (!skinny_shape_ok(c, T) || T != B) return false;
+    const int G = c.n_q_heads / c.n_kv_heads;
+    return G <= cs::DEC_MAX_G && B * c.n_kv_heads <= cs::DEC_CTL_TILE - cs::DEC_CTL_ATTN;
+}
+// Partial planes of a few-row pass's four projections (the largest one).
+size_t skinny_pass_plane_bytes(const confspec_model_cfg &c, int T) {
     const int qw = c.n_q_heads * c.head_dim, kw = c.n_kv_heads * c.head_dim;
-    size_t m = cs::dec_gemm_plane_bytes(c.d_model, (qw + 2 * kw) / 16);
-    m = std::max(m, cs::dec_gemm_plane_bytes(qw, c.d_model / 16));
-    m = std::max(m, cs::dec_gemm_plane_bytes(c.d_model, c.d_ffn / 8));
-    m = std::max(m, cs::dec_gemm_plane_bytes(c.d_ffn, c.d_model / 16));
+    size_t m = cs::skinny_plane_bytes(T, c.d_model, (qw + 2 * kw) / 16);
+    m = std::max(m, cs::skinny_plane_bytes(T, qw, c.d_model / 16));
+    m = std::max(m, cs::skinny_plane_bytes(T, c.d_model, c.d_ffn / 8));
+    m = std::max(m, cs::skinny_plane_bytes(T, c.d_ffn, c.d_model / 16));
     return m;
 }
 // Partial-result records of the step's attention: traces x pieces of the longest trace.
@@ -162,7 +164,9 @@ WsLayout ws_layout(const confspec_ctx *ctx, int64_t T, int64_t B, const confspec
     w.rope_sin = take((size_t)T * (c.head_dim / 2) * 4);
     w.x = take((size_t)T * c.d_model * 4);
     size_t terms = c.dtype == CONFSPEC_DTYPE_BF16 ? 2 : 1;   // room for hi | lo activations
-    w.h = take((size_t)T * c.d_model * eb * terms);
+    // (rows of activations: a pass over few rows pads them to a multiple of 16, which is at most 2 T from T = 8 on)
+    const size_t a_rows = terms == 2 ? std::max<size_t>((size_t)T * 2, 16) : T;
+    w.h = take(a_rows * c.d_model * eb);
     w.qkv = take((size_t)T * (qw + 2 * kw) * 4);
     w.q = take((size_t)T * qw * eb);
     w.ksuf = take((size_t)T * kw * eb);
@@ -172,8 +176,8 @@ WsLayout ws_layout(const confspec_ctx *ctx, int64_t T, int64_t B, const confspec
         w.ksuf_lo = take((size_t)T * kw * eb);
         w.vsuf_lo = take((size_t)T * kw * eb);
     }
-    w.attn = take((size_t)T * qw * eb * terms);
-    w.act = take((size_t)T * c.d_ffn * eb * terms);
+    w.attn = take(a_rows * qw * eb);
+    w.act = take(a_rows * c.d_ffn * eb);
     if (c.dtype == CONFSPEC_DTYPE_BF16) {
         const int G = c.n_q_heads / c.n_kv_heads;
         cs::attn_plan_capacity(ctx->set.attn, T, B, G, c.n_kv_heads, &w.max_tiles, &w.max_items);
@@ -233,12 +237,15 @@ WsLayout ws_layout(const confspec_ctx *ctx, int64_t T, int64_t B, const confspec
             sk = std::max(sk, cs::gemm_splitk_max_bytes(ctx->set.gemm, (int)T, 2 * c.d_ffn, c.d_model * t));
             sk = std::max(sk, cs::gemm_splitk_max_bytes(ctx->set.gemm, (int)T, c.d_model, c.d_ffn * t));
         }
-        // a general layout serves every smaller batch, generation steps included
-        if (exact ? dec_shape_ok(c, T, B) : dec_shape_ok(c, 1, 1)) sk = std::max(sk, dec_plane_bytes(c));
+        // a general layout serves every smaller batch, few-row passes included
+        const int sk_rows = (int)std::min<int64_t>(T, cs::SK_MAX_ROWS);
+        if (skinny_shape_ok(c, exact ? T : sk_rows)) sk = std::max(sk, skinny_pass_plane_bytes(c, sk_rows));
         w.splitk_bytes = sk;
         w.splitk = take(std::max<size_t>(sk, 256));
         w.dec_ctl = take((size_t)cs::DEC_CTL_INTS * 4);
-        w.dec_ssq = take((size_t)(c.d_model / 16 + 1) * cs::DEC_MAX_ROWS * 4);
+        w.sk_ssq = take((size_t)2 * sk_rows * (c.d_model / 16) * 4);
+        w.sk_sc = take((size_t)2 * sk_rows * 4);
+        w.kv_row = take((size_t)T * 4);
     }
     w.total = at;
     return w;
@@ -403,11 +410,12 @@ int longest_suffix(const confspec_batch *b) {
     return m;
 }
 
-// The token maps of a batch, with the rotary tables (rope) and the embedding rows (w not null).
+// The token maps of a batch, with the rotary tables (rope) and the embedding rows (w not null); more: further outputs of
+// the front kernel, already filled in (may be null).
 int run_front(confspec_ctx *ctx, const confspec_batch *b, int max_L, char *ws, const WsLayout &L, bool rope,
-              const confspec_weights *w, hipStream_t s) {
+              const confspec_weights *w, hipStream_t s, const cs::FrontArgs *more = nullptr) {
     const confspec_model_cfg &c = ctx->cfg;
-    cs::FrontArgs f = {};
+    cs::FrontArgs f = more ? *more : cs::FrontArgs{};
     f.cu = b->cu_suffix; f.plens = b->prefix_lens; f.B = b->B; f.T = b->T; f.max_L = max_L;
     f.tok_trace = (int32_t *)(ws + L.tok_trace); f.tok_pos = (int32_t *)(ws + L.tok_pos); f.last_row = (int32_t *)(ws + L.last_row);
     f.theta = c.rope_theta;
@@ -704,16 +712,17 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
             return 3;
         return 2;
     };
-    // A generation step (one new token per trace, at most 32 traces) runs on the kernels shaped for it when every
-    // layer's operands are single 16-bit values (bf16 or fp16) and the scratch holds its partial results; everything
-    // else, and any step that does not fit, takes the general kernels below.
-    bool use_dec = set.decode_kernels && dec_shape_ok(c, T, B) && !ex.dev_group_start &&
+    // A pass over few rows takes the projections shaped for it (skinny_bf16.hip) when every layer's operands are single
+    // 16-bit values and no launch shape of the general ones is forced; with one new token per trace (a generation step)
+    // also an attention shaped for that, where it is the faster one and the scratch holds its partial results.
+    bool skinny = skinny_shape_ok(c, T) && set.gemm.tile == 0 && set.gemm.splitk == 0;
+    for (int l = 0; l < c.n_layers && skinny; ++l) skinny = rope_fused_in(l) && format_of(l) != 2;
+    skinny = skinny && skinny_pass_plane_bytes(c, T) <= L.splitk_bytes;
+    bool use_dec = skinny && set.decode_kernels && dec_shape_ok(c, T, B) && !ex.dev_group_start &&
                    (set.decode_kernels == 2 || (d <= 64 * cs::DEC_MAX_KT && qw <= 64 * cs::DEC_MAX_KT));
-    int64_t dec_np = 0;
     if (use_dec) {
-        for (int l = 0; l < c.n_layers && use_dec; ++l) use_dec = rope_fused_in(l) && format_of(l) != 2;
-        dec_np = dec_pieces(batch->h_prefix_lens, B);
-        use_dec = use_dec && dec_plane_bytes(c) <= L.splitk_bytes && cs::dec_attn_part_o_bytes(dec_np, c.n_kv_heads) <= L.part_o_bytes &&
+        const int64_t dec_np = dec_pieces(batch->h_prefix_lens, B);
+        use_dec = cs::dec_attn_part_o_bytes(dec_np, c.n_kv_heads) <= L.part_o_bytes &&
                   cs::dec_attn_part_ml_bytes(dec_np, c.n_kv_heads) <= L.part_ml_bytes;
     }
     cs::AttnPlanCounts pc = {}, pc_last = {};
@@ -721,50 +730,58 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
     gr.dev = ex.dev_group_start; gr.host = ex.h_group_start; gr.n = ex.n_groups;
     // Only the last position of each trace feeds the verdict head, so everything of the last layer that
     // comes after its keys and values - attention rows, output projection, MLP - runs on those B rows.
-    const bool prune = c.dtype == CONFSPEC_DTYPE_BF16 && set.prune_last_layer && c.n_layers > 0;
-    if ((rc = run_front(ctx, batch, max_L, ws, L, true, w, s)) != CONFSPEC_OK) return rc;
+    const bool prune = c.dtype == CONFSPEC_DTYPE_BF16 && set.prune_last_layer && c.n_layers > 0 && !skinny;
+    float *ssq[2] = {(float *)(ws + L.sk_ssq), (float *)(ws + L.sk_ssq) + (size_t)T * (d / 16)};
+    float *sc[2] = {(float *)(ws + L.sk_sc), (float *)(ws + L.sk_sc) + T};
+    int32_t *ctl = (int32_t *)(ws + L.dec_ctl);
+    cs::FrontArgs front = {};
+    if (skinny) {
+        front.ctl = ctl; front.n_ctl = cs::DEC_CTL_INTS;
+        front.g = w->attn_norm[0]; front.xg = h; front.xg_fmt = format_of(0);
+        front.ssq = ssq[0]; front.sc = sc[0]; front.ssq_n = d / 16; front.eps = c.rms_eps;
+        if (dev_n_append) {
+            front.table = kv->block_table; front.n_append = dev_n_append;
+            front.max_blocks = kv->max_blocks_per_seq; front.n_blocks = kv->n_blocks; front.block_size = kv->block_size;
+            front.kv_row = (int32_t *)(ws + L.kv_row);
+        }
+    }
+    if ((rc = run_front(ctx, batch, max_L, ws, L, true, w, s, &front)) != CONFSPEC_OK) return rc;
     if (c.dtype == CONFSPEC_DTYPE_BF16 && !use_dec) {   // (the generation-step attention has its own, fixed cut into pieces)
         if ((rc = run_attn_plan(ctx, batch, gr, max_L, ws, L, false, &pc, s)) != CONFSPEC_OK) return rc;
         if (prune && (rc = run_attn_plan(ctx, batch, gr, max_L, ws, L, true, &pc_last, s)) != CONFSPEC_OK) return rc;
     }
     const int32_t *last_row = (const int32_t *)(ws + L.last_row);
-    if (use_dec) {
-        int32_t *ctl = (int32_t *)(ws + L.dec_ctl);
-        HIP_TRY(cs::launch_dec_init(ctl, s));
-        const size_t layer_bytes = (size_t)kv->n_blocks * c.n_kv_heads * kv->block_size * c.head_dim * eb;
-        // The RMSNorm in front of the QKV and gate/up projections: the residual projection before writes x * gain in
-        // the operand format and per-row partial sums of squares, the consumer scales its result rows (decode_bf16.hip).
-        // The first layer's input comes from the embedding: the RMSNorm kernel, once.
-        float *ssq = (float *)(ws + L.dec_ssq);
-        const int ssq_n = d / 16;
-        HIP_TRY(mark(CONFSPEC_PHASE_NORM));
-        HIP_TRY(cs::launch_rmsnorm(c.dtype, x, w->attn_norm[0], h, T, d, c.rms_eps, format_of(0), s));
-        auto proj = [&](cs::DecGemm &g, const void *X, int ldx, const void *W, int K, int n_ct) {
-            g.X = (const cs::bf16 *)X; g.ldx = ldx; g.W = (const cs::bf16 *)W; g.M = B; g.K = K; g.n_ct = n_ct;
-            cs::dec_gemm_plan(K, n_ct, &g.S, &g.nwg);
-            g.planes = (float *)(ws + L.splitk);
-            g.tile_cnt = ctl + cs::DEC_CTL_TILE;
+    const size_t layer_bytes = (size_t)kv->n_blocks * c.n_kv_heads * kv->block_size * c.head_dim * eb;
+    for (int l = 0; l < c.n_layers && skinny; ++l) {
+        // The RMSNorms are part of the projections around them: statistics and operand of the QKV projection's input in
+        // ssq[0] / sc[0] / h (left by the front kernel or the previous layer's down projection), of the gate/up projection's
+        // in ssq[1] / sc[1] / h (left by the output projection).
+        const int tm = format_of(l);
+        const bool f16 = tm == 3, prec = l < set.attn_precise_layers;
+        const void *wqkv = f16 ? w->wqkv_f16[l] : w->wqkv_perm[l], *wo = f16 ? w->wo_f16[l] : w->wo[l];
+        const void *wgu = f16 ? w->w_gate_up_f16[l] : w->w_gate_up[l], *wdn = f16 ? w->w_down_f16[l] : w->w_down[l];
+        cs::SkinnyGemm base = {};
+        base.M = T; base.d_norm = d; base.ssq_n = d / 16; base.eps = c.rms_eps;
+        base.planes = (float *)(ws + L.splitk); base.tile_cnt = ctl + cs::DEC_CTL_TILE;
+        auto proj = [&](const void *X, const void *W, int K, int n_ct, int stat) {
+            cs::SkinnyGemm g = base;
+            g.X = (const cs::bf16 *)X; g.W = (const cs::bf16 *)W; g.K = K; g.n_ct = n_ct;
+            g.ssq_in = ssq[stat]; g.sc_in = sc[stat];
+            return g;
         };
-        for (int l = 0; l < c.n_layers; ++l) {
-            const int tm = format_of(l);
-            const bool f16 = tm == 3;
-            const void *wqkv = f16 ? w->wqkv_f16[l] : w->wqkv_perm[l], *wo = f16 ? w->wo_f16[l] : w->wo[l];
-            const void *wgu = f16 ? w->w_gate_up_f16[l] : w->w_gate_up[l], *wdn = f16 ? w->w_down_f16[l] : w->w_down[l];
-            HIP_TRY(mark(CONFSPEC_PHASE_QKV));
-            cs::DecGemm gq = {};
-            proj(gq, h, d, wqkv, d, (qw + 2 * kw) / 16);
-            if (l > 0) { gq.ssq_in = ssq; gq.ssq_n = ssq_n; gq.eps = c.rms_eps; }
-            gq.rope = cs::RopeArgs{(const float *)(ws + L.rope_cos), (const float *)(ws + L.rope_sin), ws + L.q, ws + L.ksuf, ws + L.vsuf,
-                                   ws + L.q_lo, nullptr, nullptr, c.n_q_heads, c.n_kv_heads};
-            gq.perm = 1;
-            if (dev_n_append) {
-                gq.k_pages = (char *)const_cast<void *>(kv->k_pages) + layer_bytes * l;
-                gq.v_pages = (char *)const_cast<void *>(kv->v_pages) + layer_bytes * l;
-                gq.table = kv->block_table; gq.plens = batch->prefix_lens; gq.n_append = dev_n_append;
-                gq.max_blocks = kv->max_blocks_per_seq; gq.n_blocks = kv->n_blocks;
-            }
-            HIP_TRY(cs::launch_dec_gemm(gq, cs::DEC_EPI_ROPE, f16, s));
-            HIP_TRY(mark(CONFSPEC_PHASE_ATTN));
+        HIP_TRY(mark(CONFSPEC_PHASE_QKV));
+        cs::SkinnyGemm gq = proj(h, wqkv, d, (qw + 2 * kw) / 16, 0);
+        gq.rope = cs::RopeArgs{(const float *)(ws + L.rope_cos), (const float *)(ws + L.rope_sin), ws + L.q, ws + L.ksuf, ws + L.vsuf,
+                               use_dec || prec ? ws + L.q_lo : nullptr, !use_dec && prec ? ws + L.ksuf_lo : nullptr,
+                               !use_dec && prec ? ws + L.vsuf_lo : nullptr, c.n_q_heads, c.n_kv_heads};
+        if (dev_n_append) {     // (the attention that follows never reads rows at or past L_b)
+            gq.kv_row = (const int32_t *)(ws + L.kv_row);
+            gq.k_pages = (char *)const_cast<void *>(kv->k_pages) + layer_bytes * l;
+            gq.v_pages = (char *)const_cast<void *>(kv->v_pages) + layer_bytes * l;
+        }
+        HIP_TRY(cs::launch_skinny(gq, cs::SK_EPI_ROPE, f16, s));
+        HIP_TRY(mark(prec && !use_dec ? CONFSPEC_PHASE_ATTN_PRECISE : CONFSPEC_PHASE_ATTN));
+        if (use_dec) {
             cs::DecAttn at = {};
             at.q = (const cs::bf16 *)(ws + L.q); at.q_lo = (const cs::bf16 *)(ws + L.q_lo);
             at.ksuf = (const cs::bf16 *)(ws + L.ksuf); at.vsuf = (const cs::bf16 *)(ws + L.vsuf);
@@ -779,26 +796,27 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
             at.n_iter = cs::dec_attn_rounds(B, c.n_kv_heads, max_L);
             at.max_pieces = max_L / (cs::DEC_PIECE * at.n_iter) + 1;
             HIP_TRY(cs::launch_dec_attn(at, s));
-            HIP_TRY(mark(CONFSPEC_PHASE_O_PROJ));
-            cs::DecGemm go = {};
-            proj(go, ws + L.attn, qw, wo, qw, d / 16);
-            go.x = x; go.xg_out = h; go.g_next = (const cs::bf16 *)w->mlp_norm[l]; go.ssq_out = ssq; go.xg_fmt = tm;
-            HIP_TRY(cs::launch_dec_gemm(go, cs::DEC_EPI_RESID, f16, s));
-            HIP_TRY(mark(CONFSPEC_PHASE_GATE_UP));
-            cs::DecGemm gg = {};
-            proj(gg, h, d, wgu, d, c.d_ffn / 8);
-            gg.ssq_in = ssq; gg.ssq_n = ssq_n; gg.eps = c.rms_eps;
-            gg.act = ws + L.act; gg.act_fmt = tm;
-            HIP_TRY(cs::launch_dec_gemm(gg, cs::DEC_EPI_SWIGLU, f16, s));
-            HIP_TRY(mark(CONFSPEC_PHASE_DOWN));
-            cs::DecGemm gd = {};
-            proj(gd, ws + L.act, c.d_ffn, wdn, c.d_ffn, d / 16);
-            gd.x = x;
-            if (l + 1 < c.n_layers) {   // the next layer's operand, in that layer's format
-                gd.xg_out = h; gd.g_next = (const cs::bf16 *)w->attn_norm[l + 1]; gd.ssq_out = ssq; gd.xg_fmt = format_of(l + 1);
-            }
-            HIP_TRY(cs::launch_dec_gemm(gd, cs::DEC_EPI_RESID, f16, s));
+        } else {
+            cs::AttnArgs a = make_attn_args(c, kv, batch, (const int32_t *)(ws + L.tok_trace), l, ws + L.q, ws + L.ksuf, ws + L.vsuf,
+                                            gq.rope.q_lo, gq.rope.k_lo, gq.rope.v_lo, ws + L.attn, tm);
+            a.out_frag = 1;
+            if ((rc = run_attention(ctx, a, ws, L, pc, false, 0, s))) return rc;
         }
+        HIP_TRY(mark(CONFSPEC_PHASE_O_PROJ));
+        cs::SkinnyGemm go = proj(ws + L.attn, wo, qw, d / 16, 0);
+        go.x = x; go.xg_out = h; go.g_next = (const cs::bf16 *)w->mlp_norm[l]; go.ssq_out = ssq[1]; go.sc_out = sc[1]; go.xg_fmt = tm;
+        HIP_TRY(cs::launch_skinny(go, cs::SK_EPI_RESID, f16, s));
+        HIP_TRY(mark(CONFSPEC_PHASE_GATE_UP));
+        cs::SkinnyGemm gg = proj(h, wgu, d, c.d_ffn / 8, 1);
+        gg.act = ws + L.act; gg.act_fmt = tm;
+        HIP_TRY(cs::launch_skinny(gg, cs::SK_EPI_SWIGLU, f16, s));
+        HIP_TRY(mark(CONFSPEC_PHASE_DOWN));
+        cs::SkinnyGemm gd = proj(ws + L.act, wdn, c.d_ffn, d / 16, 1);
+        gd.x = x;
+        if (l + 1 < c.n_layers) {   // the next layer's operand, in that layer's format
+            gd.xg_out = h; gd.g_next = (const cs::bf16 *)w->attn_norm[l + 1]; gd.ssq_out = ssq[0]; gd.sc_out = sc[0]; gd.xg_fmt = format_of(l + 1);
+        }
+        HIP_TRY(cs::launch_skinny(gd, cs::SK_EPI_RESID, f16, s));
     }
     const bool f32 = c.dtype == CONFSPEC_DTYPE_FP32;
     const int max_S = f32 ? longest_suffix(batch) : 0;
@@ -817,7 +835,6 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         if ((rc = run_attention(ctx, a, ws, L, pc, false, max_S, s))) return rc;
         if (dev_n_append) {
             HIP_TRY(mark(CONFSPEC_PHASE_OTHER));
-            size_t layer_bytes = (size_t)kv->n_blocks * c.n_kv_heads * kv->block_size * c.head_dim * eb;
             HIP_TRY(cs::launch_kv_append(ws + L.ksuf, ws + L.vsuf, (char *)const_cast<void *>(kv->k_pages) + layer_bytes * l,
                                          (char *)const_cast<void *>(kv->v_pages) + layer_bytes * l, kv->block_table,
                                          batch->cu_suffix, batch->prefix_lens, dev_n_append,
@@ -833,7 +850,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         if ((rc = run_gemm(ctx, ws + L.act, w->w_down[l], x, T, d, c.d_ffn, cs::EPI_RESID_F32, 1, 1, s))) return rc;
     }
     bool attn_norm_done = false;   // the previous layer's down projection already wrote this layer's normalised input
-    for (int l = 0; l < c.n_layers && !use_dec && !f32; ++l) {
+    for (int l = 0; l < c.n_layers && !skinny && !f32; ++l) {
         const int tm = format_of(l);
         const void *wqkv = w->wqkv[l], *wo = w->wo[l], *wgu = w->w_gate_up[l], *wdn = w->w_down[l];
         const bool rope_fused = rope_fused_in(l);
@@ -869,7 +886,6 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         HIP_TRY(mark(CONFSPEC_PHASE_OTHER));
         if (dev_n_append) {
             // after this layer's attention has read the pages (it never reads rows at or past L_b anyway)
-            size_t layer_bytes = (size_t)kv->n_blocks * c.n_kv_heads * kv->block_size * c.head_dim * eb;
             HIP_TRY(cs::launch_kv_append(ws + L.ksuf, ws + L.vsuf, (char *)const_cast<void *>(kv->k_pages) + layer_bytes * l,
                                          (char *)const_cast<void *>(kv->v_pages) + layer_bytes * l, kv->block_table,
                                          batch->cu_suffix, batch->prefix_lens, dev_n_append,
@@ -923,10 +939,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         dev_accept = (uint8_t *)(hs + HL.v_accept);
     }
     if (want_verdict) {
-        if (use_dec)         // every row is the last row of its trace
-            HIP_TRY(cs::launch_verdict(c.dtype, x, nullptr, w->final_norm, w->lm_head, va, B, B, d, c.rms_eps, dev_verdict_logits,
-                                       dev_conf, dev_verdict, dev_accept, s));
-        else if (prune)
+        if (prune)
             HIP_TRY(cs::launch_verdict(c.dtype, (const float *)(ws + L.x_last), nullptr, w->final_norm, w->lm_head, va, B, B, d,
                                        c.rms_eps, dev_verdict_logits, dev_conf, dev_verdict, dev_accept, s));
         else
@@ -937,23 +950,24 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         // Logits of the whole vocabulary at the last position of every trace: final norm of those B rows (two bf16
         // terms, so the operand carries ~16 mantissa bits), one GEMM against the head, then arg max / log-sum-exp.
         char *hs = (char *)ex.head_scratch;
-        const float *xl = use_dec ? x : (const float *)(ws + L.x_last);
-        if (!prune && !use_dec) {
+        const float *xl = T == B ? x : (const float *)(ws + L.x_last);     // (T == B: every row is the last row of its trace)
+        if (prune) xl = (const float *)(ws + L.x_last);
+        else if (T != B) {
             HIP_TRY(cs::launch_gather_rows(x, hs + HL.x, last_row, B, T, (size_t)d * 4, s));
             xl = (const float *)(hs + HL.x);
         }
         const bool bf = c.dtype == CONFSPEC_DTYPE_BF16;
         HIP_TRY(cs::launch_rmsnorm(c.dtype, xl, w->final_norm, hs + HL.y, B, d, c.rms_eps, bf ? 2 : 1, s));
-        if (use_dec && d <= 64 * cs::DEC_MAX_KT && c.vocab % 16 == 0) {
+        if (use_dec && B <= cs::DEC_MAX_ROWS && d <= 64 * cs::DEC_MAX_KT && c.vocab % 16 == 0) {
             // generation step: the head streams once against the B rows, and every workgroup keeps only the running
             // (max, arg max, sum of exponentials) of its columns - the [B, vocab] logits are never written
-            cs::DecGemm gh = {};
-            gh.X = (const cs::bf16 *)(hs + HL.y); gh.ldx = 2 * d; gh.W = (const cs::bf16 *)w->lm_head; gh.M = B; gh.K = d;
+            cs::DecHead gh = {};
+            gh.X = (const cs::bf16 *)(hs + HL.y); gh.W = (const cs::bf16 *)w->lm_head; gh.M = B; gh.K = d;
             gh.n_ct = c.vocab / 16;
-            cs::dec_gemm_plan(d, gh.n_ct, &gh.S, &gh.nwg);
-            gh.head_part = (float *)(hs + HL.part);
-            HIP_TRY(cs::launch_dec_gemm(gh, cs::DEC_EPI_HEAD, false, s));
-            HIP_TRY(cs::launch_dec_head_final(gh.head_part, gh.nwg, B, want_verdict ? dev_verdict_logits : nullptr, va.n_verdict,
+            gh.nwg = std::min(gh.n_ct, 256);
+            gh.part = (float *)(hs + HL.part);
+            HIP_TRY(cs::launch_dec_head(gh, s));
+            HIP_TRY(cs::launch_dec_head_final(gh.part, gh.nwg, B, want_verdict ? dev_verdict_logits : nullptr, va.n_verdict,
                                               ex.head->token, ex.head->max_logit, ex.head->lse,
                                               want_verdict ? ex.head->conf_full : nullptr, s));
             HIP_TRY(mark(CONFSPEC_PHASE_END));

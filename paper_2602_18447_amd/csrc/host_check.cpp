@@ -15,9 +15,10 @@
 #include "../../include/confspec_static.h"
 #include "attn_plan.h"
 
-namespace cs {   // decode_bf16.hip: slices and workgroups of a generation step's projection
-void dec_gemm_plan(int K, int n_ct, int *S, int *nwg);
-size_t dec_gemm_plane_bytes(int K, int n_ct);
+namespace cs {   // skinny_bf16.hip: tiling of a projection over few rows
+struct SkinnyPlan { int mb, ms, ct, S; };
+SkinnyPlan skinny_plan(int M, int K, int n_ct);
+size_t skinny_plane_bytes(int M, int K, int n_ct);
 }
 
 static int g_fail = 0;
@@ -252,28 +253,28 @@ int main() {
         check_plan(t, b, h[0], h[1], 1, what);
         if (iter % 200 == 0) check_library(draft, b, what);
     }
-    // slices of the generation step's projections: every k-tile in exactly one slice of at most 24, at most 256
-    // column groups (one arrival counter each) and no more than there are column tiles, planes sized for the slices
+    // tiling of the few-row projections: the rows covered, tiles that divide the columns, every k-tile in exactly one
+    // slice, no more cut tiles than there are arrival counters, planes sized for the slices and growing with the rows
     for (int iter = 0; iter < 20000; ++iter) {
-        int K = 64 * (1 + (int)(rng() % 600)), n_ct = 1 + (int)(rng() % 12000);
+        int K = 64 * (1 + (int)(rng() % 600)), n_ct = 1 + (int)(rng() % 12000), M = 1 + (int)(rng() % 128);
         if (iter < 8) {
             const int shapes[8][2] = {{1536, 128}, {1536, 96}, {1536, 1120}, {8960, 96}, {5120, 448}, {5120, 320}, {5120, 3456}, {27648, 320}};
             K = shapes[iter][0]; n_ct = shapes[iter][1];
         }
-        int S = 0, nwg = 0;
-        cs::dec_gemm_plan(K, n_ct, &S, &nwg);
+        const cs::SkinnyPlan p = cs::skinny_plan(M, K, n_ct);
         const int nk = K / 64;
-        bool ok = S >= 1 && S <= nk && nwg >= 1 && nwg <= n_ct && nwg <= 256 && (nk + S - 1) / S <= 24;
+        bool ok = p.mb >= 1 && p.ms >= 1 && p.mb * p.ms * 16 >= M && (p.ms - 1) * p.mb * 16 < M && p.ct >= 1 && n_ct % p.ct == 0 && p.S >= 1 &&
+                  p.S <= nk && (p.S == 1 || n_ct / p.ct * p.ms <= 256);
         int covered = 0;
-        for (int sl = 0; ok && sl < S; ++sl) {
-            int k0 = (int)((long)sl * nk / S), k1 = (int)((long)(sl + 1) * nk / S);
-            ok = k1 > k0 && k1 - k0 <= 24 && k0 == covered;
+        for (int sl = 0; ok && sl < p.S; ++sl) {
+            int k0 = (int)((long)sl * nk / p.S), k1 = (int)((long)(sl + 1) * nk / p.S);
+            ok = k1 > k0 && k0 == covered;
             covered = k1;
         }
         ok = ok && covered == nk;
-        size_t pb = cs::dec_gemm_plane_bytes(K, n_ct);
-        ok = ok && pb == (S > 1 ? (size_t)S * 32 * n_ct * 16 * 4 : 0);
-        if (!ok) { printf("dec_gemm_plan(K=%d, n_ct=%d) -> S=%d nwg=%d planes=%zu\n", K, n_ct, S, nwg, pb); ++g_fail; }
+        size_t pb = cs::skinny_plane_bytes(M, K, n_ct);
+        ok = ok && pb >= (p.S > 1 ? (size_t)p.S * 16 * p.mb * p.ms * n_ct * 16 * 4 : 0) && pb <= cs::skinny_plane_bytes(128, K, n_ct);
+        if (!ok) { printf("skinny_plan(M=%d, K=%d, n_ct=%d) -> mb=%d ms=%d ct=%d S=%d planes=%zu\n", M, K, n_ct, p.mb, p.ms, p.ct, p.S, pb); ++g_fail; }
     }
     if (g_fail) { printf("host_check: %d check(s) failed\n", g_fail); return 1; }
     printf("host_check: ok\n");

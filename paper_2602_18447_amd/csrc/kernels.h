@@ -40,6 +40,12 @@ inline hipError_t set_dynamic_lds_once(std::atomic<uint32_t> &mask, const void *
     return hipSuccess;
 }
 
+// Activations of a pass over few rows are kept in fragment order: element (row, k) of a matrix of width K (K % 32 == 0).  The 16 rows x 32 k
+// of one 16x16x32 MFMA operand are 1 KiB in lane order: [k / 8 % 4][row % 16][k % 8].  Rows are padded to a multiple of 16.
+__host__ __device__ inline size_t frag_index(int row, int k, int K) {
+    return ((size_t)(row >> 4) * (K >> 5) + (k >> 5)) * 512 + ((k & 31) >> 3) * 128 + (row & 15) * 8 + (k & 7);
+}
+
 // ---- attention work description and planner arithmetic: attn_plan.h ----
 
 enum Epilogue : int { EPI_STORE_F32 = 0, EPI_RESID_F32 = 1, EPI_SWIGLU = 2, EPI_ROPE = 3 };
@@ -69,6 +75,19 @@ struct FrontArgs {
     const void *E;
     float *x;
     int32_t d, vocab;
+    // passes over few rows (null otherwise): control block to clear (n_ctl ints); operand, power of two and sums of
+    // squares of the first projection as SkinnyGemm has them (gain g, 16-bit storage)
+    int32_t *ctl;
+    int32_t n_ctl;
+    const void *g;
+    void *xg;
+    float *ssq, *sc;
+    int32_t ssq_n, xg_fmt;
+    float eps;
+    // write-back (n_append not null): token row of the cache each token goes to, or -1
+    const int32_t *table, *n_append;
+    int32_t max_blocks, n_blocks, block_size;
+    int32_t *kv_row;
 };
 hipError_t launch_front(int dtype, const FrontArgs &a, hipStream_t s);
 // x fp32 [T,d] -> out (storage dtype) [T, d]; terms == 2 (bf16 only): [T, 2d] hi | lo two-term form;
@@ -167,6 +186,7 @@ struct AttnArgs {
     int32_t B, T, Hq, Hkv, hd, n_blocks, block_size, max_blocks;
     float scale;            // 1/sqrt(hd)
     int32_t out_terms;
+    int32_t out_frag;       // 1: out in fragment order (frag_index, width Hq*hd; out_terms 1 or 3)
 };
 hipError_t launch_attn_f32(const AttnArgs &a, int max_S, hipStream_t s);   // max_S: longest suffix of the batch
 
@@ -190,58 +210,65 @@ hipError_t launch_kv_append(const void *ksuf, const void *vsuf, void *k_pages, v
                             int B, int T, int Hkv, size_t head_row_bytes, int block_size, int max_blocks, int n_blocks,
                             hipStream_t s);
 
-// ---- generation steps: one new token per trace (decode_bf16.hip) ----
-constexpr int DEC_MAX_ROWS = 32;     // traces of a step the decode-shaped kernels take
-constexpr int DEC_PIECE = 256;       // keys per attention workgroup
-constexpr int DEC_MAX_G = 8;         // q heads per kv head
-constexpr int DEC_MAX_KT = 24;       // k-tiles (of 64) of one k slice of a projection: 96 KiB of activations in LDS
-// control block (int32): the arrival counters
-constexpr int DEC_CTL_ATTN = 0;                          // + trace * Hkv + kv head
-constexpr int DEC_CTL_TILE = DEC_CTL_ATTN + 1024;        // + column group of a sliced projection (<= 256)
-constexpr int DEC_CTL_INTS = DEC_CTL_TILE + 256;
-enum DecEpilogue : int { DEC_EPI_ROPE = 0, DEC_EPI_RESID = 1, DEC_EPI_SWIGLU = 2, DEC_EPI_HEAD = 3 };
-
-// One projection of a step: out = X[M, K] . W[N, K]^T, M <= 32, K % 64 == 0, N % 16 == 0, then the epilogue.
-struct DecGemm {
-    const bf16 *X;            // [M, ldx], bf16 or (f16 != 0) IEEE half
-    // ssq_in != null (ROPE, SWIGLU): X holds x * g without the 1 / rms factor of the RMSNorm; ssq_in [ssq_n, 32] are
-    // partial sums of squares of every row (left by the preceding residual projection), the result rows are scaled by
-    // 1 / sqrt(sum / K + eps)
-    const float *ssq_in;
-    int32_t ssq_n;
-    float eps;
+// ---- passes over few rows (skinny_bf16.hip) ----
+constexpr int SK_MAX_ROWS = 128;          // suffix tokens of a pass that takes these projections
+constexpr int SK_MAX_TILES_CUT = 256;     // workgroup tiles of a projection whose k range is cut (one arrival counter each)
+enum SkinnyEpilogue : int { SK_EPI_ROPE = 0, SK_EPI_RESID = 1, SK_EPI_SWIGLU = 2 };
+// One projection: out = X[M, K] . W[N, K]^T, M <= SK_MAX_ROWS, K % 64 == 0, then the epilogue.
+struct SkinnyGemm {
+    const bf16 *X;            // [M, K] in fragment order, bf16 or (f16) IEEE half
     const bf16 *W;            // [N, K], same element type
-    int32_t ldx, M, K;
+    int32_t M, K;
     int32_t n_ct;             // 16-column tiles of the accumulator: N / 16 (ROPE, RESID), N / 16 = F / 8 (SWIGLU)
-    int32_t S, nwg;           // k slices and workgroups per slice (dec_gemm_plan)
-    float *planes;            // S > 1: [S, 32, 16 n_ct] fp32 partial products
-    int32_t *tile_cnt;        // S > 1: nwg arrival counters (zero before and after the launch)
-    // RESID: x [M, N] fp32 += product.  With xg_out (may be null) it also writes the operand of the projection that
-    // follows, x * g_next in format xg_fmt (1 bf16, 3 half) [M, N], and ssq_out [N / 16, 32]: the sum of squares of
-    // each 16 columns of every updated row.
+    int32_t S, ms;            // k slices, blocks of rows (set by the launcher)
+    float *planes;            // skinny_plane_bytes; null when that is 0
+    int32_t *tile_cnt;        // SK_MAX_TILES_CUT arrival counters (zero before and after the launch)
+    // ROPE, SWIGLU: X holds x * gain * sc; ssq_in [M, ssq_n] are partial sums of squares of the rows x of width d_norm, the
+    // result rows are scaled by 1 / sqrt(sum / d_norm + eps) / sc_in.
+    // RESID with xg_out: the same two of the rows before the update, which the new power of two is taken from.
+    const float *ssq_in, *sc_in;
+    int32_t ssq_n, d_norm;
+    float eps;
+    // RESID: x [M, N] fp32 += product.  With xg_out (may be null) it also writes the next projection's operand
+    // x * g_next * sc in format xg_fmt (1 bf16, 3 half) [M, N] in fragment order, the powers of two sc_out [M], and
+    // ssq_out [M, N / 16].
     float *x;
     void *xg_out;
     const bf16 *g_next;
-    float *ssq_out;
+    float *ssq_out, *sc_out;
     int32_t xg_fmt;
-    // SWIGLU: W rows are gate / up interleaved in groups of 32; act [M, F] in format act_fmt (1 or 3)
+    // SWIGLU: W rows are gate / up interleaved in groups of 32; act [M, F] in fragment order, format act_fmt (1 or 3)
     void *act;
     int32_t act_fmt;
-    // HEAD: X is [M, 2 K] two-term bf16 (hi | lo), W the [vocab, K] head; the logits are never stored: every workgroup
-    // leaves (max, index of the first max, sum of exp(z - max)) of its columns per row in head_part [nwg, 32, 4] fp32
-    float *head_part;
-    // ROPE: the QKV projection; perm != 0: W rows of every head reordered [0..31 | 64..95 | 32..63 | 96..127].
-    // q also leaves its second bf16 term in rope.q_lo when that is not null.  With n_append (dev, may be null) the new
-    // key / value row of every trace b with n_append[b] > 0 is also written to row plens[b] of its paged cache.
+    // ROPE: the QKV projection, W rows of every head ordered [0..31 | 64..95 | 32..63 | 96..127].  With kv_row (may be
+    // null) the key / value of row m also goes to token row kv_row[m] of this layer's pages where that is not negative.
     RopeArgs rope;
-    int32_t perm;
-    void *k_pages, *v_pages;  // this layer's pages
-    const int32_t *table, *plens, *n_append;
-    int32_t max_blocks, n_blocks;
+    const int32_t *kv_row;
+    void *k_pages, *v_pages;
 };
-void dec_gemm_plan(int K, int n_ct, int *S, int *nwg);
-size_t dec_gemm_plane_bytes(int K, int n_ct);      // 0 when the projection needs no partial planes
-hipError_t launch_dec_gemm(const DecGemm &a, int epi, bool f16, hipStream_t s);
+struct SkinnyPlan { int mb, ms, ct, S; };
+SkinnyPlan skinny_plan(int M, int K, int n_ct);
+size_t skinny_plane_bytes(int M, int K, int n_ct);      // for up to M rows; 0 when no k range is cut
+hipError_t launch_skinny(SkinnyGemm a, int epi, bool f16, hipStream_t s);
+
+// ---- generation steps: one new token per trace (decode_bf16.hip) ----
+constexpr int DEC_MAX_ROWS = 32;     // traces the language-model head of these kernels takes
+constexpr int DEC_PIECE = 256;       // keys per attention workgroup
+constexpr int DEC_MAX_G = 8;         // q heads per kv head
+constexpr int DEC_MAX_KT = 24;       // k-tiles (of 64) of the head's rows
+// control block (int32): the arrival counters
+constexpr int DEC_CTL_ATTN = 0;                          // + trace * Hkv + kv head
+constexpr int DEC_CTL_TILE = DEC_CTL_ATTN + 1024;        // + tile of a projection whose k range is cut
+constexpr int DEC_CTL_INTS = DEC_CTL_TILE + SK_MAX_TILES_CUT;
+
+// Head over the whole vocabulary: X is [M, 2 K] two-term bf16 (hi | lo), W the [16 n_ct, K] head; every one of the nwg
+// workgroups leaves (max, index of the first max, sum of exp(z - max)) of its columns per row in part [nwg, 32, 4] fp32.
+struct DecHead {
+    const bf16 *X, *W;
+    int32_t M, K, n_ct, nwg;
+    float *part;
+};
+hipError_t launch_dec_head(const DecHead &a, hipStream_t s);
 // token / max logit / log-sum-exp (and conf_full, with verdict logits) of B rows from the nwg records per row
 hipError_t launch_dec_head_final(const float *part, int nwg, int B, const float *verdict_logits, int n_verdict, int32_t *token,
                                  float *max_logit, float *lse, float *conf_full, hipStream_t s);
@@ -251,15 +278,14 @@ struct DecAttn {
     const bf16 *ksuf, *vsuf;          // [B, Hkv, 128]: key / value of the new token
     const bf16 *k_pages, *v_pages;    // this layer's pages [n_blocks, Hkv, 16, 128]
     const int32_t *table, *plens;
-    int32_t *ctl;                     // control block (launch_dec_init)
-    void *out;                        // [B, Hq * 128] in format out_fmt (1 bf16, 3 half; 2: [B, 2 Hq 128] hi | lo)
+    int32_t *ctl;                     // control block, zero
+    void *out;                        // [B, Hq * 128] in fragment order, format out_fmt (1 bf16, 3 half)
     float *part_o, *part_ml;          // per (trace, piece, kv head): [8, 128] and [8, 2] fp32; B * max_pieces * Hkv of them
     int32_t B, Hq, Hkv, G, max_blocks, n_blocks, max_L, out_fmt;
     int32_t n_iter;                   // rounds of DEC_PIECE keys per workgroup (dec_attn_rounds)
     int32_t max_pieces;               // pieces of the longest trace: max_L / (DEC_PIECE * n_iter) + 1
     float scale_log2;                 // log2(e) / sqrt(head_dim)
 };
-hipError_t launch_dec_init(int32_t *ctl, hipStream_t s);
 int dec_attn_rounds(int B, int Hkv, int max_L);
 hipError_t launch_dec_attn(const DecAttn &a, hipStream_t s);
 inline size_t dec_attn_part_o_bytes(int64_t n_pieces, int Hkv) { return (size_t)n_pieces * Hkv * DEC_MAX_G * 128 * 4; }

@@ -20,6 +20,17 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
+template <typename T>
+__device__ __forceinline__ void store_terms(T *o, int c, int d, int terms, float v) {
+    if (sizeof(T) == 2 && terms == 3) {
+        reinterpret_cast<__half *>(o)[c] = to_half_sat(v);
+        return;
+    }
+    T hi = from_f32<T>(v);
+    o[c] = hi;
+    if (terms == 2) o[d + c] = from_f32<T>(v - to_f32<T>(hi));
+}
+
 // ------------------------------------------------------------------------------------------------
 // Front of a pass, one workgroup per token: token -> (trace, absolute position); last suffix row of each trace; the
 // token's rotary table row, cos / sin of pos * theta^(-2i/hd), evaluated in double so that positions in the tens of
@@ -30,6 +41,8 @@ __device__ __forceinline__ float wave_sum(float v) {
 template <typename E>
 __global__ __launch_bounds__(128) void front_kernel(FrontArgs a, double log_theta) {
     const int t = blockIdx.x;
+    if (t == 0 && a.ctl)
+        for (int i = threadIdx.x; i < a.n_ctl; i += blockDim.x) a.ctl[i] = 0;
     if (threadIdx.x == 0 && t < a.B) a.last_row[t] = min(max(a.cu[t + 1] - 1, 0), a.T - 1);
     if (t >= a.T) return;
     int lo = 0, hi = a.B - 1;  // largest b with cu[b] <= t
@@ -42,6 +55,13 @@ __global__ __launch_bounds__(128) void front_kernel(FrontArgs a, double log_thet
     if (threadIdx.x == 0) {
         a.tok_trace[t] = lo;
         a.tok_pos[t] = pos;
+        if (a.kv_row) {
+            const int i = t - a.cu[lo], row = a.plens[lo] + i;
+            int dst = -1;
+            if (i >= 0 && i < a.n_append[lo] && row >= 0 && row < a.max_blocks * a.block_size)
+                dst = min(max(a.table[(size_t)lo * a.max_blocks + row / a.block_size], 0), a.n_blocks - 1) * a.block_size + row % a.block_size;
+            a.kv_row[t] = dst;
+        }
     }
     if (a.x) {
         const int id = min(max(a.ids[t], 0), a.vocab - 1);
@@ -55,6 +75,25 @@ __global__ __launch_bounds__(128) void front_kernel(FrontArgs a, double log_thet
                 dst[j] = make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
                                      __uint_as_float(v.y & 0xffff0000u));
             }
+        }
+    }
+    if constexpr (sizeof(E) == 2) {
+        if (a.xg) {
+            __shared__ float part[2];
+            const int id = min(max(a.ids[t], 0), a.vocab - 1);
+            const E *row = reinterpret_cast<const E *>(a.E) + (size_t)id * a.d;
+            float ss = 0.f;
+            for (int j = threadIdx.x; j < a.d; j += blockDim.x) { const float v = to_f32<E>(row[j]); ss += v * v; }
+            ss = wave_sum(ss);
+            if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
+            __syncthreads();
+            ss = part[0] + part[1];
+            const float r = 1.0f / sqrtf(ss / (float)a.d + a.eps);
+            const float sc = __uint_as_float(__float_as_uint(fminf(fmaxf(r, 0x1p-60f), 0x1p60f)) & 0x7f800000u);
+            for (int j = threadIdx.x; j < a.d; j += blockDim.x)
+                store_terms<E>(reinterpret_cast<E *>(a.xg), (int)frag_index(t, j, a.d), 0, a.xg_fmt, to_f32<E>(row[j]) * to_f32<E>(reinterpret_cast<const E *>(a.g)[j]) * sc);
+            for (int j = threadIdx.x; j < a.ssq_n; j += blockDim.x) a.ssq[(size_t)t * a.ssq_n + j] = j == 0 ? ss : 0.f;
+            if (threadIdx.x == 0) a.sc[t] = sc;
         }
     }
     if (a.cos_t)
@@ -78,17 +117,6 @@ hipError_t launch_front(int dtype, const FrontArgs &a, hipStream_t s) {
 // RMSNorm: one wavefront per row, fp32 statistics, output rounded to the storage type.  With
 // terms == 2 the row is written as hi | lo: the rounded value, then the rounding of the remainder;
 // with terms == 3 (16-bit storage only) it is written as IEEE half values.
-template <typename T>
-__device__ __forceinline__ void store_terms(T *o, int c, int d, int terms, float v) {
-    if (sizeof(T) == 2 && terms == 3) {
-        reinterpret_cast<__half *>(o)[c] = to_half_sat(v);
-        return;
-    }
-    T hi = from_f32<T>(v);
-    o[c] = hi;
-    if (terms == 2) o[d + c] = from_f32<T>(v - to_f32<T>(hi));
-}
-
 template <typename T>
 __global__ void rmsnorm_kernel(const float *__restrict__ x, const T *__restrict__ g, T *__restrict__ out,
                                int n_rows, int d, float eps, int terms) {

@@ -1,0 +1,40 @@
+// Hand-over of values between workgroups inside one launch: device-scope relaxed atomic stores and loads, which are
+// written through to, and served from, the memory side of the per-XCD L2 caches, and an arrival counter that is bumped
+// only after the stores are acknowledged.  Nobody waits for anybody: the workgroup that arrives last does the rest.
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace cs {
+
+__device__ inline void xwg_store(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline float xwg_load(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// The same with 16 bytes per lane (assembly: there is no atomic access of that width; each 4-byte part is one on its own,
+// which is all a hand-over needs).  What xwg_load4 returns may be used only behind xwg_wait4 on it.
+typedef __attribute__((ext_vector_type(4))) float xwg_f32x4;
+__device__ inline void xwg_store4(xwg_f32x4 *p, xwg_f32x4 v) { asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory"); }
+__device__ inline xwg_f32x4 xwg_load4(const xwg_f32x4 *p) {
+    xwg_f32x4 v;
+    asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
+    return v;
+}
+template <int N>
+__device__ inline void xwg_wait4(xwg_f32x4 (&v)[N]) {
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
+}
+// Every thread calls it after its hand-over stores: waits until they are acknowledged, then counts the workgroup in.
+// Returns true (to all threads) for the workgroup that arrives last of n; that one also clears the counter.
+__device__ inline bool xwg_arrive_last(int32_t *cnt, int n, volatile int *flag, int tid) {
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+    __syncthreads();
+    if (tid == 0) {
+        int last = atomicAdd(cnt, 1) == n - 1;
+        if (last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *flag = last;
+    }
+    __syncthreads();
+    return *flag != 0;
+}
+
+}  // namespace cs
