@@ -793,8 +793,6 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
             at.B = B; at.Hq = c.n_q_heads; at.Hkv = c.n_kv_heads; at.G = c.n_q_heads / c.n_kv_heads;
             at.max_blocks = kv->max_blocks_per_seq; at.n_blocks = kv->n_blocks; at.max_L = max_L;
             at.scale_log2 = 1.44269504088896340736f / sqrtf((float)c.head_dim);
-            at.n_iter = cs::dec_attn_rounds(B, c.n_kv_heads, max_L);
-            at.max_pieces = max_L / (cs::DEC_PIECE * at.n_iter) + 1;
             HIP_TRY(cs::launch_dec_attn(at, s));
         } else {
             cs::AttnArgs a = make_attn_args(c, kv, batch, (const int32_t *)(ws + L.tok_trace), l, ws + L.q, ws + L.ksuf, ws + L.vsuf,

@@ -2,13 +2,6 @@
 // per trace, beside the projections (skinny_bf16.hip): attention with one query row per head, and the language-model
 // head.  Both are streams from HBM - cached keys / values, the head's weights - and are built around keeping that
 // stream going and touching it once.
-//
-// Attention (dec_attn_kernel).  One workgroup per (trace, kv head, piece of 256 keys); each of its 8 wavefronts takes
-// 32 keys = two 16-token pages: the keys straight into registers, the values global -> LDS in one go, so a CU with two
-// workgroups has 256 KiB of keys / values on the way at any time.  Scores and the value product run on the
-// 16 x 16 x 32 MFMA with the G query rows of the kv head in the 16-row operand; q and the probabilities are carried
-// as two bf16 terms (the matrix work is negligible here, so the extra precision is free).  The pieces of a
-// (trace, kv head) leave (max, sum, O) partials; the workgroup that finishes last merges them in piece order.
 #include "kernels.h"
 #include "xwg.h"
 #include <algorithm>
@@ -274,122 +267,147 @@ hipError_t launch_dec_head_final(const float *part, int nwg, int B, const float 
 }
 
 // ---- attention ------------------------------------------------------------------------------------------------------
-// One workgroup of 8 wavefronts per (trace, kv head, piece of n_iter x 256 keys); in each round of 256 keys wavefront
-// w takes the two 16-token pages 2 w, 2 w + 1 and keeps a running (max, sum, O) over its rounds.  Keys go straight from global memory into the registers of the score product's first
-// operand (lane l: token l % 16 of a page, head-dim elements 32 ks + 8 (l / 16) .. + 7), values go global -> LDS
-// (8 KiB per wavefront, rows of 256 bytes) and come back through transposing reads as the first operand of
+// One workgroup per (trace, kv head, piece of n_iter x 256 cached keys); in each round of 256 keys wavefront w takes PAGES
+// 16-token pages and keeps a running (max, sum, O) over its rounds.  Keys go straight from global memory into the
+// registers of the score product's first operand (lane l: token l % 16 of a page, head-dim elements 32 ks + 8 (l / 16) ..
+// + 7), values go global -> LDS (rows of 256 bytes) and come back through transposing reads as the first operand of
 // O^T += V^T . P^T.  The 16-byte vector v of token k sits at slot v ^ (2 (k & 7)) of its row, so that the 32 bytes x 8
 // consecutive tokens that half a wavefront reads at a time fall into different banks; the lane that fills a slot
 // fetches the matching global vector.
 // Transposing reads (ds_read_b64_tr_b16): in a group of 16 lanes, lane i supplies the address of 4 consecutive 16-bit
 // elements and receives element i % 4 of what lanes i / 4, 4 + i / 4, 8 + i / 4, 12 + i / 4 addressed.
-// The last piece of a trace is short (with L a multiple of 256 it holds the new token only); the grid starts with the
-// last pieces, so they finish while the full pieces are still streaming instead of after them.
-constexpr int DEC_ATTN_THREADS = 512, DEC_ATTN_WAVES = 8;
-constexpr int DEC_ATTN_WAVE_LDS = 8192;
-constexpr int DEC_ATTN_SMEM = DEC_ATTN_WAVES * DEC_ATTN_WAVE_LDS;
-static_assert(DEC_PIECE == 32 * DEC_ATTN_WAVES, "a piece is two pages per wavefront");
+// The new token is not part of the pieces: the first wavefront of the last piece adds it to its state.
+//
+// What bounds it: few (trace, kv head) pairs, the chain of round trips in a workgroup - page ids, keys and values, the
+// arrival counter, the other pieces' results: the page ids are asked for before the length is known, and the last
+// workgroup's wavefronts merge the pieces side by side as they merged their own results.  One trace, 4096 keys: 14.7 us
+// when the pieces were merged one after the other by every thread.  Many pairs: the stream of keys and values (32 traces x 2
+// heads x 2048 keys, 67 MB), for which two workgroups of four wavefronts share a CU with 128 KiB each in flight.
+constexpr int DEC_ATTN_SMEM = 65536;
 
-// MULTI: the workgroup makes a.n_iter rounds (otherwise exactly one: the compiler then knows that nothing is carried
-// into the round, which keeps the kernel at 96 registers and two workgroups on a CU; the loop form needs 144).
-template <bool MULTI>
-__global__ __launch_bounds__(DEC_ATTN_THREADS, MULTI ? 1 : 2) void dec_attn_kernel(DecAttn a) {
+// The wavefronts' results [row][128] (om, stride floats per wavefront) and (max, sum) at om[1024 + row], om[1040 + row]
+// merged for (row, columns 4 c4 .. + 3), in wavefront order.
+template <int NW>
+__device__ __forceinline__ f32x4 dec_combine(const float *om, int stride, int row, int c4, float &M, float &l) {
+    float mw[NW];
+    M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        mw[w] = om[w * stride + 1024 + row];
+        M = fmaxf(M, mw[w]);
+    }
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    l = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const float wgt = mw[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[w] - M);
+        const f32x4 o = *reinterpret_cast<const f32x4 *>(om + w * stride + row * 128 + 4 * c4);
+        if (mw[w] != -INFINITY) {                        // a wavefront without keys left nothing
+            acc += wgt * o;
+            l += wgt * om[w * stride + 1040 + row];
+        }
+    }
+    return acc;
+}
+
+template <int NW, int PAGES>
+__global__ __launch_bounds__(64 * NW, 2) void dec_attn_kernel(DecAttn a) {
+    static_assert(NW * PAGES * 16 == DEC_PIECE && NW * PAGES * 4096 == DEC_ATTN_SMEM && PAGES % 2 == 0, "256 keys a round");
+    constexpr int WLDS = PAGES * 4096;                   // a wavefront's values, later its results
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     __shared__ volatile int s_last;
+    asm volatile("" : : "s"(a.q), "s"(a.q_lo), "s"(a.ksuf), "s"(a.vsuf), "s"(a.k_pages), "s"(a.v_pages), "s"(a.table), "s"(a.plens), "s"(a.out),
+                 "s"(a.part_o), "s"(a.part_ml), "s"(a.max_pieces), "s"(a.n_iter));
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // grid: x = (piece, kv head), pieces from the last one of the longest trace down; y = trace.  Everything a
-    // workgroup needs to find its keys follows from its indices and one load of the trace's length.
+    // grid: x = (piece, kv head), pieces from the last one of the longest trace down; y = trace
     const int h = blockIdx.x % a.Hkv, b = blockIdx.y;
     const int p = a.max_pieces - 1 - blockIdx.x / a.Hkv;
-    const int L = min(max(a.plens[b], 0), a.max_L);                     // keys 0 .. L-1 are cached, key L is the new token
-    const int n_iter = MULTI ? a.n_iter : 1;
-    const int piece_keys = DEC_PIECE * n_iter;                          // a workgroup makes n_iter rounds of 256 keys
-    const int n_p = L / piece_keys + 1;                                 // pieces over the L + 1 keys
+    const int piece_keys = DEC_PIECE * a.n_iter;
+    const int32_t *bt = a.table + (size_t)b * a.max_blocks;
+    int entry[PAGES];                                                   // page ids of the first round
+#pragma unroll
+    for (int i = 0; i < PAGES; ++i) entry[i] = bt[min((piece_keys >> 4) * p + wave * PAGES + i, a.max_blocks - 1)];
+    const int L = min(max(a.plens[b], 0), a.max_L);                     // cached keys; the new token sees all of them and itself
+    const int n_p = max((L + piece_keys - 1) / piece_keys, 1);          // pieces of this trace
     if (p >= n_p) return;                                               // uniform: a shorter trace
-    const int pi = b * a.max_pieces + p;                                // index of the piece's partial results
     const int G = a.G;
-    unsigned char *vst = smem + wave * DEC_ATTN_WAVE_LDS;
+    unsigned char *vst = smem + wave * WLDS;
     const unsigned lds_v = (unsigned)(size_t)(CS_LDS_AS unsigned char *)vst;
-
     const int fr = lane & 15, fg = lane >> 4;
+    const bf16 *ks_row = a.ksuf + ((size_t)b * a.Hkv + h) * 128, *vs_row = a.vsuf + ((size_t)b * a.Hkv + h) * 128;
+    // q operand: lane l holds query row l % 16 (rows >= G repeat the last one; they are never stored), head-dim elements
+    // 32 ks + 8 (l / 16) .. + 7
+    bf16x8 q_hi[4], q_lo[4];
+    const size_t qo = ((size_t)b * a.Hq + (size_t)h * G + min(fr, G - 1)) * 128 + 8 * fg;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        q_hi[ks] = *reinterpret_cast<const bf16x8 *>(a.q + qo + 32 * ks);
+        q_lo[ks] = *reinterpret_cast<const bf16x8 *>(a.q_lo + qo + 32 * ks);
+    }
     float m_w = -INFINITY, l_w = 0.f;                                   // running maximum (log2 units) and sum of this wavefront
     f32x4 o_acc[8];
 #pragma unroll
     for (int hb = 0; hb < 8; ++hb) o_acc[hb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const bool active = piece_keys * p + 32 * wave <= L;                // wave-uniform: the wavefront sees at least one key
-    for (int it = 0; it < n_iter; ++it) {
-        const int key0 = piece_keys * p + DEC_PIECE * it + 32 * wave;   // this wavefront's 32 keys of this round
-        if (key0 > L) break;                                            // wave-uniform; later rounds lie further out
-        // A token at or past L comes from the new token's row (token L itself; later ones are masked), so page rows
-        // that were never written are not read.
-        const bf16 *ks_row = a.ksuf + ((size_t)b * a.Hkv + h) * 128, *vs_row = a.vsuf + ((size_t)b * a.Hkv + h) * 128;
-        const int lrow = lane >> 4, lslot = lane & 15;
-        bf16x8 kf[2][4];
+    for (int it = 0; it < a.n_iter; ++it) {
+        const int key0 = piece_keys * p + DEC_PIECE * it + 16 * PAGES * wave;   // this wavefront's keys of this round
+        if (key0 >= L) break;                                           // wave-uniform; later rounds lie further out
+        if (it > 0) {
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            const int pg = (key0 >> 4) + kb;
-            // (asked for whether the page is used or not, so that it does not wait for the trace's length)
-            const int entry = a.table[(size_t)b * a.max_blocks + min(pg, a.max_blocks - 1)];
-            const int id = pg * 16 < L ? min(max(entry, 0), a.n_blocks - 1) : 0;
+            for (int i = 0; i < PAGES; ++i) entry[i] = bt[min((key0 >> 4) + i, a.max_blocks - 1)];
+        }
+        const int lrow = lane >> 4, lslot = lane & 15;
+        // tokens at or past L are masked; what is fetched for them is the new token's row, so that page rows that were
+        // never written are not read
+        bf16x8 kf[PAGES][4];
+#pragma unroll
+        for (int kb = 0; kb < PAGES; ++kb) {
+            const int tok0 = key0 + 16 * kb;
+            const int id = tok0 < L ? min(max(entry[kb], 0), a.n_blocks - 1) : 0;
             const size_t page = ((size_t)id * a.Hkv + h) * 16 * 128;
             // values: instruction jj fills tokens 4 jj .. 4 jj + 3 of the page; lane l: token 4 jj + l / 16, slot l % 16
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
                 const int kl = 4 * jj + lrow;
                 const int vvec = lslot ^ (2 * (kl & 7));
-                dma16(pg * 16 + kl < L ? a.v_pages + page + kl * 128 + vvec * 8 : vs_row + vvec * 8, lds_v + kb * 4096 + jj * 1024);
+                dma16(tok0 + kl < L ? a.v_pages + page + kl * 128 + vvec * 8 : vs_row + vvec * 8, lds_v + kb * 4096 + jj * 1024);
             }
             // keys: token fr of the page, 16 bytes per k-step
-            const bf16 *krow = pg * 16 + fr < L ? a.k_pages + page + fr * 128 : ks_row;
+            const bf16 *krow = tok0 + fr < L ? a.k_pages + page + fr * 128 : ks_row;
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) kf[kb][ks] = *reinterpret_cast<const bf16x8 *>(krow + 32 * ks + 8 * fg);
         }
-        // q operand: lane l holds query row l % 16 (rows >= G are zero), head-dim elements 32 ks + 8 (l / 16) .. + 7
-        // (fetched in every round rather than kept: with it live across the loop the kernel needs more than 128
-        // registers and a CU holds one workgroup instead of two)
-        bf16x8 q_hi[4], q_lo[4];
-        {
-            const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-            const size_t qo = ((size_t)b * a.Hq + (size_t)h * G + min(fr, G - 1)) * 128;
-    #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                q_hi[ks] = fr < G ? *reinterpret_cast<const bf16x8 *>(a.q + qo + 32 * ks + 8 * fg) : zero;
-                q_lo[ks] = (fr < G && a.q_lo) ? *reinterpret_cast<const bf16x8 *>(a.q_lo + qo + 32 * ks + 8 * fg) : zero;
-            }
-        }
         // scores: S^T[token][query row]; lane l ends up with query row l % 16, tokens 4 (l / 16) + e of each page
-        f32x4 sc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        f32x4 sc[PAGES];
+        float mx = -INFINITY;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < PAGES; ++kb) {
+            sc[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
                 sc[kb] = mma16(kf[kb][ks], q_hi[ks], sc[kb]);
                 sc[kb] = mma16(kf[kb][ks], q_lo[ks], sc[kb]);
             }
-        float mx = -INFINITY;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                float v = (key0 + 16 * kb + 4 * fg + e <= L) ? sc[kb][e] * a.scale_log2 : -INFINITY;
+                float v = (key0 + 16 * kb + 4 * fg + e < L) ? sc[kb][e] * a.scale_log2 : -INFINITY;
                 sc[kb][e] = v;
                 mx = fmaxf(mx, v);
             }
+        }
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));
-        // running maximum: finite from the first round on (token key0 <= L is visible to every query row)
+        // running maximum: finite from the first round on (token key0 < L is visible to every query row)
         const float m_new = fmaxf(m_w, mx);
         const float alpha = m_w == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_w - m_new);
         m_w = m_new;
-        float ps = 0.f, pv[8];
+        float ps = 0.f;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < PAGES; ++kb)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                float pr = __builtin_amdgcn_exp2f(sc[kb][e] - m_new);
-                pv[4 * kb + e] = pr;
-                ps += pr;
+                sc[kb][e] = __builtin_amdgcn_exp2f(sc[kb][e] - m_new);
+                ps += sc[kb][e];
             }
         ps += __shfl_xor(ps, 16);
         ps += __shfl_xor(ps, 32);
@@ -398,133 +416,159 @@ __global__ __launch_bounds__(DEC_ATTN_THREADS, MULTI ? 1 : 2) void dec_attn_kern
 #pragma unroll
             for (int hb = 0; hb < 8; ++hb) o_acc[hb] *= alpha;
         }
-        // probabilities as the second operand of O^T += V^T . P^T: k index 8 (l / 16) + i <-> token 4 (l / 16) + i of
-        // page 0 (i < 4) or page 1 (i >= 4), which is what the lane already holds; two bf16 terms
-        bf16x8 p_hi, p_lo;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            __bf16 hi = (__bf16)pv[i];
-            p_hi[i] = hi;
-            p_lo[i] = (__bf16)(pv[i] - (float)hi);
-        }
         dec_wait_vm<0>();                                // the values have landed
-        // V^T operand: group l / 16 reads tokens 4 (l / 16) .. + 3 of a page; lane i of the group points at token
+        // probabilities as the second operand of O^T += V^T . P^T over two pages: k index 8 (l / 16) + i <-> token
+        // 4 (l / 16) + i of the first page (i < 4) or the second (i >= 4), which is what the lane already holds; two bf16
+        // terms.  V^T operand: group l / 16 reads tokens 4 (l / 16) .. + 3 of a page; lane i of the group points at token
         // i / 4, head-dim elements 16 hb + 4 (i % 4) .. + 3 and receives the four tokens of element 16 hb + i
         const int vrow = 4 * fg + (fr >> 2), q4 = fr & 3;
 #pragma unroll
-        for (int hb = 0; hb < 8; ++hb) {
-            const unsigned char *p0 = vst + vrow * 256 + (((2 * hb + (q4 >> 1)) ^ (2 * (vrow & 7))) << 4) + ((q4 & 1) << 3);
-            i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((CS_LDS_AS i16x4 *)p0);
-            i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((CS_LDS_AS i16x4 *)(p0 + 4096));
-            bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-            o_acc[hb] = mma16(vf, p_hi, o_acc[hb]);
-            o_acc[hb] = mma16(vf, p_lo, o_acc[hb]);
+        for (int pp = 0; pp < PAGES / 2; ++pp) {
+            bf16x8 p_hi, p_lo;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float pr = sc[2 * pp + (i >> 2)][i & 3];
+                __bf16 hi = (__bf16)pr;
+                p_hi[i] = hi;
+                p_lo[i] = (__bf16)(pr - (float)hi);
+            }
+#pragma unroll
+            for (int hb = 0; hb < 8; ++hb) {
+                const unsigned char *p0 = vst + pp * 8192 + vrow * 256 + (((2 * hb + (q4 >> 1)) ^ (2 * (vrow & 7))) << 4) + ((q4 & 1) << 3);
+                i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((CS_LDS_AS i16x4 *)p0);
+                i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((CS_LDS_AS i16x4 *)(p0 + 4096));
+                bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                o_acc[hb] = mma16(vf, p_hi, o_acc[hb]);
+                o_acc[hb] = mma16(vf, p_lo, o_acc[hb]);
+            }
         }
         dec_wait_lds();                                  // the value region may be refilled (or reused below)
     }
-    // ---- the eight wavefronts' results, combined in wavefront order.  Each leaves O [8 rows][128] fp32, then max and
-    // sum per row, in its own value region (its own reads of that region are complete).
+    if (p == n_p - 1 && wave == 0) {                     // the new token
+        f32x4 sn = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {                 // (its key in all 16 rows of the operand)
+            const bf16x8 kn = *reinterpret_cast<const bf16x8 *>(ks_row + 32 * ks + 8 * fg);
+            sn = mma16(kn, q_hi[ks], sn);
+            sn = mma16(kn, q_lo[ks], sn);
+        }
+        const float v = sn[0] * a.scale_log2, m_new = fmaxf(m_w, v);
+        const float alpha = m_w == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_w - m_new), pr = __builtin_amdgcn_exp2f(v - m_new);
+        m_w = m_new;
+        l_w = l_w * alpha + pr;
+#pragma unroll
+        for (int hb = 0; hb < 8; ++hb) {
+            const uint2 vn = *reinterpret_cast<const uint2 *>(vs_row + 16 * hb + 4 * fg);
+            const f32x4 vf = {__uint_as_float(vn.x << 16), __uint_as_float(vn.x & 0xffff0000u), __uint_as_float(vn.y << 16), __uint_as_float(vn.y & 0xffff0000u)};
+            o_acc[hb] = o_acc[hb] * alpha + pr * vf;
+        }
+    }
+    // ---- the wavefronts' results, each in its own value region, combined in wavefront order
+    constexpr int OM = WLDS / 4;
     float *om = reinterpret_cast<float *>(vst);
-    if (active && fr < G) {
+    if (m_w != -INFINITY && fr < G) {
 #pragma unroll
         for (int hb = 0; hb < 8; ++hb)
             *reinterpret_cast<f32x4 *>(om + fr * 128 + 16 * hb + 4 * fg) = o_acc[hb];   // rows 16 hb + 4 (l / 16) + e
     }
     if (fg == 0 && fr < DEC_MAX_G) {
-        om[1024 + fr] = active ? m_w : -INFINITY;
-        om[1040 + fr] = active ? l_w : 0.f;
+        om[1024 + fr] = m_w;
+        om[1040 + fr] = l_w;
     }
-    __syncthreads();
-    const int hd = tid & 127;
-    const size_t item = (size_t)pi * a.Hkv + h;
-    auto store_out = [&](int jq, float v) {
-        reinterpret_cast<unsigned short *>(a.out)[frag_index(b, (h * G + jq) * 128 + hd, a.Hq * 128)] = to_fmt(v, a.out_fmt);
+    auto lds_barrier = []() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); };
+    lds_barrier();
+    const float *all = reinterpret_cast<const float *>(smem);
+    const int row = tid >> 5, c4 = tid & 31;                            // this thread's part of the result (row < G)
+    auto store_out = [&](f32x4 acc, float l) {
+        const float inv = 1.0f / l;
+        unsigned short *o = reinterpret_cast<unsigned short *>(a.out) + frag_index(b, (h * G + row) * 128 + 4 * c4, a.Hq * 128);
+        ushort4 v = {to_fmt(acc[0] * inv, a.out_fmt), to_fmt(acc[1] * inv, a.out_fmt), to_fmt(acc[2] * inv, a.out_fmt), to_fmt(acc[3] * inv, a.out_fmt)};
+        *reinterpret_cast<ushort4 *>(o) = v;
     };
-    for (int jq = tid >> 7; jq < G; jq += 4) {
-        float mw[DEC_ATTN_WAVES], M = -INFINITY;
-#pragma unroll
-        for (int w = 0; w < DEC_ATTN_WAVES; ++w) {
-            mw[w] = reinterpret_cast<const float *>(smem + w * DEC_ATTN_WAVE_LDS)[1024 + jq];
-            M = fmaxf(M, mw[w]);
-        }
-        float acc = 0.f, l = 0.f;
-#pragma unroll
-        for (int w = 0; w < DEC_ATTN_WAVES; ++w) {
-            if (mw[w] == -INFINITY) continue;            // a wavefront past the end left nothing
-            const float *ow = reinterpret_cast<const float *>(smem + w * DEC_ATTN_WAVE_LDS);
-            float wgt = __builtin_amdgcn_exp2f(mw[w] - M);
-            acc += wgt * ow[jq * 128 + hd];
-            l += wgt * ow[1040 + jq];
-        }
+    const size_t item0 = (size_t)b * a.max_pieces * a.Hkv + h;          // piece p: item0 + p Hkv
+    if (row < G) {
+        float M, l;
+        const f32x4 acc = dec_combine<NW>(all, OM, row, c4, M, l);
         if (n_p == 1) {
-            store_out(jq, acc / l);
+            store_out(acc, l);
         } else {
-            xwg_store(a.part_o + (item * DEC_MAX_G + jq) * 128 + hd, acc);
-            if (hd == 0) {
-                xwg_store(a.part_ml + (item * DEC_MAX_G + jq) * 2, M);
-                xwg_store(a.part_ml + (item * DEC_MAX_G + jq) * 2 + 1, l);
+            const size_t at = (item0 + (size_t)p * a.Hkv) * DEC_MAX_G + row;
+            xwg_store4(reinterpret_cast<f32x4 *>(a.part_o + at * 128) + c4, acc);
+            if (c4 == 0) {
+                xwg_store(a.part_ml + at * 2, M);
+                xwg_store(a.part_ml + at * 2 + 1, l);
             }
         }
     }
     if (n_p == 1) return;
-    // ---- the pieces of this (trace, kv head): the last one to arrive merges them in piece order
-    int32_t *cnt = a.ctl + DEC_CTL_ATTN + b * a.Hkv + h;
-    if (!xwg_arrive_last(cnt, n_p, &s_last, tid)) return;
-    // maxima and sums of all pieces into LDS (every thread needs them), then the weighted sums, 16 loads in flight
-    float *ml = reinterpret_cast<float *>(smem);                        // [n_p][8][2]
-    const size_t item0 = (size_t)b * a.max_pieces * a.Hkv + h;
-    const int n_ml = min(n_p, DEC_ATTN_SMEM / (DEC_MAX_G * 2 * 4));     // pieces whose (max, sum) fit LDS: 1024
-    for (int i = tid; i < n_ml * DEC_MAX_G * 2; i += DEC_ATTN_THREADS) {
-        int pp = i / (DEC_MAX_G * 2), r = i - pp * (DEC_MAX_G * 2);
-        ml[i] = (r >> 1) < G ? xwg_load(a.part_ml + (item0 + (size_t)pp * a.Hkv) * DEC_MAX_G * 2 + r) : 0.f;
-    }
-    __syncthreads();
-    for (int jq = tid >> 7; jq < G; jq += 4) {
-        float M = -INFINITY;
-        for (int pp = 0; pp < n_ml; ++pp) M = fmaxf(M, ml[(pp * DEC_MAX_G + jq) * 2]);
-        float acc = 0.f, l = 0.f;
-        for (int p0 = 0; p0 < n_ml; p0 += 16) {
-            float ov[16];
+    // ---- the pieces of this (trace, kv head): the last workgroup to arrive merges them.  Wavefront w takes the pieces w,
+    // w + NW, ... in turn; a lane has columns 4 (lane % 32) .. + 3 of the rows lane / 32, + 2, ...
+    if (!xwg_arrive_last(a.ctl + DEC_CTL_ATTN + b * a.Hkv + h, n_p, &s_last, tid)) return;
+    constexpr int RP = DEC_MAX_G / 2;
+    const int rl = lane >> 5, cl = lane & 31;
+    float mm[RP], ll[RP];
+    f32x4 oo[RP];
 #pragma unroll
-            for (int e = 0; e < 16; ++e)
-                ov[e] = p0 + e < n_ml ? xwg_load(a.part_o + ((item0 + (size_t)(p0 + e) * a.Hkv) * DEC_MAX_G + jq) * 128 + hd) : 0.f;
+    for (int i = 0; i < RP; ++i) { mm[i] = -INFINITY; ll[i] = 0.f; oo[i] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+    for (int pp = wave; pp < n_p; pp += NW) {
+        f32x4 ov[RP];
+        float mv[RP], lv[RP];
+        const size_t at = (item0 + (size_t)pp * a.Hkv) * DEC_MAX_G;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                if (p0 + e < n_ml) {
-                    float wgt = __builtin_amdgcn_exp2f(ml[((p0 + e) * DEC_MAX_G + jq) * 2] - M);
-                    acc += wgt * ov[e];
-                    l += wgt * ml[((p0 + e) * DEC_MAX_G + jq) * 2 + 1];
-                }
-            }
+        for (int i = 0; i < RP; ++i) {
+            const int r = min(2 * i + rl, G - 1);
+            ov[i] = xwg_load4(reinterpret_cast<const f32x4 *>(a.part_o + (at + r) * 128) + cl);
+            mv[i] = xwg_load(a.part_ml + (at + r) * 2);
+            lv[i] = xwg_load(a.part_ml + (at + r) * 2 + 1);
         }
-        store_out(jq, acc / l);
+        xwg_wait4(ov);
+#pragma unroll
+        for (int i = 0; i < RP; ++i) {
+            const float M = fmaxf(mm[i], mv[i]);                        // (every piece has a key: its maximum is finite)
+            const float wo = mm[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mm[i] - M), wn = __builtin_amdgcn_exp2f(mv[i] - M);
+            oo[i] = oo[i] * wo + wn * ov[i];
+            ll[i] = ll[i] * wo + wn * lv[i];
+            mm[i] = M;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < RP; ++i) {
+        const int r = 2 * i + rl;
+        if (r < G) {
+            *reinterpret_cast<f32x4 *>(om + r * 128 + 4 * cl) = oo[i];
+            if (cl == 0) { om[1024 + r] = mm[i]; om[1040 + r] = ll[i]; }
+        }
+    }
+    lds_barrier();
+    if (row < G) {
+        float M, l;
+        const f32x4 acc = dec_combine<NW>(all, OM, row, c4, M, l);
+        store_out(acc, l);
     }
 }
 
-// Rounds of 256 keys a workgroup makes: the fewest (a power of two up to 16) that keep the grid at about two workgroups
-// per CU - with many (trace, kv head) pairs, pieces of 256 keys make several rounds of short workgroups whose fixed
-// costs (dispatch, lengths and page ids, the merge) add up (16 traces x 8 kv heads x 4096 keys: 67 us per layer).
-int dec_attn_rounds(int B, int Hkv, int max_L) {
+// Rounds of 256 keys a workgroup makes: the fewest (a power of two up to 16) that keep the grid at about the two workgroups
+// a CU holds - with many (trace, kv head) pairs, pieces of 256 keys make several rounds of short workgroups whose fixed
+// costs (dispatch, lengths and page ids, the merge) add up.
+static int dec_attn_rounds(int B, int Hkv, int max_L) {
     int n = 1;
-    while (n < 16 && (long)B * Hkv * (max_L / (DEC_PIECE * n) + 1) > 640) n *= 2;
+    while (n < 16 && (long)B * Hkv * ((max_L + DEC_PIECE * n - 1) / (DEC_PIECE * n)) > 576) n *= 2;
     return n;
 }
 
-// a.n_iter from dec_attn_rounds; a.max_pieces: pieces of the longest trace, max_L / (DEC_PIECE * n_iter) + 1
-hipError_t launch_dec_attn(const DecAttn &a, hipStream_t s) {
-    if (a.B < 1 || a.G < 1 || a.G > DEC_MAX_G || a.Hkv < 1 || a.B * a.Hkv > DEC_CTL_TILE - DEC_CTL_ATTN ||
-        a.n_iter < 1 || a.max_pieces != a.max_L / (DEC_PIECE * a.n_iter) + 1 || a.max_pieces > DEC_ATTN_SMEM / (DEC_MAX_G * 2 * 4))
-        return hipErrorInvalidValue;
-    static std::atomic<uint32_t> attr_one{0}, attr_multi{0};
+hipError_t launch_dec_attn(DecAttn a, hipStream_t s) {
+    if (a.B < 1 || a.G < 1 || a.G > DEC_MAX_G || a.Hkv < 1 || a.B * a.Hkv > DEC_CTL_TILE - DEC_CTL_ATTN || !a.q_lo) return hipErrorInvalidValue;
+    a.n_iter = dec_attn_rounds(a.B, a.Hkv, a.max_L);
+    a.max_pieces = std::max((a.max_L + DEC_PIECE * a.n_iter - 1) / (DEC_PIECE * a.n_iter), 1);
     const dim3 grid(a.max_pieces * a.Hkv, a.B);
-    if (a.n_iter == 1) {
-        if (hipError_t e = set_dynamic_lds_once(attr_one, reinterpret_cast<const void *>(dec_attn_kernel<false>), DEC_ATTN_SMEM); e != hipSuccess)
-            return e;
-        dec_attn_kernel<false><<<grid, DEC_ATTN_THREADS, DEC_ATTN_SMEM, s>>>(a);
+    static std::atomic<uint32_t> attr8{0}, attr4{0};
+    // up to about one workgroup per CU: eight wavefronts, the shorter chain; beyond, four, of which two workgroups fit a CU
+    if ((long)grid.x * grid.y <= 288) {
+        if (hipError_t e = set_dynamic_lds_once(attr8, reinterpret_cast<const void *>(dec_attn_kernel<8, 2>), DEC_ATTN_SMEM); e != hipSuccess) return e;
+        dec_attn_kernel<8, 2><<<grid, 512, DEC_ATTN_SMEM, s>>>(a);
     } else {
-        if (hipError_t e = set_dynamic_lds_once(attr_multi, reinterpret_cast<const void *>(dec_attn_kernel<true>), DEC_ATTN_SMEM); e != hipSuccess)
-            return e;
-        dec_attn_kernel<true><<<grid, DEC_ATTN_THREADS, DEC_ATTN_SMEM, s>>>(a);
+        if (hipError_t e = set_dynamic_lds_once(attr4, reinterpret_cast<const void *>(dec_attn_kernel<4, 4>), DEC_ATTN_SMEM); e != hipSuccess) return e;
+        dec_attn_kernel<4, 4><<<grid, 256, DEC_ATTN_SMEM, s>>>(a);
     }
     return hipGetLastError();
 }

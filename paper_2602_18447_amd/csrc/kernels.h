@@ -274,7 +274,7 @@ hipError_t launch_dec_head_final(const float *part, int nwg, int B, const float 
                                  float *max_logit, float *lse, float *conf_full, hipStream_t s);
 
 struct DecAttn {
-    const bf16 *q, *q_lo;             // [B, Hq, 128]; q_lo may be null
+    const bf16 *q, *q_lo;             // [B, Hq, 128]: two bf16 terms
     const bf16 *ksuf, *vsuf;          // [B, Hkv, 128]: key / value of the new token
     const bf16 *k_pages, *v_pages;    // this layer's pages [n_blocks, Hkv, 16, 128]
     const int32_t *table, *plens;
@@ -282,12 +282,11 @@ struct DecAttn {
     void *out;                        // [B, Hq * 128] in fragment order, format out_fmt (1 bf16, 3 half)
     float *part_o, *part_ml;          // per (trace, piece, kv head): [8, 128] and [8, 2] fp32; B * max_pieces * Hkv of them
     int32_t B, Hq, Hkv, G, max_blocks, n_blocks, max_L, out_fmt;
-    int32_t n_iter;                   // rounds of DEC_PIECE keys per workgroup (dec_attn_rounds)
-    int32_t max_pieces;               // pieces of the longest trace: max_L / (DEC_PIECE * n_iter) + 1
+    int32_t n_iter;                   // rounds of DEC_PIECE keys per workgroup (set by the launcher)
+    int32_t max_pieces;               // pieces of the longest trace (set by the launcher)
     float scale_log2;                 // log2(e) / sqrt(head_dim)
 };
-int dec_attn_rounds(int B, int Hkv, int max_L);
-hipError_t launch_dec_attn(const DecAttn &a, hipStream_t s);
+hipError_t launch_dec_attn(DecAttn a, hipStream_t s);
 inline size_t dec_attn_part_o_bytes(int64_t n_pieces, int Hkv) { return (size_t)n_pieces * Hkv * DEC_MAX_G * 128 * 4; }
 inline size_t dec_attn_part_ml_bytes(int64_t n_pieces, int Hkv) { return (size_t)n_pieces * Hkv * DEC_MAX_G * 2 * 4; }
 
