@@ -163,12 +163,6 @@ __device__ __forceinline__ void store_out4(bf16 *o, size_t row_w, int fmt, const
     if (fmt == 2) *reinterpret_cast<uint2 *>(o + row_w) = pl.u;
 }
 
-// First element of (token, q head) in the output, row-major or in fragment order.
-__device__ __forceinline__ size_t out_offset(const AttnArgs &a, int token, int head) {
-    if (a.out_frag) return frag_index(token, head * HD, a.Hq * HD);
-    return (size_t)token * a.Hq * HD * (a.out_terms == 2 ? 2 : 1) + head * HD;
-}
-
 // What every kernel below derives from its item: the unit, its rows, the tile's key list.
 struct ItemGeom {
     int b0, c, cu0, n_rows, L, n_pc, k_start, G;
@@ -201,8 +195,7 @@ __device__ __forceinline__ void finish_item(const AttnArgs &a, const AttnItem &i
         if (row_valid) {
             float inv = 1.0f / l_tot;
             size_t row_w = (size_t)a.Hq * HD;
-            bf16 *o_row = reinterpret_cast<bf16 *>(a.out) + out_offset(a, token, head);
-            const int s32 = a.out_frag ? 512 : 32, s8 = a.out_frag ? 128 : 8;      // 32 and 8 columns further
+            bf16 *o_row = reinterpret_cast<bf16 *>(a.out) + (size_t)token * row_w * (a.out_terms == 2 ? 2 : 1) + head * HD;
 #pragma unroll
             for (int hb = 0; hb < 4; ++hb)
 #pragma unroll
@@ -210,7 +203,7 @@ __device__ __forceinline__ void finish_item(const AttnArgs &a, const AttnItem &i
                     float v4[4];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) v4[j] = acc_o[hb][q4 * 4 + j] * inv;
-                    store_out4(o_row + s32 * hb + s8 * q4 + 4 * half, row_w, a.out_terms, v4);
+                    store_out4(o_row + 32 * hb + 8 * q4 + 4 * half, row_w, a.out_terms, v4);
                 }
         }
     } else {
@@ -953,12 +946,11 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a, const AttnT
     float inv = 1.0f / l;
     int t = r / G, g = r - t * G;
     size_t row_w = (size_t)a.Hq * HD;
-    bf16 *o_row = reinterpret_cast<bf16 *>(a.out) + out_offset(a, cu_b + t, c * G + g);
+    bf16 *o_row = reinterpret_cast<bf16 *>(a.out) + (size_t)(cu_b + t) * row_w * (a.out_terms == 2 ? 2 : 1) + (c * G + g) * HD;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         float vals[4] = {o[j].x * inv, o[j].y * inv, o[j].z * inv, o[j].w * inv};
-        const int col = hv * 16 + 4 * j;
-        store_out4(o_row + (a.out_frag ? (col >> 5) * 512 + ((col & 31) >> 3) * 128 + (col & 7) : col), row_w, a.out_terms, vals);
+        store_out4(o_row + hv * 16 + 4 * j, row_w, a.out_terms, vals);
     }
 }
 

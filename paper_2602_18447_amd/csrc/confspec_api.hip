@@ -106,7 +106,8 @@ struct WsLayout {
     size_t plan_counts, plan_tiles, plan_items, part_o, part_ml;
     size_t x_last, h_last, attn_last, act_last, plan2_counts, plan2_tiles, plan2_items;   // last layer, last rows only
     size_t splitk, splitk_bytes;                                                        // split-K partial products
-    size_t dec_ctl, sk_ssq, sk_sc, kv_row;              // passes over few rows: arrival counters, row statistics; write-back rows
+    size_t few_ctl, few_tiles, sk_ssq, sk_sc, kv_row;   // passes over few rows: arrival counters, attention tiles, row
+                                                        // statistics; write-back rows
     size_t part_o_bytes, part_ml_bytes;
     size_t total;
     int64_t max_tiles, max_items, max_tiles2, max_items2;
@@ -118,13 +119,8 @@ struct WsLayout {
 bool skinny_shape_ok(const confspec_model_cfg &c, int64_t T) {
     return c.dtype == CONFSPEC_DTYPE_BF16 && T >= 1 && T <= cs::SK_MAX_ROWS && c.n_layers > 0 && c.head_dim == 128;
 }
-// A pass that the generation-step attention can take, as far as the model and the batch shape decide it: one new token
-// in every trace.
-bool dec_shape_ok(const confspec_model_cfg &c, int64_t T, int64_t B) {
-    if (!skinny_shape_ok(c, T) || T != B) return false;
-    const int G = c.n_q_heads / c.n_kv_heads;
-    return G <= cs::DEC_MAX_G && B * c.n_kv_heads <= cs::DEC_CTL_TILE - cs::DEC_CTL_ATTN;
-}
+// One new token in every trace (a generation step), as far as its attention is concerned.
+bool one_token_shape(const confspec_model_cfg &c, int64_t T, int64_t B) { return T == B && c.n_q_heads / c.n_kv_heads <= 16; }
 // Partial planes of a few-row pass's four projections (the largest one).
 size_t skinny_pass_plane_bytes(const confspec_model_cfg &c, int T) {
     const int qw = c.n_q_heads * c.head_dim, kw = c.n_kv_heads * c.head_dim;
@@ -134,11 +130,9 @@ size_t skinny_pass_plane_bytes(const confspec_model_cfg &c, int T) {
     m = std::max(m, cs::skinny_plane_bytes(T, c.d_ffn, c.d_model / 16));
     return m;
 }
-// Partial-result records of the step's attention: traces x pieces of the longest trace.
-int64_t dec_pieces(const int32_t *h_prefix_lens, int B) {
-    int max_L = 0;
-    for (int b = 0; b < B; ++b) max_L = std::max(max_L, h_prefix_lens[b]);
-    return (int64_t)B * (max_L / cs::DEC_PIECE + 1);
+// Tiles of a few-row pass's attention at most, whatever the lengths of its traces.
+int64_t few_tiles_bound(const confspec_model_cfg &c, int64_t T, int64_t B) {
+    return (c.n_q_heads / c.n_kv_heads * T) / cs::few_attn_rows(false) + B;
 }
 
 // exact (may be null): lay the workspace out for this batch alone instead of for every batch of up to T tokens in B
@@ -197,11 +191,15 @@ WsLayout ws_layout(const confspec_ctx *ctx, int64_t T, int64_t B, const confspec
         w.plan_items = take((size_t)w.max_items * sizeof(cs::AttnItem));
         w.part_o_bytes = (size_t)part_slots * cs::ATTN_BM * c.head_dim * 4;
         w.part_ml_bytes = (size_t)part_slots * cs::ATTN_BM * 2 * 4;
-        if (exact && dec_shape_ok(c, T, B)) {   // the generation-step attention keeps its pieces' partial results here
-            int64_t np = dec_pieces(exact->h_prefix_lens, exact->B);
-            w.part_o_bytes = std::max(w.part_o_bytes, cs::dec_attn_part_o_bytes(np, c.n_kv_heads));
-            w.part_ml_bytes = std::max(w.part_ml_bytes, cs::dec_attn_part_ml_bytes(np, c.n_kv_heads));
+        // the few-row attention's partial results (a general layout serves every smaller batch, few-row passes included)
+        const int64_t few_T = std::min<int64_t>(T, cs::SK_MAX_ROWS), few_B = std::min(few_T, B);
+        const int64_t few_tiles = skinny_shape_ok(c, few_T) && !(exact && few_T < T) ? few_tiles_bound(c, few_T, few_B) : 0;
+        if (few_tiles) {
+            const int64_t rec = cs::few_attn_records(few_tiles, c.n_kv_heads, false) * cs::few_attn_rows(false);
+            w.part_o_bytes = std::max(w.part_o_bytes, (size_t)rec * c.head_dim * 4);
+            w.part_ml_bytes = std::max(w.part_ml_bytes, (size_t)rec * 2 * 4);
         }
+        w.few_tiles = take(std::max<int64_t>(few_tiles, 1) * sizeof(cs::FewTile));
         w.part_o = take(w.part_o_bytes);
         w.part_ml = take(w.part_ml_bytes);
         // the last layer works on the last position of each trace only: B rows, one attention tile per
@@ -242,7 +240,7 @@ WsLayout ws_layout(const confspec_ctx *ctx, int64_t T, int64_t B, const confspec
         if (skinny_shape_ok(c, exact ? T : sk_rows)) sk = std::max(sk, skinny_pass_plane_bytes(c, sk_rows));
         w.splitk_bytes = sk;
         w.splitk = take(std::max<size_t>(sk, 256));
-        w.dec_ctl = take((size_t)cs::DEC_CTL_INTS * 4);
+        w.few_ctl = take((size_t)cs::FEW_CTL_INTS * 4);
         w.sk_ssq = take((size_t)2 * sk_rows * (c.d_model / 16) * 4);
         w.sk_sc = take((size_t)2 * sk_rows * 4);
         w.kv_row = take((size_t)T * 4);
@@ -718,13 +716,11 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
     bool skinny = skinny_shape_ok(c, T) && set.gemm.tile == 0 && set.gemm.splitk == 0;
     for (int l = 0; l < c.n_layers && skinny; ++l) skinny = rope_fused_in(l) && format_of(l) != 2;
     skinny = skinny && skinny_pass_plane_bytes(c, T) <= L.splitk_bytes;
-    bool use_dec = skinny && set.decode_kernels && dec_shape_ok(c, T, B) && !ex.dev_group_start &&
-                   (set.decode_kernels == 2 || (d <= 64 * cs::DEC_MAX_KT && qw <= 64 * cs::DEC_MAX_KT));
-    if (use_dec) {
-        const int64_t dec_np = dec_pieces(batch->h_prefix_lens, B);
-        use_dec = cs::dec_attn_part_o_bytes(dec_np, c.n_kv_heads) <= L.part_o_bytes &&
-                  cs::dec_attn_part_ml_bytes(dec_np, c.n_kv_heads) <= L.part_ml_bytes;
-    }
+    const int G = c.n_q_heads / c.n_kv_heads;
+    const bool one = skinny && one_token_shape(c, T, B) && !ex.dev_group_start;
+    const bool use_dec = one && set.decode_kernels && (set.decode_kernels == 2 || (d <= 64 * cs::DEC_MAX_KT && qw <= 64 * cs::DEC_MAX_KT));
+    const int64_t few_tiles = skinny ? cs::few_attn_tiles(batch->h_cu_suffix, B, ex.h_group_start, ex.n_groups, G, one) : 0;
+    skinny = skinny && few_tiles * c.n_kv_heads <= cs::FEW_MAX_TILES_KV;
     cs::AttnPlanCounts pc = {}, pc_last = {};
     Groups gr;
     gr.dev = ex.dev_group_start; gr.host = ex.h_group_start; gr.n = ex.n_groups;
@@ -733,10 +729,14 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
     const bool prune = c.dtype == CONFSPEC_DTYPE_BF16 && set.prune_last_layer && c.n_layers > 0 && !skinny;
     float *ssq[2] = {(float *)(ws + L.sk_ssq), (float *)(ws + L.sk_ssq) + (size_t)T * (d / 16)};
     float *sc[2] = {(float *)(ws + L.sk_sc), (float *)(ws + L.sk_sc) + T};
-    int32_t *ctl = (int32_t *)(ws + L.dec_ctl);
+    int32_t *ctl = (int32_t *)(ws + L.few_ctl);
     cs::FrontArgs front = {};
     if (skinny) {
-        front.ctl = ctl; front.n_ctl = cs::DEC_CTL_INTS;
+        front.ctl = ctl; front.n_ctl = cs::FEW_CTL_ATTN + (int)few_tiles * c.n_kv_heads;
+        if (!one || (!use_dec && set.attn_precise_layers > 0)) {
+            front.few_tiles = (cs::FewTile *)(ws + L.few_tiles); front.n_few_tiles = (int)few_tiles; front.few_rows = cs::few_attn_rows(false); front.G = G;
+            front.group_start = ex.dev_group_start; front.n_units = ex.dev_group_start ? ex.n_groups : B;
+        }
         front.g = w->attn_norm[0]; front.xg = h; front.xg_fmt = format_of(0);
         front.ssq = ssq[0]; front.sc = sc[0]; front.ssq_n = d / 16; front.eps = c.rms_eps;
         if (dev_n_append) {
@@ -746,7 +746,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         }
     }
     if ((rc = run_front(ctx, batch, max_L, ws, L, true, w, s, &front)) != CONFSPEC_OK) return rc;
-    if (c.dtype == CONFSPEC_DTYPE_BF16 && !use_dec) {   // (the generation-step attention has its own, fixed cut into pieces)
+    if (c.dtype == CONFSPEC_DTYPE_BF16 && !skinny) {    // (the few-row attention has its own cut into pieces)
         if ((rc = run_attn_plan(ctx, batch, gr, max_L, ws, L, false, &pc, s)) != CONFSPEC_OK) return rc;
         if (prune && (rc = run_attn_plan(ctx, batch, gr, max_L, ws, L, true, &pc_last, s)) != CONFSPEC_OK) return rc;
     }
@@ -762,7 +762,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         const void *wgu = f16 ? w->w_gate_up_f16[l] : w->w_gate_up[l], *wdn = f16 ? w->w_down_f16[l] : w->w_down[l];
         cs::SkinnyGemm base = {};
         base.M = T; base.d_norm = d; base.ssq_n = d / 16; base.eps = c.rms_eps;
-        base.planes = (float *)(ws + L.splitk); base.tile_cnt = ctl + cs::DEC_CTL_TILE;
+        base.planes = (float *)(ws + L.splitk); base.tile_cnt = ctl + cs::FEW_CTL_TILE;
         auto proj = [&](const void *X, const void *W, int K, int n_ct, int stat) {
             cs::SkinnyGemm g = base;
             g.X = (const cs::bf16 *)X; g.W = (const cs::bf16 *)W; g.K = K; g.n_ct = n_ct;
@@ -781,25 +781,23 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         }
         HIP_TRY(cs::launch_skinny(gq, cs::SK_EPI_ROPE, f16, s));
         HIP_TRY(mark(prec && !use_dec ? CONFSPEC_PHASE_ATTN_PRECISE : CONFSPEC_PHASE_ATTN));
-        if (use_dec) {
-            cs::DecAttn at = {};
-            at.q = (const cs::bf16 *)(ws + L.q); at.q_lo = (const cs::bf16 *)(ws + L.q_lo);
-            at.ksuf = (const cs::bf16 *)(ws + L.ksuf); at.vsuf = (const cs::bf16 *)(ws + L.vsuf);
-            at.k_pages = kv->k_pages ? (const cs::bf16 *)((const char *)kv->k_pages + layer_bytes * l) : nullptr;
-            at.v_pages = kv->v_pages ? (const cs::bf16 *)((const char *)kv->v_pages + layer_bytes * l) : nullptr;
-            at.table = kv->block_table; at.plens = batch->prefix_lens; at.ctl = ctl;
-            at.out = ws + L.attn; at.out_fmt = tm;
-            at.part_o = (float *)(ws + L.part_o); at.part_ml = (float *)(ws + L.part_ml);
-            at.B = B; at.Hq = c.n_q_heads; at.Hkv = c.n_kv_heads; at.G = c.n_q_heads / c.n_kv_heads;
-            at.max_blocks = kv->max_blocks_per_seq; at.n_blocks = kv->n_blocks; at.max_L = max_L;
-            at.scale_log2 = 1.44269504088896340736f / sqrtf((float)c.head_dim);
-            HIP_TRY(cs::launch_dec_attn(at, s));
-        } else {
-            cs::AttnArgs a = make_attn_args(c, kv, batch, (const int32_t *)(ws + L.tok_trace), l, ws + L.q, ws + L.ksuf, ws + L.vsuf,
-                                            gq.rope.q_lo, gq.rope.k_lo, gq.rope.v_lo, ws + L.attn, tm);
-            a.out_frag = 1;
-            if ((rc = run_attention(ctx, a, ws, L, pc, false, 0, s))) return rc;
-        }
+        // One token per trace: two terms of q and the probabilities in every layer where decode_kernels asks for it; the
+        // first layers otherwise take the tile form, which carries those of the suffix keys and values as well.
+        const bool as_one = one && (use_dec || !prec);
+        cs::FewAttn at = {};
+        at.q = (const cs::bf16 *)(ws + L.q); at.q_lo = (const cs::bf16 *)gq.rope.q_lo;
+        at.ksuf = (const cs::bf16 *)(ws + L.ksuf); at.vsuf = (const cs::bf16 *)(ws + L.vsuf);
+        at.ksuf_lo = (const cs::bf16 *)gq.rope.k_lo; at.vsuf_lo = (const cs::bf16 *)gq.rope.v_lo;
+        at.k_pages = kv->k_pages ? (const cs::bf16 *)((const char *)kv->k_pages + layer_bytes * l) : nullptr;
+        at.v_pages = kv->v_pages ? (const cs::bf16 *)((const char *)kv->v_pages + layer_bytes * l) : nullptr;
+        at.table = kv->block_table; at.plens = batch->prefix_lens; at.cu = batch->cu_suffix; at.tok_trace = (const int32_t *)(ws + L.tok_trace);
+        at.tiles = as_one ? nullptr : (const cs::FewTile *)(ws + L.few_tiles); at.n_tiles = (int)few_tiles; at.arrived = ctl + cs::FEW_CTL_ATTN;
+        at.out = ws + L.attn; at.out_fmt = tm;
+        at.part_o = (float *)(ws + L.part_o); at.part_ml = (float *)(ws + L.part_ml);
+        at.B = B; at.T = T; at.Hq = c.n_q_heads; at.Hkv = c.n_kv_heads; at.G = G;
+        at.max_blocks = kv->max_blocks_per_seq; at.n_blocks = kv->n_blocks; at.max_L = max_L;
+        at.scale_log2 = 1.44269504088896340736f / sqrtf((float)c.head_dim);
+        HIP_TRY(cs::launch_few_attn(at, s));
         HIP_TRY(mark(CONFSPEC_PHASE_O_PROJ));
         cs::SkinnyGemm go = proj(ws + L.attn, wo, qw, d / 16, 0);
         go.x = x; go.xg_out = h; go.g_next = (const cs::bf16 *)w->mlp_norm[l]; go.ssq_out = ssq[1]; go.sc_out = sc[1]; go.xg_fmt = tm;

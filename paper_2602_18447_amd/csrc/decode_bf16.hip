@@ -1,9 +1,7 @@
-// Kernels of a generation step (Algorithm 1: the generate calls of Stage 1 and of the Stage 3 fallback), one new token
-// per trace, beside the projections (skinny_bf16.hip): attention with one query row per head, and the language-model
-// head.  Both are streams from HBM - cached keys / values, the head's weights - and are built around keeping that
-// stream going and touching it once.
+// Kernel of a generation step (Algorithm 1: the generate calls of Stage 1 and of the Stage 3 fallback), one new token
+// per trace, beside the projections (skinny_bf16.hip) and the attention (attn_few.hip): the language-model head, a stream
+// of its weights from HBM, built around keeping that stream going and touching it once.
 #include "kernels.h"
-#include "xwg.h"
 #include <algorithm>
 
 namespace cs {
@@ -263,313 +261,6 @@ __global__ __launch_bounds__(64) void dec_head_final_kernel(const float *__restr
 hipError_t launch_dec_head_final(const float *part, int nwg, int B, const float *verdict_logits, int n_verdict, int32_t *token,
                                  float *max_logit, float *lse, float *conf_full, hipStream_t s) {
     dec_head_final_kernel<<<B, 64, 0, s>>>(part, nwg, verdict_logits, n_verdict, token, max_logit, lse, conf_full);
-    return hipGetLastError();
-}
-
-// ---- attention ------------------------------------------------------------------------------------------------------
-// One workgroup per (trace, kv head, piece of n_iter x 256 cached keys); in each round of 256 keys wavefront w takes PAGES
-// 16-token pages and keeps a running (max, sum, O) over its rounds.  Keys go straight from global memory into the
-// registers of the score product's first operand (lane l: token l % 16 of a page, head-dim elements 32 ks + 8 (l / 16) ..
-// + 7), values go global -> LDS (rows of 256 bytes) and come back through transposing reads as the first operand of
-// O^T += V^T . P^T.  The 16-byte vector v of token k sits at slot v ^ (2 (k & 7)) of its row, so that the 32 bytes x 8
-// consecutive tokens that half a wavefront reads at a time fall into different banks; the lane that fills a slot
-// fetches the matching global vector.
-// Transposing reads (ds_read_b64_tr_b16): in a group of 16 lanes, lane i supplies the address of 4 consecutive 16-bit
-// elements and receives element i % 4 of what lanes i / 4, 4 + i / 4, 8 + i / 4, 12 + i / 4 addressed.
-// The new token is not part of the pieces: the first wavefront of the last piece adds it to its state.
-//
-// What bounds it: few (trace, kv head) pairs, the chain of round trips in a workgroup - page ids, keys and values, the
-// arrival counter, the other pieces' results: the page ids are asked for before the length is known, and the last
-// workgroup's wavefronts merge the pieces side by side as they merged their own results.  One trace, 4096 keys: 14.7 us
-// when the pieces were merged one after the other by every thread.  Many pairs: the stream of keys and values (32 traces x 2
-// heads x 2048 keys, 67 MB), for which two workgroups of four wavefronts share a CU with 128 KiB each in flight.
-constexpr int DEC_ATTN_SMEM = 65536;
-
-// The wavefronts' results [row][128] (om, stride floats per wavefront) and (max, sum) at om[1024 + row], om[1040 + row]
-// merged for (row, columns 4 c4 .. + 3), in wavefront order.
-template <int NW>
-__device__ __forceinline__ f32x4 dec_combine(const float *om, int stride, int row, int c4, float &M, float &l) {
-    float mw[NW];
-    M = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        mw[w] = om[w * stride + 1024 + row];
-        M = fmaxf(M, mw[w]);
-    }
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    l = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const float wgt = mw[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[w] - M);
-        const f32x4 o = *reinterpret_cast<const f32x4 *>(om + w * stride + row * 128 + 4 * c4);
-        if (mw[w] != -INFINITY) {                        // a wavefront without keys left nothing
-            acc += wgt * o;
-            l += wgt * om[w * stride + 1040 + row];
-        }
-    }
-    return acc;
-}
-
-template <int NW, int PAGES>
-__global__ __launch_bounds__(64 * NW, 2) void dec_attn_kernel(DecAttn a) {
-    static_assert(NW * PAGES * 16 == DEC_PIECE && NW * PAGES * 4096 == DEC_ATTN_SMEM && PAGES % 2 == 0, "256 keys a round");
-    constexpr int WLDS = PAGES * 4096;                   // a wavefront's values, later its results
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    __shared__ volatile int s_last;
-    asm volatile("" : : "s"(a.q), "s"(a.q_lo), "s"(a.ksuf), "s"(a.vsuf), "s"(a.k_pages), "s"(a.v_pages), "s"(a.table), "s"(a.plens), "s"(a.out),
-                 "s"(a.part_o), "s"(a.part_ml), "s"(a.max_pieces), "s"(a.n_iter));
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // grid: x = (piece, kv head), pieces from the last one of the longest trace down; y = trace
-    const int h = blockIdx.x % a.Hkv, b = blockIdx.y;
-    const int p = a.max_pieces - 1 - blockIdx.x / a.Hkv;
-    const int piece_keys = DEC_PIECE * a.n_iter;
-    const int32_t *bt = a.table + (size_t)b * a.max_blocks;
-    int entry[PAGES];                                                   // page ids of the first round
-#pragma unroll
-    for (int i = 0; i < PAGES; ++i) entry[i] = bt[min((piece_keys >> 4) * p + wave * PAGES + i, a.max_blocks - 1)];
-    const int L = min(max(a.plens[b], 0), a.max_L);                     // cached keys; the new token sees all of them and itself
-    const int n_p = max((L + piece_keys - 1) / piece_keys, 1);          // pieces of this trace
-    if (p >= n_p) return;                                               // uniform: a shorter trace
-    const int G = a.G;
-    unsigned char *vst = smem + wave * WLDS;
-    const unsigned lds_v = (unsigned)(size_t)(CS_LDS_AS unsigned char *)vst;
-    const int fr = lane & 15, fg = lane >> 4;
-    const bf16 *ks_row = a.ksuf + ((size_t)b * a.Hkv + h) * 128, *vs_row = a.vsuf + ((size_t)b * a.Hkv + h) * 128;
-    // q operand: lane l holds query row l % 16 (rows >= G repeat the last one; they are never stored), head-dim elements
-    // 32 ks + 8 (l / 16) .. + 7
-    bf16x8 q_hi[4], q_lo[4];
-    const size_t qo = ((size_t)b * a.Hq + (size_t)h * G + min(fr, G - 1)) * 128 + 8 * fg;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-        q_hi[ks] = *reinterpret_cast<const bf16x8 *>(a.q + qo + 32 * ks);
-        q_lo[ks] = *reinterpret_cast<const bf16x8 *>(a.q_lo + qo + 32 * ks);
-    }
-    float m_w = -INFINITY, l_w = 0.f;                                   // running maximum (log2 units) and sum of this wavefront
-    f32x4 o_acc[8];
-#pragma unroll
-    for (int hb = 0; hb < 8; ++hb) o_acc[hb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int it = 0; it < a.n_iter; ++it) {
-        const int key0 = piece_keys * p + DEC_PIECE * it + 16 * PAGES * wave;   // this wavefront's keys of this round
-        if (key0 >= L) break;                                           // wave-uniform; later rounds lie further out
-        if (it > 0) {
-#pragma unroll
-            for (int i = 0; i < PAGES; ++i) entry[i] = bt[min((key0 >> 4) + i, a.max_blocks - 1)];
-        }
-        const int lrow = lane >> 4, lslot = lane & 15;
-        // tokens at or past L are masked; what is fetched for them is the new token's row, so that page rows that were
-        // never written are not read
-        bf16x8 kf[PAGES][4];
-#pragma unroll
-        for (int kb = 0; kb < PAGES; ++kb) {
-            const int tok0 = key0 + 16 * kb;
-            const int id = tok0 < L ? min(max(entry[kb], 0), a.n_blocks - 1) : 0;
-            const size_t page = ((size_t)id * a.Hkv + h) * 16 * 128;
-            // values: instruction jj fills tokens 4 jj .. 4 jj + 3 of the page; lane l: token 4 jj + l / 16, slot l % 16
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                const int kl = 4 * jj + lrow;
-                const int vvec = lslot ^ (2 * (kl & 7));
-                dma16(tok0 + kl < L ? a.v_pages + page + kl * 128 + vvec * 8 : vs_row + vvec * 8, lds_v + kb * 4096 + jj * 1024);
-            }
-            // keys: token fr of the page, 16 bytes per k-step
-            const bf16 *krow = tok0 + fr < L ? a.k_pages + page + fr * 128 : ks_row;
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) kf[kb][ks] = *reinterpret_cast<const bf16x8 *>(krow + 32 * ks + 8 * fg);
-        }
-        // scores: S^T[token][query row]; lane l ends up with query row l % 16, tokens 4 (l / 16) + e of each page
-        f32x4 sc[PAGES];
-        float mx = -INFINITY;
-#pragma unroll
-        for (int kb = 0; kb < PAGES; ++kb) {
-            sc[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                sc[kb] = mma16(kf[kb][ks], q_hi[ks], sc[kb]);
-                sc[kb] = mma16(kf[kb][ks], q_lo[ks], sc[kb]);
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float v = (key0 + 16 * kb + 4 * fg + e < L) ? sc[kb][e] * a.scale_log2 : -INFINITY;
-                sc[kb][e] = v;
-                mx = fmaxf(mx, v);
-            }
-        }
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        // running maximum: finite from the first round on (token key0 < L is visible to every query row)
-        const float m_new = fmaxf(m_w, mx);
-        const float alpha = m_w == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_w - m_new);
-        m_w = m_new;
-        float ps = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < PAGES; ++kb)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                sc[kb][e] = __builtin_amdgcn_exp2f(sc[kb][e] - m_new);
-                ps += sc[kb][e];
-            }
-        ps += __shfl_xor(ps, 16);
-        ps += __shfl_xor(ps, 32);
-        l_w = l_w * alpha + ps;
-        if (it > 0) {
-#pragma unroll
-            for (int hb = 0; hb < 8; ++hb) o_acc[hb] *= alpha;
-        }
-        dec_wait_vm<0>();                                // the values have landed
-        // probabilities as the second operand of O^T += V^T . P^T over two pages: k index 8 (l / 16) + i <-> token
-        // 4 (l / 16) + i of the first page (i < 4) or the second (i >= 4), which is what the lane already holds; two bf16
-        // terms.  V^T operand: group l / 16 reads tokens 4 (l / 16) .. + 3 of a page; lane i of the group points at token
-        // i / 4, head-dim elements 16 hb + 4 (i % 4) .. + 3 and receives the four tokens of element 16 hb + i
-        const int vrow = 4 * fg + (fr >> 2), q4 = fr & 3;
-#pragma unroll
-        for (int pp = 0; pp < PAGES / 2; ++pp) {
-            bf16x8 p_hi, p_lo;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float pr = sc[2 * pp + (i >> 2)][i & 3];
-                __bf16 hi = (__bf16)pr;
-                p_hi[i] = hi;
-                p_lo[i] = (__bf16)(pr - (float)hi);
-            }
-#pragma unroll
-            for (int hb = 0; hb < 8; ++hb) {
-                const unsigned char *p0 = vst + pp * 8192 + vrow * 256 + (((2 * hb + (q4 >> 1)) ^ (2 * (vrow & 7))) << 4) + ((q4 & 1) << 3);
-                i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((CS_LDS_AS i16x4 *)p0);
-                i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((CS_LDS_AS i16x4 *)(p0 + 4096));
-                bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-                o_acc[hb] = mma16(vf, p_hi, o_acc[hb]);
-                o_acc[hb] = mma16(vf, p_lo, o_acc[hb]);
-            }
-        }
-        dec_wait_lds();                                  // the value region may be refilled (or reused below)
-    }
-    if (p == n_p - 1 && wave == 0) {                     // the new token
-        f32x4 sn = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {                 // (its key in all 16 rows of the operand)
-            const bf16x8 kn = *reinterpret_cast<const bf16x8 *>(ks_row + 32 * ks + 8 * fg);
-            sn = mma16(kn, q_hi[ks], sn);
-            sn = mma16(kn, q_lo[ks], sn);
-        }
-        const float v = sn[0] * a.scale_log2, m_new = fmaxf(m_w, v);
-        const float alpha = m_w == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_w - m_new), pr = __builtin_amdgcn_exp2f(v - m_new);
-        m_w = m_new;
-        l_w = l_w * alpha + pr;
-#pragma unroll
-        for (int hb = 0; hb < 8; ++hb) {
-            const uint2 vn = *reinterpret_cast<const uint2 *>(vs_row + 16 * hb + 4 * fg);
-            const f32x4 vf = {__uint_as_float(vn.x << 16), __uint_as_float(vn.x & 0xffff0000u), __uint_as_float(vn.y << 16), __uint_as_float(vn.y & 0xffff0000u)};
-            o_acc[hb] = o_acc[hb] * alpha + pr * vf;
-        }
-    }
-    // ---- the wavefronts' results, each in its own value region, combined in wavefront order
-    constexpr int OM = WLDS / 4;
-    float *om = reinterpret_cast<float *>(vst);
-    if (m_w != -INFINITY && fr < G) {
-#pragma unroll
-        for (int hb = 0; hb < 8; ++hb)
-            *reinterpret_cast<f32x4 *>(om + fr * 128 + 16 * hb + 4 * fg) = o_acc[hb];   // rows 16 hb + 4 (l / 16) + e
-    }
-    if (fg == 0 && fr < DEC_MAX_G) {
-        om[1024 + fr] = m_w;
-        om[1040 + fr] = l_w;
-    }
-    auto lds_barrier = []() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); };
-    lds_barrier();
-    const float *all = reinterpret_cast<const float *>(smem);
-    const int row = tid >> 5, c4 = tid & 31;                            // this thread's part of the result (row < G)
-    auto store_out = [&](f32x4 acc, float l) {
-        const float inv = 1.0f / l;
-        unsigned short *o = reinterpret_cast<unsigned short *>(a.out) + frag_index(b, (h * G + row) * 128 + 4 * c4, a.Hq * 128);
-        ushort4 v = {to_fmt(acc[0] * inv, a.out_fmt), to_fmt(acc[1] * inv, a.out_fmt), to_fmt(acc[2] * inv, a.out_fmt), to_fmt(acc[3] * inv, a.out_fmt)};
-        *reinterpret_cast<ushort4 *>(o) = v;
-    };
-    const size_t item0 = (size_t)b * a.max_pieces * a.Hkv + h;          // piece p: item0 + p Hkv
-    if (row < G) {
-        float M, l;
-        const f32x4 acc = dec_combine<NW>(all, OM, row, c4, M, l);
-        if (n_p == 1) {
-            store_out(acc, l);
-        } else {
-            const size_t at = (item0 + (size_t)p * a.Hkv) * DEC_MAX_G + row;
-            xwg_store4(reinterpret_cast<f32x4 *>(a.part_o + at * 128) + c4, acc);
-            if (c4 == 0) {
-                xwg_store(a.part_ml + at * 2, M);
-                xwg_store(a.part_ml + at * 2 + 1, l);
-            }
-        }
-    }
-    if (n_p == 1) return;
-    // ---- the pieces of this (trace, kv head): the last workgroup to arrive merges them.  Wavefront w takes the pieces w,
-    // w + NW, ... in turn; a lane has columns 4 (lane % 32) .. + 3 of the rows lane / 32, + 2, ...
-    if (!xwg_arrive_last(a.ctl + DEC_CTL_ATTN + b * a.Hkv + h, n_p, &s_last, tid)) return;
-    constexpr int RP = DEC_MAX_G / 2;
-    const int rl = lane >> 5, cl = lane & 31;
-    float mm[RP], ll[RP];
-    f32x4 oo[RP];
-#pragma unroll
-    for (int i = 0; i < RP; ++i) { mm[i] = -INFINITY; ll[i] = 0.f; oo[i] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-    for (int pp = wave; pp < n_p; pp += NW) {
-        f32x4 ov[RP];
-        float mv[RP], lv[RP];
-        const size_t at = (item0 + (size_t)pp * a.Hkv) * DEC_MAX_G;
-#pragma unroll
-        for (int i = 0; i < RP; ++i) {
-            const int r = min(2 * i + rl, G - 1);
-            ov[i] = xwg_load4(reinterpret_cast<const f32x4 *>(a.part_o + (at + r) * 128) + cl);
-            mv[i] = xwg_load(a.part_ml + (at + r) * 2);
-            lv[i] = xwg_load(a.part_ml + (at + r) * 2 + 1);
-        }
-        xwg_wait4(ov);
-#pragma unroll
-        for (int i = 0; i < RP; ++i) {
-            const float M = fmaxf(mm[i], mv[i]);                        // (every piece has a key: its maximum is finite)
-            const float wo = mm[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mm[i] - M), wn = __builtin_amdgcn_exp2f(mv[i] - M);
-            oo[i] = oo[i] * wo + wn * ov[i];
-            ll[i] = ll[i] * wo + wn * lv[i];
-            mm[i] = M;
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < RP; ++i) {
-        const int r = 2 * i + rl;
-        if (r < G) {
-            *reinterpret_cast<f32x4 *>(om + r * 128 + 4 * cl) = oo[i];
-            if (cl == 0) { om[1024 + r] = mm[i]; om[1040 + r] = ll[i]; }
-        }
-    }
-    lds_barrier();
-    if (row < G) {
-        float M, l;
-        const f32x4 acc = dec_combine<NW>(all, OM, row, c4, M, l);
-        store_out(acc, l);
-    }
-}
-
-// Rounds of 256 keys a workgroup makes: the fewest (a power of two up to 16) that keep the grid at about the two workgroups
-// a CU holds - with many (trace, kv head) pairs, pieces of 256 keys make several rounds of short workgroups whose fixed
-// costs (dispatch, lengths and page ids, the merge) add up.
-static int dec_attn_rounds(int B, int Hkv, int max_L) {
-    int n = 1;
-    while (n < 16 && (long)B * Hkv * ((max_L + DEC_PIECE * n - 1) / (DEC_PIECE * n)) > 576) n *= 2;
-    return n;
-}
-
-hipError_t launch_dec_attn(DecAttn a, hipStream_t s) {
-    if (a.B < 1 || a.G < 1 || a.G > DEC_MAX_G || a.Hkv < 1 || a.B * a.Hkv > DEC_CTL_TILE - DEC_CTL_ATTN || !a.q_lo) return hipErrorInvalidValue;
-    a.n_iter = dec_attn_rounds(a.B, a.Hkv, a.max_L);
-    a.max_pieces = std::max((a.max_L + DEC_PIECE * a.n_iter - 1) / (DEC_PIECE * a.n_iter), 1);
-    const dim3 grid(a.max_pieces * a.Hkv, a.B);
-    static std::atomic<uint32_t> attr8{0}, attr4{0};
-    // up to about one workgroup per CU: eight wavefronts, the shorter chain; beyond, four, of which two workgroups fit a CU
-    if ((long)grid.x * grid.y <= 288) {
-        if (hipError_t e = set_dynamic_lds_once(attr8, reinterpret_cast<const void *>(dec_attn_kernel<8, 2>), DEC_ATTN_SMEM); e != hipSuccess) return e;
-        dec_attn_kernel<8, 2><<<grid, 512, DEC_ATTN_SMEM, s>>>(a);
-    } else {
-        if (hipError_t e = set_dynamic_lds_once(attr4, reinterpret_cast<const void *>(dec_attn_kernel<4, 4>), DEC_ATTN_SMEM); e != hipSuccess) return e;
-        dec_attn_kernel<4, 4><<<grid, 256, DEC_ATTN_SMEM, s>>>(a);
-    }
     return hipGetLastError();
 }
 

@@ -61,6 +61,13 @@ struct RopeArgs {
     int32_t Hq, Hkv;
 };
 
+// Work of the few-row attention (attn_few.hip).
+// One tile of query rows: rows row0 .. of context unit (traces from b0; first packed suffix token cu0, n_rows = G * suffix
+// tokens, context length L); its rows see suffix tokens k_start .. k_start + n_keys - 1 at most.  n_rows == 0: unused.
+struct FewTile {
+    int32_t b0, cu0, row0, n_rows, L, k_start, n_keys, pad;
+};
+
 // ---- small kernels (templated on storage type: float or bf16) ----
 // What a pass needs to know about its tokens, in one launch: trace and position of every token, the last row of every
 // trace, and where asked for (pointers not null) the rotary tables [T, hd / 2] and the fp32 embedding rows x [T, d].
@@ -88,6 +95,10 @@ struct FrontArgs {
     const int32_t *table, *n_append;
     int32_t max_blocks, n_blocks, block_size;
     int32_t *kv_row;
+    // tiles of few_rows query rows (few_tiles not null; at most 128 units): G rows per token; group_start as in attn_plan.h
+    FewTile *few_tiles;
+    const int32_t *group_start;
+    int32_t n_units, n_few_tiles, few_rows, G;
 };
 hipError_t launch_front(int dtype, const FrontArgs &a, hipStream_t s);
 // x fp32 [T,d] -> out (storage dtype) [T, d]; terms == 2 (bf16 only): [T, 2d] hi | lo two-term form;
@@ -186,7 +197,6 @@ struct AttnArgs {
     int32_t B, T, Hq, Hkv, hd, n_blocks, block_size, max_blocks;
     float scale;            // 1/sqrt(hd)
     int32_t out_terms;
-    int32_t out_frag;       // 1: out in fragment order (frag_index, width Hq*hd; out_terms 1 or 3)
 };
 hipError_t launch_attn_f32(const AttnArgs &a, int max_S, hipStream_t s);   // max_S: longest suffix of the batch
 
@@ -250,16 +260,15 @@ struct SkinnyPlan { int mb, ms, ct, S; };
 SkinnyPlan skinny_plan(int M, int K, int n_ct);
 size_t skinny_plane_bytes(int M, int K, int n_ct);      // for up to M rows; 0 when no k range is cut
 hipError_t launch_skinny(SkinnyGemm a, int epi, bool f16, hipStream_t s);
+// control block (int32) of a pass over few rows: the arrival counters
+constexpr int FEW_CTL_TILE = 0;                                   // + tile of a projection whose k range is cut
+constexpr int FEW_CTL_ATTN = FEW_CTL_TILE + SK_MAX_TILES_CUT;     // + attention tile * Hkv + kv head
+constexpr int FEW_MAX_TILES_KV = 4096;                            // attention tiles * kv heads
+constexpr int FEW_CTL_INTS = FEW_CTL_ATTN + FEW_MAX_TILES_KV;
 
 // ---- generation steps: one new token per trace (decode_bf16.hip) ----
 constexpr int DEC_MAX_ROWS = 32;     // traces the language-model head of these kernels takes
-constexpr int DEC_PIECE = 256;       // keys per attention workgroup
-constexpr int DEC_MAX_G = 8;         // q heads per kv head
 constexpr int DEC_MAX_KT = 24;       // k-tiles (of 64) of the head's rows
-// control block (int32): the arrival counters
-constexpr int DEC_CTL_ATTN = 0;                          // + trace * Hkv + kv head
-constexpr int DEC_CTL_TILE = DEC_CTL_ATTN + 1024;        // + tile of a projection whose k range is cut
-constexpr int DEC_CTL_INTS = DEC_CTL_TILE + SK_MAX_TILES_CUT;
 
 // Head over the whole vocabulary: X is [M, 2 K] two-term bf16 (hi | lo), W the [16 n_ct, K] head; every one of the nwg
 // workgroups leaves (max, index of the first max, sum of exp(z - max)) of its columns per row in part [nwg, 32, 4] fp32.
@@ -273,22 +282,27 @@ hipError_t launch_dec_head(const DecHead &a, hipStream_t s);
 hipError_t launch_dec_head_final(const float *part, int nwg, int B, const float *verdict_logits, int n_verdict, int32_t *token,
                                  float *max_logit, float *lse, float *conf_full, hipStream_t s);
 
-struct DecAttn {
-    const bf16 *q, *q_lo;             // [B, Hq, 128]: two bf16 terms
-    const bf16 *ksuf, *vsuf;          // [B, Hkv, 128]: key / value of the new token
+// ---- attention of passes over few rows (attn_few.hip) ----
+struct FewAttn {
+    const bf16 *q, *q_lo;             // [T, Hq, 128]; q_lo (may be null): second bf16 terms, then those of ksuf / vsuf too
+    const bf16 *ksuf, *vsuf;          // [T, Hkv, 128]: keys / values of the suffix tokens
+    const bf16 *ksuf_lo, *vsuf_lo;    // (not read where every trace has one token)
     const bf16 *k_pages, *v_pages;    // this layer's pages [n_blocks, Hkv, 16, 128]
-    const int32_t *table, *plens;
-    int32_t *ctl;                     // control block, zero
-    void *out;                        // [B, Hq * 128] in fragment order, format out_fmt (1 bf16, 3 half)
-    float *part_o, *part_ml;          // per (trace, piece, kv head): [8, 128] and [8, 2] fp32; B * max_pieces * Hkv of them
-    int32_t B, Hq, Hkv, G, max_blocks, n_blocks, max_L, out_fmt;
-    int32_t n_iter;                   // rounds of DEC_PIECE keys per workgroup (set by the launcher)
-    int32_t max_pieces;               // pieces of the longest trace (set by the launcher)
+    const int32_t *table, *plens, *cu, *tok_trace;
+    const FewTile *tiles;             // [n_tiles]; null: one suffix token per trace, tile = trace
+    int32_t *arrived;                 // n_tiles * Hkv arrival counters, zero before and after
+    void *out;                        // [T, Hq * 128] in fragment order, format out_fmt (1 bf16, 3 half)
+    float *part_o, *part_ml;          // few_attn_records of [rows, 128] and [rows, 2] fp32, rows = few_attn_rows
+    int32_t B, T, Hq, Hkv, G, max_blocks, n_blocks, max_L, out_fmt, n_tiles;
+    int32_t pieces, wave_pages, fold, inv_G;     // set by the launcher
     float scale_log2;                 // log2(e) / sqrt(head_dim)
 };
-hipError_t launch_dec_attn(DecAttn a, hipStream_t s);
-inline size_t dec_attn_part_o_bytes(int64_t n_pieces, int Hkv) { return (size_t)n_pieces * Hkv * DEC_MAX_G * 128 * 4; }
-inline size_t dec_attn_part_ml_bytes(int64_t n_pieces, int Hkv) { return (size_t)n_pieces * Hkv * DEC_MAX_G * 2 * 4; }
+// Tiles of a batch (host copies; one: one suffix token per trace), rows of a tile, records for n_tiles tiles whatever the
+// context lengths.
+int64_t few_attn_tiles(const int32_t *h_cu, int B, const int32_t *h_group_start, int n_units, int G, bool one);
+int few_attn_rows(bool one);
+int64_t few_attn_records(int64_t n_tiles, int Hkv, bool one);
+hipError_t launch_few_attn(FewAttn a, hipStream_t s);
 
 // ---- cascade (cascade.hip) ----
 hipError_t launch_cascade_select(const uint8_t *keep, const int32_t *verdict_d, const int32_t *req_start, const int32_t *parent,

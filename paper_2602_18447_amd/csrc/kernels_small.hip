@@ -38,9 +38,41 @@ __device__ __forceinline__ void store_terms(T *o, int c, int d, int terms, float
 // clamped to the host-validated bounds so that inconsistent device arrays cannot cause out-of-range accesses.
 // Bound by the embedding rows written (114 MB at 18606 tokens of width 1536); as three launches with 2-byte loads
 // this was 52 + 8 + 4 us there and 9 us where a pass has few tokens.
+// A pass over few rows takes one more workgroup, which lists the tiles of its attention: thread = context unit.
+__device__ void front_few_tiles(const FrontArgs &a) {
+    __shared__ int s_end[128];
+    const int i = threadIdx.x;
+    AttnUnit u = {};
+    int n = 0;
+    if (i < a.n_units) {
+        u = plan_unit(a.cu, a.plens, a.group_start, a.n_units, i, a.B, a.T, a.max_L, 0);
+        n = (a.G * u.S_tot + a.few_rows - 1) / a.few_rows;
+    }
+    s_end[i] = n;
+    __syncthreads();
+    for (int o = 1; o < 128; o <<= 1) {                  // inclusive scan
+        const int v = i >= o ? s_end[i - o] : 0;
+        __syncthreads();
+        s_end[i] += v;
+        __syncthreads();
+    }
+    const int first = s_end[i] - n, cu0 = min(max(a.cu[u.b0], 0), a.T - 1);
+    for (int m = 0; m < n && first + m < a.n_few_tiles; ++m) {
+        FewTile t;
+        t.b0 = u.b0; t.cu0 = cu0; t.row0 = m * a.few_rows; t.n_rows = min(a.G * u.S_tot, a.G * (a.T - cu0)); t.L = u.L;
+        const int tok_lo = t.row0 / a.G, tok_hi = (min(t.row0 + a.few_rows, t.n_rows) - 1) / a.G;
+        t.k_start = cu0 + min(plan_member_start(a.cu, a.T, u, tok_lo), tok_lo);
+        t.n_keys = max(cu0 + tok_hi + 1 - t.k_start, 1);
+        t.pad = 0;
+        a.few_tiles[first + m] = t;
+    }
+    for (int k = s_end[127] + i; k < a.n_few_tiles; k += 128) a.few_tiles[k] = FewTile{};
+}
+
 template <typename E>
 __global__ __launch_bounds__(128) void front_kernel(FrontArgs a, double log_theta) {
     const int t = blockIdx.x;
+    if (a.few_tiles && t == max(a.T, a.B)) { front_few_tiles(a); return; }
     if (t == 0 && a.ctl)
         for (int i = threadIdx.x; i < a.n_ctl; i += blockDim.x) a.ctl[i] = 0;
     if (threadIdx.x == 0 && t < a.B) a.last_row[t] = min(max(a.cu[t + 1] - 1, 0), a.T - 1);
@@ -107,7 +139,7 @@ __global__ __launch_bounds__(128) void front_kernel(FrontArgs a, double log_thet
 }
 
 hipError_t launch_front(int dtype, const FrontArgs &a, hipStream_t s) {
-    const int n = a.T > a.B ? a.T : a.B;
+    const int n = (a.T > a.B ? a.T : a.B) + (a.few_tiles ? 1 : 0);
     if (dtype == 0) front_kernel<float><<<n, 128, 0, s>>>(a, log((double)a.theta));
     else front_kernel<bf16><<<n, 128, 0, s>>>(a, log((double)a.theta));
     return hipGetLastError();

@@ -1,0 +1,47 @@
+"""Attention of passes over at most 128 suffix tokens against the oracle where its cut of rows and keys changes: contexts
+around page, round and piece borders, tiles that end inside a token's heads, suffixes around the 32-row and 16-key
+borders, one piece for context and suffix together (many tiles), groups of candidates on one context."""
+import numpy as np
+import pytest
+import torch
+
+import confspec_workloads as W
+from paper_2602_18447_amd.runner import Verifier
+from tests import gpu_cases as G
+from tests.test_gpu_verify import _shared_case
+
+pytestmark = pytest.mark.gpu
+
+HEADS = {"G1": (4, 4), "G5": (5, 1), "G6": (12, 2), "G16": (16, 1)}
+
+
+def _wl(name, seed, heads, prefix, suffix):
+    hq, hkv = HEADS[heads]
+    return W.tiny_workload(name, seed, dtype="bf16", n_layers=3, d_model=512, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, d_ffn=768,
+                           vocab=512, block_size=16, prefix_lens=prefix, suffix_lens=suffix, taus=(0.5, 0.55, 0.6, 0.9))
+
+
+@pytest.mark.parametrize("heads", list(HEADS))
+@pytest.mark.parametrize("batch", [
+    ((0,), (5,)), ((1, 0), (2, 33)), ((15, 16, 17, 255), (6, 7, 11, 17)), ((256, 257, 511, 512, 513), (16, 17, 31, 32, 32)),
+    ((4097,), (96,)), ((700, 31), (1, 127)), ((300,) * 40, (3,) * 40), ((5, 2040, 90), (1, 1, 1)), ((640,) * 64, (2,) * 64),
+], ids=lambda b: f"B{len(b[0])}T{sum(b[1])}L{max(b[0])}")
+def test_few_row_attention_matches_oracle(heads, batch):
+    print(f"few-row attention: {heads}, prefixes {batch[0]}, suffixes {batch[1]}", flush=True)
+    G.parity_case(_wl("attn_few", 9500 + sum(batch[1]), heads, *batch))
+
+
+@pytest.mark.parametrize("heads", ["G1", "G6"])
+def test_few_row_attention_on_shared_contexts(heads):
+    print(f"few-row attention on shared contexts, {heads}", flush=True)
+    hq, hkv = HEADS[heads]
+    groups = [(300, (5, 1, 17)), (0, (3, 4)), (77, (9,)), (1030, (20, 33, 2, 7))]
+    wl, weights, batch, kv, gstart = _shared_case("attn_few_shared", 9600, groups, n_q_heads=hq, n_kv_heads=hkv)
+    taus, vids = G.sweep_taus(wl), W.draw_verdict_ids(wl)
+    ver = Verifier(wl.model, weights)
+    outs = ver.verify_shared(kv, batch, gstart, vids, taus)
+    torch.cuda.synchronize()
+    gpu = dict(logits=outs[0].cpu().numpy().astype(np.float64), conf=outs[1].cpu().numpy().astype(np.float64),
+               verdict=outs[2].cpu().numpy(), accept=outs[3].cpu().numpy(), taus=taus, vids=vids)
+    G.compare(wl, gpu, G.run_oracle(wl, weights, batch, kv, taus, vids), wl.name)
+    ver.close()
