@@ -422,18 +422,19 @@ __global__ __launch_bounds__(64 * NW, 2) void few_attn_kernel(FewAttn a) {
 #pragma unroll
     for (int i = 0; i < RP; ++i) { mm[i] = -INFINITY; ll[i] = 0.f; oo[i] = f32x4{0.f, 0.f, 0.f, 0.f}; }
     constexpr int STEP = NW / RB;
+    const XwgLoads parts(a.part_o + rec0 * ROWS * 128, (unsigned)(n_p * ROWS) * 512u);
     for (int pp = wave / RB; pp < n_p; pp += 2 * STEP) {                // two pieces in flight
         f32x4 ov[2 * RP];
         float mv[2 * RP], lv[2 * RP];
 #pragma unroll
         for (int i = 0; i < 2 * RP; ++i) {
             const int r = min(row_b + 2 * (i % RP) + rl, rows - 1);
-            const size_t at = (rec0 + (i < RP ? pp : min(pp + STEP, n_p - 1))) * ROWS + r;
-            ov[i] = xwg_load4(reinterpret_cast<const f32x4 *>(a.part_o + at * 128) + c4);
+            const unsigned rec = (i < RP ? pp : min(pp + STEP, n_p - 1)) * ROWS + r;
+            const size_t at = rec0 * ROWS + rec;
+            ov[i] = parts.load4(rec * 512u + c4 * 16u);
             mv[i] = xwg_load(a.part_ml + at * 2);
             lv[i] = xwg_load(a.part_ml + at * 2 + 1);
         }
-        xwg_wait4(ov);
 #pragma unroll
         for (int i = 0; i < 2 * RP; ++i) {
             if (i >= RP && pp + STEP >= n_p) break;

@@ -42,15 +42,6 @@ namespace {
 __device__ __forceinline__ void dma16_base(const char *base, unsigned off, unsigned lds_dst) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(lds_dst), "v"(off), "s"(base) : "memory");
 }
-// 16 bytes per lane into registers that must not be touched before a wait_vm that covers the load.  Assembly for the same
-// reason: a load the compiler knows of would make it wait for the weights issued after it too.
-template <int OFFSET>
-__device__ __forceinline__ void load_x(bf16x8 &x, const char *base, unsigned off) {
-    asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=v"(x) : "v"(off), "s"(base), "n"(OFFSET) : "memory");
-}
-__device__ __forceinline__ void load_f32(float &x, const float *base, unsigned off) {
-    asm volatile("global_load_dword %0, %1, %2" : "=v"(x) : "v"(off), "s"(base) : "memory");
-}
 // Barrier for LDS data only.  (__syncthreads() also waits until every store to global memory is acknowledged, about a
 // microsecond.)
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
@@ -189,26 +180,24 @@ __global__ __launch_bounds__(64 * NW, 2) void skinny_kernel(SkinnyGemm a) {
         }
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            const unsigned row = r0 + min(p * (NT / 16) + (tid >> 4), M - 1);
+            const int row = r0 + min(p * (NT / 16) + (tid >> 4), M - 1);
+            const float *sp = a.ssq_in + (size_t)row * a.ssq_n;
 #pragma unroll
-            for (int e = 0; e < 6; ++e) load_f32(sqv[p][e], a.ssq_in, (row * a.ssq_n + min((tid & 15) + 16 * e, a.ssq_n - 1)) * 4u);
+            for (int e = 0; e < 6; ++e) sqv[p][e] = sp[min((tid & 15) + 16 * e, a.ssq_n - 1)];
             if constexpr (NSQ > 6) {
 #pragma unroll
                 for (int e = 6; e < NSQ; ++e) sqv[p][e] = 0.f;
                 if (a.ssq_n > 96) {                                        // uniform
 #pragma unroll
-                    for (int e = 6; e < NSQ; ++e) load_f32(sqv[p][e], a.ssq_in, (row * a.ssq_n + min((tid & 15) + 16 * e, a.ssq_n - 1)) * 4u);
+                    for (int e = 6; e < NSQ; ++e) sqv[p][e] = sp[min((tid & 15) + 16 * e, a.ssq_n - 1)];
                 }
             }
-            load_f32(sc_prev[p], a.sc_in, row * 4u);
+            sc_prev[p] = a.sc_in[row];
         }
     }
     auto row_factors = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-#pragma unroll
-            for (int e = 0; e < NSQ; ++e) asm volatile("" : "+v"(sqv[p][e]));
-            asm volatile("" : "+v"(sc_prev[p]));
             const int row = p * (NT / 16) + (tid >> 4);
             float sq = sq_far[p];
 #pragma unroll
@@ -272,36 +261,19 @@ __global__ __launch_bounds__(64 * NW, 2) void skinny_kernel(SkinnyGemm a) {
 #pragma unroll
         for (int q = 0; q < CT; ++q) acc[i][q] = f32x4{0.f, 0.f, 0.f, 0.f};
     const char *xbase = reinterpret_cast<const char *>(a.X) + (size_t)(MB * mi) * (a.K >> 5) * 1024;
-    if (NBUF == 2 && n_grp > 0) issue_w(0);
-    for (int g = 0; g < n_grp; ++g) {
-        if (NBUF == 1) issue_w(g);
-        bf16x8 xf[D][MB][2];
+    // Activations of group g; k-tiles past the end repeat the last one, their products are skipped.
+    auto load_x = [&](int g, bf16x8 (&xf)[D][MB][2]) __attribute__((always_inline)) {
 #pragma unroll
         for (int dd = 0; dd < D; ++dd) {
-            // (k-tiles past the end repeat the last one; their products are skipped)
-            const unsigned ko = (unsigned)(kt0 + wave + NW * min(g * D + dd, nkw - 1)) * 2048u;
+            const char *xb = xbase + (unsigned)(kt0 + wave + NW * min(g * D + dd, nkw - 1)) * 2048u;
 #pragma unroll
             for (int i = 0; i < MB; ++i) {
-                load_x<0>(xf[dd][i][0], xbase + ko, xoff[i]);
-                load_x<1024>(xf[dd][i][1], xbase + ko, xoff[i]);
+                xf[dd][i][0] = *reinterpret_cast<const bf16x8 *>(xb + xoff[i]);
+                xf[dd][i][1] = *reinterpret_cast<const bf16x8 *>(xb + xoff[i] + 1024);
             }
         }
-        // in flight, in order: this group's weights, this group's activations, the next group's weights
-        if (NBUF == 2 && g + 1 < n_grp) issue_w(g + 1);
-        if (g == 0 && want_f) {
-            if (nkw >= D) wait_vm<std::min(2 * CT * D + 2 * MB * D, 63)>();    // (at least so many were issued after the sums)
-            else wait_vm<0>();
-            row_factors();
-        }
-        if (NBUF == 2 && (g + 2) * D <= nkw) wait_vm<2 * CT * D>();
-        else wait_vm<0>();
-#pragma unroll
-        for (int dd = 0; dd < D; ++dd)
-#pragma unroll
-            for (int i = 0; i < MB; ++i) {
-                asm volatile("" : "+v"(xf[dd][i][0]));                     // (no use may be moved in front of the wait)
-                asm volatile("" : "+v"(xf[dd][i][1]));
-            }
+    };
+    auto multiply = [&](int g, const bf16x8 (&xf)[D][MB][2]) __attribute__((always_inline)) {
         const unsigned char *wg = ring + (NBUF == 2 ? (g & 1) * GB : 0);
 #pragma unroll
         for (int dd = 0; dd < D; ++dd) {
@@ -317,12 +289,43 @@ __global__ __launch_bounds__(64 * NW, 2) void skinny_kernel(SkinnyGemm a) {
             }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");               // the group's slots may be refilled
+    };
+    // The compiler places the waits for the activations.  It counts its own loads only, not the direct ones, so a use of
+    // the group's activations waits until no more memory operations are outstanding than activation loads were issued
+    // behind them.  XA groups of activations ahead are as many loads as a group of weights: then that wait never covers the
+    // weights that are to stay in flight.
+    if constexpr (NBUF == 1) {
+        for (int g = 0; g < n_grp; ++g) {
+            bf16x8 xf[D][MB][2];
+            load_x(g, xf);
+            issue_w(g);
+            if (g == 0 && want_f) row_factors();
+            wait_vm<0>();
+            multiply(g, xf);
+        }
+    } else if (n_grp > 0) {
+        constexpr int XA = (CT + MB - 1) / MB;
+        bf16x8 xf[XA + 1][D][MB][2];
+#pragma unroll
+        for (int u = 0; u < XA; ++u) load_x(u, xf[u]);
+        issue_w(0);
+        for (int g0 = 0; g0 < n_grp; g0 += XA + 1) {
+#pragma unroll
+            for (int u = 0; u <= XA; ++u) {
+                const int g = g0 + u;
+                if (g >= n_grp) break;
+                load_x(g + XA, xf[(u + XA) % (XA + 1)]);
+                if (g + 1 < n_grp) issue_w(g + 1);
+                // issued behind this group's weights: activations, and the next group's weights
+                if ((g + 2) * D <= nkw) wait_vm<2 * MB * D + 2 * CT * D>();
+                else wait_vm<2 * MB * D>();
+                multiply(g, xf[u]);
+                if (g == 0 && want_f) row_factors();
+            }
+        }
     }
 
-    if (n_grp == 0 && want_f) {                                           // a wavefront without k-tiles
-        wait_vm<0>();
-        row_factors();
-    }
+    if (n_grp == 0 && want_f) row_factors();                               // a wavefront without k-tiles
 
     auto epilogue = [&](int ch, int j, f32x4 v) __attribute__((always_inline)) {
         const int row_l = row_of(ch, j), row = r0 + row_l, tt = tile_of(j);
@@ -373,7 +376,7 @@ __global__ __launch_bounds__(64 * NW, 2) void skinny_kernel(SkinnyGemm a) {
 
     // ---- the wavefronts' products added in wavefront order, RB row blocks at a time, in the registers' own layout
     f32x4 *red = reinterpret_cast<f32x4 *>(smem);                          // [NW][NBK][64]
-    f32x4 *plane = a.S > 1 ? reinterpret_cast<f32x4 *>(a.planes) + (size_t)((t * a.ms + mi) * a.S) * (MB * CT * 64) + lane : nullptr;
+    f32x4 *plane = a.S > 1 ? reinterpret_cast<f32x4 *>(a.planes) + (size_t)((t * a.ms + mi) * a.S) * (MB * CT * 64) : nullptr;
     lds_barrier();                                                         // every wavefront is done with its ring
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
@@ -391,25 +394,25 @@ __global__ __launch_bounds__(64 * NW, 2) void skinny_kernel(SkinnyGemm a) {
 #pragma unroll
                 for (int w = 1; w < NW; ++w) v += red[(w * NBK + b) * 64 + lane];
                 if (a.S == 1) epilogue(ch, j, v);
-                else xwg_store4(plane + ((size_t)s * MB * CT + NBK * ch + b) * 64, v);
+                else xwg_store4(plane + ((size_t)s * MB * CT + NBK * ch + b) * 64 + lane, v);
             }
         }
     }
     if (a.S > 1) {
         if (!xwg_arrive_last(a.tile_cnt + t * a.ms + mi, a.S, &s_last, tid)) return;
+        const XwgLoads planes(plane, (unsigned)(a.S * MB * CT) * 1024u);
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch)
 #pragma unroll
             for (int j = 0; j < EPB; ++j) {
                 const int b = wave + NW * j;
                 if (b >= NBK) continue;
-                const f32x4 *p = plane + (NBK * ch + b) * 64;
                 f32x4 v = {0.f, 0.f, 0.f, 0.f};
                 for (int sp = 0; sp < a.S; sp += 4) {                      // loads in flight together, added in slice order
                     f32x4 pv[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) pv[q] = xwg_load4(p + (size_t)min(sp + q, a.S - 1) * (MB * CT * 64));
-                    xwg_wait4(pv);
+                    for (int q = 0; q < 4; ++q)
+                        pv[q] = planes.load4((unsigned)(min(sp + q, a.S - 1) * MB * CT + NBK * ch + b) * 1024u + lane * 16u);
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
                         if (sp + q < a.S) v += pv[q];
@@ -480,15 +483,17 @@ static hipError_t launch_one(const SkinnyGemm &a, hipStream_t s) {
 template <int EPI, bool F16, int MB>
 static hipError_t launch_mb(const SkinnyGemm &a, const SkinnyPlan &p, hipStream_t s) {
     const bool one_group = a.K <= 64 * 24;               // a wavefront's whole share of the k range at once
+    constexpr int D2 = MB < 4 ? 2 : 1;                   // (two groups of more activations than this do not fit the registers)
     if constexpr (EPI == SK_EPI_SWIGLU) {
         if (p.ct == 5) return launch_one<EPI, F16, MB, 5, 8, 1, 1>(a, s);
         if constexpr (MB <= 4) {
             if (p.ct == 4) return launch_one<EPI, F16, MB, 4, 8, 1, 1>(a, s);
-            return one_group ? launch_one<EPI, F16, MB, 1, 8, 3>(a, s) : launch_one<EPI, F16, MB, 1, 8, 2>(a, s);
+            return one_group ? launch_one<EPI, F16, MB, 1, 8, 3, 1>(a, s) : launch_one<EPI, F16, MB, 1, 8, D2>(a, s);
         }
     } else if constexpr (MB <= 4) {
-        if (p.ct == 1) return one_group || a.S > 1 ? launch_one<EPI, F16, MB, 1, 8, 3>(a, s) : launch_one<EPI, F16, MB, 1, 8, 2>(a, s);
-        if (p.ct == 2) return launch_one<EPI, F16, MB, 2, 8, 2>(a, s);
+        if (p.ct == 1 && one_group) return launch_one<EPI, F16, MB, 1, 8, 3, 1>(a, s);
+        if (p.ct == 1) return a.S > 1 && MB < 3 ? launch_one<EPI, F16, MB, 1, 8, MB < 3 ? 3 : D2>(a, s) : launch_one<EPI, F16, MB, 1, 8, D2>(a, s);
+        if (p.ct == 2) return launch_one<EPI, F16, MB, 2, 8, D2>(a, s);
         if constexpr (EPI == SK_EPI_RESID) {
             if (p.ct == 3) return launch_one<EPI, F16, MB, 3, 8, 1, 1>(a, s);
             if (p.ct == 4) return launch_one<EPI, F16, MB, 4, 8, 1, 1>(a, s);

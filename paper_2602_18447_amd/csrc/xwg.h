@@ -8,21 +8,20 @@ namespace cs {
 
 __device__ inline void xwg_store(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline float xwg_load(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-// The same with 16 bytes per lane (assembly: there is no atomic access of that width; each 4-byte part is one on its own,
-// which is all a hand-over needs).  What xwg_load4 returns may be used only behind xwg_wait4 on it.
+// The same with 16 bytes per lane (there is no atomic access of that width; each 4-byte part is one on its own, which is all
+// a hand-over needs): the store in assembly, the load as a buffer load at device scope from wave-uniform `base` plus a byte
+// offset per lane; offsets at or past `bytes` read zeros.
 typedef __attribute__((ext_vector_type(4))) float xwg_f32x4;
+typedef __attribute__((ext_vector_type(4))) unsigned xwg_u32x4;
 __device__ inline void xwg_store4(xwg_f32x4 *p, xwg_f32x4 v) { asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory"); }
-__device__ inline xwg_f32x4 xwg_load4(const xwg_f32x4 *p) {
-    xwg_f32x4 v;
-    asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
-    return v;
-}
-template <int N>
-__device__ inline void xwg_wait4(xwg_f32x4 (&v)[N]) {
-    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
-#pragma unroll
-    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
-}
+struct XwgLoads {
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ XwgLoads(const void *base, unsigned bytes) : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000)) {}
+    __device__ xwg_f32x4 load4(unsigned off) const {
+        constexpr int SC1 = 1 << 4;
+        return __builtin_bit_cast(xwg_f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, SC1));
+    }
+};
 // Every thread calls it after its hand-over stores: waits until they are acknowledged, then counts the workgroup in.
 // Returns true (to all threads) for the workgroup that arrives last of n; that one also clears the counter.
 __device__ inline bool xwg_arrive_last(int32_t *cnt, int n, volatile int *flag, int tid) {
