@@ -91,7 +91,8 @@ int confspec_op_verdict_gate(confspec_ctx *ctx, const confspec_batch *batch, con
 
 /* The slices the pass carves its workspace into, in carving order: byte offsets and lengths (host arrays of *n
  * entries on entry, *n = number of slices on return, at most 48) and the total.  exact == NULL: the layout behind
- * confspec_workspace_bytes(T, B); otherwise the layout for that one batch (confspec_static_scratch_need).  For
+ * confspec_workspace_bytes(T, B); otherwise the layout for that one batch (confspec_static_scratch_need).  What only
+ * passes of at most 128 suffix tokens use lies over slices that such passes do not use and is not listed.  For
  * checks of the layout on the host; nothing is launched. */
 int confspec_op_workspace_slices(const confspec_ctx *ctx, int32_t T, int32_t B, const confspec_batch *exact,
                                  size_t *h_offsets, size_t *h_bytes, int32_t *n, size_t *total);

@@ -485,12 +485,13 @@ int64_t few_attn_tiles(const int32_t *h_cu, int B, const int32_t *h_group_start,
     return n;
 }
 constexpr int FEW_SLOTS = 256;       // workgroups that are resident at once
-int64_t few_attn_records(int64_t n_tiles, int Hkv, bool one) { return std::max<int64_t>(FEW_SLOTS, n_tiles * Hkv * (one ? 1 : 2)); }
+static_assert(FEW_RECORDS >= FEW_SLOTS, "a record per workgroup where a tile has several pieces");
 
 // Pieces of the longest context (and the suffix, where there are several suffix tokens): as many as fill the chip once; a
 // wavefront takes an even number of pages, because the round of a single page costs nearly what one of two does (one trace
 // of 4096 keys: 32 pieces of one page per wavefront 12.5 us, 16 of two 10.6 us, 11 of three 12.2 us, 8 of four 12.1 us).
-static void few_attn_pieces(FewAttn &a, bool one) {
+// A tile has one piece or n_tiles * Hkv * pieces <= FEW_SLOTS, so FEW_RECORDS partial results are enough.
+void few_attn_pieces(FewAttn &a, bool one) {
     const int suffix = one ? 0 : 1, want = std::max(FEW_SLOTS / (a.n_tiles * a.Hkv) - suffix, 1);
     const int pages = std::max((a.max_L + 15) / 16, 1);
     a.wave_pages = 2 * ((pages - 1) / (2 * NW * want) + 1);

@@ -106,12 +106,12 @@ struct WsLayout {
     size_t plan_counts, plan_tiles, plan_items, part_o, part_ml;
     size_t x_last, h_last, attn_last, act_last, plan2_counts, plan2_tiles, plan2_items;   // last layer, last rows only
     size_t splitk, splitk_bytes;                                                        // split-K partial products
-    size_t few_ctl, few_tiles, sk_ssq, sk_sc, kv_row;   // passes over few rows: arrival counters, attention tiles, row
-                                                        // statistics; write-back rows
+    // passes over few rows: arrival counters, attention tiles and partial results, row statistics, write-back rows, planes
+    size_t few_ctl, few_tiles, few_part_o, few_part_ml, sk_ssq, sk_sc, kv_row, sk_planes, sk_planes_bytes;
     size_t part_o_bytes, part_ml_bytes;
     size_t total;
     int64_t max_tiles, max_items, max_tiles2, max_items2;
-    size_t slice_off[48], slice_len[48];   // every slice as it was carved, for checks of the layout
+    size_t slice_off[48], slice_len[48];   // every slice as it was carved (few-row ones apart), for checks of the layout
     int n_slices;
 };
 
@@ -147,6 +147,11 @@ WsLayout ws_layout(const confspec_ctx *ctx, int64_t T, int64_t B, const confspec
         size_t o = at;
         at = align_up(at + bytes);
         if (w.n_slices < 48) { w.slice_off[w.n_slices] = o; w.slice_len[w.n_slices] = bytes; ++w.n_slices; }
+        return o;
+    };
+    auto take_over = [&](size_t bytes) {     // a slice that may lie over the listed ones
+        size_t o = at;
+        at = align_up(at + bytes);
         return o;
     };
     size_t eb = elem_bytes(c.dtype);
@@ -186,20 +191,12 @@ WsLayout ws_layout(const confspec_ctx *ctx, int64_t T, int64_t B, const confspec
             w.max_items = std::max<int64_t>(pe.n_items, 1);
             part_slots = std::max<int64_t>(std::max(pe.n_part_slots, pe_last.n_part_slots), 1);
         }
+        const size_t general_at = at;
         w.plan_counts = take(256);
         w.plan_tiles = take((size_t)w.max_tiles * sizeof(cs::AttnTile));
         w.plan_items = take((size_t)w.max_items * sizeof(cs::AttnItem));
         w.part_o_bytes = (size_t)part_slots * cs::ATTN_BM * c.head_dim * 4;
         w.part_ml_bytes = (size_t)part_slots * cs::ATTN_BM * 2 * 4;
-        // the few-row attention's partial results (a general layout serves every smaller batch, few-row passes included)
-        const int64_t few_T = std::min<int64_t>(T, cs::SK_MAX_ROWS), few_B = std::min(few_T, B);
-        const int64_t few_tiles = skinny_shape_ok(c, few_T) && !(exact && few_T < T) ? few_tiles_bound(c, few_T, few_B) : 0;
-        if (few_tiles) {
-            const int64_t rec = cs::few_attn_records(few_tiles, c.n_kv_heads, false) * cs::few_attn_rows(false);
-            w.part_o_bytes = std::max(w.part_o_bytes, (size_t)rec * c.head_dim * 4);
-            w.part_ml_bytes = std::max(w.part_ml_bytes, (size_t)rec * 2 * 4);
-        }
-        w.few_tiles = take(std::max<int64_t>(few_tiles, 1) * sizeof(cs::FewTile));
         w.part_o = take(w.part_o_bytes);
         w.part_ml = take(w.part_ml_bytes);
         // the last layer works on the last position of each trace only: B rows, one attention tile per
@@ -235,15 +232,26 @@ WsLayout ws_layout(const confspec_ctx *ctx, int64_t T, int64_t B, const confspec
             sk = std::max(sk, cs::gemm_splitk_max_bytes(ctx->set.gemm, (int)T, 2 * c.d_ffn, c.d_model * t));
             sk = std::max(sk, cs::gemm_splitk_max_bytes(ctx->set.gemm, (int)T, c.d_model, c.d_ffn * t));
         }
-        // a general layout serves every smaller batch, few-row passes included
-        const int sk_rows = (int)std::min<int64_t>(T, cs::SK_MAX_ROWS);
-        if (skinny_shape_ok(c, exact ? T : sk_rows)) sk = std::max(sk, skinny_pass_plane_bytes(c, sk_rows));
         w.splitk_bytes = sk;
         w.splitk = take(std::max<size_t>(sk, 256));
-        w.few_ctl = take((size_t)cs::FEW_CTL_INTS * 4);
-        w.sk_ssq = take((size_t)2 * sk_rows * (c.d_model / 16) * 4);
-        w.sk_sc = take((size_t)2 * sk_rows * 4);
-        w.kv_row = take((size_t)T * 4);
+        // What only a pass over few rows uses (a general layout serves every smaller batch, such passes included) lies
+        // over what only the others use, so that it asks for more scratch only where the batch is tiny.
+        const int few_T = (int)std::min<int64_t>(T, cs::SK_MAX_ROWS);
+        if (skinny_shape_ok(c, exact ? T : few_T)) {
+            const size_t general_end = at;
+            at = general_at;
+            const size_t rec = (size_t)cs::FEW_RECORDS * cs::few_attn_rows(false);
+            w.few_tiles = take_over((size_t)few_tiles_bound(c, few_T, std::min<int64_t>(few_T, B)) * sizeof(cs::FewTile));
+            w.few_ctl = take_over((size_t)cs::FEW_CTL_INTS * 4);
+            w.few_part_o = take_over(rec * c.head_dim * 4);
+            w.few_part_ml = take_over(rec * 2 * 4);
+            w.sk_ssq = take_over((size_t)2 * few_T * (c.d_model / 16) * 4);
+            w.sk_sc = take_over((size_t)2 * few_T * 4);
+            w.kv_row = take_over((size_t)few_T * 4);
+            w.sk_planes_bytes = skinny_pass_plane_bytes(c, few_T);
+            w.sk_planes = take_over(w.sk_planes_bytes);
+            at = std::max(at, general_end);
+        }
     }
     w.total = at;
     return w;
@@ -715,7 +723,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
     // also an attention shaped for that, where it is the faster one and the scratch holds its partial results.
     bool skinny = skinny_shape_ok(c, T) && set.gemm.tile == 0 && set.gemm.splitk == 0;
     for (int l = 0; l < c.n_layers && skinny; ++l) skinny = rope_fused_in(l) && format_of(l) != 2;
-    skinny = skinny && skinny_pass_plane_bytes(c, T) <= L.splitk_bytes;
+    skinny = skinny && skinny_pass_plane_bytes(c, T) <= L.sk_planes_bytes;
     const int G = c.n_q_heads / c.n_kv_heads;
     const bool one = skinny && one_token_shape(c, T, B) && !ex.dev_group_start;
     const bool use_dec = one && set.decode_kernels && (set.decode_kernels == 2 || (d <= 64 * cs::DEC_MAX_KT && qw <= 64 * cs::DEC_MAX_KT));
@@ -762,7 +770,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         const void *wgu = f16 ? w->w_gate_up_f16[l] : w->w_gate_up[l], *wdn = f16 ? w->w_down_f16[l] : w->w_down[l];
         cs::SkinnyGemm base = {};
         base.M = T; base.d_norm = d; base.ssq_n = d / 16; base.eps = c.rms_eps;
-        base.planes = (float *)(ws + L.splitk); base.tile_cnt = ctl + cs::FEW_CTL_TILE;
+        base.planes = (float *)(ws + L.sk_planes); base.tile_cnt = ctl + cs::FEW_CTL_TILE;
         auto proj = [&](const void *X, const void *W, int K, int n_ct, int stat) {
             cs::SkinnyGemm g = base;
             g.X = (const cs::bf16 *)X; g.W = (const cs::bf16 *)W; g.K = K; g.n_ct = n_ct;
@@ -793,7 +801,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         at.table = kv->block_table; at.plens = batch->prefix_lens; at.cu = batch->cu_suffix; at.tok_trace = (const int32_t *)(ws + L.tok_trace);
         at.tiles = as_one ? nullptr : (const cs::FewTile *)(ws + L.few_tiles); at.n_tiles = (int)few_tiles; at.arrived = ctl + cs::FEW_CTL_ATTN;
         at.out = ws + L.attn; at.out_fmt = tm;
-        at.part_o = (float *)(ws + L.part_o); at.part_ml = (float *)(ws + L.part_ml);
+        at.part_o = (float *)(ws + L.few_part_o); at.part_ml = (float *)(ws + L.few_part_ml);
         at.B = B; at.T = T; at.Hq = c.n_q_heads; at.Hkv = c.n_kv_heads; at.G = G;
         at.max_blocks = kv->max_blocks_per_seq; at.n_blocks = kv->n_blocks; at.max_L = max_L;
         at.scale_log2 = 1.44269504088896340736f / sqrtf((float)c.head_dim);

@@ -7,11 +7,7 @@
 namespace cs {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
-typedef __attribute__((ext_vector_type(4))) short i16x4;
-typedef __attribute__((ext_vector_type(8))) short i16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 
 #define CS_LDS_AS __attribute__((address_space(3)))
 
@@ -42,10 +38,6 @@ __device__ inline void dec_wait_vm() {
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 __device__ inline void dec_wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
-
-__device__ inline unsigned short to_fmt(float v, int fmt) {   // fmt 3: IEEE half (saturating), else bf16
-    return fmt == 3 ? __half_as_ushort(to_half_sat(v)) : __bfloat16_as_ushort(__float2bfloat16(v));
-}
 
 }  // namespace
 
@@ -229,7 +221,7 @@ hipError_t launch_dec_head(const DecHead &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// The rows of the language-model head: the records of all workgroups of dec_gemm_kernel<DEC_EPI_HEAD> merged in
+// The rows of the language-model head: the records of all workgroups of dec_head_kernel merged in
 // workgroup order per row (one wavefront per row).
 __global__ __launch_bounds__(64) void dec_head_final_kernel(const float *__restrict__ part, int nwg, const float *__restrict__ verdict_logits,
                                                              int n_verdict, int32_t *__restrict__ token, float *__restrict__ max_logit,

@@ -14,12 +14,7 @@
 #include "../../include/confspec_ops.h"
 #include "../../include/confspec_static.h"
 #include "attn_plan.h"
-
-namespace cs {   // skinny_bf16.hip: tiling of a projection over few rows
-struct SkinnyPlan { int mb, ms, ct, S; };
-SkinnyPlan skinny_plan(int M, int K, int n_ct);
-size_t skinny_plane_bytes(int M, int K, int n_ct);
-}
+#include "kernels.h"
 
 static int g_fail = 0;
 #define CHECK(cond, ...)                                                         \
@@ -275,6 +270,21 @@ int main() {
         size_t pb = cs::skinny_plane_bytes(M, K, n_ct);
         ok = ok && pb >= (p.S > 1 ? (size_t)p.S * 16 * p.mb * p.ms * n_ct * 16 * 4 : 0) && pb <= cs::skinny_plane_bytes(128, K, n_ct);
         if (!ok) { printf("skinny_plan(M=%d, K=%d, n_ct=%d) -> mb=%d ms=%d ct=%d S=%d planes=%zu\n", M, K, n_ct, p.mb, p.ms, p.ct, p.S, pb); ++g_fail; }
+    }
+    // pieces of the few-row attention: the whole context covered, and a partial result for every workgroup of a tile that
+    // has several pieces
+    for (int iter = 0; iter < 20000; ++iter) {
+        const bool one = iter & 1;
+        cs::FewAttn a = {};
+        a.n_tiles = 1 + (int)(rng() % (iter % 3 ? 300 : 20));
+        a.Hkv = 1 + (int)(rng() % 8);
+        a.max_L = (int)(rng() % (iter % 5 ? 5000 : 140000));
+        cs::few_attn_pieces(a, one);
+        const int of_context = a.pieces - (one || a.fold ? 0 : 1);
+        CHECK(a.wave_pages >= 1 && of_context >= 1 && (int64_t)of_context * a.wave_pages * 8 * 16 >= a.max_L &&
+              (a.pieces == 1 || (int64_t)a.n_tiles * a.Hkv * a.pieces <= cs::FEW_RECORDS),
+              "few_attn_pieces(n_tiles=%d, Hkv=%d, max_L=%d, one=%d) -> pieces=%d wave_pages=%d fold=%d", a.n_tiles, a.Hkv, a.max_L, one,
+              a.pieces, a.wave_pages, a.fold);
     }
     if (g_fail) { printf("host_check: %d check(s) failed\n", g_fail); return 1; }
     printf("host_check: ok\n");

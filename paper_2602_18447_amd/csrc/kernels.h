@@ -264,6 +264,7 @@ hipError_t launch_skinny(SkinnyGemm a, int epi, bool f16, hipStream_t s);
 constexpr int FEW_CTL_TILE = 0;                                   // + tile of a projection whose k range is cut
 constexpr int FEW_CTL_ATTN = FEW_CTL_TILE + SK_MAX_TILES_CUT;     // + attention tile * Hkv + kv head
 constexpr int FEW_MAX_TILES_KV = 4096;                            // attention tiles * kv heads
+constexpr int FEW_RECORDS = 256;                                  // partial results of the attention's pieces
 constexpr int FEW_CTL_INTS = FEW_CTL_ATTN + FEW_MAX_TILES_KV;
 
 // ---- generation steps: one new token per trace (decode_bf16.hip) ----
@@ -292,16 +293,15 @@ struct FewAttn {
     const FewTile *tiles;             // [n_tiles]; null: one suffix token per trace, tile = trace
     int32_t *arrived;                 // n_tiles * Hkv arrival counters, zero before and after
     void *out;                        // [T, Hq * 128] in fragment order, format out_fmt (1 bf16, 3 half)
-    float *part_o, *part_ml;          // few_attn_records of [rows, 128] and [rows, 2] fp32, rows = few_attn_rows
+    float *part_o, *part_ml;          // FEW_RECORDS of [rows, 128] and [rows, 2] fp32, rows = few_attn_rows
     int32_t B, T, Hq, Hkv, G, max_blocks, n_blocks, max_L, out_fmt, n_tiles;
     int32_t pieces, wave_pages, fold, inv_G;     // set by the launcher
     float scale_log2;                 // log2(e) / sqrt(head_dim)
 };
-// Tiles of a batch (host copies; one: one suffix token per trace), rows of a tile, records for n_tiles tiles whatever the
-// context lengths.
+// Tiles of a batch (host copies; one: one suffix token per trace), rows of a tile.
 int64_t few_attn_tiles(const int32_t *h_cu, int B, const int32_t *h_group_start, int n_units, int G, bool one);
 int few_attn_rows(bool one);
-int64_t few_attn_records(int64_t n_tiles, int Hkv, bool one);
+void few_attn_pieces(FewAttn &a, bool one);      // from n_tiles, Hkv and max_L: pieces, wave_pages, fold
 hipError_t launch_few_attn(FewAttn a, hipStream_t s);
 
 // ---- cascade (cascade.hip) ----

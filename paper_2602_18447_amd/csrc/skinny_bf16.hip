@@ -427,7 +427,7 @@ __global__ __launch_bounds__(64 * NW, 2) void skinny_kernel(SkinnyGemm a) {
 //  - Wide outputs (gate/up).  One row block: one tile per workgroup, the weights' stream decides (55 MB: 11.7 us).  More
 //    rows: the activations, which every workgroup re-reads from the L2, would cost as much as the weights, so a workgroup
 //    takes as many tiles as leave about one workgroup per CU (1120 tiles: 5; 32 rows 16.2 -> 12.9 us, 96 rows 25 -> 18.5 us).
-//  - Narrow outputs over a k range of fewer than 64 k-tiles: one tile, never cut (a hand-over between slices - store,
+//  - Narrow outputs over a k range of fewer than 128 k-tiles: one tile, never cut (a hand-over between slices - store,
 //    counter and load at the memory side - is about 3 us); several row blocks are halved over two workgroups, which share
 //    the weights through their L2 (96 rows x 2048 columns x 1536: 9.0 -> 6.5 us).  From 256 tiles on two tiles.
 //  - Narrow outputs over long k ranges (down): cut so that about one workgroup per CU (about two where there are enough

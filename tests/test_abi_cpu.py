@@ -63,6 +63,20 @@ def test_workspace_size_is_monotone_and_aligned():
     cb.confspec_destroy(ctx)
 
 
+@pytest.mark.parametrize("shape, B, S, L", [("large", 110, 1, 2048), ("large", 64, 2, 1000), ("large", 96, 1, 2048), ("small", 1, 128, 16384)])
+def test_few_row_passes_fit_the_static_scratch_as_other_passes_do(shape, B, S, L):
+    """What only a pass over at most 128 tokens uses lies over what only the others use, so it does not push a batch beyond
+    the library's scratch array (64 MiB) that the others' slices leave inside."""
+    dims = dict(small=dict(n_layers=28, d_model=1536, n_q_heads=12, n_kv_heads=2, d_ffn=8960),
+                large=dict(n_layers=64, d_model=5120, n_q_heads=40, n_kv_heads=8, d_ffn=27648))[shape]
+    ctx = cb.confspec_create(_cfg(vocab=151936, **dims))
+    cu, lens = np.arange(B + 1, dtype=np.int32) * S, np.full(B, L, dtype=np.int32)
+    as_ptr = lambda a: a.ctypes.data_as(C.POINTER(C.c_int32))
+    batch = cb.Batch(B, B * S, 0x1000, 0x1000, 0x1000, as_ptr(cu), as_ptr(lens))     # (only the host arrays are read)
+    assert cb.confspec_static_scratch_need(ctx, batch) <= cb.STATIC_SCRATCH_BYTES
+    cb.confspec_destroy(ctx)
+
+
 def _no_gpu_here():
     """The calls below hand made-up addresses to the library and rely on validation stopping them before any launch;
     a mistake in such a test must never reach a real GPU, so they only run where there is none."""
