@@ -407,10 +407,10 @@ def _optional_legs(args, st, dev):
                     launch="eager", algorithmic_bytes_per_step=wbytes + kvbytes,
                     achieved_TBps=round((wbytes + kvbytes) / (dt / nst) / 1e12, 3),
                     # the step's own kernels (one token per trace, B <= 32, d_model <= 1536): per layer QKV + rotation + cache write,
-                    # attention, output projection, gate/up + SwiGLU, down projection; around them position / rotary
-                    # tables, embedding, counters, first RMSNorm, final RMSNorm, head with running arg max /
-                    # log-sum-exp, its last reduction
-                    kernel_launches_per_step=(5 * m.n_layers + 8 if wl.B <= 32 and m.d_model <= 1536 and
+                    # attention, output projection, gate/up + SwiGLU, down projection; in front the token maps with rotary
+                    # table, embedding and first norm, behind them the final RMSNorm, the head with running arg max /
+                    # log-sum-exp and its last reduction
+                    kernel_launches_per_step=(5 * m.n_layers + 4 if wl.B <= 32 and m.d_model <= 1536 and
                                               m.n_q_heads * m.head_dim <= 1536 and "decode_kernels=0" not in args.tune
                                               else None))
         # the same step without the host's launch work: one step (fixed context lengths) captured into a HIP graph and
