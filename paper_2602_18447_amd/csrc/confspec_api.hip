@@ -121,14 +121,10 @@ bool skinny_shape_ok(const confspec_model_cfg &c, int64_t T) {
 }
 // One new token in every trace (a generation step), as far as its attention is concerned.
 bool one_token_shape(const confspec_model_cfg &c, int64_t T, int64_t B) { return T == B && c.n_q_heads / c.n_kv_heads <= 16; }
-// Partial planes of a few-row pass's four projections (the largest one).
+// Partial planes of a few-row pass's residual projections (the larger one; the others' k ranges are never cut).
 size_t skinny_pass_plane_bytes(const confspec_model_cfg &c, int T) {
-    const int qw = c.n_q_heads * c.head_dim, kw = c.n_kv_heads * c.head_dim;
-    size_t m = cs::skinny_plane_bytes(T, c.d_model, (qw + 2 * kw) / 16);
-    m = std::max(m, cs::skinny_plane_bytes(T, qw, c.d_model / 16));
-    m = std::max(m, cs::skinny_plane_bytes(T, c.d_model, c.d_ffn / 8));
-    m = std::max(m, cs::skinny_plane_bytes(T, c.d_ffn, c.d_model / 16));
-    return m;
+    return std::max(cs::skinny_plane_bytes(cs::SK_EPI_RESID, T, c.n_q_heads * c.head_dim, c.d_model / 16),
+                    cs::skinny_plane_bytes(cs::SK_EPI_RESID, T, c.d_ffn, c.d_model / 16));
 }
 // Tiles of a few-row pass's attention at most, whatever the lengths of its traces.
 int64_t few_tiles_bound(const confspec_model_cfg &c, int64_t T, int64_t B) {

@@ -248,18 +248,18 @@ int main() {
         check_plan(t, b, h[0], h[1], 1, what);
         if (iter % 200 == 0) check_library(draft, b, what);
     }
-    // tiling of the few-row projections: the rows covered, tiles that divide the columns, every k-tile in exactly one
-    // slice, no more cut tiles than there are arrival counters, planes sized for the slices and growing with the rows
-    for (int iter = 0; iter < 20000; ++iter) {
-        int K = 64 * (1 + (int)(rng() % 600)), n_ct = 1 + (int)(rng() % 12000), M = 1 + (int)(rng() % 128);
-        if (iter < 8) {
+    // tiling of the few-row projections: a kernel for it, the rows covered, tiles that divide the columns, every k-tile in
+    // exactly one slice, no more cut tiles than there are arrival counters, planes sized for the slices and growing with the rows
+    for (int iter = 0; iter < 60000; ++iter) {
+        int epi = iter % 3, K = 64 * (1 + (int)(rng() % 600)), n_ct = 1 + (int)(rng() % (iter % 2 ? 12000 : 300)), M = 1 + (int)(rng() % 128);
+        if (iter < 24) {
             const int shapes[8][2] = {{1536, 128}, {1536, 96}, {1536, 1120}, {8960, 96}, {5120, 448}, {5120, 320}, {5120, 3456}, {27648, 320}};
-            K = shapes[iter][0]; n_ct = shapes[iter][1];
+            K = shapes[iter / 3][0]; n_ct = shapes[iter / 3][1];
         }
-        const cs::SkinnyPlan p = cs::skinny_plan(M, K, n_ct);
+        const cs::SkinnyPlan p = cs::skinny_plan(epi, M, K, n_ct);
         const int nk = K / 64;
-        bool ok = p.mb >= 1 && p.ms >= 1 && p.mb * p.ms * 16 >= M && (p.ms - 1) * p.mb * 16 < M && p.ct >= 1 && n_ct % p.ct == 0 && p.S >= 1 &&
-                  p.S <= nk && (p.S == 1 || n_ct / p.ct * p.ms <= 256);
+        bool ok = cs::skinny_has_kernel(epi, p) && p.mb >= 1 && p.ms >= 1 && p.mb * p.ms * 16 >= M && (p.ms - 1) * p.mb * 16 < M && p.ct >= 1 &&
+                  n_ct % p.ct == 0 && p.S >= 1 && p.S <= nk && (p.S == 1 || (epi == cs::SK_EPI_RESID && n_ct / p.ct * p.ms <= 256));
         int covered = 0;
         for (int sl = 0; ok && sl < p.S; ++sl) {
             int k0 = (int)((long)sl * nk / p.S), k1 = (int)((long)(sl + 1) * nk / p.S);
@@ -267,9 +267,10 @@ int main() {
             covered = k1;
         }
         ok = ok && covered == nk;
-        size_t pb = cs::skinny_plane_bytes(M, K, n_ct);
-        ok = ok && pb >= (p.S > 1 ? (size_t)p.S * 16 * p.mb * p.ms * n_ct * 16 * 4 : 0) && pb <= cs::skinny_plane_bytes(128, K, n_ct);
-        if (!ok) { printf("skinny_plan(M=%d, K=%d, n_ct=%d) -> mb=%d ms=%d ct=%d S=%d planes=%zu\n", M, K, n_ct, p.mb, p.ms, p.ct, p.S, pb); ++g_fail; }
+        size_t pb = cs::skinny_plane_bytes(epi, M, K, n_ct);
+        ok = ok && pb >= (p.S > 1 ? (size_t)p.S * 16 * p.mb * p.ms * n_ct * 16 * 4 : 0) && pb <= cs::skinny_plane_bytes(epi, 128, K, n_ct);
+        if (!ok && ++g_fail <= 20)
+            printf("skinny_plan(epi=%d, M=%d, K=%d, n_ct=%d) -> mb=%d ms=%d ct=%d S=%d planes=%zu\n", epi, M, K, n_ct, p.mb, p.ms, p.ct, p.S, pb);
     }
     // pieces of the few-row attention: the whole context covered, and a partial result for every workgroup of a tile that
     // has several pieces

@@ -257,8 +257,9 @@ struct SkinnyGemm {
     void *k_pages, *v_pages;
 };
 struct SkinnyPlan { int mb, ms, ct, S; };
-SkinnyPlan skinny_plan(int M, int K, int n_ct);
-size_t skinny_plane_bytes(int M, int K, int n_ct);      // for up to M rows; 0 when no k range is cut
+SkinnyPlan skinny_plan(int epi, int M, int K, int n_ct);
+bool skinny_has_kernel(int epi, const SkinnyPlan &p);
+size_t skinny_plane_bytes(int epi, int M, int K, int n_ct);      // for up to M rows; 0 when no k range is cut
 hipError_t launch_skinny(SkinnyGemm a, int epi, bool f16, hipStream_t s);
 // control block (int32) of a pass over few rows: the arrival counters
 constexpr int FEW_CTL_TILE = 0;                                   // + tile of a projection whose k range is cut

@@ -433,36 +433,45 @@ __global__ __launch_bounds__(64 * NW, 2) void skinny_kernel(SkinnyGemm a) {
 //  - Narrow outputs over long k ranges (down): cut so that about one workgroup per CU (about two where there are enough
 //    tiles) shares the work; more rows take more tiles per workgroup, again for the activations (8960 x 1536: 9.9 us for one
 //    row, 11.5 for 32, 16.3 for 96).
-SkinnyPlan skinny_plan(int M, int K, int n_ct) {
+//  - A width made for the other kind of projection (a wide model's QKV or residual projection of 1024 tiles and more, a small
+//    model's gate/up): one tile, never cut.  Rotating projections over 128 k-tiles and more: never cut either, one tile, two
+//    from 128 tiles on.
+SkinnyPlan skinny_plan(int epi, int M, int K, int n_ct) {
     SkinnyPlan p;
     const int b = (M + 15) / 16, nk = K / 64;
-    p.ms = 1;
+    p.ct = 1;
     p.S = 1;
-    if (n_ct >= 1024) {
+    p.ms = b > 4 ? 2 : 1;
+    if ((epi == SK_EPI_SWIGLU) != (n_ct >= 1024)) {
+    } else if (epi == SK_EPI_SWIGLU) {
         p.ct = b == 1 ? 1 : n_ct % 5 == 0 && n_ct / 5 <= 256 ? 5 : n_ct % 4 == 0 ? 4 : 1;
-        if (b > (p.ct == 5 ? 6 : 4)) p.ms = 2;
-        p.mb = (b + p.ms - 1) / p.ms;
-        if (p.mb == 5) p.mb = 6;
-        return p;
-    }
-    if (nk < 128) {
+        if (p.ct == 5) p.ms = b > 6 ? 2 : 1;
+    } else if (nk < 128) {
         p.ct = n_ct >= 256 && n_ct % 2 == 0 ? 2 : 1;
-        if (b > (p.ct == 2 ? 2 : 1)) p.ms = 2;
-        p.mb = (b + p.ms - 1) / p.ms;
-        return p;
+        p.ms = b > (p.ct == 2 ? 2 : 1) ? 2 : 1;
+    } else if (n_ct >= 128 || epi == SK_EPI_ROPE) {
+        p.ct = n_ct >= 128 && n_ct % 2 == 0 ? 2 : 1;
+    } else {
+        p.ct = b == 1 ? 1 : b <= 4 ? (n_ct % 3 == 0 ? 3 : 1) : n_ct % 4 == 0 ? 4 : 1;
     }
-    if (b > 4) p.ms = 2;
     p.mb = (b + p.ms - 1) / p.ms;
-    if (n_ct >= 128) p.ct = n_ct % 2 == 0 ? 2 : 1;
-    else p.ct = b == 1 ? 1 : b <= 4 ? (n_ct % 3 == 0 ? 3 : 1) : n_ct % 4 == 0 ? 4 : 1;
+    if (p.mb == 5) p.mb = 6;
     const int wgs = n_ct / p.ct * p.ms;
-    if (wgs <= SK_MAX_TILES_CUT) p.S = std::max(1, std::min((wgs >= 128 ? 480 : b == 1 ? 208 : 256) / wgs, nk / 8));
+    if (epi == SK_EPI_RESID && n_ct < 1024 && nk >= 128 && wgs <= SK_MAX_TILES_CUT)
+        p.S = std::max(1, std::min((wgs >= 128 ? 480 : b == 1 ? 208 : 256) / wgs, nk / 8));
     return p;
 }
-size_t skinny_plane_bytes(int M, int K, int n_ct) {      // the largest over all row counts up to M
+// Tilings there are kernels for (what skinny_plan may return).
+constexpr bool has_kernel(int epi, int mb, int ct) {
+    if (mb == 6) return epi == SK_EPI_SWIGLU && ct == 5;
+    if (mb < 1 || mb > 4) return false;
+    return epi == SK_EPI_SWIGLU ? ct == 1 || ct == 4 || ct == 5 : epi == SK_EPI_RESID ? ct >= 1 && ct <= 4 : ct == 1 || ct == 2;
+}
+bool skinny_has_kernel(int epi, const SkinnyPlan &p) { return has_kernel(epi, p.mb, p.ct); }
+size_t skinny_plane_bytes(int epi, int M, int K, int n_ct) {      // the largest over all row counts up to M
     size_t best = 0;
     for (int b = 1; b <= (M + 15) / 16; ++b) {
-        const SkinnyPlan p = skinny_plan(16 * b, K, n_ct);
+        const SkinnyPlan p = skinny_plan(epi, 16 * b, K, n_ct);
         if (p.S > 1) best = std::max(best, (size_t)p.S * 16 * p.mb * p.ms * 16 * n_ct * 4);
     }
     return best;
@@ -480,24 +489,30 @@ static hipError_t launch_one(const SkinnyGemm &a, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int EPI, bool F16, int MB, int CT>
+static hipError_t launch_ct(const SkinnyGemm &a, hipStream_t s) {
+    constexpr int D2 = MB < 4 ? 2 : 1;                   // (two groups of more activations than this do not fit the registers)
+    if constexpr (!has_kernel(EPI, MB, CT)) {
+        return hipErrorInvalidValue;
+    } else if constexpr (CT >= 3) {
+        return launch_one<EPI, F16, MB, CT, 8, 1, 1>(a, s);
+    } else if constexpr (CT == 2) {
+        return launch_one<EPI, F16, MB, CT, 8, D2>(a, s);
+    } else {
+        if (a.K <= 64 * 24) return launch_one<EPI, F16, MB, 1, 8, 3, 1>(a, s);       // a wavefront's whole share of the k range at once
+        if constexpr (EPI == SK_EPI_RESID && MB < 3)
+            if (a.S > 1) return launch_one<EPI, F16, MB, 1, 8, 3>(a, s);
+        return launch_one<EPI, F16, MB, 1, 8, D2>(a, s);
+    }
+}
 template <int EPI, bool F16, int MB>
 static hipError_t launch_mb(const SkinnyGemm &a, const SkinnyPlan &p, hipStream_t s) {
-    const bool one_group = a.K <= 64 * 24;               // a wavefront's whole share of the k range at once
-    constexpr int D2 = MB < 4 ? 2 : 1;                   // (two groups of more activations than this do not fit the registers)
-    if constexpr (EPI == SK_EPI_SWIGLU) {
-        if (p.ct == 5) return launch_one<EPI, F16, MB, 5, 8, 1, 1>(a, s);
-        if constexpr (MB <= 4) {
-            if (p.ct == 4) return launch_one<EPI, F16, MB, 4, 8, 1, 1>(a, s);
-            return one_group ? launch_one<EPI, F16, MB, 1, 8, 3, 1>(a, s) : launch_one<EPI, F16, MB, 1, 8, D2>(a, s);
-        }
-    } else if constexpr (MB <= 4) {
-        if (p.ct == 1 && one_group) return launch_one<EPI, F16, MB, 1, 8, 3, 1>(a, s);
-        if (p.ct == 1) return a.S > 1 && MB < 3 ? launch_one<EPI, F16, MB, 1, 8, MB < 3 ? 3 : D2>(a, s) : launch_one<EPI, F16, MB, 1, 8, D2>(a, s);
-        if (p.ct == 2) return launch_one<EPI, F16, MB, 2, 8, D2>(a, s);
-        if constexpr (EPI == SK_EPI_RESID) {
-            if (p.ct == 3) return launch_one<EPI, F16, MB, 3, 8, 1, 1>(a, s);
-            if (p.ct == 4) return launch_one<EPI, F16, MB, 4, 8, 1, 1>(a, s);
-        }
+    switch (p.ct) {
+        case 1: return launch_ct<EPI, F16, MB, 1>(a, s);
+        case 2: return launch_ct<EPI, F16, MB, 2>(a, s);
+        case 3: return launch_ct<EPI, F16, MB, 3>(a, s);
+        case 4: return launch_ct<EPI, F16, MB, 4>(a, s);
+        case 5: return launch_ct<EPI, F16, MB, 5>(a, s);
     }
     return hipErrorInvalidValue;
 }
@@ -515,18 +530,8 @@ static hipError_t launch_epi(const SkinnyGemm &a, const SkinnyPlan &p, hipStream
 
 hipError_t launch_skinny(SkinnyGemm a, int epi, bool f16, hipStream_t s) {
     if (a.M < 1 || a.M > SK_MAX_ROWS || a.K % 64 != 0 || a.K < 64 || a.n_ct < 1 || !a.X || !a.W) return hipErrorInvalidValue;
-    SkinnyPlan p = skinny_plan(a.M, a.K, a.n_ct);
-    if (epi != SK_EPI_RESID && p.S > 1) p.S = 1;
-    if ((epi == SK_EPI_SWIGLU) != (a.n_ct >= 1024)) {
-        // a tiling made for the other kind of projection (a wide model's residual or QKV projection, a small model's gate/up)
-        const int b = (a.M + 15) / 16;
-        p.ct = 1;
-        p.S = 1;
-        p.ms = b > 4 ? 2 : 1;
-        p.mb = (b + p.ms - 1) / p.ms;
-    }
-    if (p.S > 1 && (!a.planes || !a.tile_cnt || a.n_ct / p.ct * p.ms > SK_MAX_TILES_CUT)) return hipErrorInvalidValue;
-    if ((p.ms - 1) * 16 * p.mb >= a.M) p.ms = 1;        // (never a workgroup without rows)
+    const SkinnyPlan p = skinny_plan(epi, a.M, a.K, a.n_ct);
+    if (p.S > 1 && (!a.planes || !a.tile_cnt)) return hipErrorInvalidValue;
     if ((epi != SK_EPI_RESID || a.xg_out) && (!a.ssq_in || a.ssq_n < 1)) return hipErrorInvalidValue;
     a.S = p.S;
     a.ms = p.ms;

@@ -54,3 +54,13 @@ def test_few_rows_write_back_and_repeat(suffix):
                         batch.suffix_ids.cpu().numpy(), batch.h_cu_suffix, batch.h_prefix_lens, n_app)
     _check_appended(wl, batch, kv, before, n_app, ora, wl.name)
     ver.close()
+
+
+@pytest.mark.parametrize("suffix", [(20,), (40, 9), (64, 1), (128,)], ids=lambda s: f"T{sum(s)}")
+def test_few_rows_of_a_wide_model_with_few_heads(suffix):
+    """A QKV projection of fewer than 128 column tiles over 128 k-tiles (d_model 8192, 12 heads)."""
+    print(f"few rows, wide model with few heads: suffixes {suffix}", flush=True)
+    wl = W.tiny_workload("few_rows_narrow_qkv", 9350 + sum(suffix), dtype="bf16", n_layers=2, d_model=8192, n_q_heads=10, n_kv_heads=1,
+                         head_dim=128, d_ffn=192, vocab=512, block_size=16, prefix_lens=[50] * len(suffix), suffix_lens=suffix,
+                         taus=(0.5, 0.6, 0.9))
+    G.parity_case(wl)
