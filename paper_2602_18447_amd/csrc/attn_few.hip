@@ -502,9 +502,9 @@ void few_attn_pieces(FewAttn &a, bool one) {
 
 hipError_t launch_few_attn(FewAttn a, hipStream_t s) {
     const bool one = a.tiles == nullptr, two = a.q_lo != nullptr;
-    if (a.n_tiles < 1 || a.B < 1 || a.G < 1 || a.G > 64 || a.Hkv < 1 || (int64_t)a.n_tiles * a.Hkv > FEW_MAX_TILES_KV || a.T > SK_MAX_ROWS ||
-        (one && (a.G > few_attn_rows(true) || a.B != a.n_tiles)) || (!one && two && (!a.ksuf_lo || !a.vsuf_lo)))
+    if (a.B < 1 || !few_attn_takes(a.n_tiles, a.Hkv, a.G, a.T, one) || (one && a.B != a.n_tiles) || (!one && two && (!a.ksuf_lo || !a.vsuf_lo)))
         return hipErrorInvalidValue;
+    static_assert(SK_MAX_ROWS * FEW_MAX_G * FEW_MAX_G < 1 << 20, "r / G from a product");
     a.inv_G = (1 << 20) / a.G + 1;                       // r / G for r < 128 G: r G < 2^20
     few_attn_pieces(a, one);
     const int items = a.pieces * a.Hkv * a.n_tiles, grid = one ? items : (items + 7) / 8 * 8;

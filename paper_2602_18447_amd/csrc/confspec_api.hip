@@ -115,12 +115,14 @@ struct WsLayout {
     int n_slices;
 };
 
-// A pass over few rows, as far as the model and the batch shape decide it: its projections are those of skinny_bf16.hip.
+// A pass over few rows, as far as the model and the batch shape decide it: its projections are those of skinny_bf16.hip,
+// its attention that of attn_few.hip.
 bool skinny_shape_ok(const confspec_model_cfg &c, int64_t T) {
-    return c.dtype == CONFSPEC_DTYPE_BF16 && T >= 1 && T <= cs::SK_MAX_ROWS && c.n_layers > 0 && c.head_dim == 128;
+    return c.dtype == CONFSPEC_DTYPE_BF16 && T >= 1 && T <= cs::SK_MAX_ROWS && c.n_layers > 0 && c.head_dim == 128 &&
+           c.n_q_heads / c.n_kv_heads <= cs::FEW_MAX_G;
 }
 // One new token in every trace (a generation step), as far as its attention is concerned.
-bool one_token_shape(const confspec_model_cfg &c, int64_t T, int64_t B) { return T == B && c.n_q_heads / c.n_kv_heads <= 16; }
+bool one_token_shape(const confspec_model_cfg &c, int64_t T, int64_t B) { return T == B && c.n_q_heads / c.n_kv_heads <= cs::FEW_MAX_G_ONE; }
 // Partial planes of a few-row pass's residual projections (the larger one; the others' k ranges are never cut).
 size_t skinny_pass_plane_bytes(const confspec_model_cfg &c, int T) {
     return std::max(cs::skinny_plane_bytes(cs::SK_EPI_RESID, T, c.n_q_heads * c.head_dim, c.d_model / 16),
@@ -721,10 +723,11 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
     for (int l = 0; l < c.n_layers && skinny; ++l) skinny = rope_fused_in(l) && format_of(l) != 2;
     skinny = skinny && skinny_pass_plane_bytes(c, T) <= L.sk_planes_bytes;
     const int G = c.n_q_heads / c.n_kv_heads;
-    const bool one = skinny && one_token_shape(c, T, B) && !ex.dev_group_start;
-    const bool use_dec = one && set.decode_kernels && (set.decode_kernels == 2 || (d <= 64 * cs::DEC_MAX_KT && qw <= 64 * cs::DEC_MAX_KT));
+    bool one = skinny && one_token_shape(c, T, B) && !ex.dev_group_start;
     const int64_t few_tiles = skinny ? cs::few_attn_tiles(batch->h_cu_suffix, B, ex.h_group_start, ex.n_groups, G, one) : 0;
-    skinny = skinny && few_tiles * c.n_kv_heads <= cs::FEW_MAX_TILES_KV;
+    skinny = skinny && cs::few_attn_takes(few_tiles, c.n_kv_heads, G, T, one);
+    one = one && skinny;
+    const bool use_dec = one && set.decode_kernels && (set.decode_kernels == 2 || (d <= 64 * cs::DEC_MAX_KT && qw <= 64 * cs::DEC_MAX_KT));
     cs::AttnPlanCounts pc = {}, pc_last = {};
     Groups gr;
     gr.dev = ex.dev_group_start; gr.host = ex.h_group_start; gr.n = ex.n_groups;

@@ -265,6 +265,8 @@ hipError_t launch_skinny(SkinnyGemm a, int epi, bool f16, hipStream_t s);
 constexpr int FEW_CTL_TILE = 0;                                   // + tile of a projection whose k range is cut
 constexpr int FEW_CTL_ATTN = FEW_CTL_TILE + SK_MAX_TILES_CUT;     // + attention tile * Hkv + kv head
 constexpr int FEW_MAX_TILES_KV = 4096;                            // attention tiles * kv heads
+constexpr int FEW_MAX_G = 64;                                     // q heads per kv head of the few-row attention
+constexpr int FEW_MAX_G_ONE = 16;                                 // ... of its form for one token per trace
 constexpr int FEW_RECORDS = 256;                                  // partial results of the attention's pieces
 constexpr int FEW_CTL_INTS = FEW_CTL_ATTN + FEW_MAX_TILES_KV;
 
@@ -299,6 +301,10 @@ struct FewAttn {
     int32_t pieces, wave_pages, fold, inv_G;     // set by the launcher
     float scale_log2;                 // log2(e) / sqrt(head_dim)
 };
+// What launch_few_attn takes: query heads per kv head and attention tiles (one: one suffix token per trace).
+inline bool few_attn_takes(int64_t n_tiles, int Hkv, int G, int T, bool one) {
+    return n_tiles >= 1 && Hkv >= 1 && n_tiles * Hkv <= FEW_MAX_TILES_KV && G >= 1 && G <= (one ? FEW_MAX_G_ONE : FEW_MAX_G) && T <= SK_MAX_ROWS;
+}
 // Tiles of a batch (host copies; one: one suffix token per trace), rows of a tile.
 int64_t few_attn_tiles(const int32_t *h_cu, int B, const int32_t *h_group_start, int n_units, int G, bool one);
 int few_attn_rows(bool one);

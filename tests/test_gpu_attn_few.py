@@ -45,3 +45,13 @@ def test_few_row_attention_on_shared_contexts(heads):
                verdict=outs[2].cpu().numpy(), accept=outs[3].cpu().numpy(), taus=taus, vids=vids)
     G.compare(wl, gpu, G.run_oracle(wl, weights, batch, kv, taus, vids), wl.name)
     ver.close()
+
+
+@pytest.mark.parametrize("hq,suffix", [(64, (3, 20)), (65, (3, 20)), (96, (1, 1, 1)), (96, (33,)), (128, (1, 127))], ids=str)
+def test_many_q_heads_per_kv_head(hq, suffix):
+    """Around and above the q heads per kv head that the few-row attention takes (64): above, the general kernels."""
+    print(f"{hq} q heads on one kv head, suffixes {suffix}", flush=True)
+    wl = W.tiny_workload("attn_few_heads", 9700 + hq + sum(suffix), dtype="bf16", n_layers=3, d_model=512, n_q_heads=hq, n_kv_heads=1,
+                         head_dim=128, d_ffn=768, vocab=512, block_size=16, prefix_lens=[70 + 300 * i for i in range(len(suffix))],
+                         suffix_lens=suffix, taus=(0.5, 0.55, 0.6, 0.9))
+    G.parity_case(wl)
