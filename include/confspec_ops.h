@@ -134,14 +134,16 @@ int confspec_phase_times(confspec_ctx *ctx, float *h_ms /* [CONFSPEC_N_PHASES] *
  *       projection's weights once, front to back, so that they sit in the last-level cache when the down projection's
  *       strided tile loads ask for them (given where the down projection runs one workgroup per tile; results are
  *       bit-identical with 0).
- *   "decode_kernels" (default 1): a bf16 pass with one new token in every trace (a generation step, Algorithm 1's generate
- *       calls) can run its attention on a kernel with one query row per head, and with at most 32 traces the full-vocabulary
- *       head on one that never stores the logits, when every layer's operands are single 16-bit values and the scratch
- *       holds the partial results.  1: it does when d_model and the q width are at most 1536 (where those kernels are the
- *       faster ones), 2: whenever the shapes allow, 0: never.  (The projections of a pass of at most 128 suffix tokens have
- *       kernels of their own whatever this setting, unless a GEMM launch shape below is forced.)
+ *   "decode_kernels" (default 1): a bf16 pass of at most 128 suffix tokens can run on kernels of its own, when every
+ *       layer's operands are single 16-bit values and no GEMM launch shape below is forced.  0: never, it runs on the
+ *       general kernels.  1 and 2: it does; with one new token in every trace (a generation step, Algorithm 1's generate
+ *       calls) its attention then has one query row per head, and q and the probabilities two bf16 terms in every layer
+ *       where d_model and the q width are at most 1536 (1) or whatever the width (2); at those two, with at most 32 traces
+ *       and d_model at most 1536, the full-vocabulary head never stores the logits.
  *   "prune_last_layer" (default 1): in the last layer, attention rows, output projection and MLP are computed for the
- *       last position of each trace only (the only rows the verdict head reads; 0 computes every row).
+ *       last position of each trace only (the only rows the verdict head reads; 0 computes every row).  Passes on the
+ *       kernels for at most 128 suffix tokens compute every row whatever this setting, and the "attn_*" launch shapes do
+ *       not apply to them.
  *   Launch shapes, for measurements: "gemm_tile" (0 heuristic; 1 = 128x128, 4 = 256x256, 7 = 192x96 workgroup tiles; a
  *       shape that does not divide N falls back to 128x128), "gemm_group_m" (0 heuristic, else tile rows per band of
  *       the GEMM's tile order), "gemm_splitk" (0 heuristic, 1..64 = split-K factor of every bf16 GEMM that is given

@@ -42,11 +42,11 @@ struct Settings {
     int fuse_rope = 1;
     // The gate/up projection warms the last-level cache with the down projection's weights.
     int prefetch_down = 1;
-    // A bf16 pass with one new token per trace and at most 32 traces (a generation step) can run on the kernels shaped
-    // for it (decode_bf16.hip).  1: it does when d_model and the q width fit one k slice of those kernels (1536), where
-    // they win (28 layers x 1536: 1.99 against 2.68 ms per step); wider models stay on the verification pass's kernels,
-    // which stream their long k ranges better (64 layers x 5120: 18.7 against 21.6 ms).  2: whenever the shapes allow.
-    // 0: never.
+    // bf16 passes of at most 128 suffix tokens have kernels of their own (skinny_bf16.hip, attn_few.hip).  0: never, such a
+    // pass runs on the general kernels like any other.  1: with one new token per trace (a generation step) the attention
+    // carries two terms of q and the probabilities in every layer, and the full-vocabulary head is the one of
+    // decode_bf16.hip, when d_model and the q width are at most 1536: there the matrix work is free and the head's rows fit
+    // that kernel; wider models carry two terms in the attn_precise_layers only.  2: whatever the width.
     int decode_kernels = 1;
     cs::GemmTune gemm;
     cs::AttnTune attn;
@@ -717,9 +717,9 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         return 2;
     };
     // A pass over few rows takes the projections shaped for it (skinny_bf16.hip) when every layer's operands are single
-    // 16-bit values and no launch shape of the general ones is forced; with one new token per trace (a generation step)
-    // also an attention shaped for that, where it is the faster one and the scratch holds its partial results.
-    bool skinny = skinny_shape_ok(c, T) && set.gemm.tile == 0 && set.gemm.splitk == 0;
+    // 16-bit values, decode_kernels does not say otherwise and no launch shape of the general ones is forced; with one new
+    // token per trace (a generation step) also an attention shaped for that.
+    bool skinny = set.decode_kernels != 0 && skinny_shape_ok(c, T) && set.gemm.tile == 0 && set.gemm.splitk == 0;
     for (int l = 0; l < c.n_layers && skinny; ++l) skinny = rope_fused_in(l) && format_of(l) != 2;
     skinny = skinny && skinny_pass_plane_bytes(c, T) <= L.sk_planes_bytes;
     const int G = c.n_q_heads / c.n_kv_heads;
@@ -727,7 +727,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
     const int64_t few_tiles = skinny ? cs::few_attn_tiles(batch->h_cu_suffix, B, ex.h_group_start, ex.n_groups, G, one) : 0;
     skinny = skinny && cs::few_attn_takes(few_tiles, c.n_kv_heads, G, T, one);
     one = one && skinny;
-    const bool use_dec = one && set.decode_kernels && (set.decode_kernels == 2 || (d <= 64 * cs::DEC_MAX_KT && qw <= 64 * cs::DEC_MAX_KT));
+    const bool use_dec = one && (set.decode_kernels == 2 || (d <= 64 * cs::DEC_MAX_KT && qw <= 64 * cs::DEC_MAX_KT));
     cs::AttnPlanCounts pc = {}, pc_last = {};
     Groups gr;
     gr.dev = ex.dev_group_start; gr.host = ex.h_group_start; gr.n = ex.n_groups;

@@ -63,18 +63,38 @@ def test_one_token_batches_match_oracle(case):
 
 
 def test_one_token_batch_on_a_model_with_sliced_k_ranges():
-    # d_model 2048 = 32 k-tiles: every projection's k range is cut into slices whose partial planes the last workgroup
-    # to arrive adds up; 8 q heads per kv head (the most the step's attention takes).  Models this wide take the step
-    # kernels only when asked to (setting 2).
+    # d_ffn 8192 = 128 k-tiles: the down projection's k range is cut into slices whose partial planes the last workgroup to
+    # arrive adds up, over 128 column tiles (two per workgroup); 8 q heads per kv head.  A model this wide carries two terms
+    # of q and the probabilities past the first layer only when asked to (setting 2).
     print("one-token batch, d_model 2048, 16 / 2 heads", flush=True)
-    wl = _wl("dec_wide", 7105, (0, 33, 256, 700, 90), n_layers=2, d_model=2048, n_q_heads=16, n_kv_heads=2, d_ffn=2560)
+    wl = _wl("dec_wide", 7105, (0, 33, 256, 700, 90), n_layers=2, d_model=2048, n_q_heads=16, n_kv_heads=2, d_ffn=8192)
     _, _, _, auto = _run(wl, decode_kernels=1)
     weights, batch, kv, gpu = _run(wl, decode_kernels=2)
     ora = G.run_oracle(wl, weights, batch, kv, gpu["taus"], gpu["vids"])
     G.compare(wl, gpu, ora, wl.name)
+    G.compare(wl, auto, ora, wl.name + " (default)")
     _, _, _, ref = _run(wl, decode_kernels=0)
-    assert not np.array_equal(ref["logits"], gpu["logits"])
-    assert np.array_equal(ref["logits"], auto["logits"])      # the default leaves this model on the general kernels
+    G.compare(wl, ref, ora, wl.name + " (general kernels)")
+    assert not np.array_equal(auto["logits"], gpu["logits"])
+    assert not np.array_equal(ref["logits"], auto["logits"])
+
+
+@pytest.mark.parametrize("suffix", [(1,) * 5, (20, 9)], ids=["one_token", "T29"])
+def test_setting_0_runs_a_pass_of_few_tokens_on_the_general_kernels(suffix):
+    """Only the general pass has RMSNorm kernels of its own (the projections for few rows carry the norms)."""
+    print(f"decode_kernels 0 and 1, suffixes {suffix}", flush=True)
+    wl = _wl("dec_off", 7109, tuple(40 * i + 7 for i in range(len(suffix))), suffix_lens=suffix)
+    weights, batch, kv = G.build_inputs(wl)
+    norms, logits = [], []
+    for setting in (0, 1):
+        ver = Verifier(wl.model, weights)
+        cb.confspec_tune(ver.ctx, "decode_kernels", setting)
+        cb.confspec_phase_timing(ver.ctx, True)
+        logits.append(G.run_gpu(wl, weights, batch, kv, verifier=ver)["logits"])
+        norms.append(cb.confspec_phase_times(ver.ctx)["norm"][1])
+        ver.close()
+    assert norms[0] > 0 and norms[1] == 0
+    assert not np.array_equal(*logits)
 
 
 def test_one_token_batch_is_repeatable_and_runs_on_the_static_scratch():
