@@ -778,6 +778,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         };
         HIP_TRY(mark(CONFSPEC_PHASE_QKV));
         cs::SkinnyGemm gq = proj(h, wqkv, d, (qw + 2 * kw) / 16, 0);
+        gq.x = x; gq.g_next = (const cs::bf16 *)w->attn_norm[l];
         gq.rope = cs::RopeArgs{(const float *)(ws + L.rope_cos), (const float *)(ws + L.rope_sin), ws + L.q, ws + L.ksuf, ws + L.vsuf,
                                use_dec || prec ? ws + L.q_lo : nullptr, !use_dec && prec ? ws + L.ksuf_lo : nullptr,
                                !use_dec && prec ? ws + L.vsuf_lo : nullptr, c.n_q_heads, c.n_kv_heads};
@@ -811,6 +812,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         HIP_TRY(cs::launch_skinny(go, cs::SK_EPI_RESID, f16, s));
         HIP_TRY(mark(CONFSPEC_PHASE_GATE_UP));
         cs::SkinnyGemm gg = proj(h, wgu, d, c.d_ffn / 8, 1);
+        gg.x = x; gg.g_next = (const cs::bf16 *)w->mlp_norm[l];
         gg.act = ws + L.act; gg.act_fmt = tm;
         HIP_TRY(cs::launch_skinny(gg, cs::SK_EPI_SWIGLU, f16, s));
         HIP_TRY(mark(CONFSPEC_PHASE_DOWN));

@@ -233,8 +233,9 @@ struct SkinnyGemm {
     int32_t S, ms;            // k slices, blocks of rows (set by the launcher)
     float *planes;            // skinny_plane_bytes; null when that is 0
     int32_t *tile_cnt;        // SK_MAX_TILES_CUT arrival counters (zero before and after the launch)
-    // ROPE, SWIGLU: X holds x * gain * sc; ssq_in [M, ssq_n] are partial sums of squares of the rows x of width d_norm, the
-    // result rows are scaled by 1 / sqrt(sum / d_norm + eps) / sc_in.
+    // ROPE, SWIGLU: X holds x * gain * sc; ssq_in [M, ssq_n] are partial sums of squares of the rows x of width d_norm, negative
+    // where an element of X left the format's range; the result rows are scaled by 1 / sqrt(sum / d_norm + eps) / sc_in.  Rows
+    // that X does not hold are taken from x [M, K] fp32 and the gains g_next.
     // RESID with xg_out: the same two of the rows before the update, which the new power of two is taken from.
     const float *ssq_in, *sc_in;
     int32_t ssq_n, d_norm;

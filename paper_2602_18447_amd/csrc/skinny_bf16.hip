@@ -13,9 +13,12 @@
 //  - everything the epilogue reads (residual rows, gains, rotary tables, cache rows) is requested in front of the main
 //    loop, so that it arrives under the weights;
 //  - RMSNorm costs no launch: a residual projection writes, next to the fp32 rows, the 16-bit operand
-//    x * gain * (power of two near 1 / rms of the row as it was before the update: keeps the operand near one whatever
-//    the magnitude of the residual stream) and the sum of squares of each of its 16-column tiles; the projection that
-//    consumes it scales its result rows by the exact 1 / rms over that power of two;
+//    x * gain * (power of two near 1 / rms of the row as it was before the update, whatever the level of the residual
+//    stream) and the sum of squares of each of its 16-column tiles; the projection that consumes it scales its result
+//    rows by the exact 1 / rms over that power of two.  A row that one update grows or shrinks so far that its operand
+//    leaves the format's range is told by the consumer (the producer gives the partial sum of squares of a tile with such
+//    an element a negative sign), which then multiplies once more with that row's operand taken from the fp32 row and the
+//    power of two of its own rms: elements are then at most sqrt(width) * gain, as after an RMSNorm of its own;
 //  - where one workgroup per tile would leave the chip idle (long k over few columns) the k range is cut into S slices;
 //    they leave fp32 partial products and the slice that arrives last (a counter per tile) adds them in slice order and
 //    runs the epilogue: the order is fixed, whoever performs it, so results are bit-identical from run to run.
@@ -99,6 +102,13 @@ __device__ inline unsigned pack2(float a, float b, int fmt) {   // fmt 3: IEEE h
     if (fmt == 3) return (unsigned)__half_as_ushort(to_half_sat(a)) | ((unsigned)__half_as_ushort(to_half_sat(b)) << 16);
     return (unsigned)__bfloat16_as_ushort(__float2bfloat16(a)) | ((unsigned)__bfloat16_as_ushort(__float2bfloat16(b)) << 16);
 }
+// Of an operand x * gain * f: the largest magnitude that may be stored (half: the format's; bf16: one that leaves the
+// products' sums finite), and the smallest f * rms of the row that leaves its elements' precision (half: the step of
+// 2^-24 below 2^-14, against elements near f * rms).
+__device__ constexpr float operand_max(bool f16) { return f16 ? 65504.0f : 0x1p96f; }
+__device__ constexpr float operand_min_rms(bool f16) { return f16 ? 0x1p-4f : 0x1p-64f; }
+// power of two at or below r, within what keeps products and quotients of two of them finite
+__device__ inline float pow2_of(float r) { return __uint_as_float(__float_as_uint(fminf(fmaxf(r, 0x1p-60f), 0x1p60f)) & 0x7f800000u); }
 __device__ inline unsigned pack2_lo(float a, float b, unsigned hi) {   // second bf16 terms
     return pack2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u), 1);
 }
@@ -114,16 +124,20 @@ constexpr int skinny_rb(int mb, int ct, int nw) {
 }
 
 // MB: blocks of 16 rows; CT: 16-column tiles of a workgroup; NW wavefronts; D: k-tiles of a group.  A wavefront works in
-// groups of D k-tiles: the weights of group g + 1 are on their way while group g is multiplied.
+// groups of D k-tiles: the weights of group g + 1 are on their way while group g is multiplied.  (A gate/up
+// projection of one row block and tile in one buffer: three workgroups of 48 KiB fit a CU if their registers let them; with
+// two it takes 14.7 instead of 12.4 us.)
 template <int EPI, bool F16, int MB, int CT, int NW, int D, int NBUF>
-__global__ __launch_bounds__(64 * NW, 2) void skinny_kernel(SkinnyGemm a) {
+__global__ __launch_bounds__(64 * NW, EPI == SK_EPI_SWIGLU && MB * CT == 1 && NBUF == 1 ? 6 : 2) void skinny_kernel(SkinnyGemm a) {
     constexpr int NT = 64 * NW;
     constexpr int RB = skinny_rb(MB, CT, NW);            // row blocks per pass of the reduction
     constexpr int NCH = MB / RB, NBK = RB * CT, EPB = (NBK + NW - 1) / NW;     // passes; 16 x 16 blocks of one, and per wavefront
     static_assert(MB % RB == 0, "reduction passes");
     constexpr int GB = D * CT * 2048;                    // bytes of a group's weights
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];    // [NW][n_buf groups]; then the partial products
-    __shared__ float row_f[16 * MB];
+    // RESID: power of two of the row's operand.  Others: factor of its result, negative where the operand given does not hold the
+    // row; row_sc: power of two of the operand that does.
+    __shared__ float row_f[16 * MB], row_sc[EPI == SK_EPI_RESID ? 1 : 16 * MB];
     __shared__ volatile int s_last;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -171,12 +185,17 @@ __global__ __launch_bounds__(64 * NW, 2) void skinny_kernel(SkinnyGemm a) {
     constexpr int NSQ = NP == 1 ? 20 : 6;
     const bool want_f = EPI != SK_EPI_RESID || a.xg_out != nullptr;
     float sqv[NP][NSQ], sc_prev[NP], sq_far[NP];
+    float sq_min[NP];                                                      // negative: a partial says that its operand left the range
     if (want_f) {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             const int row = r0 + min(p * (NT / 16) + (tid >> 4), M - 1);
-            sq_far[p] = 0.f;
-            for (int i = (tid & 15) + 16 * NSQ; i < a.ssq_n; i += 16) sq_far[p] += a.ssq_in[(size_t)row * a.ssq_n + i];
+            sq_far[p] = sq_min[p] = 0.f;
+            for (int i = (tid & 15) + 16 * NSQ; i < a.ssq_n; i += 16) {
+                const float v = a.ssq_in[(size_t)row * a.ssq_n + i];
+                sq_far[p] += fabsf(v);
+                sq_min[p] = fminf(sq_min[p], v);
+            }
         }
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
@@ -201,15 +220,23 @@ __global__ __launch_bounds__(64 * NW, 2) void skinny_kernel(SkinnyGemm a) {
             const int row = p * (NT / 16) + (tid >> 4);
             float sq = sq_far[p];
 #pragma unroll
-            for (int e = 0; e < NSQ; ++e) sq += (tid & 15) + 16 * e < a.ssq_n ? sqv[p][e] : 0.f;
+            for (int e = 0; e < NSQ; ++e) {
+                const float v = (tid & 15) + 16 * e < a.ssq_n ? sqv[p][e] : 0.f;
+                sq += fabsf(v);
+                sq_min[p] = fminf(sq_min[p], v);
+            }
             sq = sum16(sq);
             const float rinv = 1.0f / sqrtf(sq / (float)a.d_norm + a.eps);
             float f;
             if constexpr (EPI == SK_EPI_RESID) {
-                f = __uint_as_float(__float_as_uint(fminf(fmaxf(rinv, 0x1p-60f), 0x1p60f)) & 0x7f800000u);
+                f = pow2_of(rinv);
                 if (t == 0 && s == 0 && (tid & 15) == 0 && row < M) a.sc_out[r0 + row] = f;
             } else {
-                f = rinv / sc_prev[p];
+                const bool any_left = (__builtin_amdgcn_ballot_w64(sq_min[p] < 0.f) >> (lane & 48) & 0xffff) != 0;
+                const bool own = any_left || sc_prev[p] < operand_min_rms(F16) * rinv;
+                const float sc = own ? pow2_of(rinv) : sc_prev[p];
+                f = own ? -(rinv / sc) : rinv / sc;
+                if ((tid & 15) == 0 && row < 16 * MB) row_sc[row] = sc;
             }
             if ((tid & 15) == 0 && row < 16 * MB) row_f[row] = f;
         }
@@ -341,18 +368,21 @@ __global__ __launch_bounds__(64 * NW, 2) void skinny_kernel(SkinnyGemm a) {
                 const float f = row_f[row_l];
                 const float g[4] = {__uint_as_float(gain[j].x << 16), __uint_as_float(gain[j].x & 0xffff0000u), __uint_as_float(gain[j].y << 16),
                                     __uint_as_float(gain[j].y & 0xffff0000u)};
+                const float y4[4] = {v[0] * g[0] * f, v[1] * g[1] * f, v[2] * g[2] * f, v[3] * g[3] * f};
+                const float top = fmaxf(fmaxf(fabsf(y4[0]), fabsf(y4[1])), fmaxf(fabsf(y4[2]), fabsf(y4[3])));
+                if (__builtin_amdgcn_ballot_w64(top > operand_max(a.xg_fmt == 3)) >> fr & 0x0001000100010001ull) sq = -sq;
                 if (ok) {
-                    const uint2 y = {pack2(v[0] * g[0] * f, v[1] * g[1] * f, a.xg_fmt), pack2(v[2] * g[2] * f, v[3] * g[3] * f, a.xg_fmt)};
+                    const uint2 y = {pack2(y4[0], y4[1], a.xg_fmt), pack2(y4[2], y4[3], a.xg_fmt)};
                     *reinterpret_cast<uint2 *>(reinterpret_cast<bf16 *>(a.xg_out) + frag_index(row, col, N)) = y;
                     if (fg == 0) a.ssq_out[(size_t)row * a.n_ct + tt] = sq;
                 }
             }
         } else if constexpr (EPI == SK_EPI_SWIGLU) {
-            v *= row_f[row_l];
+            v *= fabsf(row_f[row_l]);
             const float a0 = v[0] * __builtin_amdgcn_rcpf(1.0f + __expf(-v[0])) * v[2], a1 = v[1] * __builtin_amdgcn_rcpf(1.0f + __expf(-v[1])) * v[3];
             if (ok) *reinterpret_cast<unsigned *>(reinterpret_cast<bf16 *>(a.act) + frag_index(row, tt * 8 + 2 * fg, a.n_ct * 8)) = pack2(a0, a1, a.act_fmt);
         } else {
-            v *= row_f[row_l];
+            v *= fabsf(row_f[row_l]);
             if (!ok) return;
             const RopeArgs &r = a.rope;
             const int head = tt >> 3, o = 8 * (tt & 7) + 2 * fg;
@@ -377,7 +407,50 @@ __global__ __launch_bounds__(64 * NW, 2) void skinny_kernel(SkinnyGemm a) {
     // ---- the wavefronts' products added in wavefront order, RB row blocks at a time, in the registers' own layout
     f32x4 *red = reinterpret_cast<f32x4 *>(smem);                          // [NW][NBK][64]
     f32x4 *plane = a.S > 1 ? reinterpret_cast<f32x4 *>(a.planes) + (size_t)((t * a.ms + mi) * a.S) * (MB * CT * 64) : nullptr;
-    lds_barrier();                                                         // every wavefront is done with its ring
+    lds_barrier();                                                         // every wavefront is done with its ring; row_f is complete
+    if constexpr (EPI != SK_EPI_RESID) {
+        // Rows whose operand does not hold them: the products once more, every row's operand from its fp32 values (for the
+        // other rows of the block the same operand, hence the same result).  Rare, hence cut for few registers: operands
+        // straight from memory, addresses of its own.
+        bool own = false;
+        for (int r = lane; r < 16 * MB; r += 64) own |= row_f[r] < 0.f;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(own) != 0, 0)) {  // the same for every wavefront
+            int lane_ = threadIdx.x & 63;
+            asm volatile("" : "+v"(lane_));
+            const int fr_ = lane_ & 15;
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int q = 0; q < CT; ++q) acc[i][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int ks = 0; ks < 2 * nkw; ++ks) {
+                const int k = 64 * (kt0 + wave + NW * (ks >> 1)) + 32 * (ks & 1) + 8 * (lane_ >> 4);
+                const uint4 gv = *reinterpret_cast<const uint4 *>(a.g_next + k);
+                const unsigned gw[4] = {gv.x, gv.y, gv.z, gv.w};
+                bf16x8 xf[MB];
+#pragma unroll
+                for (int i = 0; i < MB; ++i) {
+                    const float *xr = a.x + (size_t)(r0 + min(16 * i + fr_, M - 1)) * a.K + k, sc = row_sc[16 * i + fr_];
+                    const f32x4 x0 = *reinterpret_cast<const f32x4 *>(xr), x1 = *reinterpret_cast<const f32x4 *>(xr + 4);
+                    unsigned y[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float xa = e < 2 ? x0[2 * e] : x1[2 * e - 4], xb = e < 2 ? x0[2 * e + 1] : x1[2 * e - 3];
+                        y[e] = pack2(xa * __uint_as_float(gw[e] << 16) * sc, xb * __uint_as_float(gw[e] & 0xffff0000u) * sc, F16 ? 3 : 1);
+                    }
+                    xf[i] = __builtin_bit_cast(bf16x8, make_uint4(y[0], y[1], y[2], y[3]));
+                }
+#pragma unroll
+                for (int q = 0; q < CT; ++q) {
+                    int rA, rB;
+                    tile_rows<EPI>(t * CT + q, rA, rB);
+                    const bf16x8 wf = *reinterpret_cast<const bf16x8 *>(a.W + (size_t)(rA + tile_row<EPI>(fr_, rB - rA)) * a.K + k);
+#pragma unroll
+                    for (int i = 0; i < MB; ++i) acc[i][q] = mma16<F16>(wf, xf[i], acc[i][q]);
+                }
+            }
+        }
+    }
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
         if (ch > 0) lds_barrier();

@@ -1,6 +1,9 @@
 """Passes over few rows (at most 128 suffix tokens) against the oracle where the projections' tilings change: row counts
 around every 16-row block and both halvings over two workgroups, gate/up widths that take five, four and one tile per
 workgroup, k ranges that are cut into slices, models wide enough for two tiles per workgroup, write-back included."""
+import dataclasses
+
+import numpy as np
 import pytest
 import torch
 
@@ -64,3 +67,50 @@ def test_few_rows_of_a_wide_model_with_few_heads(suffix):
                          head_dim=128, d_ffn=192, vocab=512, block_size=16, prefix_lens=[50] * len(suffix), suffix_lens=suffix,
                          taus=(0.5, 0.6, 0.9))
     G.parity_case(wl)
+
+
+def _one_sublayer_changes_the_rows(kind, weights):
+    """A sublayer of the first layer, one with fp16 operands, moves the rows far from what they were before it."""
+    m = weights.cfg
+    # Where every row is c e_5 + noise, its attention output without a context is close to the value of that, v: the attention
+    # can be made to add a given amount to element 5.  That element does not reach the logits itself.
+    def attention_adds(c, amount):
+        weights.embed[:, 5] = c
+        rms = (c * c / m.d_model + 0.02 ** 2) ** 0.5
+        v = weights.wqkv[0][-m.n_kv_heads * m.head_dim:, 5].float() * (c / rms) * weights.attn_norm[0][5].float()
+        v = v.reshape(m.n_kv_heads, 1, m.head_dim).expand(-1, m.group, -1).reshape(-1)
+        weights.wo[0][5] = (amount * v / (v @ v)).to(weights.wo[0].dtype)
+
+    if kind == "attention_grows":
+        attention_adds(0.5, 8000.0)
+    elif kind == "mlp_grows":
+        weights.w_down[0][5].mul_(2.0 ** 16)             # 0.1 becomes 1e3 to 1e4
+    elif kind == "attention_shrinks":
+        # rms 4.2 -> 0.2 (an operand's rounding, 2^-12, leaves 96 * 2^-12 of element 5: half a percent of what is left)
+        attention_adds(96.0, -96.0)
+    else:                                                # from_zero_rows: padding tokens; 1 / rms is 1 / sqrt(eps)
+        weights.embed.zero_()
+        weights.wo[0].mul_(64.0)
+    weights.final_norm[5] = 0.0
+
+
+@pytest.mark.parametrize("kind", ["attention_grows", "mlp_grows", "from_zero_rows", "attention_shrinks"])
+@pytest.mark.parametrize("suffix", [(1, 1, 1), (20, 9), (60, 36), (128,)], ids=lambda s: f"T{sum(s)}")
+@pytest.mark.parametrize("d_ffn", [832, 8960], ids=["F832", "F8960"])
+def test_rows_that_one_sublayer_grows_or_shrinks(kind, suffix, d_ffn):
+    """The operand of the next projection carries a power of two of the row before the sublayer; these rows leave a half's range
+    with it.  Their logits are of any size, so each trace's differences are taken over its rms on 8 verdict tokens; the bound on
+    the real models' logits (rms 0.8 to 1.4) is that over 0.8."""
+    print(f"few rows, {kind}: suffixes {suffix}, d_ffn {d_ffn}", flush=True)
+    prefix = [0 if kind.startswith("attention") else 37 * i + 5 for i in range(len(suffix))]
+    wl = W.tiny_workload("few_rows_" + kind, 9450 + sum(suffix), dtype="bf16", n_layers=4, d_model=512, n_q_heads=4, n_kv_heads=2,
+                         head_dim=128, d_ffn=d_ffn, vocab=512, block_size=16, prefix_lens=prefix, suffix_lens=suffix, n_verdict=8)
+    if kind == "from_zero_rows":
+        wl = dataclasses.replace(wl, model=dataclasses.replace(wl.model, rms_eps=1e-12))
+    weights, batch, kv = G.build_inputs(wl)
+    _one_sublayer_changes_the_rows(kind, weights)
+    gpu = G.run_gpu(wl, weights, batch, kv)
+    ora = G.run_oracle(wl, weights, batch, kv, gpu["taus"], gpu["vids"])
+    worst = float((np.abs(gpu["logits"] - ora["logits"]) / np.sqrt((ora["logits"] ** 2).mean(axis=1, keepdims=True))).max())
+    print(f"{wl.name}: largest logit difference {worst:.4f}", flush=True)
+    assert worst <= G.TOL["bf16"]["logit"] / 0.8
