@@ -99,7 +99,7 @@ __device__ inline f32x4 combine(const float *om, const float (&s_ml)[NW][ROWS][2
 }  // namespace
 
 // RB: blocks of 16 query rows.  TERMS == 2: q and the probabilities carried as two bf16 terms, in the suffix piece also keys
-// and values.  ONE: every trace has one suffix token (tile = trace).
+// and values.  ONE: every trace has one suffix token (tile = trace); second terms of its key and value where they are given.
 // What bounds it: at few tiles the chain of round trips - tile or length, page ids, keys and values, arrival counter, the
 // other pieces - and at many the stream of keys and values, for which each wavefront has 16 KiB in flight.
 template <int RB, int TERMS, bool ONE>
@@ -355,7 +355,10 @@ __global__ __launch_bounds__(64 * NW, 2) void few_attn_kernel(FewAttn a) {
         for (int ks = 0; ks < 4; ++ks) {                                // (its key in all 16 rows of the operand)
             const bf16x8 kn = *reinterpret_cast<const bf16x8 *>(new_k + 32 * ks + 8 * fg);
             sn = mma16(kn, q_hi[0][ks], sn);
-            if constexpr (TERMS == 2) sn = mma16(kn, q_lo[0][ks], sn);
+            if constexpr (TERMS == 2) {
+                sn = mma16(kn, q_lo[0][ks], sn);
+                if (a.ksuf_lo) sn = mma16(*reinterpret_cast<const bf16x8 *>(a.ksuf_lo + (new_k - a.ksuf) + 32 * ks + 8 * fg), q_hi[0][ks], sn);
+            }
         }
         const float v = sn[0] * a.scale_log2, m_new = fmaxf(m_w[0], v);
         const float alpha = exp2_from(m_w[0], m_new), pr = __builtin_amdgcn_exp2f(v - m_new);
@@ -364,7 +367,11 @@ __global__ __launch_bounds__(64 * NW, 2) void few_attn_kernel(FewAttn a) {
 #pragma unroll
         for (int hb = 0; hb < 8; ++hb) {
             const uint2 vn = *reinterpret_cast<const uint2 *>(new_v + 16 * hb + 4 * fg);
-            const f32x4 vf = {__uint_as_float(vn.x << 16), __uint_as_float(vn.x & 0xffff0000u), __uint_as_float(vn.y << 16), __uint_as_float(vn.y & 0xffff0000u)};
+            f32x4 vf = {__uint_as_float(vn.x << 16), __uint_as_float(vn.x & 0xffff0000u), __uint_as_float(vn.y << 16), __uint_as_float(vn.y & 0xffff0000u)};
+            if (TERMS == 2 && a.vsuf_lo) {
+                const uint2 vl = *reinterpret_cast<const uint2 *>(a.vsuf_lo + (new_v - a.vsuf) + 16 * hb + 4 * fg);
+                vf += f32x4{__uint_as_float(vl.x << 16), __uint_as_float(vl.x & 0xffff0000u), __uint_as_float(vl.y << 16), __uint_as_float(vl.y & 0xffff0000u)};
+            }
             o_acc[0][hb] = o_acc[0][hb] * alpha + pr * vf;
         }
     }

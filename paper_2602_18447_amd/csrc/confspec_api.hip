@@ -740,7 +740,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
     cs::FrontArgs front = {};
     if (skinny) {
         front.ctl = ctl; front.n_ctl = cs::FEW_CTL_ATTN + (int)few_tiles * c.n_kv_heads;
-        if (!one || (!use_dec && set.attn_precise_layers > 0)) {
+        if (!one) {
             front.few_tiles = (cs::FewTile *)(ws + L.few_tiles); front.n_few_tiles = (int)few_tiles; front.few_rows = cs::few_attn_rows(false); front.G = G;
             front.group_start = ex.dev_group_start; front.n_units = ex.dev_group_start ? ex.n_groups : B;
         }
@@ -780,8 +780,8 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         cs::SkinnyGemm gq = proj(h, wqkv, d, (qw + 2 * kw) / 16, 0);
         gq.x = x; gq.g_next = (const cs::bf16 *)w->attn_norm[l];
         gq.rope = cs::RopeArgs{(const float *)(ws + L.rope_cos), (const float *)(ws + L.rope_sin), ws + L.q, ws + L.ksuf, ws + L.vsuf,
-                               use_dec || prec ? ws + L.q_lo : nullptr, !use_dec && prec ? ws + L.ksuf_lo : nullptr,
-                               !use_dec && prec ? ws + L.vsuf_lo : nullptr, c.n_q_heads, c.n_kv_heads};
+                               use_dec || prec ? ws + L.q_lo : nullptr, prec ? ws + L.ksuf_lo : nullptr,
+                               prec ? ws + L.vsuf_lo : nullptr, c.n_q_heads, c.n_kv_heads};
         if (dev_n_append) {     // (the attention that follows never reads rows at or past L_b)
             gq.kv_row = (const int32_t *)(ws + L.kv_row);
             gq.k_pages = (char *)const_cast<void *>(kv->k_pages) + layer_bytes * l;
@@ -789,9 +789,8 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         }
         HIP_TRY(cs::launch_skinny(gq, cs::SK_EPI_ROPE, f16, s));
         HIP_TRY(mark(prec && !use_dec ? CONFSPEC_PHASE_ATTN_PRECISE : CONFSPEC_PHASE_ATTN));
-        // One token per trace: two terms of q and the probabilities in every layer where decode_kernels asks for it; the
-        // first layers otherwise take the tile form, which carries those of the suffix keys and values as well.
-        const bool as_one = one && (use_dec || !prec);
+        // Two terms of q, the probabilities and the suffix keys and values in the first layers; with one token per trace those
+        // of q and the probabilities in every layer where decode_kernels asks for it.
         cs::FewAttn at = {};
         at.q = (const cs::bf16 *)(ws + L.q); at.q_lo = (const cs::bf16 *)gq.rope.q_lo;
         at.ksuf = (const cs::bf16 *)(ws + L.ksuf); at.vsuf = (const cs::bf16 *)(ws + L.vsuf);
@@ -799,7 +798,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         at.k_pages = kv->k_pages ? (const cs::bf16 *)((const char *)kv->k_pages + layer_bytes * l) : nullptr;
         at.v_pages = kv->v_pages ? (const cs::bf16 *)((const char *)kv->v_pages + layer_bytes * l) : nullptr;
         at.table = kv->block_table; at.plens = batch->prefix_lens; at.cu = batch->cu_suffix; at.tok_trace = (const int32_t *)(ws + L.tok_trace);
-        at.tiles = as_one ? nullptr : (const cs::FewTile *)(ws + L.few_tiles); at.n_tiles = (int)few_tiles; at.arrived = ctl + cs::FEW_CTL_ATTN;
+        at.tiles = one ? nullptr : (const cs::FewTile *)(ws + L.few_tiles); at.n_tiles = (int)few_tiles; at.arrived = ctl + cs::FEW_CTL_ATTN;
         at.out = ws + L.attn; at.out_fmt = tm;
         at.part_o = (float *)(ws + L.few_part_o); at.part_ml = (float *)(ws + L.few_part_ml);
         at.B = B; at.T = T; at.Hq = c.n_q_heads; at.Hkv = c.n_kv_heads; at.G = G;

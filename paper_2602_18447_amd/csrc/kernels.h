@@ -291,7 +291,7 @@ hipError_t launch_dec_head_final(const float *part, int nwg, int B, const float 
 struct FewAttn {
     const bf16 *q, *q_lo;             // [T, Hq, 128]; q_lo (may be null): second bf16 terms, then those of ksuf / vsuf too
     const bf16 *ksuf, *vsuf;          // [T, Hkv, 128]: keys / values of the suffix tokens
-    const bf16 *ksuf_lo, *vsuf_lo;    // (not read where every trace has one token)
+    const bf16 *ksuf_lo, *vsuf_lo;    // (may be null where every trace has one token: single terms)
     const bf16 *k_pages, *v_pages;    // this layer's pages [n_blocks, Hkv, 16, 128]
     const int32_t *table, *plens, *cu, *tok_trace;
     const FewTile *tiles;             // [n_tiles]; null: one suffix token per trace, tile = trace

@@ -62,6 +62,22 @@ def test_one_token_batches_match_oracle(case):
     assert np.abs(ref["logits"] - gpu["logits"]).max() <= 2 * G.TOL["bf16"]["logit"]
 
 
+@pytest.mark.parametrize("B,heads", [(5, (4, 2)), (33, (4, 2)), (128, (4, 2)), (5, (12, 1)), (40, (16, 1))], ids=str)
+def test_the_first_layers_attention_carries_two_terms_of_the_new_tokens_values(B, heads):
+    """Without a context the first layer's attention is the new token's value; scaled up it makes the residual stream, and with
+    it the logits, almost alone.  What is rounded to a half on the way (operand, attention output: 2^-12 sqrt(1/3) each) leaves
+    an rms error of 2e-4 of the logits; a value of a single bf16 term 2^-9 sqrt(1/3) = 1.1e-3, a two-term one 2^-17."""
+    print(f"one-token batch without contexts: {B} traces, heads {heads}", flush=True)
+    wl = _wl("dec_terms", 7150 + B + heads[0], (0,) * B, n_layers=2, n_q_heads=heads[0], n_kv_heads=heads[1], n_verdict=8)
+    weights, batch, kv = G.build_inputs(wl)
+    weights.wo[0].mul_(256.0)
+    gpu = G.run_gpu(wl, weights, batch, kv)
+    ora = G.run_oracle(wl, weights, batch, kv, gpu["taus"], gpu["vids"])
+    err = float(np.sqrt(((gpu["logits"] - ora["logits"]) ** 2).mean() / (ora["logits"] ** 2).mean()))
+    print(f"rms error over rms of the logits {err:.2e}", flush=True)
+    assert err <= 6e-4
+
+
 def test_one_token_batch_on_a_model_with_sliced_k_ranges():
     # d_ffn 8192 = 128 k-tiles: the down projection's k range is cut into slices whose partial planes the last workgroup to
     # arrive adds up, over 128 column tiles (two per workgroup); 8 q heads per kv head.  A model this wide carries two terms
