@@ -10,6 +10,7 @@
 // the residual stream 46 -> 4 us, attention 80 -> 6 us).
 #include "kernels.h"
 #include <algorithm>
+#include <cfloat>
 
 namespace cs {
 
@@ -270,11 +271,39 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnArgs a) {
             l = l * alpha + ps;
             m = m_new;
     #pragma unroll
-            for (int i = 0; i < NK; ++i) {
-                o[i] *= alpha;
+            for (int i = 0; i < NK; ++i) o[i] *= alpha;
+            if (j0 + 16 > L + row0 / G + 1) {                                 // (uniform) a query of the tile does not see all keys
+                // Its probability of them is zero, which must not meet a NaN or an infinity: such values are taken out of the
+                // matrix product and added for the queries that see them.  Never taken with finite values.
+                bool odd = false;
+    #pragma unroll
+                for (int i = 0; i < NK; ++i)
+    #pragma unroll
+                    for (int e = 0; e < 4; ++e) odd |= !(fabsf(v[i][e]) <= FLT_MAX);
+                if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0, 0)) {
+    #pragma unroll
+                    for (int i = 0; i < NK; ++i)
+    #pragma unroll
+                        for (int e = 0; e < 4; ++e) v[i][e] = fabsf(v[i][e]) <= FLT_MAX ? v[i][e] : 0.f;
+    #pragma unroll 1
+                    for (int jj = 0; jj < 16; ++jj) {
+                        const int e = jj & 3;
+                        const float p = __shfl(e == 0 ? sc[0] : e == 1 ? sc[1] : e == 2 ? sc[2] : sc[3], 16 * (jj >> 2) + fr);
+                        const float *row = key_row(a, vp, vs, b, L, cu_b, c, min(j0 + jj, n_all - 1)) + 4 * fg;
+    #pragma unroll
+                        for (int i = 0; i < NK; ++i) {
+                            const f32x4 w = *reinterpret_cast<const f32x4 *>(row + 16 * i);
+    #pragma unroll
+                            for (int d = 0; d < 4; ++d)
+                                if (j0 + jj < n_keys && !(fabsf(w[d]) <= FLT_MAX)) o[i][d] += p * w[d];
+                        }
+                    }
+                }
+            }
+    #pragma unroll
+            for (int i = 0; i < NK; ++i)
     #pragma unroll
                 for (int e = 0; e < 4; ++e) o[i] = mma_f32(v[i][e], sc[e], o[i]);
-            }
         }
         // o[i][e]: dim 16 i + 4 (lane / 16) + e of query lane % 16
     #pragma unroll
