@@ -77,7 +77,8 @@ def _one_sublayer_changes_the_rows(kind, weights):
     """A sublayer of the first layer, one with fp16 operands, moves the rows far from what they were before it."""
     m = weights.cfg
     # Where every row is c e_5 + noise, its attention output without a context is close to the value of that, v: the attention
-    # can be made to add a given amount to element 5.  That element does not reach the logits itself.
+    # can be made to add a given amount to element 5.  With a large c the same holds for the MLP and its activations.  Element 5
+    # does not reach the logits itself.
     def attention_adds(c, amount):
         weights.embed[:, 5] = c
         rms = (c * c / m.d_model + 0.02 ** 2) ** 0.5
@@ -88,7 +89,10 @@ def _one_sublayer_changes_the_rows(kind, weights):
     if kind == "attention_grows":
         attention_adds(0.5, 8000.0)
     elif kind == "mlp_grows":
-        weights.w_down[0][5].mul_(2.0 ** 16)             # 0.1 becomes 1e3 to 1e4
+        weights.embed[:, 5] = 8.0
+        gate_up = weights.w_gate_up[0][:, 5].float() * 20.0
+        act = torch.nn.functional.silu(gate_up[:m.d_ffn]) * gate_up[m.d_ffn:]
+        weights.w_down[0][5] = (2.0 ** 17 * act / (act @ act)).to(weights.w_down[0].dtype)      # rms 0.4 -> 6e3
     elif kind == "attention_shrinks":
         # rms 4.2 -> 0.2 (an operand's rounding, 2^-12, leaves 96 * 2^-12 of element 5: half a percent of what is left)
         attention_adds(96.0, -96.0)
@@ -106,7 +110,7 @@ def test_rows_that_one_sublayer_grows_or_shrinks(kind, suffix, d_ffn):
     with it.  Their logits are of any size, so each trace's differences are taken over its rms on 8 verdict tokens; the bound on
     the real models' logits (rms 0.8 to 1.4) is that over 0.8."""
     print(f"few rows, {kind}: suffixes {suffix}, d_ffn {d_ffn}", flush=True)
-    prefix = [0 if kind.startswith("attention") else 37 * i + 5 for i in range(len(suffix))]
+    prefix = [37 * i + 5 if kind == "from_zero_rows" else 0 for i in range(len(suffix))]
     wl = W.tiny_workload("few_rows_" + kind, 9450 + sum(suffix), dtype="bf16", n_layers=4, d_model=512, n_q_heads=4, n_kv_heads=2,
                          head_dim=128, d_ffn=d_ffn, vocab=512, block_size=16, prefix_lens=prefix, suffix_lens=suffix, n_verdict=8)
     if kind == "from_zero_rows":
