@@ -114,6 +114,8 @@ struct WsLayout {
     int64_t max_tiles, max_items, max_tiles2, max_items2;
     size_t slice_off[48], slice_len[48];   // every slice as it was carved (few-row ones apart), for checks of the layout
     int n_slices;
+    size_t few_off[16], few_len[16], few_from;   // the few-row ones; what such passes share with the others ends at few_from
+    int n_few;
 };
 
 // A pass over few rows, as far as the model and the batch shape decide it: its projections are those of skinny_bf16.hip,
@@ -157,6 +159,7 @@ WsLayout ws_layout(const confspec_ctx *ctx, int64_t T, int64_t B, const confspec
     auto take_over = [&](size_t bytes) {     // a slice that may lie over the listed ones
         size_t o = at;
         at = align_up(at + bytes);
+        if (w.n_few < 16) { w.few_off[w.n_few] = o; w.few_len[w.n_few] = bytes; ++w.n_few; }
         return o;
     };
     size_t eb = elem_bytes(c.dtype);
@@ -244,7 +247,7 @@ WsLayout ws_layout(const confspec_ctx *ctx, int64_t T, int64_t B, const confspec
         const int few_T = (int)std::min<int64_t>(T, cs::SK_MAX_ROWS);
         if (skinny_shape_ok(c, exact ? T : few_T)) {
             const size_t general_end = at;
-            at = general_at;
+            at = w.few_from = general_at;
             const size_t rec = (size_t)cs::FEW_RECORDS * cs::few_attn_rows(false);
             w.few_tiles = take_over((size_t)few_tiles_bound(c, few_T, std::min<int64_t>(few_T, B)) * sizeof(cs::FewTile));
             w.few_ctl = take_over((size_t)cs::FEW_CTL_INTS * 4);
@@ -1287,6 +1290,15 @@ int confspec_op_workspace_slices(const confspec_ctx *ctx, int32_t T, int32_t B, 
     *n = L.n_slices;
     *total = L.total;
     return CONFSPEC_OK;
+}
+
+int confspec_few_row_slices(const confspec_ctx *ctx, int32_t T, int32_t B, const confspec_batch *exact, size_t *h_offsets, size_t *h_bytes,
+                            size_t *from, size_t *total) {
+    WsLayout L = ws_layout(ctx, T, B, exact);
+    for (int i = 0; i < L.n_few; ++i) { h_offsets[i] = L.few_off[i]; h_bytes[i] = L.few_len[i]; }
+    *from = L.few_from;
+    *total = L.total;
+    return L.n_few;
 }
 
 int confspec_phase_timing(confspec_ctx *ctx, int32_t enable) {

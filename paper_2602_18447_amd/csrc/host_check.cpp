@@ -163,6 +163,27 @@ static void check_library(const confspec_model_cfg &cfg, const Batch &b, const c
         std::sort(v.begin(), v.end());
         for (size_t i = 1; i < v.size(); ++i)
             CHECK(v[i - 1].first + v[i - 1].second <= v[i].first, "%s: slices overlap at %zu", what, v[i].first);
+        // the slices of passes over few rows: inside the total, clear of each other, and behind every slice that such passes
+        // share with the others (those in front of the attention plan, of which the last is the activations' slice)
+        size_t few_off[16], few_len[16], from = 0;
+        const int n_few = confspec_few_row_slices(ctx, b.T(), b.B(), exact ? &cb : nullptr, few_off, few_len, &from, &total);
+        CHECK(n_few == 0 || n_few == 8, "%s: %d few-row slices", what, n_few);
+        CHECK((n_few > 0) == (cfg.dtype == CONFSPEC_DTYPE_BF16 && cfg.n_layers > 0 && cfg.n_q_heads / cfg.n_kv_heads <= cs::FEW_MAX_G &&
+                              (!exact || b.T() <= cs::SK_MAX_ROWS)), "%s: %d few-row slices", what, n_few);
+        std::vector<std::pair<size_t, size_t>> f;
+        for (int i = 0; i < n_few; ++i) {
+            CHECK(few_off[i] % 256 == 0 && few_off[i] >= from && few_off[i] + few_len[i] <= total, "%s: few-row slice %d [%zu, +%zu)", what, i, few_off[i],
+                  few_len[i]);
+            if (few_len[i]) f.push_back({few_off[i], few_len[i]});
+        }
+        std::sort(f.begin(), f.end());
+        for (size_t i = 1; i < f.size(); ++i)
+            CHECK(f[i - 1].first + f[i - 1].second <= f[i].first, "%s: few-row slices overlap at %zu", what, f[i].first);
+        for (int i = 0, before = 0; n_few && i < n; ++i) {
+            before += off[i] + len[i] <= from;
+            CHECK(off[i] >= from || off[i] + len[i] <= from, "%s: slice %d crosses %zu", what, i, from);
+            if (i == n - 1) CHECK(before == 16, "%s: %d slices in front of the few-row ones", what, before);
+        }
     }
     // split-K planes: the bytes asked for are a whole number (2..64) of [M, N] fp32 planes, or none
     const int qw = cfg.n_q_heads * cfg.head_dim, kw = cfg.n_kv_heads * cfg.head_dim;

@@ -7,6 +7,12 @@
 #include <stdint.h>
 #include <atomic>
 #include "attn_plan.h"
+#include "../../include/confspec.h"
+
+// The slices of the workspace that only passes over few rows use (confspec_api.hip), for checks of the layout on the host:
+// their number (0: such a pass takes the general kernels), the end of what they share with the other passes, the total.
+extern "C" __attribute__((visibility("hidden"))) int confspec_few_row_slices(const confspec_ctx *ctx, int32_t T, int32_t B,
+    const confspec_batch *exact, size_t *h_offsets /*[16]*/, size_t *h_bytes, size_t *from, size_t *total);
 
 namespace cs {
 

@@ -19,6 +19,8 @@ pytestmark = pytest.mark.gpu
 SHAPES = {
     "five_tiles_cut_k": dict(d_model=512, n_q_heads=4, n_kv_heads=2, d_ffn=8960),
     "four_tiles_cut_k": dict(d_model=256, n_q_heads=6, n_kv_heads=1, d_ffn=8192),
+    "three_tiles_cut_k": dict(d_model=768, n_q_heads=4, n_kv_heads=2, d_ffn=8192),
+    "two_tiles_cut_k": dict(d_model=2048, n_q_heads=4, n_kv_heads=2, d_ffn=8192),
     "one_tile": dict(d_model=640, n_q_heads=5, n_kv_heads=5, d_ffn=832),
     "wide": dict(d_model=4096, n_q_heads=32, n_kv_heads=4, d_ffn=1088),
 }
