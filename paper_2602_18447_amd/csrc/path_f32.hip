@@ -6,8 +6,8 @@
 // kernels are therefore cut for latency: many small workgroups, every operand requested at once straight into the
 // registers the matrix instruction reads, the k range of a projection and the key range of an attention tile split
 // over the wavefronts of a workgroup, and RMSNorm, rotation, SwiGLU and the residual add done where the operands pass
-// by.  Measured on that model: 487 -> 67 us per pass (12 launches instead of 20; the projections of
-// the residual stream 46 -> 4 us, attention 80 -> 6 us).
+// by.  Measured on that model: 487 -> 67 us per pass (12 launches instead of 20; in a kernel trace 3 to 8 us a projection, 10 us
+// the attention).
 #include "kernels.h"
 #include <algorithm>
 #include <cfloat>
@@ -202,8 +202,10 @@ __device__ __forceinline__ const float *key_row(const AttnArgs &a, const float *
     return suf + ((size_t)t * a.Hkv + c) * a.hd;
 }
 
+// (Wavefronts per SIMD given: left alone, the branch for values that are not finite takes registers of a wavefront's worth at
+// head size 128; 4 traces of 2048 keys 314 us a pass with three, 329 without that branch and the bound.)
 template <int HD, int NW>
-__global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * NW, HD == 128 ? 3 : 4) void attn_f32_kernel(AttnArgs a) {
     constexpr int NK = HD / 16;
     __shared__ float om[NW][16][HD + 1];                  // O of a wavefront, [query][dim]
     __shared__ float mls[NW][2][16];
