@@ -136,11 +136,11 @@ int confspec_phase_times(confspec_ctx *ctx, float *h_ms /* [CONFSPEC_N_PHASES] *
  *       bit-identical with 0).
  *   "decode_kernels" (default 1): a bf16 pass of at most 128 suffix tokens can run on kernels of its own, when every
  *       layer's operands are single 16-bit values and no GEMM launch shape below is forced.  0: never, it runs on the
- *       general kernels.  1 and 2: it does, at 1 only up to 64 tokens where d_model is above 2048 and up to 32 where it is
- *       above 4096 (the general kernels are the faster ones beyond); with one new token in every trace (a generation step,
- *       Algorithm 1's generate calls) its attention then has one query row per head, and q and the probabilities two bf16
- *       terms in every layer where d_model and the q width are at most 1536 (1) or whatever the width (2); at those two, with
- *       at most 32 traces and d_model at most 1536, the full-vocabulary head never stores the logits.
+ *       general kernels.  1 and 2: it does, at 1 only up to 96 tokens where d_model is above 1792, 64 where it is above
+ *       2048 and 32 where it is above 4096 (the general kernels are the faster ones beyond); with one new token in every
+ *       trace (a generation step, Algorithm 1's generate calls) its attention then has one query row per head, and q and the
+ *       probabilities two bf16 terms in every layer where d_model and the q width are at most 1536 (1) or whatever the width
+ *       (2); at those two, with at most 32 traces and d_model at most 1536, the full-vocabulary head never stores the logits.
  *   "prune_last_layer" (default 1): in the last layer, attention rows, output projection and MLP are computed for the
  *       last position of each trace only (the only rows the verdict head reads; 0 computes every row).  Passes on the
  *       kernels for at most 128 suffix tokens compute every row whatever this setting, and the "attn_*" launch shapes do
