@@ -11,9 +11,8 @@
  * A step of at most 128 new tokens (96, 64, 32 for wide models) of a bf16 model runs on kernels of its own (projections
  * that stream each weight matrix once against the rows; with one new token per trace attention with one query row per head
  * and, up to 32 traces, a head fused with a running arg max / log-sum-exp so that the [B, vocab] logits are never stored);
- * every other batch takes the
- * verification pass's kernels and stores the logits in the head scratch.  confspec_tune "decode_kernels" = 0 switches the
- * former off.
+ * every other batch takes the verification pass's kernels and stores the logits in the head scratch.  confspec_tune
+ * "decode_kernels" = 0 switches the former off.
  */
 #ifndef CONFSPEC_GENERATE_H
 #define CONFSPEC_GENERATE_H

@@ -44,10 +44,10 @@ struct Settings {
     int prefetch_down = 1;
     // bf16 passes of at most 128 suffix tokens have kernels of their own (skinny_bf16.hip, attn_few.hip).  0: never, such a
     // pass runs on the general kernels like any other.  1: up to the rows where they are the faster ones (96 above a width of
-    // 1792, 64 above 2048, 32 above 4096); with one new token per trace (a generation step) the attention
-    // carries two terms of q and the probabilities in every layer, and the full-vocabulary head is the one of
-    // decode_bf16.hip, when d_model and the q width are at most 1536: there the matrix work is free and the head's rows fit
-    // that kernel; wider models carry two terms in the attn_precise_layers only.  2: all of it whatever the width.
+    // 1792, 64 above 2048, 32 above 4096); with one new token per trace (a generation step) the attention carries two terms of
+    // q and the probabilities in every layer, and the full-vocabulary head is the one of decode_bf16.hip, when d_model and the
+    // q width are at most 1536: there the matrix work is free and the head's rows fit that kernel; wider models carry two
+    // terms in the attn_precise_layers only.  2: all of it whatever the width.
     int decode_kernels = 1;
     cs::GemmTune gemm;
     cs::AttnTune attn;
@@ -127,8 +127,8 @@ bool skinny_shape_ok(const confspec_model_cfg &c, int64_t T) {
 // Rows up to which these kernels are the faster ones.  Every workgroup reads all activations, which grow with rows times
 // width, and the general kernels' tiles fill up with the rows.  Whole layer, general against these (us, one trace of 512 or
 // 1024 keys): width 1536 / 8960, 128 rows 109 : 78; 1792 / 8960, 128 rows 115 : 95; 2048 / 6144 with 8 kv heads, 96 rows 105 : 98,
-// 128 rows 111 : 107, but on 16384 keys 134 : 130 and 142 : 151; 2560 / 9728, 64 rows 126 : 109, 65 rows 128 : 132; 4096 / 14336, 64 rows 187 : 171, 65 rows 189 : 219; 5120 / 27648, 32 rows 259 : 223, 33 rows 264 : 277, 96 rows
-// 303 : 477.
+// 128 rows 111 : 107, but on 16384 keys 134 : 130 and 142 : 151; 2560 / 9728, 64 rows 126 : 109, 65 rows 128 : 132;
+// 4096 / 14336, 64 rows 187 : 171, 65 rows 189 : 219; 5120 / 27648, 32 rows 259 : 223, 33 rows 264 : 277, 96 rows 303 : 477.
 int skinny_max_rows(const confspec_model_cfg &c) { return c.d_model <= 1792 ? cs::SK_MAX_ROWS : c.d_model <= 2048 ? 96 : c.d_model <= 4096 ? 64 : 32; }
 // One new token in every trace (a generation step), as far as its attention is concerned.
 bool one_token_shape(const confspec_model_cfg &c, int64_t T, int64_t B) { return T == B && c.n_q_heads / c.n_kv_heads <= cs::FEW_MAX_G_ONE; }
