@@ -930,8 +930,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         // that kernel reads in strided pieces, into the last-level cache
         // (a down projection cut into k slices of 256 x 256 tiles reads whole 128-byte lines of 256 rows at a time and
         // does not gain from it: config 2 is 0.5 % faster without the hint, the unsplit shapes 0.1-0.2 % slower)
-        bool big_tiles = false;
-        const bool warm = set.prefetch_down && !(sk && cs::gemm_splitk_factor(set.gemm, rows, d, c.d_ffn * wide, &big_tiles) > 1);
+        const bool warm = set.prefetch_down && !(sk && cs::gemm_splitk_factor(set.gemm, rows, d, c.d_ffn * wide) > 1);
         cs::PrefetchArgs pf;
         pf.ptr = warm ? wdn : nullptr;
         pf.n16 = warm ? (unsigned)((size_t)d * c.d_ffn * eb / 16) : 0u;

@@ -11,9 +11,10 @@
 // vector instruction.  Rows are unpadded; instead the 16-byte k-vector g of row r is kept at position g ^ ((r >> 1) & 7)
 // of its row (the lane that fills a position fetches the matching global vector), so the 16 lanes of one ds_read_b128
 // phase - 16 consecutive rows, same k-vector - hit 16 different 4-bank groups.
-// Two pipelines: 256 x 256 tiles run 16x16x32 MFMAs on a ring of five half-stage LDS units with the loads spread between
+// Three pipelines: 256 x 256 tiles run 16x16x32 MFMAs on a ring of five half-stage LDS units with the loads spread between
 // the MFMAs (described where it is written); the smaller tiles, of which a CU holds two independent workgroups, keep two
-// (or four) whole stages: the loads of the next k-tile(s) are issued right behind the barrier that frees their stage.
+// (or four) whole stages: the loads of the next k-tile(s) are issued right behind the barrier that frees their stage; outputs of
+// one round of tiles have a kernel with loading wavefronts (gemm_feed_kernel).
 // Barriers inside the k loops are bare s_barrier instructions with explicit waits: __syncthreads() carries fences that
 // make the compiler wait for every outstanding direct load.
 //
@@ -78,6 +79,198 @@ __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "mem
 constexpr bool ring_tile(int BM, int BN, int BK) { return BM == 256 && BN == 256 && BK == 64; }
 constexpr int gemm_lds_bytes(int BM, int BN, int BK, int NS) { return ring_tile(BM, BN, BK) ? 5 * BM * BK * 2 : NS * (BM + BN) * BK * 2; }
 
+#if defined(__HIP_DEVICE_COMPILE__)
+// The accumulator layout of a 32x32 block gives a lane one column and 16 rows, so
+// stores straight from it are 2- or 4-byte pieces per lane, and the store path retires a wavefront
+// instruction in about 16 cycles whatever its width.  Each wavefront therefore transposes one 32-row
+// block at a time through a private piece of LDS (the operand stages are dead by now) and moves
+// 16 bytes per lane to and from global memory.
+// Rotary values of a lane's rows (pass p over a 32-row block) and columns, cos and sin, 8 each.
+struct RopeVals { f32x4 v[2][4]; };
+__device__ __forceinline__ void load_rope(RopeVals &rv, const RopeArgs &rope, int p, size_t at) {
+    const f32x4 *cp = reinterpret_cast<const f32x4 *>(rope.cos_t + at), *sp = reinterpret_cast<const f32x4 *>(rope.sin_t + at);
+    rv.v[p][0] = cp[0]; rv.v[p][1] = cp[1]; rv.v[p][2] = sp[0]; rv.v[p][3] = sp[1];
+}
+// First of a lane's 8 columns inside a head half.  64 columns of a wavefront: 32 columns and their partners.  32 columns
+// (gemm_feed_kernel's 64-column tiles, whose W rows are dealt out so): 16 and their partners.
+template <int WN>
+__device__ __forceinline__ int rope_col(int n0, int wx, int lane) {
+    if constexpr (WN == 64) return (((n0 + wx * WN) >> 6) & 1) * 32 + (lane & 3) * 8;
+    else return ((n0 >> 6) & 1) * 32 + wx * 16 + (lane & 1) * 8;
+}
+// early (EPI_ROPE with WM == 32, else null): the rotary values, loaded in front of the k loop.
+template <int EPI, bool M16, int WM, int WN, int NW, int LDS_BYTES, class Acc, class Acc16>
+__device__ __forceinline__ void gemm_epilogue(const Acc &acc, const Acc16 &acc16, unsigned char *smem, void *out_v, int M, int N, int m0, int n0,
+                                              int wy, int wx, int wave, int lane, int out_fmt, const RopeArgs &rope,
+                                              const RopeVals *early = nullptr) {
+    constexpr int MI = WM / 32, NI = WN / 32, NI16 = WN / 16;
+    const int out_terms = out_fmt == 2 ? 2 : 1;
+    constexpr int WNO = (EPI == EPI_SWIGLU) ? WN / 2 : WN;   // output columns of a wave tile
+    // staging row stride in words: the row groups of a write (two, 4 rows apart, for 32x32 blocks; four for 16x16 blocks)
+    // hit disjoint banks with 4 * SROW % 64 == 32 or 16
+    constexpr int SROW = M16 ? WNO + 4 : WNO + 8;
+    static_assert(NW * 32 * SROW * 4 <= LDS_BYTES, "epilogue staging does not fit the operand stages");
+    __syncthreads();                                         // every wavefront is done with the operand stages
+    float *stg = reinterpret_cast<float *>(smem) + wave * 32 * SROW;
+    const int col_l = lane & 31, row_l = (lane >> 5) * 4;    // C layout: column lane%32, rows 8*(e/4) + 4*(lane/32) + e%4
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        if constexpr (M16) {
+            // rows 32 i .. 32 i + 31 of the wave tile are the 16-row blocks 2 i and 2 i + 1
+#pragma unroll
+            for (int i2 = 0; i2 < 2; ++i2)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float *srow = stg + (16 * i2 + 4 * (lane >> 4) + e) * SROW + (lane & 15);
+                    if (EPI == EPI_SWIGLU) {
+                        // columns 64 c .. 64 c + 31 hold gate values and the 32 after them the matching up values
+#pragma unroll
+                        for (int j = 0; j < NI16; ++j)
+                            if ((j & 3) < 2) {
+                                float gte = acc16[2 * i + i2][j][e], up = acc16[2 * i + i2][j + 2][e];
+                                srow[(j >> 2) * 32 + (j & 1) * 16] = gte * __builtin_amdgcn_rcpf(1.0f + __expf(-gte)) * up;
+                            }
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < NI16; ++j) srow[j * 16] = acc16[2 * i + i2][j][e];
+                    }
+                }
+        } else
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            float *srow = stg + ((e >> 2) * 8 + row_l + (e & 3)) * SROW + col_l;
+            if (EPI == EPI_SWIGLU) {
+#pragma unroll
+                for (int j = 0; j < NI; j += 2) {
+                    // silu(g) * u with the hardware reciprocal (1 ulp): far below the bf16 rounding of the result,
+                    // and a third of the instructions of an IEEE division
+                    float gte = acc[i][j][e], up = acc[i][j + 1][e];
+                    srow[(j >> 1) * 32] = gte * __builtin_amdgcn_rcpf(1.0f + __expf(-gte)) * up;
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < NI; ++j) srow[j * 32] = acc[i][j][e];
+            }
+        }
+        // LDS operations of one wavefront execute in order; the fence keeps the compiler from moving the
+        // reads of other lanes' values above the writes.
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int mrow0 = m0 + wy * WM + i * 32;
+        if (EPI == EPI_SWIGLU) {
+            constexpr int LPR = WNO / 8, RP = 64 / LPR;      // lanes per output row (8 bf16 each), rows per pass
+            bf16 *out = reinterpret_cast<bf16 *>(out_v);
+            const int Fo = N >> 1;
+            const int f0 = ((n0 + wx * WN) >> 1) + (lane % LPR) * 8;
+#pragma unroll
+            for (int p = 0; p < 32 / RP; ++p) {
+                int r = p * RP + lane / LPR, m = mrow0 + r;
+                const f32x4 *src = reinterpret_cast<const f32x4 *>(stg + r * SROW + (lane % LPR) * 8);
+                f32x4 v0 = src[0], v1 = src[1];
+                float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                if (m < M) {
+                    bf16 *dst = out + (size_t)m * Fo * out_terms + f0;
+                    unsigned hi[8];
+                    if (out_fmt == 3) {
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) hi[q] = __half_as_ushort(to_half_sat(v[q]));
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) hi[q] = __bfloat16_as_ushort(__float2bfloat16(v[q]));
+                    }
+                    u32x4 ph = {hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16)};
+                    *reinterpret_cast<u32x4 *>(dst) = ph;
+                    if (out_fmt == 2) {
+                        unsigned lo[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+                            lo[q] = __bfloat16_as_ushort(
+                                __float2bfloat16(v[q] - __bfloat162float(__ushort_as_bfloat16((unsigned short)hi[q]))));
+                        u32x4 pl = {lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16)};
+                        *reinterpret_cast<u32x4 *>(dst + Fo) = pl;
+                    }
+                }
+            }
+        } else if (EPI == EPI_ROPE) {
+            // The first half of the staged columns are columns of a head's 64-column group, the second half their rotation
+            // partners, 64 further in the head.  A lane takes 8 columns of a row and the 8 partners.
+            constexpr int LR = WN / 16, RP = 64 / LR;        // lanes per row, rows per pass
+            const int head = (n0 + (WN == 64 ? wx * WN : 0)) >> 7, c0 = rope_col<WN>(n0, wx, lane);
+            const bool is_q = head < rope.Hq, is_v = head >= rope.Hq + rope.Hkv;
+            const int hh = is_q ? head : is_v ? head - rope.Hq - rope.Hkv : head - rope.Hq;
+            const int heads = is_q ? rope.Hq : rope.Hkv;
+            bf16 *dst_hi = reinterpret_cast<bf16 *>(is_q ? rope.q : is_v ? rope.v : rope.k);
+            bf16 *dst_lo = reinterpret_cast<bf16 *>(is_q ? rope.q_lo : is_v ? rope.v_lo : rope.k_lo);
+#pragma unroll
+            for (int p = 0; p < 32 / RP; ++p) {
+                int r = p * RP + lane / LR, m = mrow0 + r;
+                const f32x4 *sa = reinterpret_cast<const f32x4 *>(stg + r * SROW + (lane % LR) * 8);
+                const f32x4 *sb = reinterpret_cast<const f32x4 *>(stg + r * SROW + WN / 2 + (lane % LR) * 8);
+                f32x4 a0 = sa[0], a1 = sa[1], b0 = sb[0], b1 = sb[1];
+                if (m < M) {
+                    float va[8] = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
+                    float vb[8] = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
+                    if (!is_v) {
+                        RopeVals rv;
+                        if (early) rv = *early;
+                        else load_rope(rv, rope, p, (size_t)m * 64 + c0);
+                        const f32x4 c_0 = rv.v[p][0], c_1 = rv.v[p][1], s_0 = rv.v[p][2], s_1 = rv.v[p][3];
+                        float cs[8] = {c_0[0], c_0[1], c_0[2], c_0[3], c_1[0], c_1[1], c_1[2], c_1[3]};
+                        float sn[8] = {s_0[0], s_0[1], s_0[2], s_0[3], s_1[0], s_1[1], s_1[2], s_1[3]};
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+                            float lo_ = va[q], hi_ = vb[q];
+                            va[q] = lo_ * cs[q] - hi_ * sn[q];
+                            vb[q] = hi_ * cs[q] + lo_ * sn[q];
+                        }
+                    }
+                    size_t o = ((size_t)m * heads + hh) * 128 + c0;
+                    unsigned ha[8], hb[8];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        ha[q] = __bfloat16_as_ushort(__float2bfloat16(va[q]));
+                        hb[q] = __bfloat16_as_ushort(__float2bfloat16(vb[q]));
+                    }
+                    u32x4 pa = {ha[0] | (ha[1] << 16), ha[2] | (ha[3] << 16), ha[4] | (ha[5] << 16), ha[6] | (ha[7] << 16)};
+                    u32x4 pb = {hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16), hb[4] | (hb[5] << 16), hb[6] | (hb[7] << 16)};
+                    *reinterpret_cast<u32x4 *>(dst_hi + o) = pa;
+                    *reinterpret_cast<u32x4 *>(dst_hi + o + 64) = pb;
+                    if (dst_lo) {
+                        unsigned la[8], lb[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+                            la[q] = __bfloat16_as_ushort(__float2bfloat16(va[q] - __bfloat162float(__ushort_as_bfloat16((unsigned short)ha[q]))));
+                            lb[q] = __bfloat16_as_ushort(__float2bfloat16(vb[q] - __bfloat162float(__ushort_as_bfloat16((unsigned short)hb[q]))));
+                        }
+                        u32x4 qa = {la[0] | (la[1] << 16), la[2] | (la[3] << 16), la[4] | (la[5] << 16), la[6] | (la[7] << 16)};
+                        u32x4 qb = {lb[0] | (lb[1] << 16), lb[2] | (lb[3] << 16), lb[4] | (lb[5] << 16), lb[6] | (lb[7] << 16)};
+                        *reinterpret_cast<u32x4 *>(dst_lo + o) = qa;
+                        *reinterpret_cast<u32x4 *>(dst_lo + o + 64) = qb;
+                    }
+                }
+            }
+        } else {
+            constexpr int LPR = WNO / 4, RP = 64 / LPR;      // lanes per output row (4 floats each), rows per pass
+            float *out = reinterpret_cast<float *>(out_v);
+#pragma unroll
+            for (int p = 0; p < 32 / RP; ++p) {
+                int r = p * RP + lane / LPR, m = mrow0 + r;
+                f32x4 v = *reinterpret_cast<const f32x4 *>(stg + r * SROW + (lane % LPR) * 4);
+                if (m < M) {
+                    f32x4 *dst = reinterpret_cast<f32x4 *>(out + (size_t)m * N + n0 + wx * WN + (lane % LPR) * 4);
+                    if (EPI == EPI_RESID_F32) v += *dst;
+                    *dst = v;
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+#endif
+
 // BK: k extent of one LDS stage (64 or 32 elements); NS: number of LDS stages.  NS - 1 k-tiles are
 // kept in flight: (64, 2) has the fewest barriers, (32, 4) the deepest prefetch for the same LDS budget.
 template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int NS, int EPI, int A_FMT>
@@ -89,7 +282,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const
     constexpr int NW = WAVES_M * WAVES_N;
     constexpr int A_TERMS = A_FMT == 2 ? 2 : 1;
     constexpr bool F16 = A_FMT == 3;
-    const int out_terms = out_fmt == 2 ? 2 : 1;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;   // wave tile
     constexpr int MI = WM / 32, NI = WN / 32;             // 32x32 MFMA blocks per wave
     constexpr int ROWB = BK * 2;                          // bytes of one tile row in LDS
@@ -101,7 +293,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const
     static_assert(BK == 64 || BK == 32, "BK");
     static_assert(BM % (RPD * NW) == 0 && BN % (RPD * NW) == 0 && WM % 32 == 0 && WN % 32 == 0, "tile shape");
     static_assert(EPI != EPI_SWIGLU || WN % 64 == 0, "SwiGLU needs a gate/up column pair inside one wave tile");
-    static_assert(EPI != EPI_ROPE || WN == 64, "the rotation pairs of a head half fill a 64-column wave tile");
+    static_assert(EPI != EPI_ROPE || WN == 64 || (WN == 32 && BN == 64), "rotation pairs inside a wave tile");
     static_assert(NS >= 2 && NS <= 5, "stages");
     static_assert(MI * NI >= 2, "a k-step has at least two MFMAs");
     // 256 x 256 tiles take the loop that reads a k-tile's first operands during the previous tile's last k-step
@@ -373,11 +565,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const
     }
     }
 
-    // ---- epilogue.  The accumulator layout of a 32x32 block gives a lane one column and 16 rows, so
-    // stores straight from it are 2- or 4-byte pieces per lane, and the store path retires a wavefront
-    // instruction in about 16 cycles whatever its width.  Each wavefront therefore transposes one 32-row
-    // block at a time through a private piece of LDS (the operand stages are dead by now) and moves
-    // 16 bytes per lane to and from global memory.
     // Warm-up of memory the next kernel will read (the down projection's weights while the gate/up projection, which
     // leaves HBM idle, finishes a tile): every workgroup reads its slice once, front to back, so the data is in the
     // last-level cache when that kernel's strided tile loads ask for it.  The values are not used.
@@ -396,171 +583,188 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const
             pfv[i] = (off < per && base + off < pf.n16) ? src[base + off] : z;
         }
     }
-    constexpr int WNO = (EPI == EPI_SWIGLU) ? WN / 2 : WN;   // output columns of a wave tile
-    // staging row stride in words: the row groups of a write (two, 4 rows apart, for 32x32 blocks; four for 16x16 blocks)
-    // hit disjoint banks with 4 * SROW % 64 == 32 or 16
-    constexpr int SROW = M16 ? WNO + 4 : WNO + 8;
-    static_assert(NW * 32 * SROW * 4 <= gemm_lds_bytes(BM, BN, BK, NS), "epilogue staging does not fit the operand stages");
-    __syncthreads();                                         // every wavefront is done with the operand stages
-    float *stg = reinterpret_cast<float *>(smem) + wave * 32 * SROW;
-    const int col_l = lane & 31, row_l = (lane >> 5) * 4;    // C layout: column lane%32, rows 8*(e/4) + 4*(lane/32) + e%4
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-        if constexpr (M16) {
-            // rows 32 i .. 32 i + 31 of the wave tile are the 16-row blocks 2 i and 2 i + 1
-#pragma unroll
-            for (int i2 = 0; i2 < 2; ++i2)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float *srow = stg + (16 * i2 + 4 * (lane >> 4) + e) * SROW + (lane & 15);
-                    if (EPI == EPI_SWIGLU) {
-                        // columns 64 c .. 64 c + 31 hold gate values and the 32 after them the matching up values
-#pragma unroll
-                        for (int j = 0; j < NI16; ++j)
-                            if ((j & 3) < 2) {
-                                float gte = acc16[2 * i + i2][j][e], up = acc16[2 * i + i2][j + 2][e];
-                                srow[(j >> 2) * 32 + (j & 1) * 16] = gte * __builtin_amdgcn_rcpf(1.0f + __expf(-gte)) * up;
-                            }
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < NI16; ++j) srow[j * 16] = acc16[2 * i + i2][j][e];
-                    }
-                }
-        } else
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            float *srow = stg + ((e >> 2) * 8 + row_l + (e & 3)) * SROW + col_l;
-            if (EPI == EPI_SWIGLU) {
-#pragma unroll
-                for (int j = 0; j < NI; j += 2) {
-                    // silu(g) * u with the hardware reciprocal (1 ulp): far below the bf16 rounding of the result,
-                    // and a third of the instructions of an IEEE division
-                    float gte = acc[i][j][e], up = acc[i][j + 1][e];
-                    srow[(j >> 1) * 32] = gte * __builtin_amdgcn_rcpf(1.0f + __expf(-gte)) * up;
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < NI; ++j) srow[j * 32] = acc[i][j][e];
-            }
-        }
-        // LDS operations of one wavefront execute in order; the fence keeps the compiler from moving the
-        // reads of other lanes' values above the writes.
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const int mrow0 = m0 + wy * WM + i * 32;
-        if (EPI == EPI_SWIGLU) {
-            constexpr int LPR = WNO / 8, RP = 64 / LPR;      // lanes per output row (8 bf16 each), rows per pass
-            bf16 *out = reinterpret_cast<bf16 *>(out_v);
-            const int Fo = N >> 1;
-            const int f0 = ((n0 + wx * WN) >> 1) + (lane % LPR) * 8;
-#pragma unroll
-            for (int p = 0; p < 32 / RP; ++p) {
-                int r = p * RP + lane / LPR, m = mrow0 + r;
-                const f32x4 *src = reinterpret_cast<const f32x4 *>(stg + r * SROW + (lane % LPR) * 8);
-                f32x4 v0 = src[0], v1 = src[1];
-                float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-                if (m < M) {
-                    bf16 *dst = out + (size_t)m * Fo * out_terms + f0;
-                    unsigned hi[8];
-                    if (out_fmt == 3) {
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) hi[q] = __half_as_ushort(to_half_sat(v[q]));
-                    } else {
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) hi[q] = __bfloat16_as_ushort(__float2bfloat16(v[q]));
-                    }
-                    u32x4 ph = {hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16)};
-                    *reinterpret_cast<u32x4 *>(dst) = ph;
-                    if (out_fmt == 2) {
-                        unsigned lo[8];
-#pragma unroll
-                        for (int q = 0; q < 8; ++q)
-                            lo[q] = __bfloat16_as_ushort(
-                                __float2bfloat16(v[q] - __bfloat162float(__ushort_as_bfloat16((unsigned short)hi[q]))));
-                        u32x4 pl = {lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16)};
-                        *reinterpret_cast<u32x4 *>(dst + Fo) = pl;
-                    }
-                }
-            }
-        } else if (EPI == EPI_ROPE) {
-            // Staged columns 0..31 are columns c0..c0+31 of a head and columns 32..63 their rotation partners
-            // c0+64.. (c0 = 0 or 32).  A lane takes 8 columns of a row and the 8 partners.
-            const int n_w = n0 + wx * WN;
-            const int head = n_w >> 7, c0 = ((n_w >> 6) & 1) * 32 + (lane & 3) * 8;
-            const bool is_q = head < rope.Hq, is_v = head >= rope.Hq + rope.Hkv;
-            const int hh = is_q ? head : is_v ? head - rope.Hq - rope.Hkv : head - rope.Hq;
-            const int heads = is_q ? rope.Hq : rope.Hkv;
-            bf16 *dst_hi = reinterpret_cast<bf16 *>(is_q ? rope.q : is_v ? rope.v : rope.k);
-            bf16 *dst_lo = reinterpret_cast<bf16 *>(is_q ? rope.q_lo : is_v ? rope.v_lo : rope.k_lo);
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                int r = p * 16 + (lane >> 2), m = mrow0 + r;
-                const f32x4 *sa = reinterpret_cast<const f32x4 *>(stg + r * SROW + (lane & 3) * 8);
-                const f32x4 *sb = reinterpret_cast<const f32x4 *>(stg + r * SROW + 32 + (lane & 3) * 8);
-                f32x4 a0 = sa[0], a1 = sa[1], b0 = sb[0], b1 = sb[1];
-                if (m < M) {
-                    float va[8] = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
-                    float vb[8] = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
-                    if (!is_v) {
-                        const f32x4 *cp = reinterpret_cast<const f32x4 *>(rope.cos_t + (size_t)m * 64 + c0);
-                        const f32x4 *sp = reinterpret_cast<const f32x4 *>(rope.sin_t + (size_t)m * 64 + c0);
-                        f32x4 c_0 = cp[0], c_1 = cp[1], s_0 = sp[0], s_1 = sp[1];
-                        float cs[8] = {c_0[0], c_0[1], c_0[2], c_0[3], c_1[0], c_1[1], c_1[2], c_1[3]};
-                        float sn[8] = {s_0[0], s_0[1], s_0[2], s_0[3], s_1[0], s_1[1], s_1[2], s_1[3]};
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) {
-                            float lo_ = va[q], hi_ = vb[q];
-                            va[q] = lo_ * cs[q] - hi_ * sn[q];
-                            vb[q] = hi_ * cs[q] + lo_ * sn[q];
-                        }
-                    }
-                    size_t o = ((size_t)m * heads + hh) * 128 + c0;
-                    unsigned ha[8], hb[8];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) {
-                        ha[q] = __bfloat16_as_ushort(__float2bfloat16(va[q]));
-                        hb[q] = __bfloat16_as_ushort(__float2bfloat16(vb[q]));
-                    }
-                    u32x4 pa = {ha[0] | (ha[1] << 16), ha[2] | (ha[3] << 16), ha[4] | (ha[5] << 16), ha[6] | (ha[7] << 16)};
-                    u32x4 pb = {hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16), hb[4] | (hb[5] << 16), hb[6] | (hb[7] << 16)};
-                    *reinterpret_cast<u32x4 *>(dst_hi + o) = pa;
-                    *reinterpret_cast<u32x4 *>(dst_hi + o + 64) = pb;
-                    if (dst_lo) {
-                        unsigned la[8], lb[8];
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) {
-                            la[q] = __bfloat16_as_ushort(__float2bfloat16(va[q] - __bfloat162float(__ushort_as_bfloat16((unsigned short)ha[q]))));
-                            lb[q] = __bfloat16_as_ushort(__float2bfloat16(vb[q] - __bfloat162float(__ushort_as_bfloat16((unsigned short)hb[q]))));
-                        }
-                        u32x4 qa = {la[0] | (la[1] << 16), la[2] | (la[3] << 16), la[4] | (la[5] << 16), la[6] | (la[7] << 16)};
-                        u32x4 qb = {lb[0] | (lb[1] << 16), lb[2] | (lb[3] << 16), lb[4] | (lb[5] << 16), lb[6] | (lb[7] << 16)};
-                        *reinterpret_cast<u32x4 *>(dst_lo + o) = qa;
-                        *reinterpret_cast<u32x4 *>(dst_lo + o + 64) = qb;
-                    }
-                }
-            }
-        } else {
-            constexpr int LPR = WNO / 4, RP = 64 / LPR;      // lanes per output row (4 floats each), rows per pass
-            float *out = reinterpret_cast<float *>(out_v);
-#pragma unroll
-            for (int p = 0; p < 32 / RP; ++p) {
-                int r = p * RP + lane / LPR, m = mrow0 + r;
-                f32x4 v = *reinterpret_cast<const f32x4 *>(stg + r * SROW + (lane % LPR) * 4);
-                if (m < M) {
-                    f32x4 *dst = reinterpret_cast<f32x4 *>(out + (size_t)m * N + n0 + wx * WN + (lane % LPR) * 4);
-                    if (EPI == EPI_RESID_F32) v += *dst;
-                    *dst = v;
-                }
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
+    gemm_epilogue<EPI, M16, WM, WN, NW, gemm_lds_bytes(BM, BN, BK, NS)>(acc, acc16, smem, out_v, M, N, m0, n0, wy, wx, wave, lane, out_fmt, rope);
     if (do_pf) {
 #pragma unroll
         for (int i = 0; i < PF_VEC; ++i) asm volatile("" ::"v"(pfv[i]));   // the loads must not be dropped as unused
     }
+#endif
+}
+
+// ---- Outputs of few tiles: loads by wavefronts of their own ----------------------------------------------------------
+// At most one round of workgroups: passes of about 33 to 2000 rows, and the trailing columns of wide outputs.  What bounds the loops
+// above there is a CU on its own: its direct loads take 20 cycles per KiB at the address unit, a wavefront that issues one waits
+// at it, and its MFMAs wait behind it - a lone 256 x 128 tile of 8 such wavefronts takes 0.73 us per k-tile of 64 for 0.43 us
+// of matrix work.  Here NL wavefronts only load, half of them A and the other half W (memory operations of a wavefront
+// complete in order; the barrier of a k-tile joins them), and the others only multiply: 0.54 us, and 0.36 instead of 0.48 us for a
+// 128 x 128 tile (operands in the last-level cache).  With weights from HBM, 1.1 us away, the stages in flight decide: 64 x 64 tiles have
+// seven (512 x 2048 x 1536: 11.2 us; 64 x 128 in three stages 16; 128 x 128 in two stages, k sliced, 18.6), larger ones what fits 160 KiB.
+// The multiplying wavefronts keep the 256 x 256 loop's order: 16x16x32 MFMAs in slots (k half, 16-row block) of WN / 16
+// each, A fragments in a ring of four, W fragments of a k half double-buffered, one barrier per k-tile three slots before
+// its end; the next k-tile's first operands are read in those slots.
+template <int P, int NS>
+__device__ __forceinline__ void wait_tiles(int rem) {     // until at most min(rem, NS) k-tiles of P loads each are outstanding
+    if constexpr (NS > 0) {
+        if (rem >= NS) CS_WAIT_VMCNT_LDS(NS * P);
+        else wait_tiles<P, NS - 1>(rem);
+    } else {
+        CS_WAIT_VMCNT_LDS(0);
+    }
+}
+
+// NS: stages of (BM + BN) x 64 elements in LDS; rows unpadded and swizzled as above.  gridDim.y: k slices, interleaved as above.
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NL, int NS, int EPI, int A_FMT>
+__global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + NL)) void gemm_feed_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, void *out_v,
+                                                                                 int M, int N, int K, int tiles_m, int tiles_n, int n_base, int group_m,
+                                                                                 int out_fmt, RopeArgs rope) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int NW = WAVES_M * WAVES_N, NLW = NL / 2, NLA = NL - NLW;  // wavefronts that multiply; that load W, and A
+    constexpr int A_TERMS = A_FMT == 2 ? 2 : 1;
+    constexpr bool F16 = A_FMT == 3;
+    constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, MI = WM / 16, NI = WN / 16;
+    constexpr int PA = BM / (8 * NLA), PW = BN / (8 * NLW), PM = PA > PW ? PA : PW;   // direct loads of a wavefront per k-tile
+    constexpr int ROWB = 128, STAGE = (BM + BN) * ROWB, SLOTS = 2 * MI, SB = SLOTS - 3;   // the barrier stands in front of slot SB
+    static_assert(BM % (8 * NLA) == 0 && BN % (8 * NLW) == 0 && WM % 32 == 0 && WN % 16 == 0 && NI >= 2, "tile shape");
+    static_assert(EPI != EPI_SWIGLU || WN % 64 == 0, "SwiGLU needs a gate/up column pair inside one wave tile");
+    static_assert(EPI != EPI_ROPE || WN == 64 || (WN == 32 && BN == 64), "rotation pairs inside a wave tile");
+    static_assert(NS >= 2 && (NS - 1) * PM <= 63, "the waits count up to 63 loads");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];   // [NS] stages: A rows, then W rows
+
+    const int n_tiles = tiles_m * tiles_n;                               // tile order: as in gemm_bf16_kernel
+    const int per = (n_tiles + 7) >> 3;
+    const int lid = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if (lid >= n_tiles) return;                                          // uniform per workgroup
+    const int band = lid / (group_m * tiles_n), in_band = lid - band * group_m * tiles_n;
+    const int band_rows = min(group_m, tiles_m - band * group_m);
+    const int m0 = (band * group_m + in_band % band_rows) * BM, n0 = n_base + in_band / band_rows * BN;
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nk_w = K / 64;
+    const int kstep = gridDim.y, kb = blockIdx.y;
+    const int nk = (nk_w * A_TERMS - kb + kstep - 1) / kstep;
+    if (EPI == EPI_STORE_F32) out_v = reinterpret_cast<float *>(out_v) + (size_t)blockIdx.y * M * N;
+
+    if (wave >= NW) {
+        // load j of a k-tile fills rows 8 (lw + n_lw j) .. + 7 of its operand (A rows past M: the last one)
+        const bool is_w = wave < NW + NLW;
+        const int lw = is_w ? wave - NW : wave - NW - NLW, n_lw = is_w ? NLW : NLA, n_ld = is_w ? PW : PA;
+        const int lda = K * A_TERMS;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<bf16 *>(is_w ? W + (size_t)n0 * K : A + (size_t)m0 * lda), 0, -1, 0x00020000);
+        int off[PM];
+#pragma unroll
+        for (int j = 0; j < PM; ++j) {
+            const int row = 8 * (lw + n_lw * min(j, n_ld - 1)) + (lane >> 3);
+            // a 64-column tile of two 32-column wavefronts: each takes 16 columns of the first 32 and their partners
+            const int w_row = EPI == EPI_ROPE && WN == 32 ? (row & 15) + ((row >> 5) & 1) * 16 + ((row >> 4) & 1) * 32 : row;
+            off[j] = (is_w ? w_row * K : (min(m0 + row, M - 1) - m0) * lda) * 2 + ((lane & 7) ^ ((row >> 1) & 7)) * 16;
+        }
+        unsigned char *const dst = smem + (is_w ? BM * ROWB : 0) + lw * 1024;
+        auto issue = [&](int t, int stage) __attribute__((always_inline)) {
+            const int kt = kb + t * kstep;
+            const int kw = A_TERMS == 2 ? kt >> 1 : kt;                  // two-term A: the hi and the lo tile of every W k-tile
+            const int kk = A_TERMS == 2 && (kt & 1) && !is_w ? nk_w + kw : kw;
+#pragma unroll
+            for (int j = 0; j < PM; ++j)
+                if (j < n_ld)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (CS_LDS_AS void *)(dst + stage * STAGE + j * n_lw * 1024), 16, off[j], kk * ROWB, 0, 0);
+        };
+        __builtin_amdgcn_s_setprio(3);
+        for (int t = 0; t < min(NS, nk); ++t) issue(t, t);
+        if (is_w) wait_tiles<PW, NS - 1>(nk - 1);
+        else wait_tiles<PA, NS - 1>(nk - 1);
+        wg_barrier();                                                    // k-tile 0 is in LDS
+        int stage = 0;
+        for (int ki = 0; ki + 1 < nk; ++ki) {
+            const int rem = min(nk, ki + NS) - (ki + 2);                 // k-tiles asked for behind the next one
+            if (is_w) wait_tiles<PW, NS - 2>(rem);
+            else wait_tiles<PA, NS - 2>(rem);
+            wg_barrier();                                                // k-tile ki + 1 is in LDS, the stage of ki is free
+            if (ki + NS < nk) issue(ki + NS, stage);
+            stage = stage + 1 == NS ? 0 : stage + 1;
+        }
+        return;
+    }
+
+    const int wy = wave / WAVES_N, wx = wave % WAVES_N;
+    f32x4 acc16[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc16[i][j][e] = 0.f;
+    const int l16 = lane & 15, kq = lane >> 4, sw16 = (l16 >> 1) & 7;
+    int a_lane[2], b_lane[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int kv = ((4 * h + kq) ^ sw16) * 16;
+        a_lane[h] = (wy * WM + l16) * ROWB + kv;
+        b_lane[h] = (BM + wx * WN + l16) * ROWB + kv;
+    }
+    bf16x8 a16[4], b16[2][NI];
+    auto read_a = [&](const unsigned char *st, int s) __attribute__((always_inline)) {
+        a16[s & 3] = *reinterpret_cast<const bf16x8 *>(st + a_lane[s / MI] + (s % MI) * 16 * ROWB);
+    };
+    auto read_b = [&](const unsigned char *st, int h, int j) __attribute__((always_inline)) {
+        b16[h][j] = *reinterpret_cast<const bf16x8 *>(st + b_lane[h] + j * 16 * ROWB);
+    };
+    RopeVals rv;                                                         // (asked for early: behind the k loop their latency would show)
+    constexpr bool EARLY = EPI == EPI_ROPE && WM == 32;
+    if constexpr (EARLY) {
+        constexpr int LR = WN / 16, RP = 64 / LR;
+#pragma unroll
+        for (int p = 0; p < 32 / RP; ++p)
+            load_rope(rv, rope, p, (size_t)min(m0 + wy * WM + p * RP + lane / LR, M - 1) * 64 + rope_col<WN>(n0, wx, lane));
+    }
+    wg_barrier();
+#pragma unroll
+    for (int s = 0; s < 3; ++s) read_a(smem, s);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) read_b(smem, 0, j);
+    int stage = 0;
+    for (int ki = 0; ki < nk; ++ki) {
+        const bool more = ki + 1 < nk;                                   // uniform
+        stage = stage + 1 == NS ? 0 : stage + 1;
+        const unsigned char *cur = smem + (stage == 0 ? NS - 1 : stage - 1) * STAGE, *next = smem + stage * STAGE;
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (s == SB && more) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // this wavefront's last operands of the k-tile are in registers
+                wg_barrier();
+            }
+            const int i = s % MI, h = s / MI;
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                __builtin_amdgcn_sched_barrier(0);
+                acc16[i][j] = mma16<F16>(a16[s & 3], b16[h][j], acc16[i][j]);
+                __builtin_amdgcn_sched_barrier(0);
+                if (j == 0) {                                            // A fragment of slot s + 3
+                    if (s + 3 < SLOTS) read_a(cur, s + 3);
+                    else if (more) read_a(next, s + 3 - SLOTS);
+                }
+                if (j == 1) {
+                    constexpr int s0 = MI > 4 ? MI - 4 : 0, s1 = MI < SB ? MI : SB, nb = (NI + s1 - s0 - 1) / (s1 - s0);
+                    if (s >= s0 && s < s1) {                             // W fragments of the second k half
+#pragma unroll
+                        for (int q = 0; q < nb; ++q)
+                            if ((s - s0) * nb + q < NI) read_b(cur, 1, (s - s0) * nb + q);
+                    }
+                    constexpr int t0 = MI > SB ? MI : SB, nn = (NI + 1) / 2;
+                    if (s >= t0 && s < t0 + 2 && more) {                 // of the next k-tile's first
+#pragma unroll
+                        for (int q = 0; q < nn; ++q)
+                            if ((s - t0) * nn + q < NI) read_b(next, 0, (s - t0) * nn + q);
+                    }
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const int no_acc = 0;
+    gemm_epilogue<EPI, true, WM, WN, NW, NS * STAGE>(no_acc, acc16, smem, out_v, M, N, m0, n0, wy, wx, wave, lane, out_fmt, rope, EARLY ? &rv : nullptr);
 #endif
 }
 
@@ -612,6 +816,69 @@ static hipError_t launch_tile(const GemmTune &tune, const bf16 *A, const bf16 *W
     return launch_inst<BM, BN, WAVES_M, WAVES_N, BK, NS, EPI, 1>(tune, A, W, out, M, N, K, n_base, n_cols, out_fmt, s, rope, pf);
 }
 
+// Tiles of gemm_feed_kernel: rows, columns, and workgroups of one round (those of 72 KiB run two per CU).
+struct FeedTile { int bm, bn, cap; };
+constexpr FeedTile FEED_TILES[] = {{0, 0, 0}, {64, 64, 256}, {64, 128, 512}, {128, 128, 256}, {256, 128, 256}};
+constexpr int N_FEED = 4;
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NL, int NS, int EPI, int A_FMT>
+static hipError_t launch_feed_inst(const bf16 *A, const bf16 *W, void *out, int M, int N, int K, int n_base, int n_cols, int splits, int out_fmt,
+                                   hipStream_t s, const RopeArgs *rope) {
+    constexpr int smem = NS * (BM + BN) * 128;
+    static std::atomic<uint32_t> attr_done{0};
+    auto kern = gemm_feed_kernel<BM, BN, WAVES_M, WAVES_N, NL, NS, EPI, A_FMT>;
+    if (hipError_t e = set_dynamic_lds_once(attr_done, reinterpret_cast<const void *>(kern), smem); e != hipSuccess) return e;
+    const int tiles_m = (M + BM - 1) / BM, tiles_n = n_cols / BN, per = (tiles_m * tiles_n + 7) / 8;
+    // tile order as in launch_inst: what an XCD works on at one time forms a roughly square block
+    const int group_m = (int)std::lround(std::sqrt((double)std::min(per, 32 * (160 * 1024 / smem)) * BN / BM));
+    kern<<<dim3(8 * per, splits), 64 * (WAVES_M * WAVES_N + NL), smem, s>>>(A, W, out, M, N, K, tiles_m, tiles_n, n_base,
+                                                                            std::max(1, std::min(group_m, tiles_m)), out_fmt, rope ? *rope : RopeArgs{});
+    return hipGetLastError();
+}
+template <int EPI, int A_FMT>
+static hipError_t launch_feed_fmt(int feed, const bf16 *A, const bf16 *W, void *out, int M, int N, int K, int n_base, int n_cols, int splits, int out_fmt,
+                                  hipStream_t s, const RopeArgs *rope) {
+    switch (feed) {
+        case 1:
+            if constexpr (EPI != EPI_SWIGLU) return launch_feed_inst<64, 64, 2, 2, 2, 7, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+            break;                      // (a gate/up column pair needs 64-column wave tiles: feed_cost does not offer it)
+        case 2: return launch_feed_inst<64, 128, 2, 2, 2, 3, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+        case 3: return launch_feed_inst<128, 128, 4, 2, 4, 5, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+        case 4: return launch_feed_inst<256, 128, 4, 2, 4, 3, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+    }
+    return hipErrorInvalidValue;
+}
+// Columns n_base .. n_base + n_cols - 1 of the N columns.
+template <int EPI>
+static hipError_t launch_feed(int feed, const bf16 *A, const bf16 *W, void *out, int M, int N, int K, int n_base, int n_cols, int splits, int a_fmt, int out_fmt,
+                              hipStream_t s, const RopeArgs *rope = nullptr) {
+    return a_fmt == 2   ? launch_feed_fmt<EPI, 2>(feed, A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope)
+           : a_fmt == 3 ? launch_feed_fmt<EPI, 3>(feed, A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope)
+                        : launch_feed_fmt<EPI, 1>(feed, A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+}
+
+// Model of one round of feed tiles over M rows x n_cols columns, nk k-tiles of 64 in s slices, in us; 1e30 where there is no such round.
+// Fits of sweeps over 48 .. 2048 rows of the projections of d_model 1536 / d_ffn 8960 and 5120 / 27648, every launch with other weights
+// (from HBM: a wave of loads is then 1.1 us away, from the last-level cache 0.55): a fixed part (launch, first loads, epilogue), and
+// per k-tile a part that grows with u, the share of the CUs that work.  The workgroups of a tile and all its slices sit on one
+// XCD of 32 CUs, so an XCD's share counts: 36 tiles in 7 slices, five tiles to most XCDs, are 35 workgroups there (8960 x 1536,
+// 1536 rows: 69 us with 7 slices of 256 x 256 tiles, 47 with 6).
+static double feed_cost(int f, int M, int n_cols, int nk, int s, bool swiglu) {
+    const FeedTile &t = FEED_TILES[f];
+    if (n_cols % t.bn != 0 || (swiglu && t.bn < 128)) return 1e30;
+    const long per_xcd = ((long)((M + t.bm - 1) / t.bm) * (n_cols / t.bn) + 7) / 8 * s;
+    if (per_xcd > t.cap / 8) return 1e30;
+    const double u = per_xcd / 32.0;
+    const double c = f == 1 ? 0.20 + 0.09 * u : f == 2 ? (u <= 1 ? 0.44 + 0.06 * u : 0.42 + 0.20 * u) : f == 3 ? 0.58 + 0.10 * u : 0.80 + 0.12 * u;
+    return (f == 4 ? 7.5 : 4.4) + (nk + s - 1) / s * c;
+}
+static int best_feed(int M, int n_cols, int nk, bool swiglu, double *cost) {
+    int best = 0;
+    for (int f = 1; f <= N_FEED; ++f)
+        if (const double c = feed_cost(f, M, n_cols, nk, 1, swiglu); c < *cost) { *cost = c; best = f; }
+    return best;
+}
+
 // Tile ids: 1 = 128x128 / 4 waves, 4 = 256x256 / 8 waves, 7 = 192x96 / 6 waves (2 x 3, wave tile 96 x 32; for
 // N % 96 == 0 and no SwiGLU); all with 64-element k-tiles in 2 stages.  Measured on the draft-model shapes: 4 is the
 // fastest for the wide gate/up projection, 1 or 7 for the others.
@@ -625,6 +892,13 @@ static bool prefer_256_tiles(int M, int N) {
     double c128 = (double)(t128 / 512) * 1.1 + (rem == 0 ? 0.0 : rem <= 256 ? 0.73 : 0.73 + (double)(rem - 256) / 256.0 * 0.37);
     double c256 = (double)((t256 + 255) / 256) * 1.4;
     return c256 < c128;
+}
+
+// 128 x 128 tiles of gemm_bf16_kernel, two per CU, in s slices, in the terms of feed_cost.
+static double cost_128(int M, int n_cols, int nk, int s) {
+    const long w = (long)((M + 127) / 128) * (n_cols / 128) * s;
+    const double u = w / 256.0;
+    return 12.0 + (nk + s - 1) / s * (u <= 1 ? 0.35 + 0.28 * u : u <= 2 ? 0.5 + 0.25 * u : (w + 511) / 512 * 1.0);
 }
 
 template <int EPI>
@@ -658,9 +932,13 @@ static hipError_t launch_epi(const GemmTune &tune, const bf16 *A, const bf16 *W,
             hipError_t e = launch_tile<256, 256, 2, 4, 64, 5, EPI>(tune, A, W, out, M, N, K, 0, n1 * 256, a_terms, out_terms, s, nullptr, pf);
             if (e != hipSuccess) return e;
         }
-        if (n1 < tn)
-            return launch_tile<128, 128, 2, 2, 64, 2, EPI>(tune, A, W, out, M, N, K, n1 * 256, N - n1 * 256, a_terms,
-                                                           out_terms, s);
+        if (n1 < tn) {
+            const int n_tail = N - n1 * 256, nk = K * (a_terms == 2 ? 2 : 1) / 64;
+            double c = cost_128(M, n_tail, nk, 1);
+            if (const int f = best_feed(M, n_tail, nk, EPI == EPI_SWIGLU, &c))
+                return launch_feed<EPI>(f, A, W, out, M, N, K, n1 * 256, n_tail, 1, a_terms, out_terms, s);
+            return launch_tile<128, 128, 2, 2, 64, 2, EPI>(tune, A, W, out, M, N, K, n1 * 256, n_tail, a_terms, out_terms, s);
+        }
         return hipSuccess;
     }
     if (tile == 4 && N % 256 != 0) tile = 1;
@@ -687,7 +965,7 @@ static hipError_t launch_epi(const GemmTune &tune, const bf16 *A, const bf16 *W,
 // (3072 x 1536 x 8960: 97 us with 3 slices against 106 us for 256 tiles of 192 x 96, and the reduction can also
 // normalise the rows for the next GEMM).  From 256 k-tiles on two slices pay as well (1536 x 5120 x 27648).
 // *big_tile says which case applies.
-int gemm_splitk_factor(const GemmTune &tune, int M, int N, int K_total, bool *big_tile) {
+static int general_splitk_factor(const GemmTune &tune, int M, int N, int K_total, bool *big_tile) {
     if (big_tile) *big_tile = false;
     if (N % 128 != 0) return 1;
     int tiles = ((M + 127) / 128) * (N / 128), nk = K_total / 64;
@@ -706,7 +984,7 @@ int gemm_splitk_factor(const GemmTune &tune, int M, int N, int K_total, bool *bi
         // d_ffn 27648 over 480 rows: 38.9 ms per pass against 45.6 ms with 128 x 128 tiles; 288 rows: equal; 192 rows:
         // 28.7 against 24.6 ms, hence the row bound).
         int t256 = ((M + 255) / 256) * (N / 256);
-        int s = std::min(std::min(256 / t256, nk / 4), 64);
+        int s = std::min(std::min(32 / ((t256 + 7) / 8), nk / 4), 64);   // (32 CUs of an XCD, see feed_cost)
         if (s >= 2) {
             *big_tile = true;
             return s;
@@ -717,16 +995,55 @@ int gemm_splitk_factor(const GemmTune &tune, int M, int N, int K_total, bool *bi
     int s = std::min(want, nk / ((M <= 32 && tune.short_tile) ? 2 : 4));
     return std::max(1, std::min(s, 64));
 }
+
+// Tile and k slices of a projection: what the two functions above say, or one round of gemm_feed_kernel tiles where the
+// model below has that faster.  Never more slices than above, so that no caller needs more scratch; a long k range over an output
+// that 128 x 128 tiles cover stays as above.
+struct GemmPlan { int feed = 0, splits = 1; bool big = false; };   // feed: index into FEED_TILES, 0 = gemm_bf16_kernel
+// Beyond feed_cost: a reduction of s planes is 3.5 us + their bytes at 4.5 TB/s, written before at 6 TB/s; it normalises the rows on the way
+// where a norm follows, which is a kernel of 4.2 us + 6 bytes per element otherwise.  Whole layer before : after, contexts of 2048, us:
+// width 1536: 192 rows 117 : 95, 384 135 : 110, 512 157 : 126, 768 176 : 151, 1024 198 : 176, 1536 268 : 234, 2304 310 : 302; width 5120:
+// 96 rows 283 : 275, 192 368 : 342, 256 397 : 357, 384 532 : 526, 1200 1237 : 1199, 1536 1417 : 1370.
+static GemmPlan gemm_plan(const GemmTune &tune, int M, int N, int K_total, bool swiglu, bool norm_after, bool can_split) {
+    GemmPlan p;
+    if (tune.tile != 0) return p;
+    if (can_split) p.splits = general_splitk_factor(tune, M, N, K_total, &p.big);
+    if (tune.splitk > 0 || M <= 32 || N % 128 != 0) return p;          // (at most 32 rows: tiles of 32 rows)
+    const int nk = K_total / 64, s_max = p.splits;
+    const double mn = (double)M * N;
+    auto finish = [&](int s) { return s > 1 ? 3.5 + s * mn * 4 * (1 / 4.5e6 + 1 / 6e6) : mn * 6 / 6e6 + (norm_after ? 4.2 + mn * 6 / 5e6 : 0.0); };
+    auto slice = [&](int s) { return (nk + s - 1) / s; };
+    const long t128 = (long)((M + 127) / 128) * (N / 128), t256 = (long)((M + 255) / 256) * (N / 256);
+    const long t192 = N % 96 == 0 && !swiglu && t128 > 256 && t128 <= 384 ? (long)((M + 191) / 192) * (N / 96) : 257;
+    if (p.big && t128 >= 256) return p;
+    double best;
+    if (p.big) best = 5.5 + slice(s_max) * 1.5;
+    else if (s_max == 1 && prefer_256_tiles(M, N)) best = 2.5 + (t256 + 255) / 256 * (3.0 + nk * 1.5);
+    else if (s_max == 1 && t192 <= 256) best = 4.5 + nk * 0.83;
+    else best = cost_128(M, N, nk, s_max);
+    best += finish(s_max);
+    for (int f = 1; f <= N_FEED; ++f)
+        for (int s = 1; s <= s_max && (s == 1 || nk / s >= 4); ++s)
+            if (const double t = feed_cost(f, M, N, nk, s, swiglu) + finish(s); t < best) { best = t; p.feed = f; p.splits = s; p.big = false; }
+    return p;
+}
+int gemm_splitk_factor(const GemmTune &tune, int M, int N, int K_total) { return gemm_plan(tune, M, N, K_total, false, true, true).splits; }
+// Scratch of a split product: the largest over what may follow it.
 size_t gemm_splitk_bytes(const GemmTune &tune, int M, int N, int K_total) {
     bool big;
-    int s = gemm_splitk_factor(tune, M, N, K_total, &big);
+    int s = tune.tile != 0 ? general_splitk_factor(tune, M, N, K_total, &big) : 1;
+    for (int v = 0; v < 4; ++v) s = std::max(s, gemm_plan(tune, M, N, K_total, v & 1, v & 2, true).splits);
     return s > 1 ? (size_t)s * M * N * 4 : 0;
 }
-// Largest gemm_splitk_bytes over all row counts up to max_M (the factor changes with the number of row tiles).
+// An upper bound of gemm_splitk_bytes over all row counts up to max_M: the general factor bounds every plan's and changes with the
+// number of row tiles.
 size_t gemm_splitk_max_bytes(const GemmTune &tune, int max_M, int N, int K_total) {
     size_t best = 0;
-    for (int tm = 1; tm <= (max_M + 127) / 128; ++tm)
-        best = std::max(best, gemm_splitk_bytes(tune, std::min(tm * 128, max_M), N, K_total));
+    for (int tm = 1; tm <= (max_M + 127) / 128; ++tm) {
+        bool big;
+        const int M = std::min(tm * 128, max_M), s = general_splitk_factor(tune, M, N, K_total, &big);
+        if (s > 1) best = std::max(best, (size_t)s * M * N * 4);
+    }
     return best;
 }
 
@@ -928,10 +1245,18 @@ static hipError_t launch_splitk_short(const GemmTune &tune, const bf16 *A, const
     return hipGetLastError();
 }
 
-// The partial products of the k slices, one [M, N] fp32 plane per slice; big_tile: 256 x 256 tiles, else 128 x 128.
+// The plan for the scratch there is.
+static GemmPlan plan_with(const GemmTune &tune, int M, int N, int K_total, bool swiglu, bool norm_after, const float *ws, size_t ws_bytes) {
+    const GemmPlan p = gemm_plan(tune, M, N, K_total, swiglu, norm_after, ws != nullptr);
+    return p.splits > 1 && (size_t)p.splits * M * N * 4 > ws_bytes ? gemm_plan(tune, M, N, K_total, swiglu, norm_after, false) : p;
+}
+
+// The partial products of the k slices, one [M, N] fp32 plane per slice; big: 256 x 256 tiles, else 128 x 128.
 static hipError_t launch_splitk_main(const GemmTune &tune, const bf16 *A, const bf16 *W, float *part, int M, int N, int K,
-                                     int a_terms, int splits, bool big_tile, hipStream_t s) {
-    if (big_tile)
+                                     int a_terms, const GemmPlan &p, hipStream_t s) {
+    const int splits = p.splits;
+    if (p.feed) return launch_feed<EPI_STORE_F32>(p.feed, A, W, part, M, N, K, 0, N, splits, a_terms, 1, s);
+    if (p.big)
         return a_terms == 2   ? launch_splitk_tiles<2, 256, 4>(tune, A, W, part, M, N, K, splits, s)
                : a_terms == 3 ? launch_splitk_tiles<3, 256, 4>(tune, A, W, part, M, N, K, splits, s)
                               : launch_splitk_tiles<1, 256, 4>(tune, A, W, part, M, N, K, splits, s);
@@ -948,16 +1273,17 @@ hipError_t launch_gemm_bf16(const GemmTune &tune, const bf16 *A, const bf16 *W, 
                             int a_terms, int out_terms, float *splitk_ws, size_t splitk_ws_bytes, hipStream_t s,
                             const PrefetchArgs *pf, const NormAfter *norm, bool *norm_done) {
     if (norm_done) *norm_done = false;
-    int k_total = K * (a_terms == 2 ? 2 : 1);
-    bool big = false;
-    int splits = tune.tile == 0 ? gemm_splitk_factor(tune, M, N, k_total, &big) : 1;
-    if (splits > 1 && splitk_ws && gemm_splitk_bytes(tune, M, N, k_total) <= splitk_ws_bytes) {
-        hipError_t e = launch_splitk_main(tune, A, W, splitk_ws, M, N, K, a_terms, splits, big, s);
+    const int k_total = K * (a_terms == 2 ? 2 : 1);
+    const bool norm_here = epi == EPI_RESID_F32 && norm && norm->g && norm->h && N % 4 == 0 && N <= 6144 &&
+                           ((((uintptr_t)norm->g | (uintptr_t)norm->h) & 7) == 0);
+    const GemmPlan p = plan_with(tune, M, N, k_total, epi == EPI_SWIGLU, norm_here, splitk_ws, splitk_ws_bytes);
+    if (p.splits > 1) {
+        hipError_t e = launch_splitk_main(tune, A, W, splitk_ws, M, N, K, a_terms, p, s);
         if (e != hipSuccess) return e;
+        const int splits = p.splits;
         int n_out = epi == EPI_SWIGLU ? N / 2 : N;
         dim3 grid((n_out / 4 + 255) / 256, M);
-        if (epi == EPI_RESID_F32 && norm && norm->g && norm->h && N % 4 == 0 && N <= 6144 &&
-            ((((uintptr_t)norm->g | (uintptr_t)norm->h) & 7) == 0)) {
+        if (norm_here) {
             splitk_reduce_resid_norm_kernel<<<M, 256, 0, s>>>(splitk_ws, splits, M, N, reinterpret_cast<float *>(out),
                                                               reinterpret_cast<const bf16 *>(norm->g),
                                                               reinterpret_cast<bf16 *>(norm->h), norm->eps, norm->terms);
@@ -969,6 +1295,11 @@ hipError_t launch_gemm_bf16(const GemmTune &tune, const bf16 *A, const bf16 *W, 
         else splitk_reduce_kernel<EPI_SWIGLU><<<grid, 256, 0, s>>>(splitk_ws, splits, M, N, out, out_terms);
         return hipGetLastError();
     }
+    if (p.feed) {
+        if (epi == EPI_STORE_F32) return launch_feed<EPI_STORE_F32>(p.feed, A, W, out, M, N, K, 0, N, 1, a_terms, out_terms, s);
+        if (epi == EPI_RESID_F32) return launch_feed<EPI_RESID_F32>(p.feed, A, W, out, M, N, K, 0, N, 1, a_terms, out_terms, s);
+        return launch_feed<EPI_SWIGLU>(p.feed, A, W, out, M, N, K, 0, N, 1, a_terms, out_terms, s);
+    }
     if (epi == EPI_STORE_F32) return launch_epi<EPI_STORE_F32>(tune, A, W, out, M, N, K, a_terms, out_terms, s);
     if (epi == EPI_RESID_F32) return launch_epi<EPI_RESID_F32>(tune, A, W, out, M, N, K, a_terms, out_terms, s);
     return launch_epi<EPI_SWIGLU>(tune, A, W, out, M, N, K, a_terms, out_terms, s, pf);
@@ -978,16 +1309,15 @@ hipError_t launch_gemm_bf16(const GemmTune &tune, const bf16 *A, const bf16 *W, 
 // have 64-column wave tiles.
 hipError_t launch_gemm_bf16_rope(const GemmTune &tune, const bf16 *A, const bf16 *W_perm, int M, int N, int K, int a_terms,
                                  const RopeArgs &rope, float *splitk_ws, size_t splitk_ws_bytes, hipStream_t s) {
-    int k_total = K * (a_terms == 2 ? 2 : 1);
-    bool big = false;
-    int splits = tune.tile == 0 ? gemm_splitk_factor(tune, M, N, k_total, &big) : 1;
-    if (splits > 1 && splitk_ws && gemm_splitk_bytes(tune, M, N, k_total) <= splitk_ws_bytes) {
-        hipError_t e = launch_splitk_main(tune, A, W_perm, splitk_ws, M, N, K, a_terms, splits, big, s);
+    const GemmPlan p = plan_with(tune, M, N, K * (a_terms == 2 ? 2 : 1), false, false, splitk_ws, splitk_ws_bytes);
+    if (p.splits > 1) {
+        hipError_t e = launch_splitk_main(tune, A, W_perm, splitk_ws, M, N, K, a_terms, p, s);
         if (e != hipSuccess) return e;
         dim3 grid(((N / 128) * 16 + 255) / 256, M);
-        splitk_reduce_rope_kernel<<<grid, 256, 0, s>>>(splitk_ws, splits, M, N, rope);
+        splitk_reduce_rope_kernel<<<grid, 256, 0, s>>>(splitk_ws, p.splits, M, N, rope);
         return hipGetLastError();
     }
+    if (p.feed) return launch_feed<EPI_ROPE>(p.feed, A, W_perm, nullptr, M, N, K, 0, N, 1, a_terms, 1, s, &rope);
     if (prefer_256_tiles(M, N)) {
         // as in launch_epi: a last round of 256 x 256 tiles that would be less than half full goes to a second launch with
         // 128 x 128 tiles (18606 rows x 2048 columns: 584 tiles = 2 rounds + 72 tiles)
@@ -1001,7 +1331,11 @@ hipError_t launch_gemm_bf16_rope(const GemmTune &tune, const bf16 *A, const bf16
             hipError_t e = launch_tile<256, 256, 2, 4, 64, 5, EPI_ROPE>(tune, A, W_perm, nullptr, M, N, K, 0, n1 * 256, a_terms, 1, s, &rope);
             if (e != hipSuccess || n1 == tn) return e;
         }
-        return launch_tile<128, 128, 2, 2, 64, 2, EPI_ROPE>(tune, A, W_perm, nullptr, M, N, K, n1 * 256, N - n1 * 256, a_terms, 1, s, &rope);
+        const int n_tail = N - n1 * 256, nk = K * (a_terms == 2 ? 2 : 1) / 64;
+        double c = cost_128(M, n_tail, nk, 1);
+        if (const int f = best_feed(M, n_tail, nk, false, &c))
+            return launch_feed<EPI_ROPE>(f, A, W_perm, nullptr, M, N, K, n1 * 256, n_tail, 1, a_terms, 1, s, &rope);
+        return launch_tile<128, 128, 2, 2, 64, 2, EPI_ROPE>(tune, A, W_perm, nullptr, M, N, K, n1 * 256, n_tail, a_terms, 1, s, &rope);
     }
     return launch_tile<128, 128, 2, 2, 64, 2, EPI_ROPE>(tune, A, W_perm, nullptr, M, N, K, 0, N, a_terms, 1, s, &rope);
 }

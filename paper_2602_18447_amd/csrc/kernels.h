@@ -180,9 +180,9 @@ hipError_t launch_gemm_bf16(const GemmTune &tune, const bf16 *A, const bf16 *W, 
                             const PrefetchArgs *pf = nullptr, const NormAfter *norm = nullptr, bool *norm_done = nullptr);
 hipError_t launch_gemm_bf16_rope(const GemmTune &tune, const bf16 *A, const bf16 *W_perm, int M, int N, int K, int a_terms,
                                  const RopeArgs &rope, float *splitk_ws, size_t splitk_ws_bytes, hipStream_t s);
-int gemm_splitk_factor(const GemmTune &tune, int M, int N, int K_total, bool *big_tile = nullptr);   // *big_tile: slices of 256 x 256 tiles
+int gemm_splitk_factor(const GemmTune &tune, int M, int N, int K_total);   // of a residual projection with a norm behind it
 size_t gemm_splitk_bytes(const GemmTune &tune, int M, int N, int K_total);
-size_t gemm_splitk_max_bytes(const GemmTune &tune, int max_M, int N, int K_total);   // largest gemm_splitk_bytes over M <= max_M
+size_t gemm_splitk_max_bytes(const GemmTune &tune, int max_M, int N, int K_total);   // at least gemm_splitk_bytes for every M <= max_M
 
 // ---- attention ----
 struct AttnArgs {

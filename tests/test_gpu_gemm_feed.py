@@ -1,0 +1,83 @@
+"""GEMMs of one round of tiles with loading wavefronts of their own: every epilogue and operand format at the edges of the
+tiles, k ranges shorter than the ring of stages, uneven k slices, against the fp64 product."""
+import numpy as np
+import pytest
+import torch
+
+import confspec_workloads as W
+from oracle import confspec_oracle as O
+from paper_2602_18447_amd import binding as cb
+from tests.test_gpu_ops import _ctx, _rand, f64
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _operands(M, N, K, fmt):
+    full = _rand((M, K), torch.float32, 7 * M + K)
+    Wt = _rand((N, K), torch.float32, 11 * N + K, 0.05).to(torch.float16 if fmt == 3 else torch.bfloat16)
+    if fmt == 2:
+        hi = full.to(torch.bfloat16)
+        lo = (full - hi.float()).to(torch.bfloat16)
+        return torch.cat([hi, lo], dim=1).contiguous(), f64(hi) + f64(lo), Wt
+    A = full.to(torch.float16 if fmt == 3 else torch.bfloat16)
+    return A, f64(A), Wt
+
+
+# 64 x 128 tiles (few rows), 128 x 128 (about 2000 x 2048), 256 x 128 (2600 x 2048, 200 x 17920); rows at and next to the tiles'
+# edges, one and two k-tiles (fewer than the stages), and enough of them that the ring wraps
+@pytest.mark.parametrize("fmt", [1, 2, 3])
+@pytest.mark.parametrize("M,N,K", [(33, 128, 64), (64, 256, 128), (65, 384, 192), (129, 512, 832), (255, 2048, 320), (1290, 2048, 128),
+                                   (2040, 2048, 448), (1921, 2048, 192), (2600, 2048, 576), (257, 4096, 1024), (200, 17920, 448)])
+def test_one_round_tiles(M, N, K, fmt):
+    print(f"feed M={M} N={N} K={K} fmt={fmt}", flush=True)
+    ctx, _ = _ctx("bf16")
+    A, a64, Wt = _operands(M, N, K, fmt)
+    ref = a64 @ f64(Wt).T
+    scale = max(np.abs(ref).max(), 4.0)
+    x0 = _rand((M + 2, N), torch.float32, 5)                              # two guard rows
+    nbytes = cb.confspec_op_gemm_scratch_bytes(ctx, M, N, K, fmt)
+    for scratch in [None] + ([torch.empty(nbytes, dtype=torch.uint8, device=DEV)] if nbytes else []):
+        x, st = x0.clone(), torch.full_like(x0, 7.0)
+        cb.confspec_op_gemm(ctx, A, Wt, x, M, N, K, cb.EPI_RESID_F32, fmt, 1, scratch)
+        cb.confspec_op_gemm(ctx, A, Wt, st, M, N, K, cb.EPI_STORE_F32, fmt, 1, scratch)
+        F = N // 2
+        act = torch.zeros((M + 1, (2 if fmt == 2 else 1) * F), dtype=torch.float16 if fmt == 3 else torch.bfloat16, device=DEV)
+        cb.confspec_op_gemm(ctx, A, Wt, act, M, N, K, cb.EPI_SWIGLU, fmt, fmt, scratch)
+        torch.cuda.synchronize()
+        assert np.abs(f64(x[:M]) - ref - f64(x0[:M])).max() <= 2e-5 * scale and torch.equal(x[M:], x0[M:])
+        assert np.abs(f64(st[:M]) - ref).max() <= 2e-5 * scale and torch.all(st[M:] == 7.0)
+        r3 = ref.reshape(M, N // 64, 2, 32)
+        want = (O.silu(r3[:, :, 0, :]) * r3[:, :, 1, :]).reshape(M, F)
+        got = f64(act[:M, :F]) + (f64(act[:M, F:]) if fmt == 2 else 0.0)
+        # one rounding to 8 (11, 16) mantissa bits, and the fp32 product's error through the activation
+        assert np.all(np.abs(got - want) <= 2.0 ** {1: -8, 2: -15, 3: -11}[fmt] * np.abs(want) + 1e-4 * np.abs(want).max())
+        assert torch.all(act[M:] == 0)
+    cb.confspec_destroy(ctx)
+
+
+@pytest.mark.parametrize("fmt", [1, 2, 3])
+@pytest.mark.parametrize("lens", [(40, 33, 1), (130, 127), (1500, 541), (2600,)])   # 64 x 128 tiles (whole, in slices), 128 x 128, 256 x 128
+def test_rotating_projection(lens, fmt):
+    """The QKV projection with the rotation in its epilogue against the fp64 product and rotation."""
+    print(f"feed rope {lens} fmt={fmt}", flush=True)
+    Hq, Hkv, d, T = 12, 2, 512, sum(lens)
+    heads = Hq + 2 * Hkv
+    wl = W.tiny_workload("feed", 3, dtype="bf16", n_layers=1, d_model=d, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=128, d_ffn=256,
+                         vocab=512, block_size=16, prefix_lens=(5, 1000, 77)[:len(lens)], suffix_lens=lens)
+    ctx, base = _ctx("bf16", d_model=d, n_q_heads=Hq, n_kv_heads=Hkv)
+    b = W.make_batch(wl, DEV)
+    bs, keep = cb.make_batch(b.suffix_ids, b.cu_suffix, b.prefix_lens, b.h_cu_suffix, b.h_prefix_lens)
+    A, a64, Wt = _operands(T, heads * 128, d, fmt)
+    order = torch.as_tensor(np.arange(heads * 128).reshape(heads, 4, 32)[:, [0, 2, 1, 3]].reshape(-1), device=DEV)
+    out = [torch.zeros((T + 1, h, 128), dtype=torch.bfloat16, device=DEV) for h in (Hq, Hkv, Hkv)]
+    ws = torch.empty(cb.confspec_workspace_bytes(ctx, T, wl.B, 0), dtype=torch.uint8, device=DEV)
+    cb.confspec_op_qkv_rope(ctx, bs, 2048, A, fmt, Wt[order].contiguous(), *out, ws)
+    torch.cuda.synchronize()
+    a = (a64 @ f64(Wt).T).reshape(T, heads, 128)
+    pos = np.concatenate([L + np.arange(S) for L, S in zip(wl.prefix_lens, wl.suffix_lens)])
+    refs = (O.rope(a[:, :Hq], pos, base["rope_theta"]), O.rope(a[:, Hq:Hq + Hkv], pos, base["rope_theta"]), a[:, Hq + Hkv:])
+    for got, ref in zip(out, refs):      # one rounding to 8 mantissa bits and the fp32 sum
+        assert np.all(np.abs(f64(got[:T]) - ref) <= 2.0 ** -8 * np.abs(ref) + 2e-5 * np.abs(ref).max())
+        assert torch.all(got[T] == 0)
+    cb.confspec_destroy(ctx)
