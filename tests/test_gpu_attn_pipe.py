@@ -1,0 +1,64 @@
+"""The pipelined attention loop where scores leave the range its exponent reference covers: rows whose running maximum starts far below
+zero, rises past the range chunk by chunk, or stays below it, whole items and pieces, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import confspec_workloads as W
+from oracle import confspec_oracle as O
+from paper_2602_18447_amd import binding as cb
+from tests.test_gpu_ops import _batch_structs, _ctx, _rand, f64
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# score of a key (log2 units, before noise of a few units) by 64-key chunk, for a query along +1; queries go along +1, -1 and 0.3
+PROFILES = {
+    "rising": (-400, -300, -190, -120, -60, 0, 30, 63, 66, 129, 300),
+    "falling": (300, 129, 66, 0, -70, -150, -400),
+    "low": (-70, -80, -65, -300),
+    "flat": (0, 3, -2, 1),
+    "edge": (64, 64, 65, -64, -65, 128, 129),
+}
+
+
+@pytest.mark.parametrize("split", [1, 3])
+@pytest.mark.parametrize("name", sorted(PROFILES))
+def test_scores_past_the_reference_range(name, split):
+    print(f"attention reference range {name} split={split}", flush=True)
+    prof = PROFILES[name]
+    L, hq, hkv, hd, S = 64 * len(prof) - 5, 12, 2, 128, (40, 1, 130)
+    wl = W.tiny_workload("range", 91, dtype="bf16", n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, d_model=256,
+                         prefix_lens=(L, L, L), suffix_lens=S, block_size=16)
+    ctx, _ = _ctx("bf16", n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd)
+    cb.confspec_tune(ctx, "attn_kernel", 2)
+    cb.confspec_tune(ctx, "attn_min_chunks", 1)
+    cb.confspec_tune(ctx, "attn_split", split)
+    batch, T = W.make_batch(wl, DEV), wl.T
+    kv = W.make_seeded_kv(wl, batch, DEV)
+    u = torch.zeros(hd, device=DEV)
+    u[::2] = 1.0                                                      # 64 elements
+    per_unit = 64 * 8.0 / np.sqrt(hd) * np.log2(np.e)                 # score of a key u / 8 .. for a query 8 u
+    for b in range(wl.B):
+        for p in range((L + 15) // 16):
+            kv.k_pages[0, int(batch.block_table[b, p])] += (prof[min(p // 4, len(prof) - 1)] / per_unit * u).to(torch.bfloat16)
+    along = torch.tensor([8.0, -8.0, 2.4], device=DEV)[torch.arange(hq, device=DEV) % 3]
+    q = (_rand((T, hq, hd), torch.float32, 92, 0.3) + along[None, :, None] * u).to(torch.bfloat16)
+    ks = (_rand((T, hkv, hd), torch.float32, 93, 0.5) + prof[-1] / per_unit * u).to(torch.bfloat16)
+    vs = _rand((T, hkv, hd), torch.bfloat16, 94, 0.5)
+    out = torch.zeros((T, hq * hd), dtype=torch.bfloat16, device=DEV)
+    kvs = cb.make_kv(kv.k_pages, kv.v_pages, batch.block_table, batch.n_blocks, 16, batch.max_blocks_per_seq)
+    bs, keep = _batch_structs(wl, batch)
+    ws = torch.empty(cb.confspec_workspace_bytes(ctx, T, wl.B), dtype=torch.uint8, device=DEV)
+    cb.confspec_op_attention(ctx, kvs, bs, 0, q, ks, vs, out, ws)
+    torch.cuda.synchronize()
+    view, got = W.OracleKVView(kv, batch), f64(out).reshape(T, hq, hd)
+    for b in range(wl.B):
+        ids = batch.block_table[b, :(L + 15) // 16].cpu().numpy()
+        t0, t1 = int(batch.h_cu_suffix[b]), int(batch.h_cu_suffix[b + 1])
+        k_all = np.concatenate([O.gather_prefix(view.k_blocks(0, ids), L), f64(ks)[t0:t1]])
+        v_all = np.concatenate([O.gather_prefix(view.v_blocks(0, ids), L), f64(vs)[t0:t1]])
+        ref = O.attention(f64(q)[t0:t1], k_all, v_all, L)
+        # probabilities and the result rounded to 8 mantissa bits; fp32 scores of some hundred: 2^-15 relative in a probability
+        assert np.abs(got[t0:t1] - ref).max() <= (3 * 2.0 ** -9 + 2.0 ** -13) * np.abs(v_all).max(), (name, b)
+    cb.confspec_destroy(ctx)
