@@ -454,7 +454,7 @@ int run_attention(confspec_ctx *ctx, const cs::AttnArgs &a, char *ws, const WsLa
         if (pc.n_part_slots > 0) {
             HIP_TRY(ctx->timer.mark(CONFSPEC_PHASE_ATTN_MERGE, s));
             HIP_TRY(cs::launch_attn_merge(a, (const cs::AttnTile *)(ws + tiles), (const int32_t *)(ws + counts),
-                                          (int)pc.n_tiles, (const float *)(ws + L.part_o), (const float *)(ws + L.part_ml), s));
+                                          (int)pc.n_tiles, (int)pc.n_items, (const float *)(ws + L.part_o), (const float *)(ws + L.part_ml), s));
         }
     }
     return CONFSPEC_OK;

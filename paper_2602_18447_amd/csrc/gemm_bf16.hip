@@ -1155,28 +1155,36 @@ __global__ void splitk_reduce_rope_kernel(const float *__restrict__ part, int sp
 // Split-K slices of a residual projection summed in their fixed order, added to the residual stream, and the RMSNorm
 // of the updated row (the operand of the next projection) taken in the same kernel: one workgroup per row keeps the
 // row in registers between the two steps.  N <= 6144, N % 4 == 0.  Output formats as in the RMSNorm kernel:
-// terms 1 bf16, 2 hi | lo, 3 fp16.
-__global__ __launch_bounds__(256) void splitk_reduce_resid_norm_kernel(const float *__restrict__ part, int splits, int M, int N,
+// terms 1 bf16, 2 hi | lo, 3 fp16.  Many rows stream their planes with 256 threads each; few rows are bound by the chain of loads, which
+// is one long where every thread has one vector or two.
+template <int NT>
+__global__ __launch_bounds__(NT) void splitk_reduce_resid_norm_kernel(const float *__restrict__ part, int splits, int M, int N,
                                                                         float *__restrict__ x, const bf16 *__restrict__ g,
                                                                         bf16 *__restrict__ h, float eps, int terms) {
-    constexpr int NV = 6;
-    __shared__ float red[4];
+    constexpr int NV = 6144 / 4 / NT + (6144 / 4 % NT != 0);
+    __shared__ float red[NT / 64];
     int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     size_t plane = (size_t)M * N;
     const int nv = N >> 2;
-    f32x4 v[NV];
+    f32x4 v[NV], xv[NV];
+    uint2 gv[NV];
     float ss = 0.f;
 #pragma unroll
+    for (int i = 0; i < NV; ++i) {                           // the residual row and the gains, asked for with the first planes
+        const int j = min(tid + NT * i, nv - 1);
+        xv[i] = *reinterpret_cast<const f32x4 *>(x + (size_t)r * N + 4 * j);
+        gv[i] = *reinterpret_cast<const uint2 *>(g + 4 * j);
+    }
+#pragma unroll
     for (int i = 0; i < NV; ++i) {
-        int j = tid + 256 * i;
+        int j = tid + NT * i;
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
         if (j < nv) {
             const float *p0 = part + (size_t)r * N + 4 * j;
 #pragma unroll 8
             for (int sp = 0; sp < splits; ++sp) acc += *reinterpret_cast<const f32x4 *>(p0 + sp * plane);
-            f32x4 *dst = reinterpret_cast<f32x4 *>(x + (size_t)r * N + 4 * j);
-            acc += *dst;
-            *dst = acc;
+            acc += xv[i];
+            *reinterpret_cast<f32x4 *>(x + (size_t)r * N + 4 * j) = acc;
         }
         v[i] = acc;
         ss += acc[0] * acc[0] + acc[1] * acc[1] + acc[2] * acc[2] + acc[3] * acc[3];
@@ -1185,20 +1193,22 @@ __global__ __launch_bounds__(256) void splitk_reduce_resid_norm_kernel(const flo
     for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off);
     if (lane == 0) red[wave] = ss;
     __syncthreads();
-    float rinv = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)N + eps);
+    float sq = 0.f;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) sq += red[w];
+    float rinv = 1.0f / sqrtf(sq / (float)N + eps);
     bf16 *o = h + (size_t)r * N * (terms == 2 ? 2 : 1);
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        int j = tid + 256 * i;
+        int j = tid + NT * i;
         if (j >= nv) continue;
         int c = j << 2;
-        uint2 gp = *reinterpret_cast<const uint2 *>(g + c);
-        float gv[4] = {__uint_as_float(gp.x << 16), __uint_as_float(gp.x & 0xffff0000u), __uint_as_float(gp.y << 16),
-                       __uint_as_float(gp.y & 0xffff0000u)};
+        const float gf[4] = {__uint_as_float(gv[i].x << 16), __uint_as_float(gv[i].x & 0xffff0000u), __uint_as_float(gv[i].y << 16),
+                             __uint_as_float(gv[i].y & 0xffff0000u)};
         unsigned hi[4], lo[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            float y = v[i][q] * rinv * gv[q];
+            float y = v[i][q] * rinv * gf[q];
             if (terms == 3) {
                 hi[q] = __half_as_ushort(to_half_sat(y));
                 lo[q] = 0;
@@ -1288,9 +1298,14 @@ hipError_t launch_gemm_bf16(const GemmTune &tune, const bf16 *A, const bf16 *W, 
         int n_out = epi == EPI_SWIGLU ? N / 2 : N;
         dim3 grid((n_out / 4 + 255) / 256, M);
         if (norm_here) {
-            splitk_reduce_resid_norm_kernel<<<M, 256, 0, s>>>(splitk_ws, splits, M, N, reinterpret_cast<float *>(out),
-                                                              reinterpret_cast<const bf16 *>(norm->g),
-                                                              reinterpret_cast<bf16 *>(norm->h), norm->eps, norm->terms);
+            auto reduce = [&](auto kern, int threads) {
+                kern<<<M, threads, 0, s>>>(splitk_ws, splits, M, N, reinterpret_cast<float *>(out), reinterpret_cast<const bf16 *>(norm->g),
+                                           reinterpret_cast<bf16 *>(norm->h), norm->eps, norm->terms);
+            };
+            // 5120 columns, 96 rows, 6 planes: 256 threads 14.4 us, 1024 threads 7.0; 1536 columns, 256 rows, 10 planes: 256 threads 6.8, 512 5.4
+            if (M > 768) reduce(splitk_reduce_resid_norm_kernel<256>, 256);
+            else if (N <= 2048) reduce(splitk_reduce_resid_norm_kernel<512>, 512);
+            else reduce(splitk_reduce_resid_norm_kernel<1024>, 1024);
             if (norm_done) *norm_done = true;
             return hipGetLastError();
         }

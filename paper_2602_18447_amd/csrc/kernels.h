@@ -217,8 +217,8 @@ hipError_t launch_attn_plan(const int32_t *cu, const int32_t *plens, const int32
 // avg_chunks: average number of key chunks per item (chooses the main loop)
 hipError_t launch_attn_bf16(const AttnTune &tune, const AttnArgs &a, const AttnItem *items, const int32_t *counts,
                             int n_items_host, int max_xcd_items, int avg_chunks, float *part_o, float *part_ml, hipStream_t s);
-// Combines the partial results of every split tile in piece order and writes the output rows.
-hipError_t launch_attn_merge(const AttnArgs &a, const AttnTile *tiles, const int32_t *counts, int n_tiles_host,
+// Combines the partial results of every split tile in a fixed order and writes the output rows.
+hipError_t launch_attn_merge(const AttnArgs &a, const AttnTile *tiles, const int32_t *counts, int n_tiles_host, int n_items_host,
                              const float *part_o, const float *part_ml, hipStream_t s);
 
 // Suffix keys / values [T, Hkv, hd] of the tokens i < n_append[b] of every trace into rows L_b + i of the paged cache
