@@ -521,7 +521,8 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_pipe_kernel(AttnArgs a, 
 #pragma unroll
                     for (int e = 4 * st; e < 4 * st + 4; ++e) mloc = max3(mloc, s_cur[0][e], s_cur[1][e]);
                     if constexpr (st == 3) {
-                        mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+                        const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(mloc), __float_as_uint(mloc), false, false);
+                        mloc = fmaxf(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
                         const float m_new = fmaxf(m_run, mloc);    // true running max, log2 units
                         // The exponent reference: 0, and probabilities are exp2(score), as long as the running maximum stays
                         // within 2^+-64 of it - fp32 and bf16 hold those without loss, and neither a subtraction per score nor
