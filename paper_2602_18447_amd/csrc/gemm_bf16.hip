@@ -254,14 +254,15 @@ __device__ __forceinline__ void gemm_epilogue(const Acc &acc, const Acc16 &acc16
                 }
             }
         } else {
-            constexpr int LPR = WNO / 4, RP = 64 / LPR;      // lanes per output row (4 floats each), rows per pass
+            constexpr int LPR = WNO / 4;                     // lanes per output row (4 floats each)
+            static_assert(32 * LPR % 64 == 0, "whole passes");
             float *out = reinterpret_cast<float *>(out_v);
 #pragma unroll
-            for (int p = 0; p < 32 / RP; ++p) {
-                int r = p * RP + lane / LPR, m = mrow0 + r;
-                f32x4 v = *reinterpret_cast<const f32x4 *>(stg + r * SROW + (lane % LPR) * 4);
+            for (int p = 0; p < 32 * LPR / 64; ++p) {
+                const int r = (p * 64 + lane) / LPR, c4 = (p * 64 + lane) % LPR * 4, m = mrow0 + r;
+                f32x4 v = *reinterpret_cast<const f32x4 *>(stg + r * SROW + c4);
                 if (m < M) {
-                    f32x4 *dst = reinterpret_cast<f32x4 *>(out + (size_t)m * N + n0 + wx * WN + (lane % LPR) * 4);
+                    f32x4 *dst = reinterpret_cast<f32x4 *>(out + (size_t)m * N + n0 + wx * WN + c4);
                     if (EPI == EPI_RESID_F32) v += *dst;
                     *dst = v;
                 }
@@ -615,8 +616,10 @@ __device__ __forceinline__ void wait_tiles(int rem) {     // until at most min(r
     }
 }
 
-// NS: stages of (BM + BN) x 64 elements in LDS; rows unpadded and swizzled as above.  gridDim.y: k slices, interleaved as above.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int NL, int NS, int EPI, int A_FMT>
+// NSA, NSW: stages of the A part and the W part of a k-tile in LDS; rows unpadded and swizzled as above.  gridDim.y: k slices,
+// interleaved as above.
+constexpr int feed_lds_bytes(int BM, int BN, int NSA, int NSW) { return (NSA * BM + NSW * BN) * 128; }
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NL, int NSA, int NSW, int EPI, int A_FMT>
 __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + NL)) void gemm_feed_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, void *out_v,
                                                                                  int M, int N, int K, int tiles_m, int tiles_n, int n_base, int group_m,
                                                                                  int out_fmt, RopeArgs rope) {
@@ -626,12 +629,12 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + NL)) void gemm_feed_kerne
     constexpr bool F16 = A_FMT == 3;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, MI = WM / 16, NI = WN / 16;
     constexpr int PA = BM / (8 * NLA), PW = BN / (8 * NLW), PM = PA > PW ? PA : PW;   // direct loads of a wavefront per k-tile
-    constexpr int ROWB = 128, STAGE = (BM + BN) * ROWB, SLOTS = 2 * MI, SB = SLOTS - 3;   // the barrier stands in front of slot SB
+    constexpr int ROWB = 128, SLOTS = 2 * MI, SB = SLOTS - 3;   // the barrier stands in front of slot SB
     static_assert(BM % (8 * NLA) == 0 && BN % (8 * NLW) == 0 && WM % 32 == 0 && WN % 16 == 0 && NI >= 2, "tile shape");
     static_assert(EPI != EPI_SWIGLU || WN % 64 == 0, "SwiGLU needs a gate/up column pair inside one wave tile");
     static_assert(EPI != EPI_ROPE || WN == 64 || (WN == 32 && BN == 64), "rotation pairs inside a wave tile");
-    static_assert(NS >= 2 && (NS - 1) * PM <= 63, "the waits count up to 63 loads");
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];   // [NS] stages: A rows, then W rows
+    static_assert(NSA >= 2 && NSW >= 2 && (NSA - 1) * PA <= 63 && (NSW - 1) * PW <= 63, "the waits count up to 63 loads");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];   // [NSA] stages of A rows, then [NSW] of W rows
 
     const int n_tiles = tiles_m * tiles_n;                               // tile order: as in gemm_bf16_kernel
     const int per = (n_tiles + 7) >> 3;
@@ -652,6 +655,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + NL)) void gemm_feed_kerne
         // load j of a k-tile fills rows 8 (lw + n_lw j) .. + 7 of its operand (A rows past M: the last one)
         const bool is_w = wave < NW + NLW;
         const int lw = is_w ? wave - NW : wave - NW - NLW, n_lw = is_w ? NLW : NLA, n_ld = is_w ? PW : PA;
+        const int ns = is_w ? NSW : NSA, stage_bytes = (is_w ? BN : BM) * ROWB;
         const int lda = K * A_TERMS;
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<bf16 *>(is_w ? W + (size_t)n0 * K : A + (size_t)m0 * lda), 0, -1, 0x00020000);
@@ -663,7 +667,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + NL)) void gemm_feed_kerne
             const int w_row = EPI == EPI_ROPE && WN == 32 ? (row & 15) + ((row >> 5) & 1) * 16 + ((row >> 4) & 1) * 32 : row;
             off[j] = (is_w ? w_row * K : (min(m0 + row, M - 1) - m0) * lda) * 2 + ((lane & 7) ^ ((row >> 1) & 7)) * 16;
         }
-        unsigned char *const dst = smem + (is_w ? BM * ROWB : 0) + lw * 1024;
+        unsigned char *const dst = smem + (is_w ? NSA * BM * ROWB : 0) + lw * 1024;
         auto issue = [&](int t, int stage) __attribute__((always_inline)) {
             const int kt = kb + t * kstep;
             const int kw = A_TERMS == 2 ? kt >> 1 : kt;                  // two-term A: the hi and the lo tile of every W k-tile
@@ -671,21 +675,21 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + NL)) void gemm_feed_kerne
 #pragma unroll
             for (int j = 0; j < PM; ++j)
                 if (j < n_ld)
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (CS_LDS_AS void *)(dst + stage * STAGE + j * n_lw * 1024), 16, off[j], kk * ROWB, 0, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (CS_LDS_AS void *)(dst + stage * stage_bytes + j * n_lw * 1024), 16, off[j], kk * ROWB, 0, 0);
         };
         __builtin_amdgcn_s_setprio(3);
-        for (int t = 0; t < min(NS, nk); ++t) issue(t, t);
-        if (is_w) wait_tiles<PW, NS - 1>(nk - 1);
-        else wait_tiles<PA, NS - 1>(nk - 1);
+        for (int t = 0; t < min(ns, nk); ++t) issue(t, t);
+        if (is_w) wait_tiles<PW, NSW - 1>(nk - 1);
+        else wait_tiles<PA, NSA - 1>(nk - 1);
         wg_barrier();                                                    // k-tile 0 is in LDS
         int stage = 0;
         for (int ki = 0; ki + 1 < nk; ++ki) {
-            const int rem = min(nk, ki + NS) - (ki + 2);                 // k-tiles asked for behind the next one
-            if (is_w) wait_tiles<PW, NS - 2>(rem);
-            else wait_tiles<PA, NS - 2>(rem);
+            const int rem = min(nk, ki + ns) - (ki + 2);                 // k-tiles asked for behind the next one
+            if (is_w) wait_tiles<PW, NSW - 2>(rem);
+            else wait_tiles<PA, NSA - 2>(rem);
             wg_barrier();                                                // k-tile ki + 1 is in LDS, the stage of ki is free
-            if (ki + NS < nk) issue(ki + NS, stage);
-            stage = stage + 1 == NS ? 0 : stage + 1;
+            if (ki + ns < nk) issue(ki + ns, stage);
+            stage = stage + 1 == ns ? 0 : stage + 1;
         }
         return;
     }
@@ -704,7 +708,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + NL)) void gemm_feed_kerne
     for (int h = 0; h < 2; ++h) {
         const int kv = ((4 * h + kq) ^ sw16) * 16;
         a_lane[h] = (wy * WM + l16) * ROWB + kv;
-        b_lane[h] = (BM + wx * WN + l16) * ROWB + kv;
+        b_lane[h] = (NSA * BM + wx * WN + l16) * ROWB + kv;
     }
     bf16x8 a16[4], b16[2][NI];
     auto read_a = [&](const unsigned char *st, int s) __attribute__((always_inline)) {
@@ -726,11 +730,13 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + NL)) void gemm_feed_kerne
     for (int s = 0; s < 3; ++s) read_a(smem, s);
 #pragma unroll
     for (int j = 0; j < NI; ++j) read_b(smem, 0, j);
-    int stage = 0;
+    int sa = 0, sw = 0;                                                  // stages of the next k-tile
     for (int ki = 0; ki < nk; ++ki) {
         const bool more = ki + 1 < nk;                                   // uniform
-        stage = stage + 1 == NS ? 0 : stage + 1;
-        const unsigned char *cur = smem + (stage == 0 ? NS - 1 : stage - 1) * STAGE, *next = smem + stage * STAGE;
+        const unsigned char *cur_a = smem + sa * (BM * ROWB), *cur_w = smem + sw * (BN * ROWB);
+        sa = sa + 1 == NSA ? 0 : sa + 1;
+        sw = sw + 1 == NSW ? 0 : sw + 1;
+        const unsigned char *next_a = smem + sa * (BM * ROWB), *next_w = smem + sw * (BN * ROWB);
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
             __builtin_amdgcn_sched_barrier(0);
@@ -745,21 +751,21 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + NL)) void gemm_feed_kerne
                 acc16[i][j] = mma16<F16>(a16[s & 3], b16[h][j], acc16[i][j]);
                 __builtin_amdgcn_sched_barrier(0);
                 if (j == 0) {                                            // A fragment of slot s + 3
-                    if (s + 3 < SLOTS) read_a(cur, s + 3);
-                    else if (more) read_a(next, s + 3 - SLOTS);
+                    if (s + 3 < SLOTS) read_a(cur_a, s + 3);
+                    else if (more) read_a(next_a, s + 3 - SLOTS);
                 }
                 if (j == 1) {
                     constexpr int s0 = MI > 4 ? MI - 4 : 0, s1 = MI < SB ? MI : SB, nb = (NI + s1 - s0 - 1) / (s1 - s0);
                     if (s >= s0 && s < s1) {                             // W fragments of the second k half
 #pragma unroll
                         for (int q = 0; q < nb; ++q)
-                            if ((s - s0) * nb + q < NI) read_b(cur, 1, (s - s0) * nb + q);
+                            if ((s - s0) * nb + q < NI) read_b(cur_w, 1, (s - s0) * nb + q);
                     }
                     constexpr int t0 = MI > SB ? MI : SB, nn = (NI + 1) / 2;
                     if (s >= t0 && s < t0 + 2 && more) {                 // of the next k-tile's first
 #pragma unroll
                         for (int q = 0; q < nn; ++q)
-                            if ((s - t0) * nn + q < NI) read_b(next, 0, (s - t0) * nn + q);
+                            if ((s - t0) * nn + q < NI) read_b(next_w, 0, (s - t0) * nn + q);
                     }
                 }
             }
@@ -767,7 +773,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + NL)) void gemm_feed_kerne
         __builtin_amdgcn_sched_barrier(0);
     }
     const int no_acc = 0;
-    gemm_epilogue<EPI, true, WM, WN, NW, NS * STAGE>(no_acc, acc16, smem, out_v, M, N, m0, n0, wy, wx, wave, lane, out_fmt, rope, EARLY ? &rv : nullptr);
+    gemm_epilogue<EPI, true, WM, WN, NW, feed_lds_bytes(BM, BN, NSA, NSW)>(no_acc, acc16, smem, out_v, M, N, m0, n0, wy, wx, wave, lane, out_fmt, rope, EARLY ? &rv : nullptr);
 #endif
 }
 
@@ -821,15 +827,15 @@ static hipError_t launch_tile(const GemmTune &tune, const bf16 *A, const bf16 *W
 
 // Tiles of gemm_feed_kernel: rows, columns, and workgroups of one round (those of 72 KiB run two per CU).
 struct FeedTile { int bm, bn, cap; };
-constexpr FeedTile FEED_TILES[] = {{0, 0, 0}, {64, 64, 256}, {64, 128, 512}, {128, 128, 256}, {256, 128, 256}};
-constexpr int N_FEED = 4;
+constexpr FeedTile FEED_TILES[] = {{0, 0, 0}, {64, 64, 256}, {64, 128, 512}, {128, 128, 256}, {256, 128, 256}, {256, 192, 256}};
+constexpr int N_FEED = 5;
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int NL, int NS, int EPI, int A_FMT>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NL, int NSA, int NSW, int EPI, int A_FMT>
 static hipError_t launch_feed_inst(const bf16 *A, const bf16 *W, void *out, int M, int N, int K, int n_base, int n_cols, int splits, int out_fmt,
                                    hipStream_t s, const RopeArgs *rope) {
-    constexpr int smem = NS * (BM + BN) * 128;
+    constexpr int smem = feed_lds_bytes(BM, BN, NSA, NSW);
     static std::atomic<uint32_t> attr_done{0};
-    auto kern = gemm_feed_kernel<BM, BN, WAVES_M, WAVES_N, NL, NS, EPI, A_FMT>;
+    auto kern = gemm_feed_kernel<BM, BN, WAVES_M, WAVES_N, NL, NSA, NSW, EPI, A_FMT>;
     if (hipError_t e = set_dynamic_lds_once(attr_done, reinterpret_cast<const void *>(kern), smem); e != hipSuccess) return e;
     const int tiles_m = (M + BM - 1) / BM, tiles_n = n_cols / BN, per = (tiles_m * tiles_n + 7) / 8;
     // tile order as in launch_inst: what an XCD works on at one time forms a roughly square block
@@ -843,11 +849,15 @@ static hipError_t launch_feed_fmt(int feed, const bf16 *A, const bf16 *W, void *
                                   hipStream_t s, const RopeArgs *rope) {
     switch (feed) {
         case 1:
-            if constexpr (EPI != EPI_SWIGLU) return launch_feed_inst<64, 64, 2, 2, 2, 7, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+            if constexpr (EPI != EPI_SWIGLU) return launch_feed_inst<64, 64, 2, 2, 2, 7, 7, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
             break;                      // (a gate/up column pair needs 64-column wave tiles: feed_cost does not offer it)
-        case 2: return launch_feed_inst<64, 128, 2, 2, 2, 3, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
-        case 3: return launch_feed_inst<128, 128, 4, 2, 4, 5, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
-        case 4: return launch_feed_inst<256, 128, 4, 2, 4, 3, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+        case 2: return launch_feed_inst<64, 128, 2, 2, 2, 3, 3, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+        case 3: return launch_feed_inst<128, 128, 4, 2, 4, 5, 5, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+        case 4: return launch_feed_inst<256, 128, 4, 2, 4, 3, 3, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+        case 5:
+            if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32)
+                return launch_feed_inst<256, 192, 2, 4, 4, 3, 2, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+            break;                      // (48-column wave tiles)
     }
     return hipErrorInvalidValue;
 }
@@ -866,19 +876,19 @@ static hipError_t launch_feed(int feed, const bf16 *A, const bf16 *W, void *out,
 // per k-tile a part that grows with u, the share of the CUs that work.  The workgroups of a tile and all its slices sit on one
 // XCD of 32 CUs, so an XCD's share counts: 36 tiles in 7 slices, five tiles to most XCDs, are 35 workgroups there (8960 x 1536,
 // 1536 rows: 69 us with 7 slices of 256 x 256 tiles, 47 with 6).
-static double feed_cost(int f, int M, int n_cols, int nk, int s, bool swiglu) {
+static double feed_cost(int f, int M, int n_cols, int nk, int s, int epi) {
     const FeedTile &t = FEED_TILES[f];
-    if (n_cols % t.bn != 0 || (swiglu && t.bn < 128)) return 1e30;
+    if (n_cols % t.bn != 0 || (t.bn < 128 && epi == EPI_SWIGLU) || (t.bn == 192 && epi != EPI_STORE_F32 && epi != EPI_RESID_F32)) return 1e30;
     const long per_xcd = ((long)((M + t.bm - 1) / t.bm) * (n_cols / t.bn) + 7) / 8 * s;
     if (per_xcd > t.cap / 8) return 1e30;
     const double u = per_xcd / 32.0;
-    const double c = f == 1 ? 0.20 + 0.09 * u : f == 2 ? (u <= 1 ? 0.44 + 0.06 * u : 0.42 + 0.20 * u) : f == 3 ? 0.58 + 0.10 * u : 0.80 + 0.12 * u;
-    return (f == 4 ? 7.5 : 4.4) + (nk + s - 1) / s * c;
+    const double c = f == 1 ? 0.20 + 0.09 * u : f == 2 ? (u <= 1 ? 0.44 + 0.06 * u : 0.42 + 0.20 * u) : f == 3 ? 0.58 + 0.10 * u : f == 4 ? 0.80 + 0.12 * u : 1.05 + 0.15 * u;
+    return (f >= 4 ? 7.5 : 4.4) + (nk + s - 1) / s * c;
 }
-static int best_feed(int M, int n_cols, int nk, bool swiglu, double *cost) {
+static int best_feed(int M, int n_cols, int nk, int epi, double *cost) {
     int best = 0;
     for (int f = 1; f <= N_FEED; ++f)
-        if (const double c = feed_cost(f, M, n_cols, nk, 1, swiglu); c < *cost) { *cost = c; best = f; }
+        if (const double c = feed_cost(f, M, n_cols, nk, 1, epi); c < *cost) { *cost = c; best = f; }
     return best;
 }
 
@@ -938,7 +948,7 @@ static hipError_t launch_epi(const GemmTune &tune, const bf16 *A, const bf16 *W,
         if (n1 < tn) {
             const int n_tail = N - n1 * 256, nk = K * (a_terms == 2 ? 2 : 1) / 64;
             double c = cost_128(M, n_tail, nk, 1);
-            if (const int f = best_feed(M, n_tail, nk, EPI == EPI_SWIGLU, &c))
+            if (const int f = best_feed(M, n_tail, nk, EPI, &c))
                 return launch_feed<EPI>(f, A, W, out, M, N, K, n1 * 256, n_tail, 1, a_terms, out_terms, s);
             return launch_tile<128, 128, 2, 2, 64, 2, EPI>(tune, A, W, out, M, N, K, n1 * 256, n_tail, a_terms, out_terms, s);
         }
@@ -1005,9 +1015,10 @@ static int general_splitk_factor(const GemmTune &tune, int M, int N, int K_total
 struct GemmPlan { int feed = 0, splits = 1; bool big = false; };   // feed: index into FEED_TILES, 0 = gemm_bf16_kernel
 // Beyond feed_cost: a reduction of s planes is 3.5 us + their bytes at 4.5 TB/s, written before at 6 TB/s; it normalises the rows on the way
 // where a norm follows, which is a kernel of 4.2 us + 6 bytes per element otherwise.  Whole layer before : after, contexts of 2048, us:
-// width 1536: 192 rows 117 : 95, 384 135 : 110, 512 157 : 126, 768 176 : 151, 1024 198 : 176, 1536 268 : 234, 2304 310 : 302; width 5120:
+// width 1536: 192 rows 117 : 95, 384 135 : 110, 512 157 : 126, 768 176 : 151, 1024 198 : 176, 1536 268 : 234, 2304 310 : 302, 6400 (256 x 192
+// tiles for O and down: one round of 200 for 150 of 256 x 256) 727 : 670, 8192 839 : 809; width 5120:
 // 96 rows 283 : 275, 192 368 : 342, 256 397 : 357, 384 532 : 526, 1200 1237 : 1199, 1536 1417 : 1370.
-static GemmPlan gemm_plan(const GemmTune &tune, int M, int N, int K_total, bool swiglu, bool norm_after, bool can_split) {
+static GemmPlan gemm_plan(const GemmTune &tune, int M, int N, int K_total, int epi, bool norm_after, bool can_split) {
     GemmPlan p;
     if (tune.tile != 0) return p;
     if (can_split) p.splits = general_splitk_factor(tune, M, N, K_total, &p.big);
@@ -1017,7 +1028,7 @@ static GemmPlan gemm_plan(const GemmTune &tune, int M, int N, int K_total, bool 
     auto finish = [&](int s) { return s > 1 ? 3.5 + s * mn * 4 * (1 / 4.5e6 + 1 / 6e6) : mn * 6 / 6e6 + (norm_after ? 4.2 + mn * 6 / 5e6 : 0.0); };
     auto slice = [&](int s) { return (nk + s - 1) / s; };
     const long t128 = (long)((M + 127) / 128) * (N / 128), t256 = (long)((M + 255) / 256) * (N / 256);
-    const long t192 = N % 96 == 0 && !swiglu && t128 > 256 && t128 <= 384 ? (long)((M + 191) / 192) * (N / 96) : 257;
+    const long t192 = N % 96 == 0 && epi != EPI_SWIGLU && t128 > 256 && t128 <= 384 ? (long)((M + 191) / 192) * (N / 96) : 257;
     if (p.big && t128 >= 256) return p;
     double best;
     if (p.big) best = 5.5 + slice(s_max) * 1.5;
@@ -1027,15 +1038,16 @@ static GemmPlan gemm_plan(const GemmTune &tune, int M, int N, int K_total, bool 
     best += finish(s_max);
     for (int f = 1; f <= N_FEED; ++f)
         for (int s = 1; s <= s_max && (s == 1 || nk / s >= 4); ++s)
-            if (const double t = feed_cost(f, M, N, nk, s, swiglu) + finish(s); t < best) { best = t; p.feed = f; p.splits = s; p.big = false; }
+            if (const double t = feed_cost(f, M, N, nk, s, s > 1 ? (int)EPI_STORE_F32 : epi) + finish(s); t < best) { best = t; p.feed = f; p.splits = s; p.big = false; }
     return p;
 }
-int gemm_splitk_factor(const GemmTune &tune, int M, int N, int K_total) { return gemm_plan(tune, M, N, K_total, false, true, true).splits; }
+int gemm_splitk_factor(const GemmTune &tune, int M, int N, int K_total) { return gemm_plan(tune, M, N, K_total, EPI_RESID_F32, true, true).splits; }
 // Scratch of a split product: the largest over what may follow it.
 size_t gemm_splitk_bytes(const GemmTune &tune, int M, int N, int K_total) {
     bool big;
     int s = tune.tile != 0 ? general_splitk_factor(tune, M, N, K_total, &big) : 1;
-    for (int v = 0; v < 4; ++v) s = std::max(s, gemm_plan(tune, M, N, K_total, v & 1, v & 2, true).splits);
+    for (int epi : {EPI_STORE_F32, EPI_RESID_F32, EPI_SWIGLU, EPI_ROPE})
+        for (bool norm : {false, true}) s = std::max(s, gemm_plan(tune, M, N, K_total, epi, norm && epi == EPI_RESID_F32, true).splits);
     return s > 1 ? (size_t)s * M * N * 4 : 0;
 }
 // An upper bound of gemm_splitk_bytes over all row counts up to max_M: the general factor bounds every plan's and changes with the
@@ -1260,9 +1272,9 @@ static hipError_t launch_splitk_short(const GemmTune &tune, const bf16 *A, const
 }
 
 // The plan for the scratch there is.
-static GemmPlan plan_with(const GemmTune &tune, int M, int N, int K_total, bool swiglu, bool norm_after, const float *ws, size_t ws_bytes) {
-    const GemmPlan p = gemm_plan(tune, M, N, K_total, swiglu, norm_after, ws != nullptr);
-    return p.splits > 1 && (size_t)p.splits * M * N * 4 > ws_bytes ? gemm_plan(tune, M, N, K_total, swiglu, norm_after, false) : p;
+static GemmPlan plan_with(const GemmTune &tune, int M, int N, int K_total, int epi, bool norm_after, const float *ws, size_t ws_bytes) {
+    const GemmPlan p = gemm_plan(tune, M, N, K_total, epi, norm_after, ws != nullptr);
+    return p.splits > 1 && (size_t)p.splits * M * N * 4 > ws_bytes ? gemm_plan(tune, M, N, K_total, epi, norm_after, false) : p;
 }
 
 // The partial products of the k slices, one [M, N] fp32 plane per slice; big: 256 x 256 tiles, else 128 x 128.
@@ -1290,7 +1302,7 @@ hipError_t launch_gemm_bf16(const GemmTune &tune, const bf16 *A, const bf16 *W, 
     const int k_total = K * (a_terms == 2 ? 2 : 1);
     const bool norm_here = epi == EPI_RESID_F32 && norm && norm->g && norm->h && N % 4 == 0 && N <= 6144 &&
                            ((((uintptr_t)norm->g | (uintptr_t)norm->h) & 7) == 0);
-    const GemmPlan p = plan_with(tune, M, N, k_total, epi == EPI_SWIGLU, norm_here, splitk_ws, splitk_ws_bytes);
+    const GemmPlan p = plan_with(tune, M, N, k_total, epi, norm_here, splitk_ws, splitk_ws_bytes);
     if (p.splits > 1) {
         hipError_t e = launch_splitk_main(tune, A, W, splitk_ws, M, N, K, a_terms, p, s);
         if (e != hipSuccess) return e;
@@ -1328,7 +1340,7 @@ hipError_t launch_gemm_bf16(const GemmTune &tune, const bf16 *A, const bf16 *W, 
 // have 64-column wave tiles.
 hipError_t launch_gemm_bf16_rope(const GemmTune &tune, const bf16 *A, const bf16 *W_perm, int M, int N, int K, int a_terms,
                                  const RopeArgs &rope, float *splitk_ws, size_t splitk_ws_bytes, hipStream_t s) {
-    const GemmPlan p = plan_with(tune, M, N, K * (a_terms == 2 ? 2 : 1), false, false, splitk_ws, splitk_ws_bytes);
+    const GemmPlan p = plan_with(tune, M, N, K * (a_terms == 2 ? 2 : 1), EPI_ROPE, false, splitk_ws, splitk_ws_bytes);
     if (p.splits > 1) {
         hipError_t e = launch_splitk_main(tune, A, W_perm, splitk_ws, M, N, K, a_terms, p, s);
         if (e != hipSuccess) return e;
@@ -1352,7 +1364,7 @@ hipError_t launch_gemm_bf16_rope(const GemmTune &tune, const bf16 *A, const bf16
         }
         const int n_tail = N - n1 * 256, nk = K * (a_terms == 2 ? 2 : 1) / 64;
         double c = cost_128(M, n_tail, nk, 1);
-        if (const int f = best_feed(M, n_tail, nk, false, &c))
+        if (const int f = best_feed(M, n_tail, nk, EPI_ROPE, &c))
             return launch_feed<EPI_ROPE>(f, A, W_perm, nullptr, M, N, K, n1 * 256, n_tail, 1, a_terms, 1, s, &rope);
         return launch_tile<128, 128, 2, 2, 64, 2, EPI_ROPE>(tune, A, W_perm, nullptr, M, N, K, n1 * 256, n_tail, a_terms, 1, s, &rope);
     }

@@ -24,11 +24,11 @@ def _operands(M, N, K, fmt):
     return A, f64(A), Wt
 
 
-# 64 x 128 tiles (few rows), 128 x 128 (about 2000 x 2048), 256 x 128 (2600 x 2048, 200 x 17920); rows at and next to the tiles'
+# 64 x 64 and 64 x 128 tiles (few rows), 128 x 128 (about 2000 x 2048), 256 x 128 (2600 x 2048, 200 x 17920), 256 x 192 (7937 x 1536); rows at and next to the tiles'
 # edges, one and two k-tiles (fewer than the stages), and enough of them that the ring wraps
 @pytest.mark.parametrize("fmt", [1, 2, 3])
 @pytest.mark.parametrize("M,N,K", [(33, 128, 64), (64, 256, 128), (65, 384, 192), (129, 512, 832), (255, 2048, 320), (1290, 2048, 128),
-                                   (2040, 2048, 448), (1921, 2048, 192), (2600, 2048, 576), (257, 4096, 1024), (200, 17920, 448)])
+                                   (2040, 2048, 448), (1921, 2048, 192), (2600, 2048, 576), (257, 4096, 1024), (200, 17920, 448), (7937, 1536, 576)])
 def test_one_round_tiles(M, N, K, fmt):
     print(f"feed M={M} N={N} K={K} fmt={fmt}", flush=True)
     ctx, _ = _ctx("bf16")
