@@ -816,7 +816,7 @@ static hipError_t launch_tile(const GemmTune &tune, const bf16 *A, const bf16 *W
         // fp16 operands: built for the tile shapes the default choice uses
         constexpr bool has_f16 = (BK == 64 && NS == 2 && ((BM == 128 && BN == 128 && WAVES_M == 2 && WAVES_N == 2) ||
                                                             (BM == 192 && BN == 96 && WAVES_M == 2 && WAVES_N == 3))) ||
-                                 (BM == 256 && BN == 256 && WAVES_M == 2);
+                                 (BM == 256 && BN == 256 && WAVES_M == 2) || (BM == 32 && BN == 128 && NS == 4);
         if constexpr (has_f16)
             return launch_inst<BM, BN, WAVES_M, WAVES_N, BK, NS, EPI, 3>(tune, A, W, out, M, N, K, n_base, n_cols, out_fmt, s, rope, pf);
         else
@@ -918,6 +918,11 @@ template <int EPI>
 static hipError_t launch_epi(const GemmTune &tune, const bf16 *A, const bf16 *W, void *out, int M, int N, int K, int a_terms,
                              int out_terms, hipStream_t s, const PrefetchArgs *pf = nullptr) {
     int tile = tune.tile;
+    // At most 32 rows over an output of 256 tiles and more (the full-vocabulary head, a wide model's gate/up projection of the last layer's
+    // rows): a stream of the weights, for which the 32-row tile keeps three k-tiles in flight, two workgroups per CU (8 rows x 152064 x
+    // 2 x 5120: 324 us; 128 x 128 tiles with two stages 443).
+    if (tile == 0 && M <= 32 && tune.short_tile)
+        return launch_tile<32, 128, 1, 2, 64, 4, EPI>(tune, A, W, out, M, N, K, 0, N, a_terms, out_terms, s);
     if (tile == 0) {
         // Wide outputs take 256x256 tiles, one workgroup per CU, in rounds of 256 tiles.  A last round
         // that would be less than half full costs as much as a full one, so those columns are cut off

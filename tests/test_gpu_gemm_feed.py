@@ -28,7 +28,8 @@ def _operands(M, N, K, fmt):
 # edges, one and two k-tiles (fewer than the stages), and enough of them that the ring wraps
 @pytest.mark.parametrize("fmt", [1, 2, 3])
 @pytest.mark.parametrize("M,N,K", [(33, 128, 64), (64, 256, 128), (65, 384, 192), (129, 512, 832), (255, 2048, 320), (1290, 2048, 128),
-                                   (2040, 2048, 448), (1921, 2048, 192), (2600, 2048, 576), (257, 4096, 1024), (200, 17920, 448), (7937, 1536, 576)])
+                                   (2040, 2048, 448), (1921, 2048, 192), (2600, 2048, 576), (257, 4096, 1024), (200, 17920, 448), (7937, 1536, 576),
+                                   (1, 128, 64), (8, 33024, 320), (32, 32768, 192)])     # the last three: tiles of 32 rows
 def test_one_round_tiles(M, N, K, fmt):
     print(f"feed M={M} N={N} K={K} fmt={fmt}", flush=True)
     ctx, _ = _ctx("bf16")
