@@ -308,6 +308,15 @@ int main() {
               "few_attn_pieces(n_tiles=%d, Hkv=%d, max_L=%d, one=%d) -> pieces=%d wave_pages=%d fold=%d", a.n_tiles, a.Hkv, a.max_L, one,
               a.pieces, a.wave_pages, a.fold);
     }
+    // split-K planes of a projection: a pass of fewer rows never asks for more than the workspace laid out for more rows holds
+    for (int iter = 0; iter < 20000; ++iter) {
+        const cs::GemmTune g{};
+        const int N = 32 * (1 + (int)(rng() % (iter % 2 ? 1800 : 200))), K = 64 * (1 + (int)(rng() % 500));
+        const int max_M = 1 + (int)(rng() % (iter % 3 ? 2200 : 20000)), M = 1 + (int)(rng() % max_M);
+        CHECK(cs::gemm_splitk_bytes(g, M, N, K) <= cs::gemm_splitk_max_bytes(g, max_M, N, K) &&
+              (size_t)cs::gemm_splitk_factor(g, M, N, K) * M * N * 4 <= std::max((size_t)M * N * 4, cs::gemm_splitk_bytes(g, M, N, K)),
+              "split-K planes of M=%d, N=%d, K=%d exceed those of up to %d rows", M, N, K, max_M);
+    }
     if (g_fail) { printf("host_check: %d check(s) failed\n", g_fail); return 1; }
     printf("host_check: ok\n");
     return 0;
