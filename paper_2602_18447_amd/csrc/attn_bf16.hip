@@ -602,6 +602,10 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_pipe_kernel(AttnArgs a, 
 // (hi + lo); products hi*hi, hi*lo and lo*hi are accumulated (lo*lo is below fp32 resolution of the
 // sum).  Cached context keys / values are exact bf16 values and need no second term.  Used for the
 // first layer(s), where score noise from rounding q and k is amplified by every later layer.
+// Within a wavefront a chunk's score product, softmax and value product follow each other, so what overlaps them is a second
+// workgroup on the CU: the second terms of a suffix chunk are staged where the chunk before it was (a load that is waited for, in the few
+// chunks that have them) instead of in stages of their own, and two workgroups fit the LDS and the registers.  Layer with one
+// workgroup per CU -> two: 32 x 2048 (96 suffix tokens) 225 -> 135 us, 64 x 8192 (128) 1257 -> 872, ragged 128 traces 4022 -> 2471.
 constexpr int K_STRIDE = 136;             // elements per K row in LDS (128 + 8 pad = 272 bytes)
 constexpr int VT_STRIDE = 72;             // elements per V^T row in LDS (64 + 8 pad = 144 bytes)
 constexpr int K_TILE = ATTN_BN * K_STRIDE;
@@ -610,13 +614,12 @@ constexpr int ATTN_STAGE = K_TILE + VT_TILE;   // elements per stage
 constexpr int ATTN_SMEM_BYTES = 2 * ATTN_STAGE * 2;
 
 template <bool PRECISE>
-__global__ __launch_bounds__(ATTN_THREADS, PRECISE ? 1 : 2) void attn_staged_kernel(AttnArgs a, const AttnItem *__restrict__ items,
+__global__ __launch_bounds__(ATTN_THREADS, 2) void attn_staged_kernel(AttnArgs a, const AttnItem *__restrict__ items,
                                                                   const int32_t *__restrict__ counts, int n_items_host,
                                                                   float *__restrict__ part_o,
                                                                   float *__restrict__ part_ml) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     __bf16 *smem = reinterpret_cast<__bf16 *>(smem_raw);
-    constexpr int STAGE = PRECISE ? 2 * ATTN_STAGE : ATTN_STAGE;   // PRECISE: [K | Vt | K_lo | Vt_lo]
 
     // workgroup id % 8 is the XCD; each XCD walks its own range of the item list in order
     int n_items = min(counts[1], n_items_host);
@@ -707,7 +710,6 @@ __global__ __launch_bounds__(ATTN_THREADS, PRECISE ? 1 : 2) void attn_staged_ker
     };
 
     u32x4 k_reg[4], v_reg[4];
-    u32x4 kl_reg[PRECISE ? 4 : 1], vl_reg[PRECISE ? 4 : 1];
     const bf16 *ksl_ = reinterpret_cast<const bf16 *>(a.ksuf_lo), *vsl_ = reinterpret_cast<const bf16 *>(a.vsuf_lo);
     auto load_chunk = [&](int u) {
         if (u < n_pc && u * ATTN_BN + ATTN_BN <= L) {          // uniform: a whole chunk of the cached context
@@ -730,42 +732,32 @@ __global__ __launch_bounds__(ATTN_THREADS, PRECISE ? 1 : 2) void attn_staged_ker
                 k_reg[i] = *reinterpret_cast<const u32x4 *>(kr[i]);
                 v_reg[i] = *reinterpret_cast<const u32x4 *>(vr[i]);
             }
-            if constexpr (PRECISE) {
-                if (u >= n_pc) {                               // second terms exist for suffix tokens only
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        kl_reg[i] = *reinterpret_cast<const u32x4 *>(row_general(ksl_, ksl_, u, (tid >> 4) + 16 * i) + (tid & 15) * 8);
-                        vl_reg[i] = *reinterpret_cast<const u32x4 *>(row_general(vsl_, vsl_, u, 4 * v_kq + i) + v_g * 8);
-                    }
-                }
-            }
         }
     };
-    auto store_tiles = [&](__bf16 *base, const u32x4 (&kr)[4], const u32x4 (&vr)[4]) {
+    auto load_second = [&](int u) {                            // second terms, of suffix tokens
 #pragma unroll
-        for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4 *>(base + k_dst[i]) = kr[i];
+        for (int i = 0; i < 4; ++i) {
+            k_reg[i] = *reinterpret_cast<const u32x4 *>(row_general(ksl_, ksl_, u, (tid >> 4) + 16 * i) + (tid & 15) * 8);
+            v_reg[i] = *reinterpret_cast<const u32x4 *>(row_general(vsl_, vsl_, u, 4 * v_kq + i) + v_g * 8);
+        }
+    };
+    auto store_stage = [&](int stage) {
+        __bf16 *base = smem + stage * ATTN_STAGE;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4 *>(base + k_dst[i]) = k_reg[i];
         // 4 keys x 8 hd  ->  8 rows of 4 keys
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
             uint2 lo, hi;
             // one byte permute per output word (low halves of two keys, high halves of two keys)
-            lo.x = __builtin_amdgcn_perm(vr[1][d], vr[0][d], 0x05040100u);
-            lo.y = __builtin_amdgcn_perm(vr[3][d], vr[2][d], 0x05040100u);
-            hi.x = __builtin_amdgcn_perm(vr[1][d], vr[0][d], 0x07060302u);
-            hi.y = __builtin_amdgcn_perm(vr[3][d], vr[2][d], 0x07060302u);
+            lo.x = __builtin_amdgcn_perm(v_reg[1][d], v_reg[0][d], 0x05040100u);
+            lo.y = __builtin_amdgcn_perm(v_reg[3][d], v_reg[2][d], 0x05040100u);
+            hi.x = __builtin_amdgcn_perm(v_reg[1][d], v_reg[0][d], 0x07060302u);
+            hi.y = __builtin_amdgcn_perm(v_reg[3][d], v_reg[2][d], 0x07060302u);
             *reinterpret_cast<uint2 *>(base + v_dst + (2 * d) * VT_STRIDE) = lo;
             *reinterpret_cast<uint2 *>(base + v_dst + (2 * d + 1) * VT_STRIDE) = hi;
         }
     };
-    // u: the chunk held in the registers (its lo tiles exist only for chunks of suffix tokens)
-    auto store_chunk = [&](int stage, int u) {
-        __bf16 *base = smem + stage * STAGE;
-        store_tiles(base, k_reg, v_reg);
-        if constexpr (PRECISE) {
-            if (u >= n_pc) store_tiles(base + ATTN_STAGE, kl_reg, vl_reg);
-        }
-    };
-
     f32x16 acc_o[4];
 #pragma unroll
     for (int hb = 0; hb < 4; ++hb)
@@ -784,11 +776,17 @@ __global__ __launch_bounds__(ATTN_THREADS, PRECISE ? 1 : 2) void attn_staged_ker
     bcast_ids();
     load_chunk(ch0);
     fetch_ids(ch0 + 1);
-    store_chunk(0, ch0);      // waits for every load issued so far, the Q fragments included
+    store_stage(0);           // waits for every load issued so far, the Q fragments included
     __syncthreads();
     for (int ch = ch0; ch < ch1; ++ch) {
         int stage = (ch - ch0) & 1;
         bool more = ch + 1 < ch1;
+        const bool has_lo = PRECISE && ch >= n_pc;   // uniform
+        if (has_lo) {                                // the second terms, in the stage that the chunk before has left
+            load_second(ch);
+            store_stage(stage ^ 1);
+            __syncthreads();
+        }
         if (more) {
             bcast_ids();            // ids of chunk ch+1, fetched during the previous iteration
             load_chunk(ch + 1);
@@ -796,8 +794,7 @@ __global__ __launch_bounds__(ATTN_THREADS, PRECISE ? 1 : 2) void attn_staged_ker
         }
         // keep the consumers of these loads (the LDS stores below) behind the MFMA work of this chunk
         __builtin_amdgcn_sched_barrier(0);
-        const __bf16 *base = smem + stage * STAGE;
-        const bool has_lo = PRECISE && ch >= n_pc;   // uniform
+        const __bf16 *base = smem + stage * ATTN_STAGE, *base_lo = smem + (stage ^ 1) * ATTN_STAGE;
 
         if (wave_active) {
             f32x16 acc_s[2];
@@ -819,7 +816,7 @@ __global__ __launch_bounds__(ATTN_THREADS, PRECISE ? 1 : 2) void attn_staged_ker
                 for (int ks = 0; ks < 8; ++ks)
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb) {
-                        bf16x8 kf = *reinterpret_cast<const bf16x8 *>(base + ATTN_STAGE + kb * 32 * K_STRIDE + k_frag + ks * 16);
+                        bf16x8 kf = *reinterpret_cast<const bf16x8 *>(base_lo + kb * 32 * K_STRIDE + k_frag + ks * 16);
                         acc_s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], acc_s[kb], 0, 0, 0);
                     }
             }
@@ -846,7 +843,8 @@ __global__ __launch_bounds__(ATTN_THREADS, PRECISE ? 1 : 2) void attn_staged_ker
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) mloc = fmaxf(mloc, acc_s[kb][e]);
-            mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+            const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(mloc), __float_as_uint(mloc), false, false);
+            mloc = fmaxf(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
             float m_new = fmaxf(m_run, mloc * sc);     // true running max, log2 units
             m_run = m_new;
             // Lazy rescale: the exponent reference m_ref only follows the running max when some query of
@@ -896,13 +894,14 @@ __global__ __launch_bounds__(ATTN_THREADS, PRECISE ? 1 : 2) void attn_staged_ker
                     for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
                         for (int hb = 0; hb < 4; ++hb) {
-                            bf16x8 vf = *reinterpret_cast<const bf16x8 *>(base + ATTN_STAGE + v_frag + hb * 32 * VT_STRIDE + kb * 32 + s2 * 16);
+                            bf16x8 vf = *reinterpret_cast<const bf16x8 *>(base_lo + v_frag + hb * 32 * VT_STRIDE + kb * 32 + s2 * 16);
                             acc_o[hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[kb][s2], acc_o[hb], 0, 0, 0);
                         }
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (more) store_chunk(stage ^ 1, ch + 1);
+        if (has_lo) __syncthreads();                 // every wavefront is done with the second terms
+        if (more) store_stage(stage ^ 1);
         __syncthreads();
     }
 
@@ -987,7 +986,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a, const AttnT
 template <bool PRECISE>
 static hipError_t launch_staged(const AttnArgs &a, const AttnItem *items, const int32_t *counts, int n_items_host,
                                 int max_xcd_items, float *part_o, float *part_ml, hipStream_t s) {
-    constexpr int smem = PRECISE ? 2 * ATTN_SMEM_BYTES : ATTN_SMEM_BYTES;
+    constexpr int smem = ATTN_SMEM_BYTES;
     static std::atomic<uint32_t> attr_done{0};
     if (hipError_t e = set_dynamic_lds_once(attr_done, reinterpret_cast<const void *>(attn_staged_kernel<PRECISE>), smem);
         e != hipSuccess)

@@ -62,3 +62,21 @@ def test_scores_past_the_reference_range(name, split):
         # probabilities and the result rounded to 8 mantissa bits; fp32 scores of some hundred: 2^-15 relative in a probability
         assert np.abs(got[t0:t1] - ref).max() <= (3 * 2.0 ** -9 + 2.0 ** -13) * np.abs(v_all).max(), (name, b)
     cb.confspec_destroy(ctx)
+
+
+# suffixes of one to nine chunks, whole items and pieces that begin inside the suffix, chunk boundaries on either side
+@pytest.mark.parametrize("split", [1, 4])
+@pytest.mark.parametrize("prefix_lens,suffix_lens", [((40, 0, 700), (300, 65, 128)), ((64, 129), (513, 64))])
+def test_second_terms_of_several_suffix_chunks(prefix_lens, suffix_lens, split, monkeypatch):
+    print(f"two-term attention L={prefix_lens} S={suffix_lens} split={split}", flush=True)
+    from tests import test_gpu_ops
+
+    def ctx_with_split(*args, **kw):
+        ctx, cfg = _ctx(*args, **kw)
+        cb.confspec_tune(ctx, "attn_min_chunks", 1)
+        cb.confspec_tune(ctx, "attn_split", split)
+        return ctx, cfg
+
+    monkeypatch.setattr(test_gpu_ops, "_ctx", ctx_with_split)
+    # as for short suffixes: two terms are 16 bits of mantissa, 2^-17 relative in q and k, scores of up to about 20
+    assert test_gpu_ops._attention_case("bf16", 12, 2, 128, prefix_lens, suffix_lens, out_terms=2, precise=True) <= 2e-4
