@@ -907,7 +907,8 @@ static bool prefer_256_tiles(int M, int N) {
     return c256 < c128;
 }
 
-// 128 x 128 tiles of gemm_bf16_kernel, two per CU, in s slices, in the terms of feed_cost.
+// A round of 256 x 256 tiles, and 128 x 128 tiles of gemm_bf16_kernel, two per CU, in s slices, in the terms of feed_cost.
+static double cost_256(int nk) { return 3.0 + nk * 1.5; }
 static double cost_128(int M, int n_cols, int nk, int s) {
     const long w = (long)((M + 127) / 128) * (n_cols / 128) * s;
     const double u = w / 256.0;
@@ -946,12 +947,33 @@ static hipError_t launch_epi(const GemmTune &tune, const bf16 *A, const bf16 *W,
             int full = (int)(rounds * 256 / tm);             // tile columns that fill whole rounds
             if ((long)(tn - full) * tm <= 128) n1 = full;
         }
+        const int nk = K * (a_terms == 2 ? 2 : 1) / 64;
+        if constexpr (EPI != EPI_SWIGLU) {
+            // Or the rows behind whole rounds are done by one round of gemm_feed_kernel's tiles, where the model has that shorter than the
+            // round or the columns that it stands for (8960 x 1536 with residual, before : after, us: 11009 rows 355 : 288, 12000
+            // 364 : 312, 18606 458 : 443, 22000 640 : 537, 24000 635 : 593, 27000 679 : 647; 1536 x 1536: 11009 rows 74.6 : 69.0,
+            // 18606 100.3 : 98.5, 22000 125.8 : 117.8).
+            const int m1 = (int)(rounds * 256 / tn);         // tile rows that fill whole rounds
+            if (m1 > 0 && m1 < tm) {
+                double c = cost_256(nk);                     // of what follows the whole rounds
+                if (n1 < tn) {
+                    c = cost_128(M, N - n1 * 256, nk, 1);
+                    best_feed(M, N - n1 * 256, nk, EPI, &c);
+                }
+                if (const int f = best_feed(M - m1 * 256, N, nk, EPI, &c)) {
+                    hipError_t e = launch_tile<256, 256, 2, 4, 64, 5, EPI>(tune, A, W, out, m1 * 256, N, K, 0, N, a_terms, out_terms, s, nullptr, pf);
+                    if (e != hipSuccess) return e;
+                    return launch_feed<EPI>(f, A + (size_t)m1 * 256 * nk * 64, W, reinterpret_cast<float *>(out) + (size_t)m1 * 256 * N, M - m1 * 256, N, K, 0, N,
+                                            1, a_terms, out_terms, s);
+                }
+            }
+        }
         if (n1 > 0) {
             hipError_t e = launch_tile<256, 256, 2, 4, 64, 5, EPI>(tune, A, W, out, M, N, K, 0, n1 * 256, a_terms, out_terms, s, nullptr, pf);
             if (e != hipSuccess) return e;
         }
         if (n1 < tn) {
-            const int n_tail = N - n1 * 256, nk = K * (a_terms == 2 ? 2 : 1) / 64;
+            const int n_tail = N - n1 * 256;
             double c = cost_128(M, n_tail, nk, 1);
             if (const int f = best_feed(M, n_tail, nk, EPI, &c))
                 return launch_feed<EPI>(f, A, W, out, M, N, K, n1 * 256, n_tail, 1, a_terms, out_terms, s);
@@ -1037,7 +1059,7 @@ static GemmPlan gemm_plan(const GemmTune &tune, int M, int N, int K_total, int e
     if (p.big && t128 >= 256) return p;
     double best;
     if (p.big) best = 5.5 + slice(s_max) * 1.5;
-    else if (s_max == 1 && prefer_256_tiles(M, N)) best = 2.5 + (t256 + 255) / 256 * (3.0 + nk * 1.5);
+    else if (s_max == 1 && prefer_256_tiles(M, N)) best = 2.5 + (t256 + 255) / 256 * cost_256(nk);
     else if (s_max == 1 && t192 <= 256) best = 4.5 + nk * 0.83;
     else best = cost_128(M, N, nk, s_max);
     best += finish(s_max);

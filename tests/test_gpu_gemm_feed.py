@@ -29,6 +29,7 @@ def _operands(M, N, K, fmt):
 @pytest.mark.parametrize("fmt", [1, 2, 3])
 @pytest.mark.parametrize("M,N,K", [(33, 128, 64), (64, 256, 128), (65, 384, 192), (129, 512, 832), (255, 2048, 320), (1290, 2048, 128),
                                    (2040, 2048, 448), (1921, 2048, 192), (2600, 2048, 576), (257, 4096, 1024), (200, 17920, 448), (7937, 1536, 576),
+                                   (10753, 1536, 192), (18606, 1536, 320),               # 256 x 256 tiles, and the rows behind them on smaller ones
                                    (1, 128, 64), (8, 33024, 320), (32, 32768, 192)])     # the last three: tiles of 32 rows
 def test_one_round_tiles(M, N, K, fmt):
     print(f"feed M={M} N={N} K={K} fmt={fmt}", flush=True)
