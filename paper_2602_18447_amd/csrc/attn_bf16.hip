@@ -48,13 +48,6 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
     return r;
 }
 
-// sum + p[e - 1] + p[e]: the normaliser adds up the probabilities as the value product takes them (rounded), two in one instruction
-__device__ __forceinline__ float add_pair(const bf16x8 &p, int e, float sum) {
-    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-    const bf16x2 v = {p[e - 1], p[e]}, one = {(__bf16)1.0f, (__bf16)1.0f};
-    return __builtin_amdgcn_fdot2_f32_bf16(v, one, sum, false);
-}
-
 // f(integral_constant<int, 0>{}), ..., f(integral_constant<int, N - 1>{}): a loop whose index is a compile-time
 // constant in every round (no loop is left for the optimizer to unroll or not)
 template <class F, int... I>
@@ -256,9 +249,11 @@ __device__ __forceinline__ void finish_item(const AttnArgs &a, const AttnItem &i
 //
 // What bounds it: the matrix work of a chunk (32 MFMAs, 1024 cycles a wavefront) and its vector work overlap in part only - the two
 // wavefronts of a SIMD are in different workgroups - so every vector instruction counts, and so does what stands in front of the first
-// exponential.  With the softmax scale in q, no subtraction of a reference in the common case, pairwise sums of the rounded
-// probabilities and the row maximum exchanged by v_permlane32_swap instead of through LDS: 127 -> 77 vector instructions a
-// chunk; per layer 32 x 2048 (96 suffix tokens) 72.6 -> 67.5 us, 64 x 8192 (128) 420 -> 410, ragged 128 traces 1320 -> 1150.
+// exponential.  The row maximum exchanged by v_permlane32_swap instead of through LDS: 164 -> 158 vector instructions a chunk beside the
+// MFMAs (compiled steady state); per layer 32 x 2048 (96 suffix tokens) 74.8 -> 74.5 us, 64 x 8192 (128) 414 -> 410, ragged 128 traces
+// 1242 -> 1147.  Not kept: scale in q, exponent reference 0 while scores stay within 2^+-64, and a normaliser that adds the rounded
+// probabilities in pairs (101 instructions; 70.2, 397, 1091 us).  A key with most of a row's weight then puts its rounding into
+// the result (relative error 3.6e-3 where it has no value of its own; 3e-4 bounds this form), and values above about 1e19 overflow.
 constexpr int PIPE_TILE_BYTES = ATTN_BN * HD * 2;          // one K or V stage: 16 KiB
 constexpr int PIPE_SMEM_BYTES = 4 * PIPE_TILE_BYTES;       // K0 K1 V0 V1
 
@@ -400,8 +395,8 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_pipe_kernel(AttnArgs a, 
     for (int hb = 0; hb < 4; ++hb)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc_o[hb][e] = 0.f;
-    float m_run = -INFINITY, m_ref = 0.f, l_run = 0.f;         // true max, exponent reference, sum (vs m_ref)
-    const float sc = a.scale * 1.44269504088896340736f;        // scores in log2 units, where q does not have it already
+    float m_run = -INFINITY, m_ref = -INFINITY, l_run = 0.f;   // true max, exponent reference, sum (vs m_ref)
+    const float sc = a.scale * 1.44269504088896340736f;        // scores in log2 units
 
     const int u0 = item.chunk_begin, n = item.chunk_end - item.chunk_begin;
 
@@ -458,12 +453,6 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_pipe_kernel(AttnArgs a, 
         const unsigned char *kst = smem + (1 - par) * PIPE_TILE_BYTES, *vst = smem + (2 + par) * PIPE_TILE_BYTES;
 
         if (wave_active) {
-            if (!a.q_scaled) {                                   // uniform
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) s_cur[kb][e] *= sc;
-            }
             // -- masks of chunk i: the tail of the context, or the visibility window of the suffix tokens
             if (u >= n_pc) {
                 int kt0 = ge.k_start + ATTN_BN * (u - n_pc) + 4 * half;
@@ -502,7 +491,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_pipe_kernel(AttnArgs a, 
                     fr[st % 3] = __builtin_bit_cast(bf16x8, both);
                 }
             };
-            float mloc = -INFINITY, psum = 0.f;
+            float mloc = -INFINITY, neg_off = 0.f, psum = 0.f;
             bf16x8 pf[2][2];
             fetch(std::integral_constant<int, 0>{});
             fetch(std::integral_constant<int, 1>{});
@@ -529,41 +518,37 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_pipe_kernel(AttnArgs a, 
                     if constexpr (st == 3) {
                         const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(mloc), __float_as_uint(mloc), false, false);
                         mloc = fmaxf(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
-                        const float m_new = fmaxf(m_run, mloc);    // true running max, log2 units
-                        // The exponent reference: 0, and probabilities are exp2(score), as long as the running maximum stays
-                        // within 2^+-64 of it - fp32 and bf16 hold those without loss, and neither a subtraction per score nor
-                        // a rescale per chunk is needed.  Where some query's maximum leaves that range the reference becomes it (a
-                        // maximum only grows: below the range it can only be the first one, with nothing accumulated yet).
-                        const bool move = fabsf(m_new - m_ref) > 64.0f && m_new != -INFINITY;
-                        if (__builtin_amdgcn_ballot_w64(move) != 0) {
-                            const float alpha = !move ? 1.0f : m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref - m_new);
-                            m_ref = move ? m_new : m_ref;
+                        const float m_new = fmaxf(m_run, mloc * sc);   // true running max, log2 units
+                        m_run = m_new;
+                        // Lazy rescale: the exponent reference m_ref only follows the running max when some query of
+                        // the wave has moved more than 8 (a factor 256) above it; until then probabilities may exceed
+                        // 1, which bf16 / fp32 hold without loss, and the accumulators need no per-chunk rescale.  (Without a
+                        // reference yet nothing is accumulated; exp2 of minus a first maximum below -128 would be infinite.)
+                        if (__builtin_amdgcn_ballot_w64(m_new > m_ref + 8.0f) != 0) {
+                            const float alpha = m_ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref - m_new);
+                            m_ref = m_new;
                             l_run *= alpha;
 #pragma unroll
                             for (int hb = 0; hb < 4; ++hb)
 #pragma unroll
                                 for (int e = 0; e < 16; ++e) acc_o[hb][e] *= alpha;
                         }
-                        m_run = m_new;
-                        if (__builtin_amdgcn_ballot_w64(m_ref != 0.f) != 0) {
-#pragma unroll
-                            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                                for (int e = 0; e < 16; ++e) s_cur[kb][e] -= m_ref;
-                        }
+                        neg_off = (m_ref == -INFINITY) ? 0.f : -m_ref;
                     }
                 } else if constexpr (st < 16) {
                     constexpr int e0 = ((st - 4) * 16) / 12, e1 = ((st - 3) * 16) / 12;
 #pragma unroll
                     for (int e = e0; e < e1; ++e) {
-                        pf[0][e >> 3][e & 7] = (__bf16)__builtin_amdgcn_exp2f(s_cur[0][e]);
-                        if (e & 1) psum = add_pair(pf[0][e >> 3], e & 7, psum);
+                        float p = __builtin_amdgcn_exp2f(fmaf(s_cur[0][e], sc, neg_off));
+                        psum += p;
+                        pf[0][e >> 3][e & 7] = (__bf16)p;
                     }
                 } else if constexpr (st < 24) {
 #pragma unroll
                     for (int e = 2 * (st - 16); e < 2 * (st - 16) + 2; ++e) {
-                        pf[1][e >> 3][e & 7] = (__bf16)__builtin_amdgcn_exp2f(s_cur[1][e]);
-                        if (e & 1) psum = add_pair(pf[1][e >> 3], e & 7, psum);
+                        float p = __builtin_amdgcn_exp2f(fmaf(s_cur[1][e], sc, neg_off));
+                        psum += p;
+                        pf[1][e >> 3][e & 7] = (__bf16)p;
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -588,7 +573,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_pipe_kernel(AttnArgs a, 
         }
     }
 
-    finish_item(a, item, acc_o, l_run, m_run == -INFINITY ? -INFINITY : m_ref, wave_active, row_valid, wave, lq, half, token, c * G + g, part_o, part_ml);
+    finish_item(a, item, acc_o, l_run, m_ref, wave_active, row_valid, wave, lq, half, token, c * G + g, part_o, part_ml);
 }
 
 // =================================================================================================
@@ -764,7 +749,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_staged_kernel(AttnArgs a
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc_o[hb][e] = 0.f;
     float m_run = -INFINITY, m_ref = -INFINITY, l_run = 0.f;   // true max, exponent reference, sum (vs m_ref)
-    const float sc = a.q_scaled ? 1.0f : a.scale * 1.44269504088896340736f;   // scores in log2 units
+    const float sc = a.scale * 1.44269504088896340736f;   // scores in log2 units
 
     // K operand row (key) for MFMA row lq, see the comment above the kernel: pi(m)
     int pi_m = 16 * (lq >> 4) + 8 * ((lq >> 2) & 1) + 4 * ((lq >> 3) & 1) + (lq & 3);

@@ -884,7 +884,7 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         if (rope_fused) {
             cs::RopeArgs ra = {(const float *)(ws + L.rope_cos), (const float *)(ws + L.rope_sin), ws + L.q, ws + L.ksuf,
                                ws + L.vsuf, prec ? ws + L.q_lo : nullptr, prec ? ws + L.ksuf_lo : nullptr,
-                               prec ? ws + L.vsuf_lo : nullptr, c.n_q_heads, c.n_kv_heads, 1.44269504088896340736f / sqrtf((float)c.head_dim)};
+                               prec ? ws + L.vsuf_lo : nullptr, c.n_q_heads, c.n_kv_heads};
             HIP_TRY(cs::launch_gemm_bf16_rope(set.gemm, (const cs::bf16 *)h, (const cs::bf16 *)(tm == 3 ? wqkv : w->wqkv_perm[l]), T,
                                               qw + 2 * kw, d, tm, ra, sk, skb, s));
         } else {
@@ -896,7 +896,6 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         }
         cs::AttnArgs a = make_attn_args(c, kv, batch, (const int32_t *)(ws + L.tok_trace), l, ws + L.q, ws + L.ksuf, ws + L.vsuf, prec ? ws + L.q_lo : nullptr,
                                         prec ? ws + L.ksuf_lo : nullptr, prec ? ws + L.vsuf_lo : nullptr, ws + L.attn, tm);
-        a.q_scaled = rope_fused;
         HIP_TRY(mark(prec ? CONFSPEC_PHASE_ATTN_PRECISE : CONFSPEC_PHASE_ATTN));
         if ((rc = run_attention(ctx, a, ws, L, last ? pc_last : pc, last, 0, s))) return rc;
         HIP_TRY(mark(CONFSPEC_PHASE_OTHER));

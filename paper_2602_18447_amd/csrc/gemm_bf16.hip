@@ -224,9 +224,6 @@ __device__ __forceinline__ void gemm_epilogue(const Acc &acc, const Acc16 &acc16
                             va[q] = lo_ * cs[q] - hi_ * sn[q];
                             vb[q] = hi_ * cs[q] + lo_ * sn[q];
                         }
-                        if (is_q)
-#pragma unroll
-                            for (int q = 0; q < 8; ++q) { va[q] *= rope.q_scale; vb[q] *= rope.q_scale; }
                     }
                     size_t o = ((size_t)m * heads + hh) * 128 + c0;
                     unsigned ha[8], hb[8];
@@ -1168,7 +1165,6 @@ __global__ void splitk_reduce_rope_kernel(const float *__restrict__ part, int sp
             a[q] = lo_ * c[q] - hi_ * sn[q];
             b[q] = hi_ * c[q] + lo_ * sn[q];
         }
-        if (is_q) { a *= rope.q_scale; b *= rope.q_scale; }
     }
     size_t o = ((size_t)m * heads + hh) * 128 + c0;
     unsigned ha[4], hb[4];

@@ -65,7 +65,6 @@ struct RopeArgs {
     void *q, *k, *v;              // [M, Hq, 128], [M, Hkv, 128], [M, Hkv, 128]
     void *q_lo, *k_lo, *v_lo;
     int32_t Hq, Hkv;
-    float q_scale = 1.0f;         // q is stored times this (one rounding, like without)
 };
 
 // Work of the few-row attention (attn_few.hip).
@@ -204,7 +203,6 @@ struct AttnArgs {
     int32_t B, T, Hq, Hkv, hd, n_blocks, block_size, max_blocks;
     float scale;            // 1/sqrt(hd)
     int32_t out_terms;
-    int32_t q_scaled;       // q (and q_lo) are already times scale * log2(e)
 };
 hipError_t launch_attn_f32(const AttnArgs &a, int max_S, hipStream_t s);   // max_S: longest suffix of the batch
 

@@ -1,5 +1,6 @@
-"""The pipelined attention loop where scores leave the range its exponent reference covers: rows whose running maximum starts far below
-zero, rises past the range chunk by chunk, or stays below it, whole items and pieces, against the oracle."""
+"""The pipelined attention loop where its exponent reference has to move: rows whose running maximum starts far below zero, rises by
+hundreds chunk by chunk, or stays low, whole items and pieces; one key with most of the weight, and values of extreme size; against the
+oracle."""
 import numpy as np
 import pytest
 import torch
@@ -80,3 +81,73 @@ def test_second_terms_of_several_suffix_chunks(prefix_lens, suffix_lens, split, 
     monkeypatch.setattr(test_gpu_ops, "_ctx", ctx_with_split)
     # as for short suffixes: two terms are 16 bits of mantissa, 2^-17 relative in q and k, scores of up to about 20
     assert test_gpu_ops._attention_case("bf16", 12, 2, 128, prefix_lens, suffix_lens, out_terms=2, precise=True) <= 2e-4
+
+
+def _attend(L, S, seed, split, offset_of_key, spread, value, along, out_terms=1):
+    """Attention of suffixes S behind contexts of L keys (a key: offset_of_key(i) score units along u, plus noise; a value: value(noise, key));
+    row r of head h of q goes along[(r + h) % len(along)] of u.  Returns the result and the oracle's, [T, Hq, 128]."""
+    hq, hkv, hd = 12, 2, 128
+    wl = W.tiny_workload("range", seed, dtype="bf16", n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, d_model=256,
+                         prefix_lens=(L,) * len(S), suffix_lens=S, block_size=16)
+    ctx, _ = _ctx("bf16", n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd)
+    cb.confspec_tune(ctx, "attn_kernel", 2)
+    cb.confspec_tune(ctx, "attn_min_chunks", 1)
+    cb.confspec_tune(ctx, "attn_split", split)
+    batch, T = W.make_batch(wl, DEV), wl.T
+    kv = W.make_seeded_kv(wl, batch, DEV)                             # N(0, 0.5): scaled below
+    u = torch.zeros(hd, device=DEV)
+    u[::2] = 1.0                                                      # 64 elements
+    per_unit = 64 * 8.0 / np.sqrt(hd) * np.log2(np.e)                 # score (log2 units) of a key u / 8 .. for a query 8 u
+    keys = torch.arange(batch.max_blocks_per_seq * 16, device=DEV)
+    off, vcol = offset_of_key(keys).float() / per_unit, keys.view(-1, 16)
+    for b in range(wl.B):
+        for p in range((L + 15) // 16):
+            blk = int(batch.block_table[b, p])
+            k, v = kv.k_pages[0, blk].float(), kv.v_pages[0, blk].float()
+            kv.k_pages[0, blk] = (2 * spread * k + off[16 * p:16 * p + 16, None] * u).to(torch.bfloat16)
+            kv.v_pages[0, blk] = value(2 * v, vcol[p][:, None]).to(torch.bfloat16)
+    a = torch.tensor(along, device=DEV)[(torch.arange(T, device=DEV)[:, None] + torch.arange(hq, device=DEV)) % len(along)]
+    q = (_rand((T, hq, hd), torch.float32, seed + 1, 0.3) + 8.0 * a[..., None] * u).to(torch.bfloat16)
+    later = torch.full((1, 1, 1), L, device=DEV)
+    ks = (_rand((T, hkv, hd), torch.float32, seed + 2, spread) + float(offset_of_key(later)) / per_unit * u).to(torch.bfloat16)
+    vs = value(_rand((T, hkv, hd), torch.float32, seed + 3), later).to(torch.bfloat16)
+    out = torch.zeros((T, out_terms * hq * hd), dtype=torch.bfloat16, device=DEV)
+    kvs = cb.make_kv(kv.k_pages, kv.v_pages, batch.block_table, batch.n_blocks, 16, batch.max_blocks_per_seq)
+    bs, keep = _batch_structs(wl, batch)
+    ws = torch.empty(cb.confspec_workspace_bytes(ctx, T, wl.B), dtype=torch.uint8, device=DEV)
+    cb.confspec_op_attention(ctx, kvs, bs, 0, q, ks, vs, out, ws, out_terms=out_terms)
+    torch.cuda.synchronize()
+    got = f64(out).reshape(T, out_terms, hq, hd).sum(axis=1)
+    view, ref = W.OracleKVView(kv, batch), np.zeros((T, hq, hd))
+    for b in range(wl.B):
+        ids = batch.block_table[b, :(L + 15) // 16].cpu().numpy()
+        t0, t1 = int(batch.h_cu_suffix[b]), int(batch.h_cu_suffix[b + 1])
+        k_all = np.concatenate([O.gather_prefix(view.k_blocks(0, ids), L), f64(ks)[t0:t1]])
+        v_all = np.concatenate([O.gather_prefix(view.v_blocks(0, ids), L), f64(vs)[t0:t1]])
+        ref[t0:t1] = O.attention(f64(q)[t0:t1], k_all, v_all, L)
+    cb.confspec_destroy(ctx)
+    return got, ref
+
+
+@pytest.mark.parametrize("split", [1, 3])
+def test_a_key_with_most_of_the_weight_and_no_value(split):
+    """The first key takes about half to nine tenths of every row's weight and has no value, the other 1100 have values about 1.  The result is
+    the others' share: rounding of the first key's probability in the normaliser, or off the reference, would show in full."""
+    print(f"attention sink split={split}", flush=True)
+    L, S = 1100, (70, 33)
+    along = [1.0 + 0.01 * i for i in range(-9, 10)]                   # the first key's score differs from row to row
+    got, ref = _attend(L, S, 95, split, lambda i: 11.0 * (i == 0), 0.12, lambda x, i: (1.0 + 0.25 * x) * (i > 0), along, out_terms=2)
+    assert 0.02 < ref.min() and ref.max() < 0.9                       # q's own noise moves the share, too
+    # the others' probabilities are rounded to 8 mantissa bits: 2^-9 / sqrt(3) relative each, independent, spread over about a factor of
+    # two (rms to mean 1.3) - six standard deviations of the mean of 1100; fp32 sums of 1100 terms and the two-term result 2^-15
+    bound = 6 * 2.0 ** -9 / np.sqrt(3.0) * 1.3 / np.sqrt(L) + 2.0 ** -15
+    assert (np.abs(got - ref) / ref).max() <= bound
+
+
+@pytest.mark.parametrize("split", [1, 3])
+@pytest.mark.parametrize("size", [2.0 ** 100, 2.0 ** -110])
+def test_values_of_extreme_size(size, split):
+    """Rows whose scores all lie near +50, or near -50 (log2 units): neither large nor small values leave the range."""
+    print(f"attention values {size:g} split={split}", flush=True)
+    got, ref = _attend(1000, (40, 1, 130), 97, split, lambda i: 50.0 + 0 * i, 0.12, lambda x, i: size * x, [1.0, -1.0])
+    assert np.abs(got - ref).max() <= (3 * 2.0 ** -9 + 2.0 ** -13) * np.abs(ref).max()
