@@ -834,11 +834,10 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_staged_kernel(AttnArgs a
             m_run = m_new;
             // Lazy rescale: the exponent reference m_ref only follows the running max when some query of
             // the wave has moved more than 8 (a factor 256) above it; until then probabilities may exceed
-            // 1, which bf16 / fp32 hold without loss, and the accumulators need no per-chunk rescale.
+            // 1, which bf16 / fp32 hold without loss, and the accumulators need no per-chunk rescale.  (Without a reference yet
+            // nothing is accumulated; exp2 of minus a first maximum below -128 would be infinite.)
             if (__builtin_amdgcn_ballot_w64(m_new > m_ref + 8.0f) != 0) {
-                float off_old = (m_ref == -INFINITY) ? 0.f : m_ref;
-                float off_new = (m_new == -INFINITY) ? 0.f : m_new;
-                float alpha = __builtin_amdgcn_exp2f(off_old - off_new);
+                const float alpha = m_ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref - m_new);
                 m_ref = m_new;
                 l_run *= alpha;
 #pragma unroll

@@ -83,14 +83,15 @@ def test_second_terms_of_several_suffix_chunks(prefix_lens, suffix_lens, split, 
     assert test_gpu_ops._attention_case("bf16", 12, 2, 128, prefix_lens, suffix_lens, out_terms=2, precise=True) <= 2e-4
 
 
-def _attend(L, S, seed, split, offset_of_key, spread, value, along, out_terms=1):
+def _attend(L, S, seed, split, offset_of_key, spread, value, along, out_terms=1, kernel=2, two_term=False):
     """Attention of suffixes S behind contexts of L keys (a key: offset_of_key(i) score units along u, plus noise; a value: value(noise, key));
     row r of head h of q goes along[(r + h) % len(along)] of u.  Returns the result and the oracle's, [T, Hq, 128]."""
     hq, hkv, hd = 12, 2, 128
+    lo = {n: torch.zeros((sum(S), h, hd), dtype=torch.bfloat16, device=DEV) for n, h in (("q_lo", hq), ("k_lo", hkv), ("v_lo", hkv))}
     wl = W.tiny_workload("range", seed, dtype="bf16", n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, d_model=256,
                          prefix_lens=(L,) * len(S), suffix_lens=S, block_size=16)
     ctx, _ = _ctx("bf16", n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd)
-    cb.confspec_tune(ctx, "attn_kernel", 2)
+    cb.confspec_tune(ctx, "attn_kernel", kernel)
     cb.confspec_tune(ctx, "attn_min_chunks", 1)
     cb.confspec_tune(ctx, "attn_split", split)
     batch, T = W.make_batch(wl, DEV), wl.T
@@ -115,7 +116,7 @@ def _attend(L, S, seed, split, offset_of_key, spread, value, along, out_terms=1)
     kvs = cb.make_kv(kv.k_pages, kv.v_pages, batch.block_table, batch.n_blocks, 16, batch.max_blocks_per_seq)
     bs, keep = _batch_structs(wl, batch)
     ws = torch.empty(cb.confspec_workspace_bytes(ctx, T, wl.B), dtype=torch.uint8, device=DEV)
-    cb.confspec_op_attention(ctx, kvs, bs, 0, q, ks, vs, out, ws, out_terms=out_terms)
+    cb.confspec_op_attention(ctx, kvs, bs, 0, q, ks, vs, out, ws, out_terms=out_terms, **(lo if two_term else {}))
     torch.cuda.synchronize()
     got = f64(out).reshape(T, out_terms, hq, hd).sum(axis=1)
     view, ref = W.OracleKVView(kv, batch), np.zeros((T, hq, hd))
@@ -150,4 +151,14 @@ def test_values_of_extreme_size(size, split):
     """Rows whose scores all lie near +50, or near -50 (log2 units): neither large nor small values leave the range."""
     print(f"attention values {size:g} split={split}", flush=True)
     got, ref = _attend(1000, (40, 1, 130), 97, split, lambda i: 50.0 + 0 * i, 0.12, lambda x, i: size * x, [1.0, -1.0])
+    assert np.abs(got - ref).max() <= (3 * 2.0 ** -9 + 2.0 ** -13) * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("split", [1, 3])
+@pytest.mark.parametrize("kernel,two_term", [(1, False), (2, False), (0, True)])
+def test_first_keys_far_below_zero(kernel, two_term, split):
+    """Every loop: the first 64 keys score about -400 for half of the rows, so exp2 of minus their maximum is not a number to scale by."""
+    print(f"attention low first keys kernel={kernel} two_term={two_term} split={split}", flush=True)
+    got, ref = _attend(700, (40, 1, 130), 99, split, lambda i: -400.0 * (i < 64), 0.12, lambda x, i: x, [1.0, -1.0], kernel=kernel, two_term=two_term)
+    # as above; the +400 of the other rows makes fp32 scores of some hundred: 2^-15 relative in a probability
     assert np.abs(got - ref).max() <= (3 * 2.0 ** -9 + 2.0 ** -13) * np.abs(ref).max()
