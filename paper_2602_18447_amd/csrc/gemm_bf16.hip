@@ -1075,12 +1075,12 @@ size_t gemm_splitk_bytes(const GemmTune &tune, int M, int N, int K_total) {
     return s > 1 ? (size_t)s * M * N * 4 : 0;
 }
 // An upper bound of gemm_splitk_bytes over all row counts up to max_M: the general factor bounds every plan's and changes with the
-// number of row tiles.
+// number of row tiles, and behind the 32 rows of the short tile.
 size_t gemm_splitk_max_bytes(const GemmTune &tune, int max_M, int N, int K_total) {
     size_t best = 0;
-    for (int tm = 1; tm <= (max_M + 127) / 128; ++tm) {
+    for (int tm = 0; tm <= (max_M + 127) / 128; ++tm) {
         bool big;
-        const int M = std::min(tm * 128, max_M), s = general_splitk_factor(tune, M, N, K_total, &big);
+        const int M = std::min(tm == 0 ? 32 : tm * 128, max_M), s = general_splitk_factor(tune, M, N, K_total, &big);
         if (s > 1) best = std::max(best, (size_t)s * M * N * 4);
     }
     return best;

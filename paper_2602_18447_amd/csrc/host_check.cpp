@@ -317,6 +317,17 @@ int main() {
               (size_t)cs::gemm_splitk_factor(g, M, N, K) * M * N * 4 <= std::max((size_t)M * N * 4, cs::gemm_splitk_bytes(g, M, N, K)),
               "split-K planes of M=%d, N=%d, K=%d exceed those of up to %d rows", M, N, K, max_M);
     }
+    // few k-tiles: at most 32 rows are cut into shorter slices than a whole tile row is
+    for (int M : {1, 31, 32, 33, 128})
+        for (int max_M : {M, 128, 129, 2000})
+            for (int N : {128, 512, 1536, 24576})
+                for (int nk = 1; nk <= 16; ++nk)
+                    for (int short_tile : {0, 1}) {
+                        cs::GemmTune g{};
+                        g.short_tile = short_tile;
+                        CHECK(M > max_M || cs::gemm_splitk_bytes(g, M, N, nk * 64) <= cs::gemm_splitk_max_bytes(g, max_M, N, nk * 64),
+                              "split-K planes of M=%d, N=%d, K=%d exceed those of up to %d rows (short_tile %d)", M, N, nk * 64, max_M, short_tile);
+                    }
     if (g_fail) { printf("host_check: %d check(s) failed\n", g_fail); return 1; }
     printf("host_check: ok\n");
     return 0;
