@@ -294,7 +294,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const
     static_assert(BK == 64 || BK == 32, "BK");
     static_assert(BM % (RPD * NW) == 0 && BN % (RPD * NW) == 0 && WM % 32 == 0 && WN % 32 == 0, "tile shape");
     static_assert(EPI != EPI_SWIGLU || WN % 64 == 0, "SwiGLU needs a gate/up column pair inside one wave tile");
-    static_assert(EPI != EPI_ROPE || WN == 64 || (WN == 32 && BN == 64), "rotation pairs inside a wave tile");
+    static_assert(EPI != EPI_ROPE || WN == 64, "the rotation pairs of a head half fill a 64-column wave tile");
     static_assert(NS >= 2 && NS <= 5, "stages");
     static_assert(MI * NI >= 2, "a k-step has at least two MFMAs");
     // 256 x 256 tiles take the loop that reads a k-tile's first operands during the previous tile's last k-step
@@ -629,7 +629,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + NL)) void gemm_feed_kerne
     constexpr int ROWB = 128, SLOTS = 2 * MI, SB = SLOTS - 3;   // the barrier stands in front of slot SB
     static_assert(BM % (8 * NLA) == 0 && BN % (8 * NLW) == 0 && WM % 32 == 0 && WN % 16 == 0 && NI >= 2, "tile shape");
     static_assert(EPI != EPI_SWIGLU || WN % 64 == 0, "SwiGLU needs a gate/up column pair inside one wave tile");
-    static_assert(EPI != EPI_ROPE || WN == 64 || (WN == 32 && BN == 64), "rotation pairs inside a wave tile");
+    static_assert(EPI != EPI_ROPE || WN == 64 || (WN == 32 && BN == 64), "rotation pairs inside a wave tile (32 columns: dealt out by the loads of W)");
     static_assert(NSA >= 2 && NSW >= 2 && (NSA - 1) * PA <= 63 && (NSW - 1) * PW <= 63, "the waits count up to 63 loads");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];   // [NSA] stages of A rows, then [NSW] of W rows
 
@@ -1359,8 +1359,8 @@ hipError_t launch_gemm_bf16(const GemmTune &tune, const bf16 *A, const bf16 *W, 
     return launch_epi<EPI_SWIGLU>(tune, A, W, out, M, N, K, a_terms, out_terms, s, pf);
 }
 
-// QKV projection with the rotation in the epilogue (see RopeArgs): the default tile choice, both shapes
-// have 64-column wave tiles.
+// QKV projection with the rotation in the epilogue (see RopeArgs): the planned tile, or the default choice; all have 64-column wave
+// tiles except gemm_feed_kernel's 64 x 64 ones, which deal out their W rows accordingly.
 hipError_t launch_gemm_bf16_rope(const GemmTune &tune, const bf16 *A, const bf16 *W_perm, int M, int N, int K, int a_terms,
                                  const RopeArgs &rope, float *splitk_ws, size_t splitk_ws_bytes, hipStream_t s) {
     const GemmPlan p = plan_with(tune, M, N, K * (a_terms == 2 ? 2 : 1), EPI_ROPE, false, splitk_ws, splitk_ws_bytes);
