@@ -774,6 +774,18 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + NL)) void gemm_feed_kerne
 #endif
 }
 
+// Tile rows per band of the tile order.  Workgroups of one XCD that run at the same time: its share of the tiles, at most 32 CUs x the
+// workgroups that fit one CU's 160 KiB of LDS.  A square block of that many tiles, weighted by the tile's aspect, has
+// sqrt(resident * BN / BM) rows.
+int gemm_band_rows(const GemmTune &tune, int BM, int BN, int smem, int tiles_m, int tiles_n) {
+    int group_m = tune.group_m;
+    if (group_m <= 0) {
+        const int resident = std::min((tiles_m * tiles_n + 7) / 8, 32 * std::max(160 * 1024 / smem, 1));
+        group_m = (int)std::lround(std::sqrt((double)resident * BN / BM));
+    }
+    return std::max(1, std::min(group_m, tiles_m));
+}
+
 // The number of activation terms is a template parameter, so the one-term and the two-term launches
 // are different kernels (and show up under different names in a kernel trace).
 // Launches the kernel on the column range [n_base, n_base + n_cols) of the N columns.
@@ -788,16 +800,7 @@ static hipError_t launch_inst(const GemmTune &tune, const bf16 *A, const bf16 *W
     int tiles_m = (M + BM - 1) / BM, tiles_n = n_cols / BN;
     int n_tiles = tiles_m * tiles_n;
     int grid = ((n_tiles + 7) / 8) * 8;
-    // Workgroups of one XCD that run at the same time: its share of the tiles, at most 32 CUs x the
-    // workgroups that fit one CU's 160 KiB of LDS.  A square block of that many tiles, weighted by the
-    // tile's aspect, has sqrt(resident * BN / BM) rows.
-    int group_m = tune.group_m;
-    if (group_m <= 0) {
-        int fit = 160 * 1024 / smem;
-        int resident = std::min((n_tiles + 7) / 8, 32 * std::max(fit, 1));
-        group_m = (int)std::lround(std::sqrt((double)resident * BN / BM));
-    }
-    group_m = std::max(1, std::min(group_m, tiles_m));
+    const int group_m = gemm_band_rows(tune, BM, BN, smem, tiles_m, tiles_n);
     kern<<<grid, 64 * WAVES_M * WAVES_N, smem, s>>>(A, W, out, M, N, K, tiles_m, tiles_n, n_base, group_m, out_terms,
                                                     rope ? *rope : RopeArgs{}, pf ? *pf : PrefetchArgs{});
     return hipGetLastError();
@@ -828,43 +831,41 @@ constexpr FeedTile FEED_TILES[] = {{0, 0, 0}, {64, 64, 256}, {64, 128, 512}, {12
 constexpr int N_FEED = 5;
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int NL, int NSA, int NSW, int EPI, int A_FMT>
-static hipError_t launch_feed_inst(const bf16 *A, const bf16 *W, void *out, int M, int N, int K, int n_base, int n_cols, int splits, int out_fmt,
-                                   hipStream_t s, const RopeArgs *rope) {
+static hipError_t launch_feed_inst(const GemmTune &tune, const bf16 *A, const bf16 *W, void *out, int M, int N, int K, int n_base, int n_cols, int splits,
+                                   int out_fmt, hipStream_t s, const RopeArgs *rope) {
     constexpr int smem = feed_lds_bytes(BM, BN, NSA, NSW);
     static std::atomic<uint32_t> attr_done{0};
     auto kern = gemm_feed_kernel<BM, BN, WAVES_M, WAVES_N, NL, NSA, NSW, EPI, A_FMT>;
     if (hipError_t e = set_dynamic_lds_once(attr_done, reinterpret_cast<const void *>(kern), smem); e != hipSuccess) return e;
     const int tiles_m = (M + BM - 1) / BM, tiles_n = n_cols / BN, per = (tiles_m * tiles_n + 7) / 8;
-    // tile order as in launch_inst: what an XCD works on at one time forms a roughly square block
-    const int group_m = (int)std::lround(std::sqrt((double)std::min(per, 32 * (160 * 1024 / smem)) * BN / BM));
     kern<<<dim3(8 * per, splits), 64 * (WAVES_M * WAVES_N + NL), smem, s>>>(A, W, out, M, N, K, tiles_m, tiles_n, n_base,
-                                                                            std::max(1, std::min(group_m, tiles_m)), out_fmt, rope ? *rope : RopeArgs{});
+                                                                            gemm_band_rows(tune, BM, BN, smem, tiles_m, tiles_n), out_fmt, rope ? *rope : RopeArgs{});
     return hipGetLastError();
 }
 template <int EPI, int A_FMT>
-static hipError_t launch_feed_fmt(int feed, const bf16 *A, const bf16 *W, void *out, int M, int N, int K, int n_base, int n_cols, int splits, int out_fmt,
+static hipError_t launch_feed_fmt(const GemmTune &tune, int feed, const bf16 *A, const bf16 *W, void *out, int M, int N, int K, int n_base, int n_cols, int splits, int out_fmt,
                                   hipStream_t s, const RopeArgs *rope) {
     switch (feed) {
         case 1:
-            if constexpr (EPI != EPI_SWIGLU) return launch_feed_inst<64, 64, 2, 2, 2, 7, 7, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+            if constexpr (EPI != EPI_SWIGLU) return launch_feed_inst<64, 64, 2, 2, 2, 7, 7, EPI, A_FMT>(tune, A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
             break;                      // (a gate/up column pair needs 64-column wave tiles: feed_cost does not offer it)
-        case 2: return launch_feed_inst<64, 128, 2, 2, 2, 3, 3, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
-        case 3: return launch_feed_inst<128, 128, 4, 2, 4, 5, 5, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
-        case 4: return launch_feed_inst<256, 128, 4, 2, 4, 3, 3, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+        case 2: return launch_feed_inst<64, 128, 2, 2, 2, 3, 3, EPI, A_FMT>(tune, A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+        case 3: return launch_feed_inst<128, 128, 4, 2, 4, 5, 5, EPI, A_FMT>(tune, A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+        case 4: return launch_feed_inst<256, 128, 4, 2, 4, 3, 3, EPI, A_FMT>(tune, A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
         case 5:
             if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32)
-                return launch_feed_inst<256, 192, 2, 4, 4, 3, 2, EPI, A_FMT>(A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+                return launch_feed_inst<256, 192, 2, 4, 4, 3, 2, EPI, A_FMT>(tune, A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
             break;                      // (48-column wave tiles)
     }
     return hipErrorInvalidValue;
 }
 // Columns n_base .. n_base + n_cols - 1 of the N columns.
 template <int EPI>
-static hipError_t launch_feed(int feed, const bf16 *A, const bf16 *W, void *out, int M, int N, int K, int n_base, int n_cols, int splits, int a_fmt, int out_fmt,
-                              hipStream_t s, const RopeArgs *rope = nullptr) {
-    return a_fmt == 2   ? launch_feed_fmt<EPI, 2>(feed, A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope)
-           : a_fmt == 3 ? launch_feed_fmt<EPI, 3>(feed, A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope)
-                        : launch_feed_fmt<EPI, 1>(feed, A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
+static hipError_t launch_feed(const GemmTune &tune, int feed, const bf16 *A, const bf16 *W, void *out, int M, int N, int K, int n_base, int n_cols, int splits,
+                              int a_fmt, int out_fmt, hipStream_t s, const RopeArgs *rope = nullptr) {
+    return a_fmt == 2   ? launch_feed_fmt<EPI, 2>(tune, feed, A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope)
+           : a_fmt == 3 ? launch_feed_fmt<EPI, 3>(tune, feed, A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope)
+                        : launch_feed_fmt<EPI, 1>(tune, feed, A, W, out, M, N, K, n_base, n_cols, splits, out_fmt, s, rope);
 }
 
 // Model of one round of feed tiles over M rows x n_cols columns, nk k-tiles of 64 in s slices, in us; 1e30 where there is no such round.
@@ -960,7 +961,7 @@ static hipError_t launch_epi(const GemmTune &tune, const bf16 *A, const bf16 *W,
                 if (const int f = best_feed(M - m1 * 256, N, nk, EPI, &c)) {
                     hipError_t e = launch_tile<256, 256, 2, 4, 64, 5, EPI>(tune, A, W, out, m1 * 256, N, K, 0, N, a_terms, out_terms, s, nullptr, pf);
                     if (e != hipSuccess) return e;
-                    return launch_feed<EPI>(f, A + (size_t)m1 * 256 * nk * 64, W, reinterpret_cast<float *>(out) + (size_t)m1 * 256 * N, M - m1 * 256, N, K, 0, N,
+                    return launch_feed<EPI>(tune, f, A + (size_t)m1 * 256 * nk * 64, W, reinterpret_cast<float *>(out) + (size_t)m1 * 256 * N, M - m1 * 256, N, K, 0, N,
                                             1, a_terms, out_terms, s);
                 }
             }
@@ -973,7 +974,7 @@ static hipError_t launch_epi(const GemmTune &tune, const bf16 *A, const bf16 *W,
             const int n_tail = N - n1 * 256;
             double c = cost_128(M, n_tail, nk, 1);
             if (const int f = best_feed(M, n_tail, nk, EPI, &c))
-                return launch_feed<EPI>(f, A, W, out, M, N, K, n1 * 256, n_tail, 1, a_terms, out_terms, s);
+                return launch_feed<EPI>(tune, f, A, W, out, M, N, K, n1 * 256, n_tail, 1, a_terms, out_terms, s);
             return launch_tile<128, 128, 2, 2, 64, 2, EPI>(tune, A, W, out, M, N, K, n1 * 256, n_tail, a_terms, out_terms, s);
         }
         return hipSuccess;
@@ -1036,17 +1037,16 @@ static int general_splitk_factor(const GemmTune &tune, int M, int N, int K_total
 // Tile and k slices of a projection: what the two functions above say, or one round of gemm_feed_kernel tiles where the
 // model below has that faster.  Never more slices than above, so that no caller needs more scratch; a long k range over an output
 // that 128 x 128 tiles cover stays as above.
-struct GemmPlan { int feed = 0, splits = 1; bool big = false; };   // feed: index into FEED_TILES, 0 = gemm_bf16_kernel
 // Beyond feed_cost: a reduction of s planes is 3.5 us + their bytes at 4.5 TB/s, written before at 6 TB/s; it normalises the rows on the way
 // where a norm follows, which is a kernel of 4.2 us + 6 bytes per element otherwise.  Whole layer before : after, contexts of 2048, us:
 // width 1536: 192 rows 117 : 95, 384 135 : 110, 512 157 : 126, 768 176 : 151, 1024 198 : 176, 1536 268 : 234, 2304 310 : 302, 6400 (256 x 192
 // tiles for O and down: one round of 200 for 150 of 256 x 256) 727 : 670, 8192 839 : 809; width 5120:
 // 96 rows 283 : 275, 192 368 : 342, 256 397 : 357, 384 532 : 526, 1200 1237 : 1199, 1536 1417 : 1370.
-static GemmPlan gemm_plan(const GemmTune &tune, int M, int N, int K_total, int epi, bool norm_after, bool can_split) {
+GemmPlan gemm_plan(const GemmTune &tune, int M, int N, int K_total, int epi, bool norm_after, bool can_split) {
     GemmPlan p;
     if (tune.tile != 0) return p;
     if (can_split) p.splits = general_splitk_factor(tune, M, N, K_total, &p.big);
-    if (tune.splitk > 0 || M <= 32 || N % 128 != 0) return p;          // (at most 32 rows: tiles of 32 rows)
+    if (tune.splitk > 1 || M <= 32 || N % 128 != 0) return p;          // (at most 32 rows: tiles of 32 rows)
     const int nk = K_total / 64, s_max = p.splits;
     const double mn = (double)M * N;
     auto finish = [&](int s) { return s > 1 ? 3.5 + s * mn * 4 * (1 / 4.5e6 + 1 / 6e6) : mn * 6 / 6e6 + (norm_after ? 4.2 + mn * 6 / 5e6 : 0.0); };
@@ -1268,11 +1268,7 @@ static hipError_t launch_splitk_tiles(const GemmTune &tune, const bf16 *A, const
     if (hipError_t e = set_dynamic_lds_once(attr_done, reinterpret_cast<const void *>(kern), smem); e != hipSuccess) return e;
     int tiles_m = (M + BT - 1) / BT, tiles_n = N / BT;
     dim3 grid(((tiles_m * tiles_n + 7) / 8) * 8, splits);
-    // tile order as in launch_inst: the tiles an XCD works on at one time (its share of the list; every slice of a tile
-    // lands on the same XCD) form a roughly square block, so that they ask the fabric for the fewest operand panels
-    int group_m = tune.group_m;
-    if (group_m <= 0) group_m = (int)std::lround(std::sqrt((double)std::min((tiles_m * tiles_n + 7) / 8, 32 * std::max(160 * 1024 / smem, 1))));
-    group_m = std::max(1, std::min(group_m, tiles_m));
+    const int group_m = gemm_band_rows(tune, BT, BT, smem, tiles_m, tiles_n);   // (every slice of a tile lands on the same XCD)
     kern<<<grid, 128 * WAVES_N, smem, s>>>(A, W, part, M, N, K, tiles_m, tiles_n, 0, group_m, 1, RopeArgs{}, PrefetchArgs{});
     return hipGetLastError();
 }
@@ -1304,7 +1300,7 @@ static GemmPlan plan_with(const GemmTune &tune, int M, int N, int K_total, int e
 static hipError_t launch_splitk_main(const GemmTune &tune, const bf16 *A, const bf16 *W, float *part, int M, int N, int K,
                                      int a_terms, const GemmPlan &p, hipStream_t s) {
     const int splits = p.splits;
-    if (p.feed) return launch_feed<EPI_STORE_F32>(p.feed, A, W, part, M, N, K, 0, N, splits, a_terms, 1, s);
+    if (p.feed) return launch_feed<EPI_STORE_F32>(tune, p.feed, A, W, part, M, N, K, 0, N, splits, a_terms, 1, s);
     if (p.big)
         return a_terms == 2   ? launch_splitk_tiles<2, 256, 4>(tune, A, W, part, M, N, K, splits, s)
                : a_terms == 3 ? launch_splitk_tiles<3, 256, 4>(tune, A, W, part, M, N, K, splits, s)
@@ -1350,9 +1346,9 @@ hipError_t launch_gemm_bf16(const GemmTune &tune, const bf16 *A, const bf16 *W, 
         return hipGetLastError();
     }
     if (p.feed) {
-        if (epi == EPI_STORE_F32) return launch_feed<EPI_STORE_F32>(p.feed, A, W, out, M, N, K, 0, N, 1, a_terms, out_terms, s);
-        if (epi == EPI_RESID_F32) return launch_feed<EPI_RESID_F32>(p.feed, A, W, out, M, N, K, 0, N, 1, a_terms, out_terms, s);
-        return launch_feed<EPI_SWIGLU>(p.feed, A, W, out, M, N, K, 0, N, 1, a_terms, out_terms, s);
+        if (epi == EPI_STORE_F32) return launch_feed<EPI_STORE_F32>(tune, p.feed, A, W, out, M, N, K, 0, N, 1, a_terms, out_terms, s);
+        if (epi == EPI_RESID_F32) return launch_feed<EPI_RESID_F32>(tune, p.feed, A, W, out, M, N, K, 0, N, 1, a_terms, out_terms, s);
+        return launch_feed<EPI_SWIGLU>(tune, p.feed, A, W, out, M, N, K, 0, N, 1, a_terms, out_terms, s);
     }
     if (epi == EPI_STORE_F32) return launch_epi<EPI_STORE_F32>(tune, A, W, out, M, N, K, a_terms, out_terms, s);
     if (epi == EPI_RESID_F32) return launch_epi<EPI_RESID_F32>(tune, A, W, out, M, N, K, a_terms, out_terms, s);
@@ -1371,7 +1367,7 @@ hipError_t launch_gemm_bf16_rope(const GemmTune &tune, const bf16 *A, const bf16
         splitk_reduce_rope_kernel<<<grid, 256, 0, s>>>(splitk_ws, p.splits, M, N, rope);
         return hipGetLastError();
     }
-    if (p.feed) return launch_feed<EPI_ROPE>(p.feed, A, W_perm, nullptr, M, N, K, 0, N, 1, a_terms, 1, s, &rope);
+    if (p.feed) return launch_feed<EPI_ROPE>(tune, p.feed, A, W_perm, nullptr, M, N, K, 0, N, 1, a_terms, 1, s, &rope);
     if (prefer_256_tiles(M, N)) {
         // as in launch_epi: a last round of 256 x 256 tiles that would be less than half full goes to a second launch with
         // 128 x 128 tiles (18606 rows x 2048 columns: 584 tiles = 2 rounds + 72 tiles)
@@ -1388,7 +1384,7 @@ hipError_t launch_gemm_bf16_rope(const GemmTune &tune, const bf16 *A, const bf16
         const int n_tail = N - n1 * 256, nk = K * (a_terms == 2 ? 2 : 1) / 64;
         double c = cost_128(M, n_tail, nk, 1);
         if (const int f = best_feed(M, n_tail, nk, EPI_ROPE, &c))
-            return launch_feed<EPI_ROPE>(f, A, W_perm, nullptr, M, N, K, n1 * 256, n_tail, 1, a_terms, 1, s, &rope);
+            return launch_feed<EPI_ROPE>(tune, f, A, W_perm, nullptr, M, N, K, n1 * 256, n_tail, 1, a_terms, 1, s, &rope);
         return launch_tile<128, 128, 2, 2, 64, 2, EPI_ROPE>(tune, A, W_perm, nullptr, M, N, K, n1 * 256, n_tail, a_terms, 1, s, &rope);
     }
     return launch_tile<128, 128, 2, 2, 64, 2, EPI_ROPE>(tune, A, W_perm, nullptr, M, N, K, 0, N, a_terms, 1, s, &rope);

@@ -328,6 +328,18 @@ int main() {
                         CHECK(M > max_M || cs::gemm_splitk_bytes(g, M, N, nk * 64) <= cs::gemm_splitk_max_bytes(g, max_M, N, nk * 64),
                               "split-K planes of M=%d, N=%d, K=%d exceed those of up to %d rows (short_tile %d)", M, N, nk * 64, max_M, short_tile);
                     }
+    // launch-shape settings reach every tile: a band height that is set is taken, and "never split" changes nothing else
+    for (int iter = 0; iter < 20000; ++iter) {
+        cs::GemmTune g{}, never{};
+        never.splitk = 1;
+        g.group_m = 1 + (int)(rng() % 100);
+        const int tm = 1 + (int)(rng() % 80), tn = 1 + (int)(rng() % 200);
+        CHECK(cs::gemm_band_rows(g, 64, 128, 73728, tm, tn) == std::min(g.group_m, tm), "group_m %d of %d tile rows is not taken", g.group_m, tm);
+        const int M = 1 + (int)(rng() % 12000), N = 128 * (1 + (int)(rng() % 300)), K = 64 * (1 + (int)(rng() % 500)), epi = (int)(rng() % 4);
+        const cs::GemmPlan a = cs::gemm_plan(never, M, N, K, epi, false, true), b = cs::gemm_plan(cs::GemmTune{}, M, N, K, epi, false, false);
+        CHECK(a.splits == 1 && b.splits == 1 && a.feed == b.feed, "never split: M=%d, N=%d, K=%d, epilogue %d on feed tile %d, without scratch on %d", M, N, K, epi,
+              a.feed, b.feed);
+    }
     if (g_fail) { printf("host_check: %d check(s) failed\n", g_fail); return 1; }
     printf("host_check: ok\n");
     return 0;

@@ -180,6 +180,11 @@ hipError_t launch_gemm_bf16(const GemmTune &tune, const bf16 *A, const bf16 *W, 
                             const PrefetchArgs *pf = nullptr, const NormAfter *norm = nullptr, bool *norm_done = nullptr);
 hipError_t launch_gemm_bf16_rope(const GemmTune &tune, const bf16 *A, const bf16 *W_perm, int M, int N, int K, int a_terms,
                                  const RopeArgs &rope, float *splitk_ws, size_t splitk_ws_bytes, hipStream_t s);
+// How a product of M rows runs.  feed: 0 gemm_bf16_kernel, else the tile of gemm_feed_kernel (1 = 64x64, 2 = 64x128, 3 = 128x128,
+// 4 = 256x128, 5 = 256x192); splits: k slices; big: they are 256 x 256 tiles.
+struct GemmPlan { int feed = 0, splits = 1; bool big = false; };
+GemmPlan gemm_plan(const GemmTune &tune, int M, int N, int K_total, int epi, bool norm_after, bool can_split);
+int gemm_band_rows(const GemmTune &tune, int BM, int BN, int smem, int tiles_m, int tiles_n);
 int gemm_splitk_factor(const GemmTune &tune, int M, int N, int K_total);   // of a residual projection with a norm behind it
 size_t gemm_splitk_bytes(const GemmTune &tune, int M, int N, int K_total);
 size_t gemm_splitk_max_bytes(const GemmTune &tune, int max_M, int N, int K_total);   // at least gemm_splitk_bytes for every M <= max_M
