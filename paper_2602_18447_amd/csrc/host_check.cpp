@@ -340,6 +340,31 @@ int main() {
         CHECK(a.splits == 1 && b.splits == 1 && a.feed == b.feed, "never split: M=%d, N=%d, K=%d, epilogue %d on feed tile %d, without scratch on %d", M, N, K, epi,
               a.feed, b.feed);
     }
+    // the GPU tests of gemm_feed_kernel reach every tile, whole and in slices, with these shapes (tests/test_gpu_gemm_feed.py)
+    struct Whole { int M, N, K, feed, feed_swiglu; };
+    for (const Whole &w : {Whole{33, 128, 64, 1, 2}, {64, 256, 128, 1, 2}, {65, 384, 192, 1, 2}, {129, 512, 832, 1, 2}, {255, 2048, 320, 1, 2}, {1290, 2048, 128, 3, 3},
+                           {2040, 2048, 448, 3, 3}, {1921, 2048, 192, 3, 3}, {2600, 2048, 576, 4, 4}, {257, 4096, 1024, 2, 2}, {200, 17920, 448, 4, 4}, {7937, 1536, 576, 5, 0},
+                           {10753, 1536, 192, 0, 0}, {18606, 1536, 320, 0, 0}, {1, 128, 64, 0, 0}, {8, 33024, 320, 0, 0}, {32, 32768, 192, 0, 0}})
+        for (int epi : {cs::EPI_STORE_F32, cs::EPI_RESID_F32, cs::EPI_SWIGLU})
+            for (int terms : {1, 2}) {
+                const cs::GemmPlan p = cs::gemm_plan(cs::GemmTune{}, w.M, w.N, w.K * terms, epi, false, false);
+                CHECK(p.splits == 1 && p.feed == (epi == cs::EPI_SWIGLU ? w.feed_swiglu : w.feed), "M=%d, N=%d, K=%d, epilogue %d: feed tile %d, %d slices", w.M, w.N,
+                      w.K * terms, epi, p.feed, p.splits);
+            }
+    struct Cut { int epi, M, N, K, feed, splits; };   // epi -1: store, residual and SwiGLU
+    for (const Cut &c : {Cut{-1, 33, 256, 1664, 1, 6}, {-1, 65, 3072, 2432, 2, 5}, {-1, 66, 3072, 2944, 3, 8}, {-1, 641, 3072, 2816, 4, 3}, {-1, 769, 3072, 4224, 5, 4},
+                         {cs::EPI_ROPE, 74, 2048, 512, 1, 1}, {cs::EPI_ROPE, 257, 2048, 512, 1, 1}, {cs::EPI_ROPE, 2041, 2048, 512, 3, 1}, {cs::EPI_ROPE, 2600, 2048, 512, 4, 1},
+                         {cs::EPI_ROPE, 641, 1536, 768, 2, 1}, {cs::EPI_ROPE, 65, 1536, 1792, 1, 5}, {cs::EPI_ROPE, 65, 3072, 2816, 2, 5}, {cs::EPI_ROPE, 66, 3072, 3328, 3, 9},
+                         {cs::EPI_ROPE, 641, 3072, 2816, 4, 3}, {cs::EPI_ROPE, 769, 3072, 4096, 5, 4}})
+        for (int epi : {cs::EPI_STORE_F32, cs::EPI_RESID_F32, cs::EPI_SWIGLU, cs::EPI_ROPE})
+            if (c.epi < 0 ? epi != cs::EPI_ROPE : epi == c.epi) {
+                const cs::GemmPlan p = cs::gemm_plan(cs::GemmTune{}, c.M, c.N, c.K, epi, false, true);
+                CHECK(p.feed == c.feed && p.splits == c.splits, "M=%d, N=%d, K=%d, epilogue %d: feed tile %d, %d slices",
+                      c.M, c.N, c.K, epi, p.feed, p.splits);
+            }
+    for (const auto &[d, F] : {std::pair{2048, 6144}, {2176, 6144}, {4224, 4096}, {6144, 16384}})
+        for (int M : {100, 768, 769})
+            CHECK(cs::gemm_plan(cs::GemmTune{}, M, d, F, cs::EPI_RESID_F32, true, true).splits > 1, "down projection %d x %d x %d is not cut", M, d, F);
     if (g_fail) { printf("host_check: %d check(s) failed\n", g_fail); return 1; }
     printf("host_check: ok\n");
     return 0;

@@ -288,7 +288,7 @@ def test_qkv_projection_many_rows_last_round_cut_off(a_terms):
 
 @pytest.mark.parametrize("a_terms,with_lo", [(1, False), (3, False), (2, True)])
 @pytest.mark.parametrize("suffix_lens", [(5, 3, 9), (200, 77, 130)])
-@pytest.mark.parametrize("d", [256, 1024])      # 1024: enough k-tiles for the split-K path at these row counts
+@pytest.mark.parametrize("d", [256, 1024])      # 1024: enough k-tiles for the split-K path at 17 rows
 def test_qkv_projection_with_rotary_epilogue(a_terms, with_lo, suffix_lens, d):
     print(f"qkv + rope fused a_terms={a_terms} lo={with_lo} S={suffix_lens} d={d}", flush=True)
     hd = 128
