@@ -589,7 +589,8 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_pipe_kernel(AttnArgs a, 
 // first layer(s), where score noise from rounding q and k is amplified by every later layer.
 // Within a wavefront a chunk's score product, softmax and value product follow each other, so what overlaps them is a second
 // workgroup on the CU: the second terms of a suffix chunk are staged where the chunk before it was (a load that is waited for, in the few
-// chunks that have them) instead of in stages of their own, and two workgroups fit the LDS and the registers.  Layer with one
+// chunks that have them) instead of in stages of their own, so that two workgroups fit the LDS.  Their 256 registers a lane do not quite
+// do: 11 are spilled (48 bytes a lane; none with one workgroup per CU).  Layer with one
 // workgroup per CU -> two: 32 x 2048 (96 suffix tokens) 225 -> 135 us, 64 x 8192 (128) 1257 -> 872, ragged 128 traces 4022 -> 2471.
 constexpr int K_STRIDE = 136;             // elements per K row in LDS (128 + 8 pad = 272 bytes)
 constexpr int VT_STRIDE = 72;             // elements per V^T row in LDS (64 + 8 pad = 144 bytes)

@@ -124,11 +124,12 @@ bool skinny_shape_ok(const confspec_model_cfg &c, int64_t T) {
     return c.dtype == CONFSPEC_DTYPE_BF16 && T >= 1 && T <= cs::SK_MAX_ROWS && c.n_layers > 0 && c.head_dim == 128 &&
            c.n_q_heads / c.n_kv_heads <= cs::FEW_MAX_G;
 }
-// Rows up to which these kernels are the faster ones.  Every workgroup reads all activations, which grow with rows times
-// width, and the general kernels' tiles fill up with the rows.  Whole layer, general against these (us, one trace of 512 or
-// 1024 keys): width 1536 / 8960, 128 rows 109 : 78; 1792 / 8960, 128 rows 115 : 95; 2048 / 6144 with 8 kv heads, 96 rows 105 : 98,
-// 128 rows 111 : 107, but on 16384 keys 134 : 130 and 142 : 151; 2560 / 9728, 64 rows 126 : 109, 65 rows 128 : 132;
-// 4096 / 14336, 64 rows 187 : 171, 65 rows 189 : 219; 5120 / 27648, 32 rows 259 : 223, 33 rows 264 : 277, 96 rows 303 : 477.
+// Rows up to which a pass takes these kernels.  Every workgroup reads all activations, which grow with rows times width, and the
+// general kernels' tiles fill up with the rows.  The lines were drawn against general kernels without gemm_feed_kernel, which has
+// made those the faster ones earlier at widths of 2048 to 4096.  Whole layer now, general against these (us, HIP graphs, one trace of
+// 512 or 1024 keys): width 1536 / 8960, 128 rows 85 : 74; 2048 / 11008, 64 rows 86 : 83, 65 rows 88 : 102, 96 rows 94 : 105; 2560 / 9728, 32 rows
+// 94 : 80, 33 rows 87 : 93, 64 rows 95 : 101; 4096 / 14336, 32 rows 141 : 119, 33 rows 138 : 144, 64 rows 141 : 156; 5120 / 27648, 32 rows
+// 228 : 210, 33 rows 227 : 266.  So 32 to 64 rows would be the line from width 2048 on; no pass is slower than it was.
 int skinny_max_rows(const confspec_model_cfg &c) { return c.d_model <= 1792 ? cs::SK_MAX_ROWS : c.d_model <= 2048 ? 96 : c.d_model <= 4096 ? 64 : 32; }
 // One new token in every trace (a generation step), as far as its attention is concerned.
 bool one_token_shape(const confspec_model_cfg &c, int64_t T, int64_t B) { return T == B && c.n_q_heads / c.n_kv_heads <= cs::FEW_MAX_G_ONE; }
@@ -928,8 +929,9 @@ static int verify_impl(confspec_ctx *ctx, const confspec_weights *w, const confs
         if (!mlp_norm_done) HIP_TRY(cs::launch_rmsnorm(c.dtype, xr, w->mlp_norm[l], hr, rows, d, c.rms_eps, tm, s));
         // the gate/up projection is compute-bound: while it runs it also pulls the down projection's weights, which
         // that kernel reads in strided pieces, into the last-level cache
-        // (a down projection cut into k slices of 256 x 256 tiles reads whole 128-byte lines of 256 rows at a time and
-        // does not gain from it: config 2 is 0.5 % faster without the hint, the unsplit shapes 0.1-0.2 % slower)
+        // (a down projection that is cut into k slices does not gain from it: 32 x 96 rows of the small model, three slices of
+        // 256 x 256 tiles, are 0.5 % faster without the hint, the unsplit shapes 0.1-0.2 % slower; gate/up on tiles of
+        // gemm_feed_kernel, up to about 250 rows, does not take the hint)
         const bool warm = set.prefetch_down && !(sk && cs::gemm_splitk_factor(set.gemm, rows, d, c.d_ffn * wide) > 1);
         cs::PrefetchArgs pf;
         pf.ptr = warm ? wdn : nullptr;

@@ -593,8 +593,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const
 }
 
 // ---- Outputs of few tiles: loads by wavefronts of their own ----------------------------------------------------------
-// At most one round of workgroups: passes of about 33 to 2000 rows, and the trailing columns of wide outputs.  What bounds the loops
-// above there is a CU on its own: its direct loads take 20 cycles per KiB at the address unit, a wavefront that issues one waits
+// At most one round of workgroups: narrow projections of 33 to about 8192 rows (wide ones to about 250), the trailing columns of
+// wide outputs, and the rows behind whole rounds of 256 x 256 tiles.  What bounds the loops above there is a CU on its own: its
+// direct loads take 20 cycles per KiB at the address unit, a wavefront that issues one waits
 // at it, and its MFMAs wait behind it - a lone 256 x 128 tile of 8 such wavefronts takes 0.73 us per k-tile of 64 for 0.43 us
 // of matrix work.  Here NL wavefronts only load, half of them A and the other half W (memory operations of a wavefront
 // complete in order; the barrier of a k-tile joins them), and the others only multiply: 0.54 us, and 0.36 instead of 0.48 us for a
@@ -873,7 +874,9 @@ static hipError_t launch_feed(const GemmTune &tune, int feed, const bf16 *A, con
 // (from HBM: a wave of loads is then 1.1 us away, from the last-level cache 0.55): a fixed part (launch, first loads, epilogue), and
 // per k-tile a part that grows with u, the share of the CUs that work.  The workgroups of a tile and all its slices sit on one
 // XCD of 32 CUs, so an XCD's share counts: 36 tiles in 7 slices, five tiles to most XCDs, are 35 workgroups there (8960 x 1536,
-// 1536 rows: 69 us with 7 slices of 256 x 256 tiles, 47 with 6).
+// 1536 rows: 69 us with 7 slices of 256 x 256 tiles, 47 with 6).  Widths between and beyond those fitted gain as well: passes of eight
+// layers, 40 .. 11000 rows on contexts of 128, are 1.00 to 1.35 times as fast as before these tiles (and the reductions with more threads) at
+// width 1024, to 1.18 at 2048, 1.20 at 2560, 1.19 at 3584, 1.17 at 4096 and 1.08 at 8192; none of 23 row counts is slower by more than 1 %.
 static double feed_cost(int f, int M, int n_cols, int nk, int s, int epi) {
     const FeedTile &t = FEED_TILES[f];
     if (n_cols % t.bn != 0 || (t.bn < 128 && epi == EPI_SWIGLU) || (t.bn == 192 && epi != EPI_STORE_F32 && epi != EPI_RESID_F32)) return 1e30;
@@ -890,9 +893,9 @@ static int best_feed(int M, int n_cols, int nk, int epi, double *cost) {
     return best;
 }
 
-// Tile ids: 1 = 128x128 / 4 waves, 4 = 256x256 / 8 waves, 7 = 192x96 / 6 waves (2 x 3, wave tile 96 x 32; for
-// N % 96 == 0 and no SwiGLU); all with 64-element k-tiles in 2 stages.  Measured on the draft-model shapes: 4 is the
-// fastest for the wide gate/up projection, 1 or 7 for the others.
+// Tile ids ("gemm_tile"): 1 = 128x128 / 4 waves, two stages; 4 = 256x256 / 8 waves, the ring; 7 = 192x96 / 6 waves (2 x 3, wave tile
+// 96 x 32; for N % 96 == 0 and no SwiGLU), two stages; 64-element k-tiles.  Where gemm_plan names no tile of gemm_feed_kernel, launch_epi takes
+// 4 for outputs of about a round of it and more, 7 for a little over 256 tiles of 128 x 128, else 1.
 // 256 x 256 tiles (one workgroup per CU, rounds of 256) or 128 x 128 tiles (two per CU, rounds of 512) for an output
 // that is not split?  Measured time per k-tile of a round: 1.4 us for the large tile however full the round is; for the
 // small tile 1.1 us for a full round, 0.73 us when every CU holds at most one workgroup, in between linearly.
@@ -1035,13 +1038,15 @@ static int general_splitk_factor(const GemmTune &tune, int M, int N, int K_total
 }
 
 // Tile and k slices of a projection: what the two functions above say, or one round of gemm_feed_kernel tiles where the
-// model below has that faster.  Never more slices than above, so that no caller needs more scratch; a long k range over an output
-// that 128 x 128 tiles cover stays as above.
+// model below has that faster.  Never more slices than above, so that no caller needs more scratch.  A long k range over an output that
+// 128 x 128 tiles cover stays on slices of 256 x 256 tiles: with the other tiles in the choice as well the product takes the same time
+// (3072 x 1536 x 8960 93.0 : 91.7 us, 1100 x 5120 x 27648 327 : 326, 1344 x 4096 x 14336 203 : 204).
 // Beyond feed_cost: a reduction of s planes is 3.5 us + their bytes at 4.5 TB/s, written before at 6 TB/s; it normalises the rows on the way
 // where a norm follows, which is a kernel of 4.2 us + 6 bytes per element otherwise.  Whole layer before : after, contexts of 2048, us:
 // width 1536: 192 rows 117 : 95, 384 135 : 110, 512 157 : 126, 768 176 : 151, 1024 198 : 176, 1536 268 : 234, 2304 310 : 302, 6400 (256 x 192
 // tiles for O and down: one round of 200 for 150 of 256 x 256) 727 : 670, 8192 839 : 809; width 5120:
-// 96 rows 283 : 275, 192 368 : 342, 256 397 : 357, 384 532 : 526, 1200 1237 : 1199, 1536 1417 : 1370.
+// 96 rows 283 : 275, 192 368 : 342, 256 397 : 357, 384 532 : 526, 1200 1237 : 1199, 1536 1417 : 1370.  (256 x 256 tiles stand here in whole
+// rounds, also where launch_epi cuts a short last round off: 1000 rows of the small model's gate/up are 99 us here and 65 measured.)
 GemmPlan gemm_plan(const GemmTune &tune, int M, int N, int K_total, int epi, bool norm_after, bool can_split) {
     GemmPlan p;
     if (tune.tile != 0) return p;
