@@ -233,7 +233,7 @@ def _roofline(entry, state):
     achieved = wk["gate_up"] / (ms * 1e-3) / 1e12
     T, d, F = wl.T, m.d_model, m.d_ffn
     rec = _counter_record(f"gate_up_gemm_config{entry['config']}_l2_miss_counters.json", ["gemm_bf16.hip"])
-    return dict(bound="mfma", kernel="gate/up projection + SwiGLU (256x256 tiles, trailing columns on 128x128 tiles)",
+    return dict(bound="mfma", kernel="gate/up projection + SwiGLU (256x256 tiles, trailing columns on smaller ones)",
                 achieved=round(achieved, 1), peak=PEAK_BF16_TFLOPS, unit="TFLOP/s",
                 frac=round(achieved / PEAK_BF16_TFLOPS, 4),
                 traffic=None if rec is None else rec["l2_miss_bytes_per_launch"], traffic_label=label,
