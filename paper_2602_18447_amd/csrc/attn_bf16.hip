@@ -19,7 +19,7 @@
 //    transposition on the way), V^T fragments come from transposing LDS reads, and the loop is software
 //    pipelined inside each wavefront: the score MFMAs of chunk i+1 are issued between the softmax
 //    instructions of chunk i, so the matrix pipe and the vector ALU of a SIMD work at the same time.
-//  * attn_staged_kernel (the two-term variant of the first layer(s); selectable for measurements): chunks go
+//  * attn_staged_kernel (the two-term variant of the first layer(s), and short items, see launch_attn_bf16): chunks go
 //    through registers, V is transposed with byte permutes on the way into LDS.
 #include "kernels.h"
 #include <type_traits>

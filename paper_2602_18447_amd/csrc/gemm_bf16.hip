@@ -928,7 +928,8 @@ static hipError_t launch_epi(const GemmTune &tune, const bf16 *A, const bf16 *W,
     if (tile == 0) {
         // Wide outputs take 256x256 tiles, one workgroup per CU, in rounds of 256 tiles.  A last round
         // that would be less than half full costs as much as a full one, so those columns are cut off
-        // and done by a second launch with 128x128 tiles (two workgroups per CU), which is shorter.
+        // and done by a second launch with smaller tiles (128x128, two workgroups per CU, or one round of
+        // gemm_feed_kernel's), which is shorter.
         int tm = (M + 255) / 256, tn = N / 256;
         long t256 = (long)tm * tn;
         if (!prefer_256_tiles(M, N)) {
@@ -1375,7 +1376,7 @@ hipError_t launch_gemm_bf16_rope(const GemmTune &tune, const bf16 *A, const bf16
     if (p.feed) return launch_feed<EPI_ROPE>(tune, p.feed, A, W_perm, nullptr, M, N, K, 0, N, 1, a_terms, 1, s, &rope);
     if (prefer_256_tiles(M, N)) {
         // as in launch_epi: a last round of 256 x 256 tiles that would be less than half full goes to a second launch with
-        // 128 x 128 tiles (18606 rows x 2048 columns: 584 tiles = 2 rounds + 72 tiles)
+        // smaller tiles (18606 rows x 2048 columns: 584 tiles = 2 rounds + 72 tiles)
         int tm = (M + 255) / 256, tn = N / 256, n1 = tn;
         long t256 = (long)tm * tn, rounds = t256 / 256;
         if (rounds >= 1 && t256 - rounds * 256 > 0) {

@@ -251,7 +251,7 @@ def _perm_head_rows(n_heads):
 @pytest.mark.parametrize("a_terms", [1, 3])
 def test_qkv_projection_many_rows_last_round_cut_off(a_terms):
     """8448 rows x 2048 columns are 264 tiles of 256 x 256: one full round and a last column of 33 tiles, which the
-    launcher hands to a second launch with 128 x 128 tiles; every element against the oracle's projection + rope."""
+    launcher hands to a second launch with smaller tiles; every element against the oracle's projection + rope."""
     print(f"qkv + rope fused, 8448 rows, a_terms={a_terms}", flush=True)
     hd, d = 128, 256
     wl = W.tiny_workload("qkvwide", 33, dtype="bf16", n_q_heads=12, n_kv_heads=2, head_dim=hd, d_model=d,
@@ -499,7 +499,7 @@ def test_verdict_head_and_gate(dtype):
 @pytest.mark.parametrize("epi", ["store", "resid", "swiglu"])
 def test_gemm_bf16_wide_output_split_into_two_launches(epi):
     """Default tile choice on an output wide enough for 256x256 tiles whose last round of 256 tiles
-    would be nearly empty: the trailing columns go to a second launch with 128x128 tiles."""
+    would be nearly empty: the trailing columns go to a second launch with smaller tiles."""
     print(f"gemm bf16 wide split {epi}", flush=True)
     ctx, _ = _ctx("bf16")
     M, N, K = 700, 256 * 90, 128                      # 3 x 90 tiles of 256: one full round + 14 tiles
