@@ -21,6 +21,10 @@ struct XwgLoads {
         constexpr int SC1 = 1 << 4;
         return __builtin_bit_cast(xwg_f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, SC1));
     }
+    __device__ float2 load2(unsigned off) const {
+        constexpr int SC1 = 1 << 4;
+        return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)off, 0, SC1));
+    }
 };
 // Every thread calls it after its hand-over stores: waits until they are acknowledged, then counts the workgroup in.
 // Returns true (to all threads) for the workgroup that arrives last of n; that one also clears the counter.

@@ -55,3 +55,12 @@ def test_many_q_heads_per_kv_head(hq, suffix):
                          head_dim=128, d_ffn=768, vocab=512, block_size=16, prefix_lens=[70 + 300 * i for i in range(len(suffix))],
                          suffix_lens=suffix, taus=(0.5, 0.55, 0.6, 0.9))
     G.parity_case(wl)
+
+
+# pieces of 256 keys each, which the last workgroup of a tile adds up 12 at a time: one of them, every border of a round, rows taken by
+# all threads (16 heads) or by half of them for the even and the odd pieces (up to 8 heads)
+@pytest.mark.parametrize("heads", ["G5", "G6", "G16"])
+@pytest.mark.parametrize("prefix", [(260,), (12 * 256,), (12 * 256 + 1, 9), (24 * 256, 24 * 256 + 3), (25 * 256 - 15,)], ids=lambda p: f"L{max(p)}")
+def test_pieces_of_one_token(heads, prefix):
+    print(f"pieces of one token: {heads}, prefixes {prefix}", flush=True)
+    G.parity_case(_wl("attn_few_pieces", 9800 + len(prefix), heads, prefix, (1,) * len(prefix)))
