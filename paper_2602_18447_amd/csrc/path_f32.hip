@@ -6,8 +6,8 @@
 // kernels are therefore cut for latency: many small workgroups, every operand requested at once straight into the
 // registers the matrix instruction reads, the k range of a projection and the key range of an attention tile split
 // over the wavefronts of a workgroup, and RMSNorm, rotation, SwiGLU and the residual add done where the operands pass
-// by.  Measured on that model: 487 -> 67 us per pass (12 launches instead of 20; in a kernel trace 3 to 8 us a projection, 10 us
-// the attention).
+// by.  Measured on that model: 487 -> 62 us per pass (12 launches instead of 20; in a kernel trace 3 to 6 us a projection, 8 us
+// the attention; the launches alone take the host about 47 us).
 #include "kernels.h"
 #include <algorithm>
 #include <cfloat>
@@ -158,12 +158,16 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmF32 p) {
     }
 }
 
-// 16 x 16 tiles while they leave the chip room (about eight of their wavefronts per SIMD), 32 x 32 beyond, which read
-// half the operand bytes per flop.  Long k ranges are split over eight wavefronts instead of four.
+// 16 x 16 tiles while they leave the chip room (two of them a CU), 32 x 32 beyond, which read half the operand bytes per flop; eight
+// wavefronts while those are about one to two a CU and a k range of up to 512 is one or two rounds of theirs (128 rows, 256 x 2048, gate/up: 8.1 -> 6.0 us),
+// 16 x 16 up to 2048 tiles for longer ranges.  Long k ranges are split over eight wavefronts instead of four.
 template <int EPI, bool NORM>
 static hipError_t launch_gemm_f32_epi(const GemmF32 &p, hipStream_t s) {
     const long tiles16 = (long)((p.M + 15) / 16) * (p.N / 16);
-    if (tiles16 <= 2048) {
+    if (tiles16 > 512 && tiles16 <= 2048 && p.K <= 512) {
+        const dim3 grid((p.M + 31) / 32, p.N / 32);
+        gemm_f32_kernel<EPI, NORM, 2, 8><<<grid, 512, 0, s>>>(p);
+    } else if (tiles16 <= 2048) {
         const dim3 grid((p.M + 15) / 16, p.N / 16);
         if (p.K >= 512) gemm_f32_kernel<EPI, NORM, 1, 8><<<grid, 512, 0, s>>>(p);
         else gemm_f32_kernel<EPI, NORM, 1, 4><<<grid, 256, 0, s>>>(p);
@@ -191,31 +195,56 @@ hipError_t launch_gemm_f32(const GemmF32 &p, int epi, hipStream_t s) {
 // of its own (online softmax), and merge through LDS in wavefront order at the end.  Scores are computed transposed,
 // S^T = K . Q^T, so a lane owns one query (lane % 16) and ends up holding the probabilities of keys 4 (lane / 16) .. + 3,
 // which is what O^T += V^T . P^T wants of it.
-__device__ __forceinline__ const float *key_row(const AttnArgs &a, const float *pages, const float *suf, int b, int L, int cu_b,
-                                                int c, int j) {
+__device__ __forceinline__ size_t key_block(const AttnArgs &a, int b, int j) {   // block-table index of cached key j (of the last column past it)
+    return (size_t)b * a.max_blocks + min((unsigned)j / (unsigned)a.block_size, (unsigned)a.max_blocks - 1u);
+}
+__device__ __forceinline__ const float *key_row(const AttnArgs &a, const float *pages, const float *suf, int L, int cu_b, int c, int j, int blk) {
     if (j < L) {
-        int blk = a.block_table[(size_t)b * a.max_blocks + j / a.block_size];
         blk = min(max(blk, 0), a.n_blocks - 1);
-        return pages + (((size_t)blk * a.Hkv + c) * a.block_size + (j % a.block_size)) * a.hd;
+        return pages + (((size_t)blk * a.Hkv + c) * a.block_size + (unsigned)j % (unsigned)a.block_size) * a.hd;
     }
     int t = min(cu_b + (j - L), a.T - 1);
     return suf + ((size_t)t * a.Hkv + c) * a.hd;
 }
+// Wave-uniform loads of what no kernel of this launch writes: into scalar registers, apart from the vector memory counter.
+typedef __attribute__((address_space(4))) const int32_t scalar_i32;
+__device__ __forceinline__ int scalar_load(const int32_t *p) { return *(scalar_i32 *)(uintptr_t)p; }
 
-// (Wavefronts per SIMD given: left alone, the branch for values that are not finite takes registers of a wavefront's worth at
-// head size 128; 4 traces of 2048 keys 314 us a pass with three, 329 without that branch and the bound.)
-template <int HD, int NW>
-__global__ __launch_bounds__(64 * NW, HD == 128 ? 3 : 4) void attn_f32_kernel(AttnArgs a) {
-    constexpr int NK = HD / 16;
-    __shared__ float om[NW][16][HD + 1];                  // O of a wavefront, [query][dim]
+// What bounds it is a chain of round trips: lengths, block-table entries, keys and values, once per round of 16 NW keys.  So the
+// entries are asked for before the lengths are known, the next round's before this one's products, twelve wavefronts take 192 keys in a round
+// where the grid leaves a CU to a workgroup, and four of them merge the results, four dims a lane.  Where a tile's keys lie in one block, its entry
+// and address are wave-uniform.  Launch, 4 traces of 128 + 32 keys, 4 heads of 64: 11 -> 7.8 us; whole pass (two layers), 4 traces of 512 + 64: 100 -> 80 us,
+// 16: 155 -> 142, 4 of 2048 + 32 with head size 128: 338 -> 178, the same with blocks of 5: 339 -> 250.
+// (Wavefronts per SIMD given: left alone, the branch for values that are not finite takes registers of a wavefront's worth at head size 128.)
+// PAGE: block_size is a multiple of 16, so the 16 keys of a tile lie in one block.
+template <int HD, int NW, bool PAGE>
+__global__ __launch_bounds__(64 * NW, HD == 128 || NW == 12 ? 3 : 4) void attn_f32_kernel(AttnArgs a) {
+    constexpr int NK = HD / 16, OS = HD + 4;
+    __shared__ __attribute__((aligned(16))) float om[NW][16][OS];       // O of a wavefront, [query][dim]
     __shared__ float mls[NW][2][16];
+    asm volatile("" : : "s"(a.q), "s"(a.ksuf), "s"(a.vsuf), "s"(a.k_pages), "s"(a.v_pages), "s"(a.block_table), "s"(a.cu), "s"(a.plens), "s"(a.out), "s"(a.scale),
+                 "s"(a.block_size), "s"(a.max_blocks), "s"(a.n_blocks), "s"(a.T), "s"(a.Hq), "s"(a.Hkv));
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int fr = lane & 15, fg = lane >> 4;
     const int c = blockIdx.y, G = a.Hq / a.Hkv;
     for (int b = blockIdx.z; b < a.B; b += gridDim.z) {
-        const int cu_b = min(max(a.cu[b], 0), a.T - 1), S = min(max(a.cu[b + 1], cu_b + 1), a.T) - cu_b;
-        const int L = min(max(a.plens[b], 0), a.max_blocks * a.block_size);
+        // Block-table entries of the round to come: one for the 16 keys of a tile, or one for this lane's key and for each of its four values.
+        int blk[PAGE ? 1 : 5];
+        auto fetch_blocks = [&](int j0) __attribute__((always_inline)) {
+            if constexpr (PAGE) {
+                blk[0] = scalar_load(a.block_table + key_block(a, b, j0));
+            } else {
+                blk[0] = a.block_table[key_block(a, b, j0 + fr)];
+    #pragma unroll
+                for (int e = 0; e < 4; ++e) blk[1 + e] = a.block_table[key_block(a, b, j0 + 4 * fg + e)];
+            }
+        };
+        fetch_blocks(16 * wave);
+        const int cu_0 = scalar_load(a.cu + b), cu_1 = scalar_load(a.cu + b + 1), len = scalar_load(a.plens + b);
+        asm volatile("" : : "s"(cu_0), "s"(cu_1), "s"(len));   // (in one round)
+        const int cu_b = min(max(cu_0, 0), a.T - 1), S = min(max(cu_1, cu_b + 1), a.T) - cu_b;
+        const int L = min(max(len, 0), a.max_blocks * a.block_size);
         const int row0 = blockIdx.x * 16, n_rows = G * S;
         if (row0 >= n_rows) continue;                         // a shorter trace (uniform)
         const int r = min(row0 + fr, n_rows - 1), tt = r / G, g = r - tt * G;
@@ -223,20 +252,34 @@ __global__ __launch_bounds__(64 * NW, HD == 128 ? 3 : 4) void attn_f32_kernel(At
         const int n_all = L + min(row0 + 15, n_rows - 1) / G + 1;
         f32x4 q[NK];
         const float *qr = reinterpret_cast<const float *>(a.q) + ((size_t)(cu_b + tt) * a.Hq + c * G + g) * HD + 4 * fg;
-    #pragma unroll
-        for (int i = 0; i < NK; ++i) q[i] = *reinterpret_cast<const f32x4 *>(qr + 16 * i) * a.scale;
         const float *kp = reinterpret_cast<const float *>(a.k_pages), *vp = reinterpret_cast<const float *>(a.v_pages);
         const float *ks = reinterpret_cast<const float *>(a.ksuf), *vs = reinterpret_cast<const float *>(a.vsuf);
         float m = -INFINITY, l = 0.f;
         f32x4 o[NK];
     #pragma unroll
-        for (int i = 0; i < NK; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < NK; ++i) {
+            q[i] = *reinterpret_cast<const f32x4 *>(qr + 16 * i);
+            o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        bool scaled = false;
         for (int j0 = 16 * wave; j0 < n_all; j0 += 16 * NW) {
-            // keys past the last one are clamped to it and masked
-            const float *kr = key_row(a, kp, ks, b, L, cu_b, c, min(j0 + fr, n_all - 1)) + 4 * fg;
-            const float *vr[4];
+            // keys past the last one are clamped to it, which is a suffix token (no entry is used for it), and masked
+            const float *kr, *vr[4];
+            if constexpr (PAGE) {
+                const int bs = a.block_size;
+                const size_t at = (((size_t)min(max(blk[0], 0), a.n_blocks - 1) * a.Hkv + c) * bs + (unsigned)j0 % (unsigned)bs) * HD;
+                auto row = [&](const float *pages, const float *suf, int i) {
+                    const int j = min(j0 + i, n_all - 1);
+                    return j < L ? pages + at + i * HD : suf + ((size_t)min(cu_b + (j - L), a.T - 1) * a.Hkv + c) * HD;
+                };
+                kr = row(kp, ks, fr) + 4 * fg;
     #pragma unroll
-            for (int e = 0; e < 4; ++e) vr[e] = key_row(a, vp, vs, b, L, cu_b, c, min(j0 + 4 * fg + e, n_all - 1)) + fr;
+                for (int e = 0; e < 4; ++e) vr[e] = row(vp, vs, 4 * fg + e) + fr;
+            } else {
+                kr = key_row(a, kp, ks, L, cu_b, c, min(j0 + fr, n_all - 1), blk[0]) + 4 * fg;
+    #pragma unroll
+                for (int e = 0; e < 4; ++e) vr[e] = key_row(a, vp, vs, L, cu_b, c, min(j0 + 4 * fg + e, n_all - 1), blk[1 + e]) + fr;
+            }
             f32x4 k[NK];
             float v[NK][4];
     #pragma unroll
@@ -245,6 +288,12 @@ __global__ __launch_bounds__(64 * NW, HD == 128 ? 3 : 4) void attn_f32_kernel(At
             for (int i = 0; i < NK; ++i)
     #pragma unroll
                 for (int e = 0; e < 4; ++e) v[i][e] = vr[e][16 * i];
+            if (j0 + 16 * NW < n_all) fetch_blocks(j0 + 16 * NW);
+            if (!scaled) {                                                    // (here, behind the first round's loads)
+    #pragma unroll
+                for (int i = 0; i < NK; ++i) q[i] *= a.scale;
+                scaled = true;
+            }
             f32x4 s2[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};      // two chains: the instruction's latency is 8 cycles a link
     #pragma unroll
             for (int i = 0; i < NK; ++i)
@@ -291,7 +340,8 @@ __global__ __launch_bounds__(64 * NW, HD == 128 ? 3 : 4) void attn_f32_kernel(At
                     for (int jj = 0; jj < 16; ++jj) {
                         const int e = jj & 3;
                         const float p = __shfl(e == 0 ? sc[0] : e == 1 ? sc[1] : e == 2 ? sc[2] : sc[3], 16 * (jj >> 2) + fr);
-                        const float *row = key_row(a, vp, vs, b, L, cu_b, c, min(j0 + jj, n_all - 1)) + 4 * fg;
+                        const int jk = min(j0 + jj, n_all - 1);
+                        const float *row = key_row(a, vp, vs, L, cu_b, c, jk, a.block_table[key_block(a, b, jk)]) + 4 * fg;
     #pragma unroll
                         for (int i = 0; i < NK; ++i) {
                             const f32x4 w = *reinterpret_cast<const f32x4 *>(row + 16 * i);
@@ -309,31 +359,32 @@ __global__ __launch_bounds__(64 * NW, HD == 128 ? 3 : 4) void attn_f32_kernel(At
         }
         // o[i][e]: dim 16 i + 4 (lane / 16) + e of query lane % 16
     #pragma unroll
-        for (int i = 0; i < NK; ++i)
-    #pragma unroll
-            for (int e = 0; e < 4; ++e) om[wave][fr][16 * i + 4 * fg + e] = o[i][e];
+        for (int i = 0; i < NK; ++i) *reinterpret_cast<f32x4 *>(&om[wave][fr][16 * i + 4 * fg]) = o[i];
         if (fg == 0) {
             mls[wave][0][fr] = m;
             mls[wave][1][fr] = l;
         }
         __syncthreads();
-        for (int idx = threadIdx.x; idx < 16 * HD; idx += 64 * NW) {
-            const int rr = idx / HD, d = idx % HD;
+        for (int idx = threadIdx.x; idx < 16 * HD / 4; idx += 64 * NW) {
+            const int rr = idx / (HD / 4), d = idx % (HD / 4) * 4;
             if (row0 + rr >= n_rows) continue;
             float M = -INFINITY;
     #pragma unroll
             for (int w = 0; w < NW; ++w) M = fmaxf(M, mls[w][0][rr]);
-            float acc = 0.f, lt = 0.f;
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            float lt = 0.f;
     #pragma unroll
             for (int w = 0; w < NW; ++w) {
                 const float mw = mls[w][0][rr];
+                const f32x4 ow = *reinterpret_cast<const f32x4 *>(&om[w][rr][d]);
                 if (mw == -INFINITY) continue;
                 const float wgt = expf(mw - M);
-                acc += wgt * om[w][rr][d];
+                acc += wgt * ow;
                 lt += wgt * mls[w][1][rr];
             }
             const int t = (row0 + rr) / G;
-            reinterpret_cast<float *>(a.out)[((size_t)(cu_b + t) * a.Hq + c * G + (row0 + rr - t * G)) * HD + d] = acc / lt;
+            *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.out) + ((size_t)(cu_b + t) * a.Hq + c * G + (row0 + rr - t * G)) * HD + d) =
+                f32x4{acc[0] / lt, acc[1] / lt, acc[2] / lt, acc[3] / lt};
         }
         __syncthreads();                                      // om and mls are free for the next trace
     }
@@ -341,8 +392,11 @@ __global__ __launch_bounds__(64 * NW, HD == 128 ? 3 : 4) void attn_f32_kernel(At
 
 hipError_t launch_attn_f32(const AttnArgs &a, int max_S, hipStream_t s) {
     const dim3 grid(((a.Hq / a.Hkv) * max_S + 15) / 16, a.Hkv, std::min(a.B, 32768));
-    if (a.hd == 64) attn_f32_kernel<64, 8><<<grid, 512, 0, s>>>(a);
-    else if (a.hd == 128) attn_f32_kernel<128, 4><<<grid, 256, 0, s>>>(a);
+    const bool page = a.block_size % 16 == 0;
+    auto run = [&](auto kern, auto general, int threads) { (page ? kern : general)<<<grid, threads, 0, s>>>(a); };
+    if (a.hd == 64 && (long)grid.x * grid.y * grid.z <= 256) run(attn_f32_kernel<64, 12, true>, attn_f32_kernel<64, 12, false>, 768);
+    else if (a.hd == 64) run(attn_f32_kernel<64, 8, true>, attn_f32_kernel<64, 8, false>, 512);
+    else if (a.hd == 128) run(attn_f32_kernel<128, 4, true>, attn_f32_kernel<128, 4, false>, 256);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

@@ -15,6 +15,9 @@ pytestmark = pytest.mark.gpu
     ((6, 2), 64, 7, (33, 0), (17, 33)),
     ((4, 1), 128, 16, (16, 5, 300), (1, 31, 40)),
     ((6, 3), 128, 5, (64,), (130,)),
+    ((4, 4), 64, 32, (200, 31), (20, 63)),                                       # 192 keys of a round and past them; a block of two tiles
+    ((4, 4), 64, 48, (47, 0, 90, 16, 33, 1, 49, 96), (130, 20, 64, 5, 97, 33, 80, 70)),      # a grid of more workgroups than CUs, 32 x 32 tiles of narrow outputs
+    ((6, 2), 128, 32, (70, 33), (33, 8)),
 ])
 @pytest.mark.parametrize("d_ffn", [96, 4096])
 def test_fp32_pass_matches_oracle(heads, hd, block, prefix, suffix, d_ffn):
