@@ -4,8 +4,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <functional>
-#include <queue>
 #include <vector>
 
 namespace cs {
@@ -20,6 +18,7 @@ void attn_plan_capacity(const AttnTune &tune, int64_t max_T, int64_t max_B, int 
 namespace {
 struct UnitShape { int tiles, nc; };
 struct Candidate { int cpi, equalize; };
+struct ItemCost { float chunks, fixed; };     // in chunk-times
 
 UnitPlan shape_plan(const UnitShape &t, Candidate cd) {
     UnitPlan p;
@@ -31,15 +30,19 @@ UnitPlan shape_plan(const UnitShape &t, Candidate cd) {
     return p;
 }
 
-// Cost of an item beside its chunks, in chunk-times: filling the pipeline, loading q, writing the result - rows of the
-// output (whole tiles) or fp32 partial results (pieces).  From the uniform 64-trace batch: whole tiles 424 us, halves
-// 411 us + 26 us of merging per layer.
-constexpr float ITEM_OVERHEAD_WHOLE = 6.0f, ITEM_OVERHEAD_PIECE = 8.0f;
+// The model of the planner: an item costs its chunks and a fixed part - filling the pipeline, loading q, writing the result (rows of the
+// output, or fp32 partial results) - and a workgroup alone on its CU runs through its chunks, not its fixed part, 1.4 times as fast as one of
+// two.  Units: the time a workgroup takes for one chunk while its CU holds two (about 2 us).  The constants are those with the smallest loss
+// against the fastest of all candidates over 63 measured batches (1 - 128 traces, contexts to 16384, steps of 8 - 300 tokens, with and
+// without shared contexts, 150 - 19000 tokens in all): a layer then takes 0.4 % longer than with the best candidate on average, 3.4 % at worst.
+// (6 and 8 chunk-times, all of an item 1.5 times as fast alone, 4 for the merge, longer pieces only: 1.5 and 11 %; it left tiles whole that cover half the
+// chip - 12 candidates on contexts of 1211 - 2890, 1317 tokens: 243 us a layer, 221 in pieces.)
+constexpr float ITEM_OVERHEAD_WHOLE = 14.0f, ITEM_OVERHEAD_PIECE = 12.5f;
 
 // Items, partial slots and the largest per-XCD item count of a candidate; lens (optional) receives the
-// per-XCD item costs (chunks + overhead) in dispatch order.  Same arithmetic as the list builder.
+// per-XCD items in dispatch order.  Same arithmetic as the list builder.
 void candidate_counts(const std::vector<UnitShape> &tr, Candidate cd, int64_t n_tiles, int64_t work_total,
-                      AttnPlanCounts *r, std::vector<float> *lens /* [8] */) {
+                      AttnPlanCounts *r, std::vector<ItemCost> *lens /* [8] */) {
     r->n_items = 0; r->n_part_slots = 0; r->max_xcd_items = 0;
     int tile_lo[9] = {0}, seg_base[9] = {0};
     int tile_base = 0, rest_base = 0;
@@ -59,7 +62,11 @@ void candidate_counts(const std::vector<UnitShape> &tr, Candidate cd, int64_t n_
     seg_base[8] = (int)r->n_items;
     for (int x = 0; x < 8; ++x) r->max_xcd_items = std::max<int64_t>(r->max_xcd_items, seg_base[x + 1] - seg_base[x]);
     if (!lens) return;
-    std::vector<float> rest_lens[8];
+    std::vector<ItemCost> rest_lens[8];
+    for (int x = 0; x < 8; ++x) {
+        lens[x].reserve((size_t)r->max_xcd_items);
+        rest_lens[x].reserve((size_t)r->max_xcd_items);
+    }
     int ti = 0;
     for (size_t i = 0; i < tr.size(); ++i)
         for (int j = 0; j < tr[i].tiles; ++j, ++ti) {
@@ -67,74 +74,89 @@ void candidate_counts(const std::vector<UnitShape> &tr, Candidate cd, int64_t n_
             while (x > 0 && tile_lo[x] > ti) --x;
             const UnitPlan &p = plans[i];
             const float ov = p.n_split > 1 ? ITEM_OVERHEAD_PIECE : ITEM_OVERHEAD_WHOLE;
-            lens[x].push_back((float)std::min(p.piece, p.nc_max) + ov);
+            lens[x].push_back({(float)std::min(p.piece, p.nc_max), ov});
             for (int sp = 1; sp < p.n_split; ++sp)
-                rest_lens[x].push_back((float)std::max(0, std::min(p.piece, p.nc_max - sp * p.piece)) + ov);
+                rest_lens[x].push_back({(float)std::max(0, std::min(p.piece, p.nc_max - sp * p.piece)), ov});
         }
     for (int x = 0; x < 8; ++x) lens[x].insert(lens[x].end(), rest_lens[x].begin(), rest_lens[x].end());
 }
 
 // Makespan of the item list of the busiest XCD, in chunk-times (the time a workgroup takes for one chunk while its CU
 // holds two workgroups).  An XCD has slots / 8 workgroup slots, two per CU; items are handed out in list order as
-// slots free up.  A workgroup that has its CU to itself runs faster - measured about 1.5 times - which decides the
-// value of a last round that does not fill the chip: 96 equal items on 64 slots take 1.67 rounds, not 2.
-double simulate(const std::vector<float> *lens, int slots) {
-    constexpr double ALONE = 1.5;
+// slots free up.  A workgroup that has its CU to itself runs faster, which decides the value of a last round that does not fill the chip.
+// A makespan of enough or more is not followed to its end (two workgroups a CU get most done, so the work bounds it from below).
+double simulate(const std::vector<ItemCost> *lens, int slots, double enough) {
+    constexpr double ALONE = 1.4;
     const int n_cu = std::max(1, slots / 16);
     int x_busy = 0;
     double most = -1;
     for (int x = 0; x < 8; ++x) {
         double w = 0;
-        for (float len : lens[x]) w += len;
+        for (const ItemCost &c : lens[x]) w += c.chunks + c.fixed;
         if (w > most) { most = w; x_busy = x; }
     }
-    const std::vector<float> &q = lens[x_busy];
-    std::vector<double> rem(2 * (size_t)n_cu, -1.0);    // remaining work of slot s of CU c at rem[2 c + s]; < 0: empty
+    const std::vector<ItemCost> &q = lens[x_busy];
+    if (most / (2 * n_cu) >= enough) return 1e300;
+    struct Cu { double rem[2], chunks[2], at; int busy; };         // remaining work (down to chunks it is the fixed part; < 0: empty) at time at
+    std::vector<Cu> cus((size_t)n_cu, Cu{{-1.0, -1.0}, {0.0, 0.0}, 0.0, 0});
+    std::vector<double> change((size_t)n_cu, 1e300);     // of a CU: an item done, or the fixed part of one that is alone
     size_t next = 0;
-    // free slots are filled in list order, emptier CUs first (the dispatcher spreads workgroups over the CUs)
-    auto fill = [&]() {
-        while (next < q.size()) {
-            int pick = -1, pick_busy = 3;
-            for (int c = 0; c < n_cu; ++c) {
-                const int busy = (rem[2 * c] >= 0) + (rem[2 * c + 1] >= 0);
-                if (busy < 2 && busy < pick_busy) { pick = rem[2 * c] < 0 ? 2 * c : 2 * c + 1; pick_busy = busy; }
-            }
-            if (pick < 0) break;
-            rem[pick] = (double)q[next++];
-        }
+    auto speed = [&](const Cu &c, int s) { return c.busy == 1 && c.rem[s] <= c.chunks[s] ? ALONE : 1.0; };
+    auto take = [&](Cu &c) {
+        const int s = c.rem[0] < 0 ? 0 : 1;
+        c.chunks[s] = q[next].chunks;
+        c.rem[s] = c.chunks[s] + q[next].fixed;
+        ++c.busy;
+        ++next;
     };
-    fill();
+    auto schedule = [&](int i) {
+        const Cu &c = cus[i];
+        double t = 1e300;
+        for (int s = 0; s < 2; ++s)
+            if (c.rem[s] >= 0) t = std::min(t, c.at + (c.busy == 1 && c.rem[s] > c.chunks[s] ? c.rem[s] - c.chunks[s] : c.rem[s] / speed(c, s)));
+        change[i] = t;
+    };
+    // Items are handed out in list order as slots free up, emptier CUs first (the dispatcher spreads workgroups over the CUs).
+    for (int round = 0; round < 2; ++round)
+        for (int i = 0; i < n_cu && next < q.size(); ++i) take(cus[i]);
+    for (int i = 0; i < n_cu; ++i) schedule(i);
     double now = 0.0;
+    std::vector<int> freed;
     for (;;) {
-        double dt = -1.0;
-        for (int c = 0; c < n_cu; ++c) {
-            const double speed = (rem[2 * c] >= 0 && rem[2 * c + 1] >= 0) ? 1.0 : ALONE;
+        int i = 0;
+        for (int k = 1; k < n_cu; ++k)
+            if (change[k] < change[i]) i = k;
+        if (change[i] == 1e300) break;
+        if (change[i] >= enough) return 1e300;
+        now = change[i];
+        freed.clear();
+        for (int k = i; k < n_cu; ++k) {                 // (items of the same length end together)
+            if (change[k] > now + 1e-9) continue;
+            Cu &c = cus[k];
+            const double step[2] = {(now - c.at) * speed(c, 0), (now - c.at) * speed(c, 1)};
+            c.at = now;
             for (int s = 0; s < 2; ++s)
-                if (rem[2 * c + s] >= 0 && (dt < 0 || rem[2 * c + s] / speed < dt)) dt = rem[2 * c + s] / speed;
-        }
-        if (dt < 0) break;
-        now += dt;
-        for (int c = 0; c < n_cu; ++c) {
-            const double speed = (rem[2 * c] >= 0 && rem[2 * c + 1] >= 0) ? 1.0 : ALONE;
-            for (int s = 0; s < 2; ++s)
-                if (rem[2 * c + s] >= 0) {
-                    rem[2 * c + s] -= dt * speed;
-                    if (rem[2 * c + s] <= 1e-9) rem[2 * c + s] = -1.0;   // done: the slot is free
+                if (c.rem[s] >= 0) {
+                    const bool fixed = c.rem[s] > c.chunks[s];
+                    c.rem[s] -= step[s];
+                    if (fixed && std::abs(c.rem[s] - c.chunks[s]) < 1e-9) c.rem[s] = c.chunks[s];
+                    if (c.rem[s] <= 1e-9) { c.rem[s] = -1.0; --c.busy; }
                 }
+            freed.push_back(k);
         }
-        fill();
+        for (int busy = 0; busy < 2; ++busy)
+            for (int k : freed)
+                if (cus[k].busy == busy && next < q.size()) take(cus[k]);
+        for (int k : freed) schedule(k);
     }
     return now;
 }
 }  // namespace
 
-// Choice of the pieces: equal pieces with a split factor 1..4 of the average tile, or front-loaded
-// pieces of 1.07x / 1.2x the per-slot share of all chunks (and of twice that share: half as many pieces); the
-// candidate with the smallest simulated makespan plus the cost of its merge pass wins.  The merge pass is a launch
-// (about 4 chunk-times) plus the partial results it reads back, 64 KiB written and read per piece: measured 26 us for
-// 1536 pieces and 90 us for about 4000, against about 1.9 us per chunk-time of the attention kernel - 0.01 chunk-times
-// per piece.  (With a flat 8 chunk-times the ragged 128-trace batch was cut into pieces whose merge cost 2.5 ms per
-// pass to save 1 ms of attention.)
+// Choice of the pieces: equal pieces with a split factor 1..4 of the average tile, or front-loaded pieces of the chunks' share of 480, 420,
+// 360, 300 or 240 slots (fewer slots: less to merge, and room for the pieces that tiles of uneven length leave over); the
+// candidate with the smallest simulated makespan plus the cost of its merge pass wins.  The merge pass is a launch plus the partial results it
+// reads back, 64 KiB written and read per piece: measured 26 us for 1536 pieces and 90 us for about 4000 - 0.011 chunk-times per piece.
 AttnPlanCounts attn_plan_counts(const AttnTune &tune, const int32_t *h_cu, const int32_t *h_plens, int B, int T,
                                 const int32_t *h_group_start, int n_units, int G, int Hkv, int last_only) {
     AttnPlanCounts r = {};
@@ -166,17 +188,24 @@ AttnPlanCounts attn_plan_counts(const AttnTune &tune, const int32_t *h_cu, const
             if (sp > 1 && avg / sp < tune.min_chunks) break;
             cands.push_back({equal_cpi(sp), 1});
         }
-        for (double f : {1.07, 1.2, 2.14, 2.4})
+        for (double f : {1.07, 1.22, 1.43, 1.71, 2.14})
             if (front_cpi(f) < nc_longest) cands.push_back({front_cpi(f), 0});
+    }
+    for (size_t i = 1; i < cands.size();) {              // (short lists: several clamp to min_chunks)
+        const bool again = std::any_of(cands.begin(), cands.begin() + i, [&](const Candidate &c) { return c.cpi == cands[i].cpi && c.equalize == cands[i].equalize; });
+        if (again) cands.erase(cands.begin() + i);
+        else ++i;
     }
     double best = 1e300;
     Candidate pick = {1 << 30, 1};
     for (size_t i = 0; i < cands.size(); ++i) {
         AttnPlanCounts c = {};
-        std::vector<float> lens[8];
+        std::vector<ItemCost> lens[8];
         candidate_counts(tr, cands[i], n_tiles, total, &c, lens);
         if (c.n_items > cap_items && cands.size() > 1 && cands[i].cpi != (1 << 30)) continue;
-        double est = simulate(lens, (int)slots) + (c.n_part_slots > 0 ? 4.0 + 0.01 * (double)c.n_part_slots : 0.0);
+        const double merge = c.n_part_slots > 0 ? 3.0 + 0.011 * (double)c.n_part_slots : 0.0;
+        const double even = c.n_part_slots > 0 ? 1.01 : 1.0;     // (whole tiles where it makes no difference)
+        const double est = even * (simulate(lens, (int)slots, best / even - merge) + merge);
         if (est < best) { best = est; pick = cands[i]; }
     }
     r.chunks_per_item = pick.cpi;
