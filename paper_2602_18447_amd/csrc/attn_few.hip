@@ -21,6 +21,7 @@
 #include "kernels.h"
 #include "xwg.h"
 #include <algorithm>
+#include <type_traits>
 
 namespace cs {
 
@@ -419,7 +420,8 @@ __global__ __launch_bounds__(64 * NW, 2) void few_attn_kernel(FewAttn a) {
     }
     if (n_p == 1) return;
     // ---- the pieces of this tile and kv head: the last workgroup to arrive merges them.  A thread has columns 4 c4 .. + 3 of a row (of two where
-    // there are 32) and adds the pieces up in order, 12 or 8 of them in flight; up to 8 rows take half of the threads each for the even and
+    // there are 32) and adds the pieces up in order, 12 or 8 of them in flight, 4 where that is all, weighed by their common maximum (a running one chains
+    // their exponentials: generate one token at 4096 keys, 17 pieces, 1388 -> 1340 us a step); up to 8 rows take half of the threads each for the even and
     // the odd pieces, whose sums meet in LDS.  What bounds it is a round of loads from the memory side (about a microsecond), so the rounds
     // are few and little else is between them and the result: whole launch against wavefronts that took every eighth piece two at a time and met
     // in LDS, one trace of 2048 keys and 96 tokens (5 pieces) 16.8 -> 15.5 us, 32 tokens of 2048 keys (4) 19.0 -> 18.2, one of 4096 (17) 12.9 -> 12.1.
@@ -427,35 +429,44 @@ __global__ __launch_bounds__(64 * NW, 2) void few_attn_kernel(FewAttn a) {
     const bool halves = ONE && rows <= 8;                               // uniform
     const int odd = halves ? tid >> 8 : 0, step = halves ? 2 : 1, row0 = halves ? (tid >> 5) & 7 : tid >> 5;
     const XwgLoads parts(a.part_o + rec0 * ROWS * 128, (unsigned)(n_p * ROWS) * 512u), stats(a.part_ml + rec0 * ROWS * 2, (unsigned)(n_p * ROWS) * 8u);
-    constexpr int FLY = RB == 1 ? 12 : 8;
     float mm[RB], ll[RB];
     f32x4 oo[RB];
 #pragma unroll
     for (int i = 0; i < RB; ++i) { mm[i] = -INFINITY; ll[i] = 0.f; oo[i] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-    for (int pp = odd; pp < n_p; pp += FLY * step) {
-        f32x4 ov[FLY][RB];
-        float2 ml[FLY][RB];
+    auto add_pieces = [&](auto fly) __attribute__((always_inline)) {
+        constexpr int FLY = decltype(fly)::value;
+        for (int pp = odd; pp < n_p; pp += FLY * step) {
+            f32x4 ov[FLY][RB];
+            float2 ml[FLY][RB];
 #pragma unroll
-        for (int q = 0; q < FLY; ++q)
+            for (int q = 0; q < FLY; ++q)
 #pragma unroll
-            for (int i = 0; i < RB; ++i) {
-                const unsigned rec = min(pp + q * step, n_p - 1) * ROWS + min(row0 + 16 * i, rows - 1);
-                ov[q][i] = parts.load4(rec * 512u + c4 * 16u);
-                ml[q][i] = stats.load2(rec * 8u);
-            }
+                for (int i = 0; i < RB; ++i) {
+                    const unsigned rec = min(pp + q * step, n_p - 1) * ROWS + min(row0 + 16 * i, rows - 1);
+                    ov[q][i] = parts.load4(rec * 512u + c4 * 16u);
+                    ml[q][i] = stats.load2(rec * 8u);
+                }
 #pragma unroll
-        for (int q = 0; q < FLY; ++q) {
-            if (pp + q * step >= n_p) break;
+            for (int i = 0; i < RB; ++i) {                                  // (every row sees a key of every piece)
+                float M = mm[i];
 #pragma unroll
-            for (int i = 0; i < RB; ++i) {
-                const float M = fmaxf(mm[i], ml[q][i].x);               // (every row sees a key of every piece)
-                const float wo = exp2_from(mm[i], M), wn = __builtin_amdgcn_exp2f(ml[q][i].x - M);
-                oo[i] = oo[i] * wo + wn * ov[q][i];
-                ll[i] = ll[i] * wo + wn * ml[q][i].y;
+                for (int q = 0; q < FLY; ++q) M = fmaxf(M, ml[q][i].x);     // (past the end: the last piece again)
+                const float wo = exp2_from(mm[i], M);
+                oo[i] *= wo;
+                ll[i] *= wo;
                 mm[i] = M;
+#pragma unroll
+                for (int q = 0; q < FLY; ++q) {
+                    const bool here = pp + q * step < n_p;              // (nothing of the repeated piece: it may hold an infinity)
+                    const float wn = here ? __builtin_amdgcn_exp2f(ml[q][i].x - M) : 0.f;
+                    oo[i] += wn * (here ? ov[q][i] : f32x4{0.f, 0.f, 0.f, 0.f});
+                    ll[i] += here ? wn * ml[q][i].y : 0.f;
+                }
             }
         }
-    }
+    };
+    if (n_p <= 4 * step) add_pieces(std::integral_constant<int, 4>{});
+    else add_pieces(std::integral_constant<int, RB == 1 ? 12 : 8>{});
     if (halves) {
         f32x4 *meet = reinterpret_cast<f32x4 *>(smem);                  // [8 rows][32]
         if (odd == 1) {
