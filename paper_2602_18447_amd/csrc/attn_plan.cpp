@@ -129,9 +129,12 @@ double simulate(const std::vector<ItemCost> *lens, int slots, double enough) {
         if (change[i] == 1e300) break;
         if (change[i] >= enough) return 1e300;
         now = change[i];
+        // What counts as no time: more than rounding leaves of the item whose end now is (some 1e-16 of now), or that item would stay
+        // in its slot with a rest too short to move now, and the loop would not end (makespans from about 1e7 chunk-times on).
+        const double none = std::max(1e-9, 1e-12 * now);
         freed.clear();
         for (int k = i; k < n_cu; ++k) {                 // (items of the same length end together)
-            if (change[k] > now + 1e-9) continue;
+            if (change[k] > now + none) continue;
             Cu &c = cus[k];
             const double step[2] = {(now - c.at) * speed(c, 0), (now - c.at) * speed(c, 1)};
             c.at = now;
@@ -139,8 +142,8 @@ double simulate(const std::vector<ItemCost> *lens, int slots, double enough) {
                 if (c.rem[s] >= 0) {
                     const bool fixed = c.rem[s] > c.chunks[s];
                     c.rem[s] -= step[s];
-                    if (fixed && std::abs(c.rem[s] - c.chunks[s]) < 1e-9) c.rem[s] = c.chunks[s];
-                    if (c.rem[s] <= 1e-9) { c.rem[s] = -1.0; --c.busy; }
+                    if (fixed && std::abs(c.rem[s] - c.chunks[s]) < none) c.rem[s] = c.chunks[s];
+                    if (c.rem[s] <= none) { c.rem[s] = -1.0; --c.busy; }
                 }
             freed.push_back(k);
         }

@@ -3,6 +3,8 @@ arguments before any launch."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -75,6 +77,23 @@ def test_few_row_passes_fit_the_static_scratch_as_other_passes_do(shape, B, S, L
     batch = cb.Batch(B, B * S, 0x1000, 0x1000, 0x1000, as_ptr(cu), as_ptr(lens))     # (only the host arrays are read)
     assert cb.confspec_static_scratch_need(ctx, batch) <= cb.STATIC_SCRATCH_BYTES
     cb.confspec_destroy(ctx)
+
+
+def test_planner_ends_on_the_longest_batches():
+    """Attention's planner simulates a schedule; at makespans where a step in time is lost to rounding it still has to end.  Lengths of
+    millions of keys are far beyond what a pass is run on, but the layout is asked for before anything is checked against memory."""
+    code = ("import numpy as np, ctypes as C\n"
+            "from paper_2602_18447_amd import binding as cb\n"
+            "ctx = cb.confspec_create(cb.make_model_cfg(28, 1536, 12, 2, 128, 8960, 151936, 1e6, 1e-6, 'bf16'))\n"
+            "rng = np.random.default_rng(7)\n"
+            "p = lambda a: a.ctypes.data_as(C.POINTER(C.c_int32))\n"
+            "for top in (1 << 20, 1 << 24, 1 << 30):\n"
+            "    for B in (1, 16, 24):\n"
+            "        lens = rng.integers(top // 2, top, B).astype(np.int32)\n"
+            "        cu = np.concatenate([[0], np.cumsum(rng.integers(1, (1 << 22) // B, B))]).astype(np.int32)\n"
+            "        print(top, B, cb.confspec_static_scratch_need(ctx, cb.Batch(B, int(cu[-1]), 0x1000, 0x1000, 0x1000, p(cu), p(lens))), flush=True)\n")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=60, cwd=ROOT)
+    assert r.returncode == 0 and len(r.stdout.split("\n")) == 10, r.stdout + r.stderr
 
 
 def _no_gpu_here():
