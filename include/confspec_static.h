@@ -16,14 +16,15 @@ extern "C" {
 
 /* Size of the library's own scratch array.  Every GPU the library runs on holds one copy from the time the
  * library is loaded there until the process ends. */
-#define CONFSPEC_STATIC_SCRATCH_BYTES (64u << 20)
+#define CONFSPEC_STATIC_SCRATCH_BYTES (128u << 20)
 
 /* Scratch bytes this batch needs with this context's settings.  Unlike confspec_workspace_bytes, which bounds every
  * batch of up to T tokens in B traces, the figure is for this batch alone (the attention plan's lists and partial
  * results and the split-K planes sized by what its lengths need), computed from the host arrays of `batch`
  * (B, T, h_cu_suffix, h_prefix_lens; the dev pointers are not touched).  confspec_verify_static accepts the batch iff
- * it is <= CONFSPEC_STATIC_SCRATCH_BYTES.  Draft-shaped model (d_model 1536, d_ffn 8960): about 200 suffix tokens,
- * or a one-token-per-trace batch of 64 traces. */
+ * it is <= CONFSPEC_STATIC_SCRATCH_BYTES, and that is so for every batch that needs at most half of it while attention's
+ * tiles are whole: its plan is cut into no more pieces than the rest holds.  Draft-shaped model (d_model 1536, d_ffn 8960): about
+ * 750 suffix tokens. */
 int confspec_static_scratch_need(const confspec_ctx *ctx, const confspec_batch *batch, size_t *out_bytes);
 
 /* confspec_verify without the workspace arguments: same inputs, same outputs, same kernels and launch shapes, bit-identical results.

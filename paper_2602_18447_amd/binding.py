@@ -241,7 +241,7 @@ def confspec_verify_shared(ctx, w: Weights, kv: KV, batch: Batch, group_start, h
                                            _ptr(accept), _stream_handle(stream)))
 
 
-STATIC_SCRATCH_BYTES = 64 << 20
+STATIC_SCRATCH_BYTES = 128 << 20
 
 
 def confspec_static_scratch_need(ctx, batch: Batch) -> int:

@@ -207,7 +207,8 @@ __device__ __forceinline__ void finish_item(const AttnArgs &a, const AttnItem &i
                 }
         }
     } else {
-        size_t row_slot = (size_t)item.part_slot * ATTN_BM + wave * 32 + lq;
+        if (wave * 32 >= a.part_rows) return;                // (no row of any tile is its)
+        size_t row_slot = (size_t)item.part_slot * a.part_rows + wave * 32 + lq;
         if (wave_active) {
             float *po = part_o + row_slot * HD;
 #pragma unroll
@@ -283,8 +284,8 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_pipe_kernel(AttnArgs a, 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (item.chunk_begin >= item.chunk_end) {
         // a piece that received no chunks: mark its rows as "nothing seen" for the merge
-        if (item.part_slot >= 0 && tid < ATTN_BM) {
-            size_t row_slot = (size_t)item.part_slot * ATTN_BM + tid;
+        if (item.part_slot >= 0 && tid < a.part_rows) {
+            size_t row_slot = (size_t)item.part_slot * a.part_rows + tid;
             part_ml[row_slot * 2] = -INFINITY;
             part_ml[row_slot * 2 + 1] = 0.f;
         }
@@ -617,8 +618,8 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_staged_kernel(AttnArgs a
     int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (item.chunk_begin >= item.chunk_end) {
         // a split that received no chunks: mark its rows as "nothing seen" for the merge
-        if (item.part_slot >= 0 && tid < ATTN_BM) {
-            size_t row_slot = (size_t)item.part_slot * ATTN_BM + tid;
+        if (item.part_slot >= 0 && tid < a.part_rows) {
+            size_t row_slot = (size_t)item.part_slot * a.part_rows + tid;
             part_ml[row_slot * 2] = -INFINITY;
             part_ml[row_slot * 2 + 1] = 0.f;
         }
@@ -914,7 +915,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a, const AttnT
     int n_rows = G * (min(max(a.cu[b1], cu_b + 1), a.T) - cu_b);
     const int row = (blockIdx.x % WGS_PER_TILE) * MERGE_ROWS + threadIdx.x / (8 * CLASSES), cls = (threadIdx.x >> 3) & (CLASSES - 1), hv = threadIdx.x & 7;
     const int r = tile.row0 + row;
-    if (r >= n_rows) return;                                 // (the threads of a row leave together)
+    if (r >= n_rows || row >= a.part_rows) return;           // (the threads of a row leave together)
     const int ns = tile.n_splits;
     float m = -INFINITY, l = 0.f;
     float4 o[4];
@@ -937,7 +938,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a, const AttnT
         float2 ml[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const size_t at = (size_t)(tile.part_base + min(s + q * CLASSES, ns - 1)) * ATTN_BM + row;
+            const size_t at = (size_t)(tile.part_base + min(s + q * CLASSES, ns - 1)) * a.part_rows + row;
             ml[q] = *reinterpret_cast<const float2 *>(part_ml + at * 2);
             const float4 *p = reinterpret_cast<const float4 *>(part_o + at * HD + hv * 16);
 #pragma unroll

@@ -161,7 +161,7 @@ double simulate(const std::vector<ItemCost> *lens, int slots, double enough) {
 // candidate with the smallest simulated makespan plus the cost of its merge pass wins.  The merge pass is a launch plus the partial results it
 // reads back, 64 KiB written and read per piece: measured 26 us for 1536 pieces and 90 us for about 4000 - 0.011 chunk-times per piece.
 AttnPlanCounts attn_plan_counts(const AttnTune &tune, const int32_t *h_cu, const int32_t *h_plens, int B, int T,
-                                const int32_t *h_group_start, int n_units, int G, int Hkv, int last_only) {
+                                const int32_t *h_group_start, int n_units, int G, int Hkv, int last_only, int64_t max_part_slots) {
     AttnPlanCounts r = {};
     if (!h_group_start || last_only) n_units = B;
     std::vector<UnitShape> tr;
@@ -175,7 +175,9 @@ AttnPlanCounts attn_plan_counts(const AttnTune &tune, const int32_t *h_cu, const
         total += (int64_t)Hkv * p.n_qt * p.nc_max;
         n_tiles += (int64_t)Hkv * p.n_qt;
         if (p.n_qt > 0) nc_longest = std::max(nc_longest, p.nc_max);
+        r.part_rows = std::max(r.part_rows, last_only ? G : (int)std::min<int64_t>((int64_t)G * u.S_tot, ATTN_BM));
     }
+    r.part_rows = std::min((r.part_rows + 31) / 32 * 32, ATTN_BM);
     r.n_tiles = n_tiles;
     r.total_chunks = total;
     double avg = n_tiles > 0 ? (double)total / (double)n_tiles : 1.0;
@@ -205,7 +207,7 @@ AttnPlanCounts attn_plan_counts(const AttnTune &tune, const int32_t *h_cu, const
         AttnPlanCounts c = {};
         std::vector<ItemCost> lens[8];
         candidate_counts(tr, cands[i], n_tiles, total, &c, lens);
-        if (c.n_items > cap_items && cands.size() > 1 && cands[i].cpi != (1 << 30)) continue;
+        if ((c.n_items > cap_items || c.n_part_slots > max_part_slots) && cands.size() > 1 && cands[i].cpi != (1 << 30)) continue;
         const double merge = c.n_part_slots > 0 ? 3.0 + 0.011 * (double)c.n_part_slots : 0.0;
         const double even = c.n_part_slots > 0 ? 1.01 : 1.0;     // (whole tiles where it makes no difference)
         const double est = even * (simulate(lens, (int)slots, best / even - merge) + merge);

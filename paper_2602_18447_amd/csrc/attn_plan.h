@@ -56,6 +56,9 @@ struct AttnPlanCounts {
     int64_t max_xcd_items;      // largest number of items any of the 8 XCDs gets
     int32_t chunks_per_item;
     int32_t equalize;           // 1: equal pieces per tile, 0: pieces of chunks_per_item, remainder last
+    // Rows that a partial result has room for: those of the largest tile, in wavefronts' shares of 32.  (Of all 128 rows, the partial
+    // results of 200 traces of one to four tokens take 230 MiB.)
+    int32_t part_rows;
 };
 
 CS_HD inline int plan_ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -192,8 +195,9 @@ CS_HD inline void plan_emit_unit(const int32_t *cu, int T, const AttnUnit &u, in
 
 // ---- host planner (attn_plan.cpp) ----
 // Choice of the pieces and the resulting counts.  h_group_start: null, or n_units + 1 trace indices (see plan_unit).
+// Plans of more than max_part_slots partial results are not chosen (whole tiles need none; a forced split factor is taken as it is).
 AttnPlanCounts attn_plan_counts(const AttnTune &tune, const int32_t *h_cu, const int32_t *h_plens, int B, int T,
-                                const int32_t *h_group_start, int n_units, int G, int Hkv, int last_only);
+                                const int32_t *h_group_start, int n_units, int G, int Hkv, int last_only, int64_t max_part_slots = INT64_MAX);
 // Upper bounds used to size the workspace for any batch of up to max_T tokens in max_B traces.
 void attn_plan_capacity(const AttnTune &tune, int64_t max_T, int64_t max_B, int G, int Hkv, int64_t *max_tiles,
                         int64_t *max_items);

@@ -143,11 +143,13 @@ int64_t few_tiles_bound(const confspec_model_cfg &c, int64_t T, int64_t B) {
     return (c.n_q_heads / c.n_kv_heads * T) / cs::few_attn_rows(false) + B;
 }
 
+cs::AttnPlanCounts plan_attention(const confspec_ctx *ctx, const confspec_batch *b, const int32_t *h_group_start, int n_units, bool last_only);
+
 // exact (may be null): lay the workspace out for this batch alone instead of for every batch of up to T tokens in B
 // traces - the attention plans' lists and partial results and the split-K planes are then sized by what this batch's
 // plans and row counts need, which is a small fraction of the general bound (the general bound holds 64 KiB of
-// partial results for each of 3 * tiles + 2048 possible pieces).
-WsLayout ws_layout(const confspec_ctx *ctx, int64_t T, int64_t B, const confspec_batch *exact = nullptr) {
+// partial results for each of 3 * tiles + 2048 possible pieces).  whole: the same with every attention tile in one piece.
+WsLayout ws_layout(const confspec_ctx *ctx, int64_t T, int64_t B, const confspec_batch *exact = nullptr, bool whole = false) {
     const confspec_model_cfg &c = ctx->cfg;
     WsLayout w = {};
     size_t at = 0;
@@ -189,23 +191,29 @@ WsLayout ws_layout(const confspec_ctx *ctx, int64_t T, int64_t B, const confspec
     if (c.dtype == CONFSPEC_DTYPE_BF16) {
         const int G = c.n_q_heads / c.n_kv_heads;
         cs::attn_plan_capacity(ctx->set.attn, T, B, G, c.n_kv_heads, &w.max_tiles, &w.max_items);
-        int64_t part_slots = w.max_items;
+        int64_t part_rows = w.max_items * cs::ATTN_BM;
         cs::AttnPlanCounts pe = {}, pe_last = {};
+        if (exact && whole) {
+            for (int b = 0; b < exact->B; ++b)
+                pe.n_tiles += (int64_t)c.n_kv_heads * cs::plan_ceil_div(G * (exact->h_cu_suffix[b + 1] - exact->h_cu_suffix[b]), cs::ATTN_BM);
+            pe_last.n_tiles = (int64_t)c.n_kv_heads * exact->B;
+            pe.n_items = pe.n_tiles;
+            pe_last.n_items = pe_last.n_tiles;
+        } else if (exact) {
+            pe = plan_attention(ctx, exact, nullptr, 0, false);
+            pe_last = plan_attention(ctx, exact, nullptr, 0, true);
+        }
         if (exact) {
-            pe = cs::attn_plan_counts(ctx->set.attn, exact->h_cu_suffix, exact->h_prefix_lens, exact->B, exact->T, nullptr, 0, G,
-                                      c.n_kv_heads, 0);
-            pe_last = cs::attn_plan_counts(ctx->set.attn, exact->h_cu_suffix, exact->h_prefix_lens, exact->B, exact->T, nullptr,
-                                           0, G, c.n_kv_heads, 1);
             w.max_tiles = std::max<int64_t>(pe.n_tiles, 1);
             w.max_items = std::max<int64_t>(pe.n_items, 1);
-            part_slots = std::max<int64_t>(std::max(pe.n_part_slots, pe_last.n_part_slots), 1);
+            part_rows = std::max<int64_t>(std::max(pe.n_part_slots * pe.part_rows, pe_last.n_part_slots * pe_last.part_rows), 1);
         }
         const size_t general_at = at;
         w.plan_counts = take(256);
         w.plan_tiles = take((size_t)w.max_tiles * sizeof(cs::AttnTile));
         w.plan_items = take((size_t)w.max_items * sizeof(cs::AttnItem));
-        w.part_o_bytes = (size_t)part_slots * cs::ATTN_BM * c.head_dim * 4;
-        w.part_ml_bytes = (size_t)part_slots * cs::ATTN_BM * 2 * 4;
+        w.part_o_bytes = (size_t)part_rows * c.head_dim * 4;
+        w.part_ml_bytes = (size_t)part_rows * 2 * 4;
         w.part_o = take(w.part_o_bytes);
         w.part_ml = take(w.part_ml_bytes);
         // the last layer works on the last position of each trace only: B rows, one attention tile per
@@ -264,6 +272,26 @@ WsLayout ws_layout(const confspec_ctx *ctx, int64_t T, int64_t B, const confspec
     }
     w.total = at;
     return w;
+}
+
+// The plan of an attention launch.  Where every trace is on its own and the batch needs at most half of the library's scratch array
+// with whole tiles, the plan has no more partial results than the rest of the array holds: confspec_verify_static takes every such batch, and
+// every pass over it has the one plan.  The rest is 1000 pieces of 128 rows or 4000 of 32, so this is a guarantee and no trade: a search
+// for the largest plans of 0.9 million such batches on twelve model shapes met it nowhere (124 MiB at most).
+cs::AttnPlanCounts plan_attention(const confspec_ctx *ctx, const confspec_batch *b, const int32_t *h_group_start, int n_units, bool last_only) {
+    const confspec_model_cfg &c = ctx->cfg;
+    auto plan = [&](int64_t max_part_slots) {
+        return cs::attn_plan_counts(ctx->set.attn, b->h_cu_suffix, b->h_prefix_lens, b->B, b->T, h_group_start, n_units,
+                                    c.n_q_heads / c.n_kv_heads, c.n_kv_heads, last_only ? 1 : 0, max_part_slots);
+    };
+    const cs::AttnPlanCounts p = plan(INT64_MAX);
+    constexpr size_t array = CONFSPEC_STATIC_SCRATCH_BYTES, slack = 4 * 256;      // (four slices grow with the pieces)
+    const size_t piece = (size_t)p.part_rows * (c.head_dim + 2) * 4 + 2 * sizeof(cs::AttnItem);
+    if (h_group_start || p.n_part_slots <= (int64_t)((array / 2 - slack) / piece)) return p;
+    const size_t whole = ws_layout(ctx, b->T, b->B, b, true).total;
+    if (whole > array / 2) return p;
+    const int64_t room = (int64_t)((array - whole - slack) / piece);
+    return p.n_part_slots <= room ? p : plan(room);
 }
 
 // Scratch of the full-vocabulary head for B rows: the last rows of the residual stream, their normalised form (two
@@ -441,13 +469,15 @@ int run_front(confspec_ctx *ctx, const confspec_batch *b, int max_L, char *ws, c
 }
 
 // Attention of one layer on an already planned batch; last_only selects the plan of the last positions.
-int run_attention(confspec_ctx *ctx, const cs::AttnArgs &a, char *ws, const WsLayout &L,
+int run_attention(confspec_ctx *ctx, const cs::AttnArgs &in, char *ws, const WsLayout &L,
                   const cs::AttnPlanCounts &pc, bool last_only, int max_S, hipStream_t s) {
     if (ctx->cfg.dtype == CONFSPEC_DTYPE_FP32) {
-        HIP_TRY(cs::launch_attn_f32(a, max_S, s));
+        HIP_TRY(cs::launch_attn_f32(in, max_S, s));
     } else {
         size_t items = last_only ? L.plan2_items : L.plan_items, tiles = last_only ? L.plan2_tiles : L.plan_tiles;
         size_t counts = last_only ? L.plan2_counts : L.plan_counts;
+        cs::AttnArgs a = in;
+        a.part_rows = pc.part_rows;
         HIP_TRY(cs::launch_attn_bf16(ctx->set.attn, a, (const cs::AttnItem *)(ws + items), (const int32_t *)(ws + counts),
                                      (int)pc.n_items, (int)pc.max_xcd_items,
                                      (int)(pc.total_chunks / std::max<int64_t>(pc.n_items, 1)), (float *)(ws + L.part_o),
@@ -471,8 +501,7 @@ int run_attn_plan(confspec_ctx *ctx, const confspec_batch *b, const Groups &gr, 
     const confspec_model_cfg &c = ctx->cfg;
     int G = c.n_q_heads / c.n_kv_heads;
     int64_t cap_tiles = last_only ? L.max_tiles2 : L.max_tiles, cap_items = last_only ? L.max_items2 : L.max_items;
-    *pc = cs::attn_plan_counts(ctx->set.attn, b->h_cu_suffix, b->h_prefix_lens, b->B, b->T, gr.host, gr.n, G, c.n_kv_heads,
-                               last_only ? 1 : 0);
+    *pc = plan_attention(ctx, b, gr.host, gr.n, last_only);
     if (pc->n_tiles > cap_tiles || pc->n_items > cap_items)
         return fail(ctx, CONFSPEC_E_WORKSPACE, "attention plan (%lld tiles, %lld items) exceeds workspace capacity",
                     (long long)pc->n_tiles, (long long)pc->n_items);

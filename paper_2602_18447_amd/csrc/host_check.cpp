@@ -44,6 +44,12 @@ static void check_plan(const cs::AttnTune &tune, const Batch &b, int G, int Hkv,
     CHECK(pc.n_tiles <= cap_tiles && (pc.n_items <= cap_items || tune.force_split != 0),
           "%s: plan %lld tiles %lld items exceeds capacity %lld / %lld", what, (long long)pc.n_tiles, (long long)pc.n_items,
           (long long)cap_tiles, (long long)cap_items);
+    // a limit on the partial results is kept, and changes nothing where the plan keeps it already
+    for (int64_t limit : {(int64_t)0, pc.n_part_slots / 2, pc.n_part_slots}) {
+        const cs::AttnPlanCounts lc = cs::attn_plan_counts(tune, b.cu.data(), b.plens.data(), B, T, gs, n_units, G, Hkv, last_only, limit);
+        CHECK((lc.n_part_slots <= limit || tune.force_split != 0) && (limit < pc.n_part_slots || (lc.chunks_per_item == pc.chunks_per_item && lc.equalize == pc.equalize)),
+              "%s: %lld partial slots with a limit of %lld, %lld without", what, (long long)lc.n_part_slots, (long long)limit, (long long)pc.n_part_slots);
+    }
     // exact-size arrays with guard entries behind them: a write past the counted size is an ASan error
     std::vector<cs::AttnTile> tiles((size_t)std::max<int64_t>(pc.n_tiles, 1));
     std::vector<cs::AttnItem> items((size_t)std::max<int64_t>(pc.n_items, 1));

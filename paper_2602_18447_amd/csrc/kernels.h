@@ -208,6 +208,7 @@ struct AttnArgs {
     int32_t B, T, Hq, Hkv, hd, n_blocks, block_size, max_blocks;
     float scale;            // 1/sqrt(hd)
     int32_t out_terms;
+    int32_t part_rows;      // rows of a partial result (AttnPlanCounts), a multiple of 32 up to ATTN_BM
 };
 hipError_t launch_attn_f32(const AttnArgs &a, int max_S, hipStream_t s);   // max_S: longest suffix of the batch
 
@@ -216,7 +217,8 @@ hipError_t launch_attn_plan(const int32_t *cu, const int32_t *plens, const int32
                             int T, int max_L, int G, int Hkv, int chunks_per_item, int equalize, int last_only,
                             int max_tiles, int max_items, AttnTile *tiles, AttnItem *items,
                             int32_t *counts /*[11]: tiles, items, first item of XCD 0..8*/, hipStream_t s);
-// The attention kernel over the planned items; pieces of split tiles leave fp32 partial results in part_o / part_ml.
+// The attention kernel over the planned items; pieces of split tiles leave fp32 partial results in part_o / part_ml
+// ([slots, a.part_rows, hd] and [slots, a.part_rows, 2]).
 // avg_chunks: average number of key chunks per item (chooses the main loop)
 hipError_t launch_attn_bf16(const AttnTune &tune, const AttnArgs &a, const AttnItem *items, const int32_t *counts,
                             int n_items_host, int max_xcd_items, int avg_chunks, float *part_o, float *part_ml, hipStream_t s);

@@ -68,13 +68,32 @@ def test_workspace_size_is_monotone_and_aligned():
 @pytest.mark.parametrize("shape, B, S, L", [("large", 110, 1, 2048), ("large", 64, 2, 1000), ("large", 96, 1, 2048), ("small", 1, 128, 16384)])
 def test_few_row_passes_fit_the_static_scratch_as_other_passes_do(shape, B, S, L):
     """What only a pass over at most 128 tokens uses lies over what only the others use, so it does not push a batch beyond
-    the library's scratch array (64 MiB) that the others' slices leave inside."""
+    the library's scratch array that the others' slices leave inside."""
     dims = dict(small=dict(n_layers=28, d_model=1536, n_q_heads=12, n_kv_heads=2, d_ffn=8960),
                 large=dict(n_layers=64, d_model=5120, n_q_heads=40, n_kv_heads=8, d_ffn=27648))[shape]
     ctx = cb.confspec_create(_cfg(vocab=151936, **dims))
     cu, lens = np.arange(B + 1, dtype=np.int32) * S, np.full(B, L, dtype=np.int32)
     as_ptr = lambda a: a.ctypes.data_as(C.POINTER(C.c_int32))
     batch = cb.Batch(B, B * S, 0x1000, 0x1000, 0x1000, as_ptr(cu), as_ptr(lens))     # (only the host arrays are read)
+    assert cb.confspec_static_scratch_need(ctx, batch) <= cb.STATIC_SCRATCH_BYTES
+    cb.confspec_destroy(ctx)
+
+
+@pytest.mark.parametrize("shape, B, S, L", [("small", 114, [4], [2410]), ("large", 30, [3], [2322]), ("even", 29, [10], [4404]),
+                                            ("own", 200, [1, 2, 3, 4], [7919 * i % 28000 for i in range(200)]),
+                                            ("own", 89, [1, 2], [32 + 6831 * i % 7084 for i in range(89)])])
+def test_batches_that_fit_the_static_scratch_with_whole_tiles_are_taken(shape, B, S, L):
+    """Partial results of attention do not push a batch beyond the array that its other slices fit: with partial results of 128 rows for tiles
+    of one to 64 the last two, many tiles on contexts of uneven length, took 277 and 125 MiB."""
+    dims = dict(small=dict(n_layers=28, d_model=1536, n_q_heads=12, n_kv_heads=2, d_ffn=8960),
+                large=dict(n_layers=64, d_model=5120, n_q_heads=40, n_kv_heads=8, d_ffn=27648),
+                even=dict(n_layers=24, d_model=2048, n_q_heads=16, n_kv_heads=8, d_ffn=6144),
+                own=dict(n_layers=2, d_model=1024, n_q_heads=8, n_kv_heads=8, d_ffn=4096))[shape]
+    ctx = cb.confspec_create(_cfg(vocab=151936, **dims))
+    cu = np.concatenate([[0], np.cumsum([S[i % len(S)] for i in range(B)])]).astype(np.int32)
+    lens = np.asarray([L[i % len(L)] for i in range(B)], dtype=np.int32)
+    as_ptr = lambda a: a.ctypes.data_as(C.POINTER(C.c_int32))
+    batch = cb.Batch(B, int(cu[-1]), 0x1000, 0x1000, 0x1000, as_ptr(cu), as_ptr(lens))
     assert cb.confspec_static_scratch_need(ctx, batch) <= cb.STATIC_SCRATCH_BYTES
     cb.confspec_destroy(ctx)
 

@@ -83,6 +83,25 @@ def test_second_terms_of_several_suffix_chunks(prefix_lens, suffix_lens, split, 
     assert test_gpu_ops._attention_case("bf16", 12, 2, 128, prefix_lens, suffix_lens, out_terms=2, precise=True) <= 2e-4
 
 
+# partial results with room for 32, 64, 96 and 128 rows (the largest tile's), pieces without chunks among them
+@pytest.mark.parametrize("kernel", [1, 2])
+@pytest.mark.parametrize("suffix_lens", [(1, 5, 2, 1), (1, 9, 2, 10), (3, 1, 16, 11), (17, 1, 21, 2), (1, 22, 64, 3)])
+def test_partial_results_of_few_rows(suffix_lens, kernel, monkeypatch):
+    print(f"attention partial results S={suffix_lens} kernel={kernel}", flush=True)
+    from tests import test_gpu_ops
+
+    def ctx_with_split(*args, **kw):
+        ctx, cfg = _ctx(*args, **kw)
+        for key, val in (("attn_kernel", kernel), ("attn_min_chunks", 1), ("attn_split", 4)):
+            cb.confspec_tune(ctx, key, val)
+        return ctx, cfg
+
+    monkeypatch.setattr(test_gpu_ops, "_ctx", ctx_with_split)
+    # as for other suffixes (tests/test_gpu_ops.py)
+    assert test_gpu_ops._attention_case("bf16", 12, 2, 128, (1700, 64, 900, 0), suffix_lens) <= 6e-3
+    assert test_gpu_ops._attention_case("bf16", 12, 2, 128, (1700, 64, 900, 0), suffix_lens, out_terms=2, precise=True) <= 2e-4
+
+
 def _attend(L, S, seed, split, offset_of_key, spread, value, along, out_terms=1, kernel=2, two_term=False):
     """Attention of suffixes S behind contexts of L keys (a key: offset_of_key(i) score units along u, plus noise; a value: value(noise, key));
     row r of head h of q goes along[(r + h) % len(along)] of u.  Returns the result and the oracle's, [T, Hq, 128]."""

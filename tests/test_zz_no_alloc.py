@@ -59,6 +59,28 @@ def test_static_scratch_pass_equals_workspace_pass_on_two_calls_in_a_row():
     ver.close()
 
 
+@pytest.mark.parametrize("heads, suffix_lens, prefix_lens", [((4, 2), (28,) * 107, (2114,) * 107),
+                                                             ((8, 8), (1, 2) * 44 + (1,), tuple(32 + 6831 * i % 7084 for i in range(89)))])
+def test_static_scratch_pass_equals_workspace_pass_with_many_pieces(heads, suffix_lens, prefix_lens):
+    """Pieces of 64 rows that take half of the array, and some 1300 of 32 rows: both entry points take the same ones."""
+    wl = W.tiny_workload("static_pieces", 5003, dtype="bf16", n_layers=2, d_model=128 * heads[0], n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=128,
+                         d_ffn=1024, vocab=1024, block_size=16, taus=(0.5, 0.9), prefix_lens=prefix_lens, suffix_lens=suffix_lens)
+    ver = Verifier(wl.model, W.make_weights(wl.model, wl.seed, G.DEV))
+    vids, taus = W.draw_verdict_ids(wl), list(wl.taus)
+    batch = W.make_batch(wl, G.DEV)
+    kv = W.make_seeded_kv(wl, batch, G.DEV)
+    need = cb.confspec_static_scratch_need(ver.ctx, ver.bind(kv, batch)[1])
+    print(f"  {heads}: {need} bytes of scratch needed", flush=True)
+    assert need <= cb.STATIC_SCRATCH_BYTES
+    ref = ver.verify(kv, batch, vids, taus)
+    outs = ver.alloc_outputs(wl.B, len(vids), len(taus))
+    ver.verify_static(kv, batch, vids, taus, outs)
+    torch.cuda.synchronize()
+    for got, want in zip(outs, ref):
+        assert torch.equal(got, want)
+    ver.close()
+
+
 def test_static_scratch_refuses_batches_beyond_its_size():
     print("no-allocation entry point: size limit", flush=True)
     wl = _wl("static_limit", 5002, (16,), (8,))
