@@ -6,8 +6,8 @@
 // where a trace brings several suffix tokens, the suffix keys are one more piece, and where it brings one, the first
 // wavefront of the last piece adds that one key.  Inside a workgroup every wavefront walks its own run of 16-token pages,
 // two per round, and keeps its own (max, sum, O): no workgroup barrier before the results are combined.  The workgroup
-// that finishes a tile last merges the pieces, in piece order per wavefront and then in wavefront order, so the result
-// does not depend on which one that is.
+// that finishes a tile last merges the pieces, in piece order (the even and then the odd ones where the rows are few), so the
+// result does not depend on which one that is.
 //
 // Keys and values travel global -> LDS directly, rows of 256 bytes: reading the score product's operand straight from
 // memory instead takes 16 rows per load, four different rows in neighbouring lanes, which the address unit works off
@@ -427,46 +427,53 @@ __global__ __launch_bounds__(64 * NW, 2) void few_attn_kernel(FewAttn a) {
     // in LDS, one trace of 2048 keys and 96 tokens (5 pieces) 16.8 -> 15.5 us, 32 tokens of 2048 keys (4) 19.0 -> 18.2, one of 4096 (17) 12.9 -> 12.1.
     if (!xwg_arrive_last(a.arrived + tile * a.Hkv + h, n_p, &s_last, tid)) return;
     const bool halves = ONE && rows <= 8;                               // uniform
-    const int odd = halves ? tid >> 8 : 0, step = halves ? 2 : 1, row0 = halves ? (tid >> 5) & 7 : tid >> 5;
+    const int odd = halves ? wave >> 2 : 0, step = halves ? 2 : 1, row0 = halves ? (tid >> 5) & 7 : tid >> 5;
     const XwgLoads parts(a.part_o + rec0 * ROWS * 128, (unsigned)(n_p * ROWS) * 512u), stats(a.part_ml + rec0 * ROWS * 2, (unsigned)(n_p * ROWS) * 8u);
     float mm[RB], ll[RB];
     f32x4 oo[RB];
 #pragma unroll
     for (int i = 0; i < RB; ++i) { mm[i] = -INFINITY; ll[i] = 0.f; oo[i] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-    auto add_pieces = [&](auto fly) __attribute__((always_inline)) {
+    // FLY pieces from pp on; last: the final one of them may be past the end
+    auto add_pieces = [&](int pp, auto fly, auto last) __attribute__((always_inline)) {
         constexpr int FLY = decltype(fly)::value;
-        for (int pp = odd; pp < n_p; pp += FLY * step) {
-            f32x4 ov[FLY][RB];
-            float2 ml[FLY][RB];
+        f32x4 ov[FLY][RB];
+        float2 ml[FLY][RB];
 #pragma unroll
-            for (int q = 0; q < FLY; ++q)
+        for (int q = 0; q < FLY; ++q)
 #pragma unroll
-                for (int i = 0; i < RB; ++i) {
-                    const unsigned rec = min(pp + q * step, n_p - 1) * ROWS + min(row0 + 16 * i, rows - 1);
-                    ov[q][i] = parts.load4(rec * 512u + c4 * 16u);
-                    ml[q][i] = stats.load2(rec * 8u);
-                }
+            for (int i = 0; i < RB; ++i) {
+                const unsigned rec = min(pp + q * step, n_p - 1) * ROWS + min(row0 + 16 * i, rows - 1);
+                ov[q][i] = parts.load4(rec * 512u + c4 * 16u);
+                ml[q][i] = stats.load2(rec * 8u);
+            }
 #pragma unroll
-            for (int i = 0; i < RB; ++i) {                                  // (every row sees a key of every piece)
-                float M = mm[i];
+        for (int i = 0; i < RB; ++i) {                                  // (every row sees a key of every piece)
+            float M = mm[i];
 #pragma unroll
-                for (int q = 0; q < FLY; ++q) M = fmaxf(M, ml[q][i].x);     // (past the end: the last piece again)
-                const float wo = exp2_from(mm[i], M);
-                oo[i] *= wo;
-                ll[i] *= wo;
-                mm[i] = M;
+            for (int q = 0; q < FLY; ++q) M = fmaxf(M, ml[q][i].x);     // (past the end: the last piece again)
+            const float wo = exp2_from(mm[i], M);
+            oo[i] *= wo;
+            ll[i] *= wo;
+            mm[i] = M;
 #pragma unroll
-                for (int q = 0; q < FLY; ++q) {
-                    const bool here = pp + q * step < n_p;              // (nothing of the repeated piece: it may hold an infinity)
-                    const float wn = here ? __builtin_amdgcn_exp2f(ml[q][i].x - M) : 0.f;
-                    oo[i] += wn * (here ? ov[q][i] : f32x4{0.f, 0.f, 0.f, 0.f});
-                    ll[i] += here ? wn * ml[q][i].y : 0.f;
-                }
+            for (int q = 0; q < FLY; ++q) {
+                const bool here = !decltype(last)::value || pp + q * step < n_p;      // (nothing of the repeated piece: it may hold an infinity)
+                const float wn = here ? __builtin_amdgcn_exp2f(ml[q][i].x - M) : 0.f;
+                oo[i] += wn * (here ? ov[q][i] : f32x4{0.f, 0.f, 0.f, 0.f});
+                ll[i] += here ? wn * ml[q][i].y : 0.f;
             }
         }
     };
-    if (n_p <= 4 * step) add_pieces(std::integral_constant<int, 4>{});
-    else add_pieces(std::integral_constant<int, RB == 1 ? 12 : 8>{});
+    constexpr int MOST = RB == 1 ? 12 : 8;
+    int pp = odd;
+    for (; pp + (MOST - 1) * step < n_p; pp += MOST * step) add_pieces(pp, std::integral_constant<int, MOST>{}, std::false_type{});
+    // (the rest in a round of about its size: what is loaded for nothing takes its share of the CU's stream,
+    // too: 33 pieces of 32 rows read as 40, four layers of 1536 x 8960, 3 x 5 tokens of 16000 keys, 273 us, as 34 265; 17 as 24, 32 tokens of 8000 keys, 255, as 18 246)
+    const int left = (n_p - pp + step - 1) / step;
+    if (left > (RB == 1 ? 8 : 6)) add_pieces(pp, std::integral_constant<int, MOST>{}, std::true_type{});
+    else if (left > 4) add_pieces(pp, std::integral_constant<int, RB == 1 ? 8 : 6>{}, std::true_type{});
+    else if (left > 2) add_pieces(pp, std::integral_constant<int, 4>{}, std::true_type{});
+    else if (left > 0) add_pieces(pp, std::integral_constant<int, 2>{}, std::true_type{});
     if (halves) {
         f32x4 *meet = reinterpret_cast<f32x4 *>(smem);                  // [8 rows][32]
         if (odd == 1) {
