@@ -323,11 +323,19 @@ __global__ __launch_bounds__(64 * NW, EPI == SK_EPI_SWIGLU && MB * CT == 1 && NB
     // weights that are to stay in flight.
     if constexpr (NBUF == 1 && D == 1 && CT >= 4) {
         // A group's operands go to registers before they are multiplied, so that the next group's weights are on their way meanwhile; its
-        // activations follow as the registers of a row block become free (gate/up of 96 rows, 55 MB: 19.6 -> 19.0 us, the reduction in two passes
-        // instead of three included).
-        bf16x8 xf[D][MB][2];
+        // activations follow as the registers of a row block become free.  Whole pass of four layers, graphs, with the wait for the activations behind
+        // the next weights and as it is: 1536 / 8960, 96 rows 274.0 -> 271.2 us, 2048 / 11008, 64 rows 362.0 -> 356.5, 4096 / 14336 (two layers), 64 rows 364.5 -> 359.9.
+        bf16x8 xf[MB][2];
+        unsigned f16 = (unsigned)fr * 16u;
+        auto load_block = [&](int g, int i) __attribute__((always_inline)) {         // (its offset is made here: six of them kept take registers that six
+            const unsigned off = (unsigned)fg * 256u + min(f16, (unsigned)max(M - 1 - 16 * i, 0) * 16u);     // row blocks do not have)
+            const char *xb = xbase + (size_t)i * (a.K >> 5) * 1024 + (unsigned)(kt0 + wave + NW * g) * 2048u;
+            xf[i][0] = *reinterpret_cast<const bf16x8 *>(xb + off);
+            xf[i][1] = *reinterpret_cast<const bf16x8 *>(xb + off + 1024);
+        };
         if (n_grp > 0) {
-            load_x(0, xf);
+#pragma unroll
+            for (int i = 0; i < MB; ++i) load_block(0, i);
             issue_w(0);
         }
         for (int g = 0; g < n_grp; ++g) {
@@ -338,20 +346,26 @@ __global__ __launch_bounds__(64 * NW, EPI == SK_EPI_SWIGLU && MB * CT == 1 && NB
             for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
                 for (int q = 0; q < CT; ++q) wf[ks][q] = *reinterpret_cast<const bf16x8 *>(ring + q * 2048 + w_frag[ks]);
-            asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+            // Here the compiler's own waits for the activations belong: it counts those loads only, so behind the next group's direct
+            // loads a wait for them would cover these, too.
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    f32x4 x = __builtin_bit_cast(f32x4, xf[i][ks]);
+                    asm volatile("" : "+v"(x));
+                    xf[i][ks] = __builtin_bit_cast(bf16x8, x);
+                }
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f16) : : "memory");
             const bool more = g + 1 < n_grp;                               // wave-uniform
             if (more) issue_w(g + 1);
-            const char *xb = xbase + (unsigned)(kt0 + wave + NW * (g + 1)) * 2048u;
 #pragma unroll
             for (int i = 0; i < MB; ++i) {
 #pragma unroll
                 for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-                    for (int q = 0; q < CT; ++q) acc[i][q] = mma16<F16>(wf[ks][q], xf[0][i][ks], acc[i][q]);
-                if (more) {
-                    xf[0][i][0] = *reinterpret_cast<const bf16x8 *>(xb + xoff[i]);
-                    xf[0][i][1] = *reinterpret_cast<const bf16x8 *>(xb + xoff[i] + 1024);
-                }
+                    for (int q = 0; q < CT; ++q) acc[i][q] = mma16<F16>(wf[ks][q], xf[i][ks], acc[i][q]);
+                if (more) load_block(g + 1, i);
             }
         }
     } else if constexpr (NBUF == 1) {
