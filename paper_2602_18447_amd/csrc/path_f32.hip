@@ -214,11 +214,13 @@ __device__ __forceinline__ int scalar_load(const int32_t *p) { return *(scalar_i
 // entries are asked for before the lengths are known, the next round's before this one's products, twelve wavefronts take 192 keys in a round
 // where the grid leaves a CU to a workgroup, and four of them merge the results, four dims a lane.  Where a tile's keys lie in one block, its entry
 // and address are wave-uniform.  Launch, 4 traces of 128 + 32 keys, 4 heads of 64: 11 -> 7.8 us; whole pass (two layers), 4 traces of 512 + 64: 100 -> 80 us,
-// 16: 155 -> 142, 4 of 2048 + 32 with head size 128: 338 -> 178, the same with blocks of 5: 339 -> 250.
-// (Wavefronts per SIMD given: left alone, the branch for values that are not finite takes registers of a wavefront's worth at head size 128.)
+// 16: 155 -> 142; head size 128, 32 of 2048 + 32, 4 / 2 heads: 568 -> 367, the same with blocks of 5: 600 -> 392.
+// (Wavefronts per SIMD given: left alone, the branch for values that are not finite takes registers of a wavefront's worth.  At head size 128 it
+// is two, 174 and 185 registers: with three, 168, keys asked for ahead and addresses spilled, 20 and 48 bytes - 367 and 426 us in those two cases, 16 of
+// 4096 + 100 with 2 / 2 heads and blocks of 5 584 for 506.)
 // PAGE: block_size is a multiple of 16, so the 16 keys of a tile lie in one block.
 template <int HD, int NW, bool PAGE>
-__global__ __launch_bounds__(64 * NW, HD == 128 || NW == 12 ? 3 : 4) void attn_f32_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * NW, HD == 128 ? 2 : NW == 12 ? 3 : 4) void attn_f32_kernel(AttnArgs a) {
     constexpr int NK = HD / 16, OS = HD + 4;
     __shared__ __attribute__((aligned(16))) float om[NW][16][OS];       // O of a wavefront, [query][dim]
     __shared__ float mls[NW][2][16];
