@@ -158,9 +158,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmF32 p) {
     }
 }
 
-// 16 x 16 tiles while they leave the chip room (two of them a CU), 32 x 32 beyond, which read half the operand bytes per flop; eight
-// wavefronts while those are about one to two a CU and a k range of up to 512 is one or two rounds of theirs (128 rows, 256 x 2048, gate/up: 8.1 -> 6.0 us),
-// 16 x 16 up to 2048 tiles for longer ranges.  Long k ranges are split over eight wavefronts instead of four.
+// 16 x 16 tiles while they leave the chip room (up to two of them a CU), 32 x 32 beyond, which read half the operand bytes per flop.  Those have
+// eight wavefronts while they are about half of one to two a CU (513 to 2048 tiles of 16 x 16) and a k range of up to 512 is one or two rounds
+// of theirs: 128 rows, 256 x 2048, gate/up, 8.1 -> 6.0 us.  The line is the right one in the lower half, too, though not every CU has a tile there - whole pass
+// of two layers, 16 x 16 against 32 x 32 from 513 tiles on: 640 tiles (80 rows, 2048 columns) at K 256 61.0 : 58.2 us, at K 512 71.6 : 68.8, 896 tiles at
+// K 512 79.3 : 72.7, 832 tiles (208 rows, 1024 columns, the QKV of 624 with it) at K 256 64.7 : 60.8; nowhere slower between 513 and 1023.  Longer k ranges:
+// 16 x 16 up to 2048 tiles, k split over eight wavefronts instead of four.
 template <int EPI, bool NORM>
 static hipError_t launch_gemm_f32_epi(const GemmF32 &p, hipStream_t s) {
     const long tiles16 = (long)((p.M + 15) / 16) * (p.N / 16);

@@ -18,6 +18,7 @@ pytestmark = pytest.mark.gpu
     ((4, 4), 64, 32, (200, 31), (20, 63)),                                       # 192 keys of a round and past them; a block of two tiles
     ((4, 4), 64, 48, (47, 0, 90, 16, 33, 1, 49, 96), (130, 20, 64, 5, 97, 33, 80, 70)),      # a grid of more workgroups than CUs, 32 x 32 tiles of narrow outputs
     ((6, 2), 128, 32, (70, 33), (33, 8)),
+    ((4, 4), 64, 7, (47, 0, 90, 16, 33, 1, 49, 300), (130, 20, 64, 5, 97, 33, 80, 70)),      # such a grid, blocks that do not divide a tile
 ])
 @pytest.mark.parametrize("d_ffn", [96, 4096])
 def test_fp32_pass_matches_oracle(heads, hd, block, prefix, suffix, d_ffn):
