@@ -988,9 +988,10 @@ hipError_t launch_attn_bf16(const AttnTune &tune, const AttnArgs &a, const AttnI
     if (precise) return launch_staged<true>(a, items, counts, n_items_host, max_xcd_items, part_o, part_ml, s);
     // Short items (one-token batches cut into pieces of a few chunks): the pipelined loop's prologue and epilogue -
     // three chunk loads and an unoverlapped score product before the first iteration - weigh more than its steady
-    // state gains; the register-staged loop is the faster one there (22.5 against 30.8 us per layer at 32 x 2048).  The line at 10
-    // chunks loses least over the batches that the planner's constants are fitted to (8, 10, 12, 14 and 16 compared).
-    if (tune.kernel == 1 || (tune.kernel == 0 && avg_chunks < 10))
+    // state gains; the register-staged loop is the faster one there (22.5 against 30.8 us per layer at 32 x 2048).  The line at 10 chunks is where the
+    // two meet with full tiles (1000 random batches on five head layouts: staged 2 % faster below 8, 2 - 3 % slower from 12 to 18, 22 % above 80).  Tiles with
+    // less than 60 % of their rows on a full chip would have it at about 50: staged is 2 - 7 % faster up to there.
+    if (tune.kernel == 1 || (tune.kernel == 0 && avg_chunks < ATTN_STAGED_BELOW))
         return launch_staged<false>(a, items, counts, n_items_host, max_xcd_items, part_o, part_ml, s);
     static std::atomic<uint32_t> attr_done{0};
     if (hipError_t e = set_dynamic_lds_once(attr_done, reinterpret_cast<const void *>(attn_pipe_kernel), PIPE_SMEM_BYTES);

@@ -18,7 +18,6 @@ void attn_plan_capacity(const AttnTune &tune, int64_t max_T, int64_t max_B, int 
 namespace {
 struct UnitShape { int tiles, nc; };
 struct Candidate { int cpi, equalize; };
-struct ItemCost { float chunks, fixed; };     // in chunk-times
 
 UnitPlan shape_plan(const UnitShape &t, Candidate cd) {
     UnitPlan p;
@@ -34,15 +33,18 @@ UnitPlan shape_plan(const UnitShape &t, Candidate cd) {
 // output, or fp32 partial results) - and a workgroup alone on its CU runs through its chunks, not its fixed part, 1.4 times as fast as one of
 // two.  Units: the time a workgroup takes for one chunk while its CU holds two (about 2 us).  The constants are those with the smallest loss
 // against the fastest of all candidates over 63 measured batches (1 - 128 traces, contexts to 16384, steps of 8 - 300 tokens, with and
-// without shared contexts, 150 - 19000 tokens in all): a layer then takes 0.4 % longer than with the best candidate on average, 3.4 % at worst.
-// (6 and 8 chunk-times, all of an item 1.5 times as fast alone, 4 for the merge, longer pieces only: 1.5 and 11 %; it left tiles whole that cover half the
-// chip - 12 candidates on contexts of 1211 - 2890, 1317 tokens: 243 us a layer, 221 in pieces.)
+// without shared contexts, 150 - 19000 tokens in all), all with 12 q heads on 2 kv heads: there a layer takes 0.4 % longer than with the best candidate on
+// average, 3.4 % at worst, which says how well it fits and no more.  On 200 other batches (profiles/attention_plans_of_random_batches.txt, attention and
+// little else in a layer) it is 3.0 % on average and 18 % at worst: 1.8 with 12/2 heads, 2.2 with 40/8, 2.6, 3.9 and 4.4 with 32/8, 16/8 and 8/8.  1.3 points of that are the
+// choice of the loop; the rest is mostly tiles of few rows, whose keys no other tile reads: such a batch is bound by its stream of keys, and cutting 200 to 256
+// of them in two gains nothing.  (6 and 8 chunk-times, all of an item 1.5 times as fast alone, 4 for the merge, longer pieces only: 4.2 % there; it left tiles
+// whole that cover half the chip - 12 candidates on contexts of 1211 - 2890, 1317 tokens: 243 us a layer, 221 in pieces.)
 constexpr float ITEM_OVERHEAD_WHOLE = 14.0f, ITEM_OVERHEAD_PIECE = 12.5f;
 
 // Items, partial slots and the largest per-XCD item count of a candidate; lens (optional) receives the
 // per-XCD items in dispatch order.  Same arithmetic as the list builder.
 void candidate_counts(const std::vector<UnitShape> &tr, Candidate cd, int64_t n_tiles, int64_t work_total,
-                      AttnPlanCounts *r, std::vector<ItemCost> *lens /* [8] */) {
+                      AttnPlanCounts *r, std::vector<AttnItemCost> *lens /* [8] */) {
     r->n_items = 0; r->n_part_slots = 0; r->max_xcd_items = 0;
     int tile_lo[9] = {0}, seg_base[9] = {0};
     int tile_base = 0, rest_base = 0;
@@ -62,7 +64,7 @@ void candidate_counts(const std::vector<UnitShape> &tr, Candidate cd, int64_t n_
     seg_base[8] = (int)r->n_items;
     for (int x = 0; x < 8; ++x) r->max_xcd_items = std::max<int64_t>(r->max_xcd_items, seg_base[x + 1] - seg_base[x]);
     if (!lens) return;
-    std::vector<ItemCost> rest_lens[8];
+    std::vector<AttnItemCost> rest_lens[8];
     for (int x = 0; x < 8; ++x) {
         lens[x].reserve((size_t)r->max_xcd_items);
         rest_lens[x].reserve((size_t)r->max_xcd_items);
@@ -81,26 +83,33 @@ void candidate_counts(const std::vector<UnitShape> &tr, Candidate cd, int64_t n_
     for (int x = 0; x < 8; ++x) lens[x].insert(lens[x].end(), rest_lens[x].begin(), rest_lens[x].end());
 }
 
-// Makespan of the item list of the busiest XCD, in chunk-times (the time a workgroup takes for one chunk while its CU
-// holds two workgroups).  An XCD has slots / 8 workgroup slots, two per CU; items are handed out in list order as
-// slots free up.  A workgroup that has its CU to itself runs faster, which decides the value of a last round that does not fill the chip.
-// A makespan of enough or more is not followed to its end (two workgroups a CU get most done, so the work bounds it from below).
-double simulate(const std::vector<ItemCost> *lens, int slots, double enough) {
-    constexpr double ALONE = 1.4;
-    const int n_cu = std::max(1, slots / 16);
+// Makespan of the item list of the busiest XCD.
+double simulate(const std::vector<AttnItemCost> *lens, int slots, double enough) {
     int x_busy = 0;
     double most = -1;
     for (int x = 0; x < 8; ++x) {
         double w = 0;
-        for (const ItemCost &c : lens[x]) w += c.chunks + c.fixed;
+        for (const AttnItemCost &c : lens[x]) w += c.chunks + c.fixed;
         if (w > most) { most = w; x_busy = x; }
     }
-    const std::vector<ItemCost> &q = lens[x_busy];
-    if (most / (2 * n_cu) >= enough) return 1e300;
+    return attn_plan_makespan(lens[x_busy].data(), (int64_t)lens[x_busy].size(), slots, enough);
+}
+}  // namespace
+
+// In chunk-times (the time a workgroup takes for one chunk while its CU holds two workgroups).  An XCD has slots / 8 workgroup slots, two per
+// CU; items are handed out in list order as slots free up.  A workgroup that has its CU to itself runs faster, which decides the value of a last
+// round that does not fill the chip.  A makespan of enough or more is not followed to its end (two workgroups a CU get most done, so the work
+// bounds it from below).
+double attn_plan_makespan(const AttnItemCost *q, int64_t n, int slots, double enough) {
+    constexpr double ALONE = 1.4;
+    const int n_cu = std::max(1, slots / 16);
+    double work = 0;
+    for (int64_t i = 0; i < n; ++i) work += q[i].chunks + q[i].fixed;
+    if (work / (2 * n_cu) >= enough) return 1e300;
     struct Cu { double rem[2], chunks[2], at; int busy; };         // remaining work (down to chunks it is the fixed part; < 0: empty) at time at
     std::vector<Cu> cus((size_t)n_cu, Cu{{-1.0, -1.0}, {0.0, 0.0}, 0.0, 0});
     std::vector<double> change((size_t)n_cu, 1e300);     // of a CU: an item done, or the fixed part of one that is alone
-    size_t next = 0;
+    int64_t next = 0;
     auto speed = [&](const Cu &c, int s) { return c.busy == 1 && c.rem[s] <= c.chunks[s] ? ALONE : 1.0; };
     auto take = [&](Cu &c) {
         const int s = c.rem[0] < 0 ? 0 : 1;
@@ -118,7 +127,7 @@ double simulate(const std::vector<ItemCost> *lens, int slots, double enough) {
     };
     // Items are handed out in list order as slots free up, emptier CUs first (the dispatcher spreads workgroups over the CUs).
     for (int round = 0; round < 2; ++round)
-        for (int i = 0; i < n_cu && next < q.size(); ++i) take(cus[i]);
+        for (int i = 0; i < n_cu && next < n; ++i) take(cus[i]);
     for (int i = 0; i < n_cu; ++i) schedule(i);
     double now = 0.0;
     std::vector<int> freed;
@@ -149,12 +158,11 @@ double simulate(const std::vector<ItemCost> *lens, int slots, double enough) {
         }
         for (int busy = 0; busy < 2; ++busy)
             for (int k : freed)
-                if (cus[k].busy == busy && next < q.size()) take(cus[k]);
+                if (cus[k].busy == busy && next < n) take(cus[k]);
         for (int k : freed) schedule(k);
     }
     return now;
 }
-}  // namespace
 
 // Choice of the pieces: equal pieces with a split factor 1..4 of the average tile, or front-loaded pieces of the chunks' share of 480, 420,
 // 360, 300 or 240 slots (fewer slots: less to merge, and room for the pieces that tiles of uneven length leave over); the
@@ -205,7 +213,7 @@ AttnPlanCounts attn_plan_counts(const AttnTune &tune, const int32_t *h_cu, const
     Candidate pick = {1 << 30, 1};
     for (size_t i = 0; i < cands.size(); ++i) {
         AttnPlanCounts c = {};
-        std::vector<ItemCost> lens[8];
+        std::vector<AttnItemCost> lens[8];
         candidate_counts(tr, cands[i], n_tiles, total, &c, lens);
         if ((c.n_items > cap_items || c.n_part_slots > max_part_slots) && cands.size() > 1 && cands[i].cpi != (1 << 30)) continue;
         const double merge = c.n_part_slots > 0 ? 3.0 + 0.011 * (double)c.n_part_slots : 0.0;

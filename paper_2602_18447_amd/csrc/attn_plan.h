@@ -42,6 +42,7 @@ constexpr int ATTN_BM = 128;      // q rows per tile: 4 wavefronts x 32 rows
 constexpr int ATTN_THREADS = 256;
 constexpr int ATTN_BN = 64;       // keys per chunk
 constexpr int ATTN_MAX_SPLIT = 32;
+constexpr int ATTN_STAGED_BELOW = 10;   // average chunks of an item from which on the software-pipelined main loop is taken (attn_bf16.hip)
 
 struct AttnTune {
     int target_items = 512;   // concurrent workgroup slots the planner assumes
@@ -198,6 +199,10 @@ CS_HD inline void plan_emit_unit(const int32_t *cu, int T, const AttnUnit &u, in
 // Plans of more than max_part_slots partial results are not chosen (whole tiles need none; a forced split factor is taken as it is).
 AttnPlanCounts attn_plan_counts(const AttnTune &tune, const int32_t *h_cu, const int32_t *h_plens, int B, int T,
                                 const int32_t *h_group_start, int n_units, int G, int Hkv, int last_only, int64_t max_part_slots = INT64_MAX);
+// The schedule that the planner simulates: time, in chunk-times, in which an XCD with slots / 16 CUs of two workgroups each runs through a list
+// of items, or 1e300 if that is enough or more.
+struct AttnItemCost { float chunks, fixed; };     // in chunk-times
+double attn_plan_makespan(const AttnItemCost *items, int64_t n, int slots, double enough);
 // Upper bounds used to size the workspace for any batch of up to max_T tokens in max_B traces.
 void attn_plan_capacity(const AttnTune &tune, int64_t max_T, int64_t max_B, int G, int Hkv, int64_t *max_tiles,
                         int64_t *max_items);

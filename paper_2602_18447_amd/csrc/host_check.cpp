@@ -4,10 +4,14 @@
 // thousand seeded random batches, and checks the properties whose violation would become an out-of-bounds access
 // on the device: every index in range, every key range covered exactly once, slices disjoint.
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <random>
+#include <sstream>
+#include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/confspec.h"
@@ -133,6 +137,42 @@ static void check_plan(const cs::AttnTune &tune, const Batch &b, int G, int Hkv,
     }
 }
 
+// The schedule of attn_plan_makespan from its definition: every slot moved at every event.
+static double plain_makespan(const std::vector<cs::AttnItemCost> &q, int n_cu) {
+    struct Slot { double fixed = 0, chunks = 0; bool busy = false; };
+    std::vector<Slot> sl(2 * (size_t)n_cu);
+    size_t next = 0;
+    double now = 0;
+    for (;;) {
+        for (int busy = 0; busy < 2; ++busy)                                // emptier CUs first
+            for (int c = 0; c < n_cu; ++c)
+                while (next < q.size() && sl[2 * c].busy + sl[2 * c + 1].busy <= busy) {
+                    Slot &s = sl[2 * c + (sl[2 * c].busy ? 1 : 0)];
+                    s.fixed = q[next].fixed;
+                    s.chunks = q[next++].chunks;
+                    s.busy = true;
+                }
+        double dt = 1e300;
+        for (int c = 0; c < n_cu; ++c) {
+            const double speed = sl[2 * c].busy + sl[2 * c + 1].busy == 1 ? 1.4 : 1.0;
+            for (int i = 0; i < 2; ++i)
+                if (const Slot &s = sl[2 * c + i]; s.busy) dt = std::min(dt, s.fixed > 0 ? s.fixed : s.chunks / speed);
+        }
+        if (dt == 1e300) return now;
+        now += dt;
+        for (int c = 0; c < n_cu; ++c) {
+            const double speed = sl[2 * c].busy + sl[2 * c + 1].busy == 1 ? 1.4 : 1.0;
+            for (int i = 0; i < 2; ++i) {
+                Slot &s = sl[2 * c + i];
+                if (!s.busy) continue;
+                (s.fixed > 0 ? s.fixed : s.chunks) -= s.fixed > 0 ? dt : dt * speed;
+                if (s.fixed > 0 && s.fixed < 1e-9) s.fixed = 0;
+                if (s.fixed == 0 && s.chunks < 1e-9) s.busy = false;
+            }
+        }
+    }
+}
+
 static Batch uniform_batch(int B, int L, int S) {
     Batch b;
     b.cu.push_back(0);
@@ -214,7 +254,68 @@ static void check_library(const confspec_model_cfg &cfg, const Batch &b, const c
     confspec_destroy(ctx);
 }
 
-int main() {
+// The planner on measured batches (profiles/attention_plans_of_random_batches.txt says how they are written): its pick's time against
+// the best plan with either loop, per head layout and in all.
+static int replay(const char *path) {
+    FILE *f = fopen(path, "r");
+    if (!f) { printf("cannot open %s\n", path); return 1; }
+    std::vector<std::pair<std::string, std::vector<double>>> losses = {{"all", {}}};
+    std::string line;
+    for (int c; (c = fgetc(f)) != EOF;) {
+        if (c != '\n') { line += (char)c; continue; }
+        if (line.empty() || line[0] == '#') { line.clear(); continue; }
+        std::istringstream in(line);
+        line.clear();
+        int hq, hkv, group;
+        std::string word;
+        in >> hq >> hkv >> group >> word;
+        Batch b;
+        b.cu.push_back(0);
+        while (in >> word && word != "|") {
+            int L = 0, S = 0, n = 1;
+            if (sscanf(word.c_str(), "%d:%d*%d", &L, &S, &n) < 2) return 1;
+            for (; n > 0; --n) { b.plens.push_back(L); b.cu.push_back(b.cu.back() + S); }
+        }
+        double t[2][9], best = 1e300;
+        for (auto &loop : t) {
+            for (double &v : loop) { in >> v; best = std::min(best, v); }
+            in >> word;
+        }
+        for (int i = 0; group > 1 && i <= b.B(); i += group) b.groups.push_back(i);
+        const cs::AttnTune tune;
+        const int G = hq / hkv, n_units = group > 1 ? b.B() / group : b.B();
+        auto plan = [&](const cs::AttnTune &tn) {
+            return cs::attn_plan_counts(tn, b.cu.data(), b.plens.data(), b.B(), b.T(), group > 1 ? b.groups.data() : nullptr, n_units, G, hkv, 0);
+        };
+        const cs::AttnPlanCounts pick = plan(tune);
+        int found = -1;
+        for (int k = 0; k < 9 && found < 0; ++k) {
+            cs::AttnTune forced = tune;
+            const int shares[5] = {512, 449, 383, 320, 256};       // (pieces of 1.07 times the chunks' share of these)
+            forced.force_split = std::min(k + 1, 5);
+            if (k >= 4) forced.target_items = shares[k - 4];
+            const cs::AttnPlanCounts p = plan(forced);
+            if (p.n_items == pick.n_items && (p.chunks_per_item == pick.chunks_per_item || p.n_part_slots == 0)) found = k;
+        }
+        CHECK(found >= 0, "%d/%d, %d traces: the pick of %lld items, %d chunks each, was not measured", hq, hkv, b.B(), (long long)pick.n_items, pick.chunks_per_item);
+        if (found < 0) continue;
+        const double loss = t[pick.total_chunks / pick.n_items < cs::ATTN_STAGED_BELOW ? 0 : 1][found] / best - 1;
+        const std::string layout = std::to_string(hq) + "/" + std::to_string(hkv);
+        losses[0].second.push_back(loss);
+        if (losses.back().first != layout) losses.push_back({layout, {}});
+        losses.back().second.push_back(loss);
+    }
+    fclose(f);
+    for (auto &[name, v] : losses) {
+        double sum = 0;
+        for (double x : v) sum += x;
+        printf("%s: %zu batches, mean loss %.4f, worst %.4f\n", name.c_str(), v.size(), sum / (double)v.size(), *std::max_element(v.begin(), v.end()));
+    }
+    return g_fail ? 1 : 0;
+}
+
+int main(int argc, char **argv) {
+    if (argc > 1) return replay(argv[1]);
     cs::AttnTune tune;
     const confspec_model_cfg draft = {28, 1536, 12, 2, 128, 8960, 151936, 1e6f, 1e-6f, CONFSPEC_DTYPE_BF16};
     const confspec_model_cfg target = {64, 5120, 40, 8, 128, 27648, 152064, 1e6f, 1e-6f, CONFSPEC_DTYPE_BF16};
@@ -274,6 +375,21 @@ int main() {
         check_plan(t, b, h[0], h[1], 0, what);
         check_plan(t, b, h[0], h[1], 1, what);
         if (iter % 200 == 0) check_library(draft, b, what);
+    }
+    // the planner's schedule against the plain one, and its early end: with a bound it says the makespan, or that it is not below the bound
+    for (int iter = 0; iter < 3000; ++iter) {
+        const int slots = 16 << (rng() % 6), n = 1 + (int)(rng() % (iter % 4 ? 3 * (slots / 8) : 400)), kinds = 1 + (int)(rng() % 6);
+        float len[6];
+        for (float &l : len) l = (float)(rng() % (iter % 3 ? 60 : 400));
+        std::vector<cs::AttnItemCost> q;
+        for (int i = 0; i < n; ++i) q.push_back({iter % 2 ? (float)(rng() % 100) : len[rng() % kinds], rng() % 3 ? 12.5f : 14.0f});
+        if (iter % 5 == 0) std::sort(q.begin(), q.end(), [](const auto &a, const auto &b) { return a.chunks > b.chunks; });
+        const double want = plain_makespan(q, std::max(1, slots / 16)), got = cs::attn_plan_makespan(q.data(), n, slots, 1e300);
+        CHECK(std::abs(got - want) <= 1e-6 * want, "schedule %d: %d items on %d slots take %.9g, plain %.9g", iter, n, slots, got, want);
+        for (double f : {0.3, 0.99, 1.0, 1.01, 2.0}) {
+            const double e = cs::attn_plan_makespan(q.data(), n, slots, f * got);
+            CHECK(f > 1 ? e == got : e == 1e300, "schedule %d: bound of %.9g, makespan %.9g, result %.9g", iter, f * got, got, e);
+        }
     }
     // tiling of the few-row projections: a kernel for it, the rows covered, tiles that divide the columns, every k-tile in
     // exactly one slice, no more cut tiles than there are arrival counters, planes sized for the slices and growing with the rows
