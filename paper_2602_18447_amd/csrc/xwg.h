@@ -7,10 +7,9 @@
 namespace cs {
 
 __device__ inline void xwg_store(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline float xwg_load(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 // The same with 16 bytes per lane (there is no atomic access of that width; each 4-byte part is one on its own, which is all
-// a hand-over needs): the store in assembly, the load as a buffer load at device scope from wave-uniform `base` plus a byte
-// offset per lane; offsets at or past `bytes` read zeros.
+// a hand-over needs): the store in assembly.  Loads, of 16 or 8 bytes, are buffer loads at device scope from wave-uniform `base` plus a
+// byte offset per lane; offsets at or past `bytes` read zeros.
 typedef __attribute__((ext_vector_type(4))) float xwg_f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned xwg_u32x4;
 __device__ inline void xwg_store4(xwg_f32x4 *p, xwg_f32x4 v) { asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory"); }
