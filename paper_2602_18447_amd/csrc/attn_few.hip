@@ -420,11 +420,12 @@ __global__ __launch_bounds__(64 * NW, 2) void few_attn_kernel(FewAttn a) {
     }
     if (n_p == 1) return;
     // ---- the pieces of this tile and kv head: the last workgroup to arrive merges them.  A thread has columns 4 c4 .. + 3 of a row (of two where
-    // there are 32) and adds the pieces up in order, 12 or 8 of them in flight, 4 where that is all, weighed by their common maximum (a running one chains
-    // their exponentials: generate one token at 4096 keys, 17 pieces, 1388 -> 1340 us a step); up to 8 rows take half of the threads each for the even and
-    // the odd pieces, whose sums meet in LDS.  What bounds it is a round of loads from the memory side (about a microsecond), so the rounds
-    // are few and little else is between them and the result: whole launch against wavefronts that took every eighth piece two at a time and met
-    // in LDS, one trace of 2048 keys and 96 tokens (5 pieces) 16.8 -> 15.5 us, 32 tokens of 2048 keys (4) 19.0 -> 18.2, one of 4096 (17) 12.9 -> 12.1.
+    // there are 32) and adds the pieces up in order, 12 or 8 of them in flight, weighed by their common maximum (a running one chains their
+    // exponentials: generate one token at 4096 keys, 17 pieces, 1388 -> 1340 us a step); up to 8 rows take half of the threads each for the even and
+    // the odd pieces, whose sums meet in LDS.  What bounds it is a round of loads from the memory side (about a microsecond) and what is loaded, so
+    // the rounds are few, little else is between them and the result, and the last one is of about the size of what is left.  Whole launch in a pass
+    // against wavefronts that took every eighth piece two at a time and met in LDS: one trace of 2048 keys and 96 tokens (5 pieces) 16.6 -> 15.4 us,
+    // 32 traces of 2048 keys and one token (4) 19.0 -> 18.4, one of 4096 (17) 12.6 -> 11.7.
     if (!xwg_arrive_last(a.arrived + tile * a.Hkv + h, n_p, &s_last, tid)) return;
     const bool halves = ONE && rows <= 8;                               // uniform
     const int odd = halves ? wave >> 2 : 0, step = halves ? 2 : 1, row0 = halves ? (tid >> 5) & 7 : tid >> 5;

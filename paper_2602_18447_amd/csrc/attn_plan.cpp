@@ -34,8 +34,8 @@ UnitPlan shape_plan(const UnitShape &t, Candidate cd) {
 // two.  Units: the time a workgroup takes for one chunk while its CU holds two (about 2 us).  The constants are those with the smallest loss
 // against the fastest of all candidates over 63 measured batches (1 - 128 traces, contexts to 16384, steps of 8 - 300 tokens, with and
 // without shared contexts, 150 - 19000 tokens in all), all with 12 q heads on 2 kv heads: there a layer takes 0.4 % longer than with the best candidate on
-// average, 3.4 % at worst, which says how well it fits and no more.  On 200 other batches (profiles/attention_plans_of_random_batches.txt, attention and
-// little else in a layer) it is 3.0 % on average and 18 % at worst: 1.8 with 12/2 heads, 2.2 with 40/8, 2.6, 3.9 and 4.4 with 32/8, 16/8 and 8/8.  0.9 points of that are the
+// average, 3.4 % at worst, which says how well it fits and no more.  On 200 other batches (random ones of the same ranges on five head
+// layouts, attention and little else in a layer) it is 3.0 % on average and 18 % at worst: 1.8 with 12/2 heads, 2.2 with 40/8, 2.6, 3.9 and 4.4 with 32/8, 16/8 and 8/8.  0.9 points of that are the
 // choice of the loop; the rest is mostly tiles of few rows, whose keys no other tile reads: such a batch is bound by its stream of keys, and cutting 200 to 256
 // of them in two gains nothing.  (6 and 8 chunk-times, all of an item 1.5 times as fast alone, 4 for the merge, longer pieces only: 4.2 and 41 % there; it left tiles
 // whole that cover half the chip - 12 candidates on contexts of 1211 - 2890, 1317 tokens: 243 us a layer, 221 in pieces.)

@@ -324,7 +324,8 @@ __global__ __launch_bounds__(64 * NW, EPI == SK_EPI_SWIGLU && MB * CT == 1 && NB
     if constexpr (NBUF == 1 && D == 1 && CT >= 4) {
         // A group's operands go to registers before they are multiplied, so that the next group's weights are on their way meanwhile; its
         // activations follow as the registers of a row block become free.  Whole pass of four layers, graphs, with the wait for the activations behind
-        // the next weights and as it is: 1536 / 8960, 96 rows 274.0 -> 271.2 us, 2048 / 11008, 64 rows 362.0 -> 356.5, 4096 / 14336 (two layers), 64 rows 364.5 -> 359.9.
+        // the next weights and as it is: 1536 / 8960, 96 rows 274.0 -> 271.2 us, 2048 / 11008, 64 rows 362.0 -> 356.5, 4096 / 14336 (two layers), 64 rows 364.5 -> 359.9;
+        // gate/up of 96 rows, 1536 / 8960 (55 MB), 19.6 us a launch without any of it, 18.5 now, the reduction in two passes instead of three included.
         bf16x8 xf[MB][2];
         unsigned f16 = (unsigned)fr * 16u;
         auto load_block = [&](int g, int i) __attribute__((always_inline)) {         // (its offset is made here: six of them kept take registers that six
@@ -522,7 +523,7 @@ __global__ __launch_bounds__(64 * NW, EPI == SK_EPI_SWIGLU && MB * CT == 1 && NB
         if (!xwg_arrive_last(a.tile_cnt + t * a.ms + mi, a.S, &s_last, tid)) return;
         const XwgLoads planes(plane, (unsigned)(a.S * MB * CT) * 1024u);
         // a pass's blocks at once, four or eight slices of each in flight, added in slice order (a round of loads takes about a microsecond;
-        // 96 rows, 8960 x 1536, five slices and two blocks a wavefront: one round instead of four, 17.3 -> 16.5 us with groups of two k-tiles)
+        // 96 rows, 8960 x 1536, five slices and two blocks a wavefront: one round instead of four, 17.3 -> 16.4 us with groups of two k-tiles)
         constexpr int IN_FLIGHT = CT >= 3 && EPB <= 2 ? 8 : 4;
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) {
@@ -550,7 +551,8 @@ __global__ __launch_bounds__(64 * NW, EPI == SK_EPI_SWIGLU && MB * CT == 1 && NB
 }
 
 // Tiling of a projection: blocks of 16 rows per workgroup (mb) and workgroups over the rows (ms), 16-column tiles per
-// workgroup (ct), k slices (S).  Times are of single launches over weights that come from HBM, MI355X.
+// workgroup (ct), k slices (S).  Times are of single launches over weights that come from HBM, MI355X; those inside a pass differ by up to a
+// microsecond.
 //  - Wide outputs (gate/up).  One row block: one tile per workgroup, the weights' stream decides (55 MB: 11.7 us).  More
 //    rows: the activations, which every workgroup re-reads from the L2, would cost as much as the weights, so a workgroup
 //    takes as many tiles as leave about one workgroup per CU (1120 tiles: 5; 32 rows 16.2 -> 12.9 us, 96 rows 25 -> 18.5 us).
@@ -559,7 +561,7 @@ __global__ __launch_bounds__(64 * NW, EPI == SK_EPI_SWIGLU && MB * CT == 1 && NB
 //    the weights through their L2 (96 rows x 2048 columns x 1536: 9.0 -> 6.5 us).  From 256 tiles on two tiles.
 //  - Narrow outputs over long k ranges (down): cut so that about one workgroup per CU (about two where there are enough
 //    tiles) shares the work; more rows take more tiles per workgroup, again for the activations (8960 x 1536: 9.9 us for one
-//    row, 11.5 for 32, 16.3 for 96).
+//    row, 11.5 for 32, 16.4 for 96).
 //  - A width made for the other kind of projection (a wide model's QKV or residual projection of 1024 tiles and more, a small
 //    model's gate/up): one tile, never cut.  Rotating projections over 128 k-tiles and more: never cut either, one tile, two
 //    from 128 tiles on.
