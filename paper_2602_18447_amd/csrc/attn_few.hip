@@ -420,61 +420,72 @@ __global__ __launch_bounds__(64 * NW, 2) void few_attn_kernel(FewAttn a) {
     }
     if (n_p == 1) return;
     // ---- the pieces of this tile and kv head: the last workgroup to arrive merges them.  A thread has columns 4 c4 .. + 3 of a row (of two where
-    // there are 32) and adds the pieces up in order, 12 or 8 of them in flight, weighed by their common maximum (a running one chains their
+    // there are 32) and adds the pieces up in order, 12 or 8 of them in flight, 4 where that is all, weighed by their common maximum (a running one chains their
     // exponentials: generate one token at 4096 keys, 17 pieces, 1388 -> 1340 us a step); up to 8 rows take half of the threads each for the even and
     // the odd pieces, whose sums meet in LDS.  What bounds it is a round of loads from the memory side (about a microsecond) and what is loaded, so
-    // the rounds are few, little else is between them and the result, and the last one is of about the size of what is left.  Whole launch in a pass
+    // the rounds are few, little else is between them and the result, and with 32 rows the last one is of about the size of what is left.  Whole launch in a pass
     // against wavefronts that took every eighth piece two at a time and met in LDS: one trace of 2048 keys and 96 tokens (5 pieces) 16.6 -> 15.4 us,
     // 32 traces of 2048 keys and one token (4) 19.0 -> 18.4, one of 4096 (17) 12.6 -> 11.7.
     if (!xwg_arrive_last(a.arrived + tile * a.Hkv + h, n_p, &s_last, tid)) return;
     const bool halves = ONE && rows <= 8;                               // uniform
-    const int odd = halves ? wave >> 2 : 0, step = halves ? 2 : 1, row0 = halves ? (tid >> 5) & 7 : tid >> 5;
+    const int odd = halves ? tid >> 8 : 0, step = halves ? 2 : 1, row0 = halves ? (tid >> 5) & 7 : tid >> 5;
     const XwgLoads parts(a.part_o + rec0 * ROWS * 128, (unsigned)(n_p * ROWS) * 512u), stats(a.part_ml + rec0 * ROWS * 2, (unsigned)(n_p * ROWS) * 8u);
     float mm[RB], ll[RB];
     f32x4 oo[RB];
 #pragma unroll
     for (int i = 0; i < RB; ++i) { mm[i] = -INFINITY; ll[i] = 0.f; oo[i] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-    // FLY pieces from pp on; last: the final one of them may be past the end
-    auto add_pieces = [&](int pp, auto fly, auto last) __attribute__((always_inline)) {
+    // the pieces from first on, FLY at a time, in rounds that begin before end; rest: such a round may go past the last piece
+    auto add_pieces = [&](int first, int end, auto fly, auto rest) __attribute__((always_inline)) {
         constexpr int FLY = decltype(fly)::value;
-        f32x4 ov[FLY][RB];
-        float2 ml[FLY][RB];
+        for (int pp = first; pp < end; pp += FLY * step) {
+            f32x4 ov[FLY][RB];
+            float2 ml[FLY][RB];
 #pragma unroll
-        for (int q = 0; q < FLY; ++q)
+            for (int q = 0; q < FLY; ++q)
 #pragma unroll
-            for (int i = 0; i < RB; ++i) {
-                const unsigned rec = min(pp + q * step, n_p - 1) * ROWS + min(row0 + 16 * i, rows - 1);
-                ov[q][i] = parts.load4(rec * 512u + c4 * 16u);
-                ml[q][i] = stats.load2(rec * 8u);
-            }
+                for (int i = 0; i < RB; ++i) {
+                    const unsigned rec = (decltype(rest)::value ? min(pp + q * step, n_p - 1) : pp + q * step) * ROWS + min(row0 + 16 * i, rows - 1);
+                    ov[q][i] = parts.load4(rec * 512u + c4 * 16u);
+                    ml[q][i] = stats.load2(rec * 8u);
+                }
 #pragma unroll
-        for (int i = 0; i < RB; ++i) {                                  // (every row sees a key of every piece)
-            float M = mm[i];
+            for (int i = 0; i < RB; ++i) {                                  // (every row sees a key of every piece)
+                float M = mm[i];
 #pragma unroll
-            for (int q = 0; q < FLY; ++q) M = fmaxf(M, ml[q][i].x);     // (past the end: the last piece again)
-            const float wo = exp2_from(mm[i], M);
-            oo[i] *= wo;
-            ll[i] *= wo;
-            mm[i] = M;
+                for (int q = 0; q < FLY; ++q) M = fmaxf(M, ml[q][i].x);     // (past the end: the last piece again)
+                const float wo = exp2_from(mm[i], M);
+                oo[i] *= wo;
+                ll[i] *= wo;
+                mm[i] = M;
 #pragma unroll
-            for (int q = 0; q < FLY; ++q) {
-                const bool here = !decltype(last)::value || pp + q * step < n_p;      // (nothing of the repeated piece: it may hold an infinity)
-                const float wn = here ? __builtin_amdgcn_exp2f(ml[q][i].x - M) : 0.f;
-                oo[i] += wn * (here ? ov[q][i] : f32x4{0.f, 0.f, 0.f, 0.f});
-                ll[i] += here ? wn * ml[q][i].y : 0.f;
+                for (int q = 0; q < FLY; ++q) {
+                    const bool here = !decltype(rest)::value || pp + q * step < n_p;      // (nothing of the repeated piece: it may hold an infinity)
+                    const float wn = here ? __builtin_amdgcn_exp2f(ml[q][i].x - M) : 0.f;
+                    oo[i] += wn * (here ? ov[q][i] : f32x4{0.f, 0.f, 0.f, 0.f});
+                    if (!decltype(rest)::value && q > 0) {               // (unfused, as behind the select: the same bits whatever the round)
+#pragma clang fp contract(off)
+                        ll[i] += wn * ml[q][i].y;
+                    } else {
+                        ll[i] += here ? wn * ml[q][i].y : 0.f;
+                    }
+                }
             }
         }
     };
-    constexpr int MOST = RB == 1 ? 12 : 8;
-    int pp = odd;
-    for (; pp + (MOST - 1) * step < n_p; pp += MOST * step) add_pieces(pp, std::integral_constant<int, MOST>{}, std::false_type{});
-    // (the rest in a round of about its size: what is loaded for nothing takes its share of the CU's stream,
-    // too: 33 pieces of 32 rows read as 40, four layers of 1536 x 8960, 3 x 5 tokens of 16000 keys, 273 us, as 34 265; 17 as 24, 32 tokens of 8000 keys, 255, as 18 246)
-    const int left = (n_p - pp + step - 1) / step;
-    if (left > (RB == 1 ? 8 : 6)) add_pieces(pp, std::integral_constant<int, MOST>{}, std::true_type{});
-    else if (left > 4) add_pieces(pp, std::integral_constant<int, RB == 1 ? 8 : 6>{}, std::true_type{});
-    else if (left > 2) add_pieces(pp, std::integral_constant<int, 4>{}, std::true_type{});
-    else if (left > 0) add_pieces(pp, std::integral_constant<int, 2>{}, std::true_type{});
+    if constexpr (RB == 1) {
+        if (n_p <= 4 * step) add_pieces(odd, n_p, std::integral_constant<int, 4>{}, std::true_type{});
+        else add_pieces(odd, n_p, std::integral_constant<int, 12>{}, std::true_type{});
+    } else {
+        // The rest in a round of about its size: what is loaded for nothing takes its share of the CU's stream, too.  33 pieces of 32 rows read as
+        // 40, four layers of 1536 x 8960, 3 x 5 tokens of 16000 keys, 272 us, as 34 265; 17 as 24, 32 tokens of 8000 keys, 254, as 18 245.  (With 16 rows
+        // and fewer, half and a quarter of the bytes, a second size of the round costs as much as it saves.)
+        const int whole = n_p / 8 * 8, left = n_p - whole;
+        add_pieces(0, whole, std::integral_constant<int, 8>{}, std::false_type{});
+        if (left > 6) add_pieces(whole, n_p, std::integral_constant<int, 8>{}, std::true_type{});
+        else if (left > 4) add_pieces(whole, n_p, std::integral_constant<int, 6>{}, std::true_type{});
+        else if (left > 2) add_pieces(whole, n_p, std::integral_constant<int, 4>{}, std::true_type{});
+        else if (left > 0) add_pieces(whole, n_p, std::integral_constant<int, 2>{}, std::true_type{});
+    }
     if (halves) {
         f32x4 *meet = reinterpret_cast<f32x4 *>(smem);                  // [8 rows][32]
         if (odd == 1) {

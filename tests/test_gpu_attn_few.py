@@ -58,7 +58,7 @@ def test_many_q_heads_per_kv_head(hq, suffix):
     G.parity_case(wl)
 
 
-# pieces of 256 keys each, which the last workgroup of a tile adds up 12 at a time and the rest in a round of 2, 4, 8 or 12: one of them, every border of a
+# pieces of 256 keys each, which the last workgroup of a tile adds up 12 at a time, or 4 where that is all: one of them, every border of a
 # round, rows taken by all threads (16 heads) or by half of them for the even and the odd pieces (up to 8 heads)
 @pytest.mark.parametrize("heads", ["G5", "G6", "G16"])
 @pytest.mark.parametrize("prefix", [(256,), (260,), (4 * 256, 4 * 256 + 1), (8 * 256, 8 * 256 + 1), (12 * 256,), (12 * 256 + 1, 9), (24 * 256, 24 * 256 + 3), (25 * 256 - 15,)], ids=lambda p: f"L{max(p)}")
